@@ -1151,9 +1151,7 @@ int qs_get_state(qs_handle* h, float* d_state, uint64_t* substep_index, void* st
   if (!h || !d_state) return QS_ERR_NULL;
   if (!aligned(d_state, 4)) return QS_ERR_ALIGN;
   if (hipSetDevice(h->dev) != hipSuccess) return QS_ERR_HIP;
-  const long long n = (long long)h->Q * qs::NSTATE;
-  const int tb = 256;
-  hipLaunchKernelGGL(qs::get_state_kernel, dim3((unsigned)((n + tb - 1) / tb)), dim3(tb), 0,
+  hipLaunchKernelGGL(qs::get_state_kernel, dim3(h->Qp / qs::IO_QUADS), dim3(qs::IO_THREADS), 0,
                      (hipStream_t)stream, h->d_st, h->Qp, h->Q, d_state);
   if (hipGetLastError() != hipSuccess) return QS_ERR_HIP;
   if (substep_index) *substep_index = h->t;
@@ -1165,9 +1163,7 @@ int qs_set_state(qs_handle* h, const float* d_state, uint64_t substep_index,
   if (!h || !d_state) return QS_ERR_NULL;
   if (!aligned(d_state, 4)) return QS_ERR_ALIGN;
   if (hipSetDevice(h->dev) != hipSuccess) return QS_ERR_HIP;
-  const long long n = (long long)h->Q * qs::NSTATE;
-  const int tb = 256;
-  hipLaunchKernelGGL(qs::set_state_kernel, dim3((unsigned)((n + tb - 1) / tb)), dim3(tb), 0,
+  hipLaunchKernelGGL(qs::set_state_kernel, dim3(h->Qp / qs::IO_QUADS), dim3(qs::IO_THREADS), 0,
                      (hipStream_t)stream, h->d_st, h->Qp, h->Q, d_state, h->d_qenv, d_env_mask);
   if (hipGetLastError() != hipSuccess) return QS_ERR_HIP;
   h->t = substep_index;
