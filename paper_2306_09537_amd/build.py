@@ -5,23 +5,25 @@ calls :func:`build`.
 """
 from __future__ import annotations
 
+import concurrent.futures
+import glob
 import os
 import subprocess
 import sys
+import tempfile
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libquadswarm.so")
-SOURCES = [os.path.join(CSRC, "qs_abi.hip")]
-DEPS = SOURCES + [os.path.join(CSRC, f) for f in ("qs_device.h", "qs_kernels.h", "qs_adjoint.h",
-                                                  "qs_rollout.h", "qs_checks.h")] + [
+SOURCES = sorted(glob.glob(os.path.join(CSRC, "*.hip")))
+DEPS = SOURCES + sorted(glob.glob(os.path.join(CSRC, "*.h"))) + [
     os.path.join(INCLUDE, "quadswarm.h")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # multiply-adds fuse only within one source expression, so every kernel
     # specialisation (and the adjoint's recomputation) rounds identically
     "-ffp-contract=on",
@@ -37,14 +39,23 @@ FLAGS = [
 
 
 def build(force: bool = True, verbose: bool = False) -> str:
+    """Compile the translation units side by side and link them."""
     if not force and os.path.exists(LIB) and all(
             os.path.getmtime(LIB) >= os.path.getmtime(d) for d in DEPS):
         return LIB
+
+    def run(cmd):
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        subprocess.check_call(cmd)
+
     tmp = LIB + ".tmp"
-    cmd = [HIPCC, *FLAGS, *SOURCES, "-o", tmp]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.check_call(cmd)
+    with tempfile.TemporaryDirectory() as objs:
+        out = [os.path.join(objs, os.path.basename(s) + ".o") for s in SOURCES]
+        with concurrent.futures.ThreadPoolExecutor(len(SOURCES)) as pool:
+            list(pool.map(lambda so: run([HIPCC, *FLAGS, "-c", so[0], "-o", so[1]]),
+                          zip(SOURCES, out)))
+        run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *out, "-o", tmp])
     os.replace(tmp, LIB)
     return LIB
 
