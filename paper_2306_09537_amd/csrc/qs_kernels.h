@@ -467,8 +467,16 @@ __device__ __forceinline__ void step_body(const Consts& c, const Ptrs& p,
             }
           } else if constexpr (NU == 0) {
             if (live)
-              for (int jj = 0; jj < n; ++jj)
-                cand(jj, tile[0][ls + jj], tile[1][ls + jj], tile[2][ls + jj]);
+              for (int j0 = 0; j0 < n; j0 += 4) {
+                float px[4][3];
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+#pragma unroll
+                  for (int r = 0; r < 3; ++r) px[u][r] = tile[r][ls + min(j0 + u, n - 1)];
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                  cand(j0 + u, j0 + u < n ? px[u][0] : 1e30f, px[u][1], px[u][2]);
+              }
           }
         }
         bool tie = false;

@@ -478,6 +478,7 @@ __device__ __forceinline__ unsigned long long mark_contacts(const Consts& c, T t
   };
   for_partners<BS, N, PEN ? 12 : -1>(tile, ls, n, mark);
   if constexpr (ACC) cm32 = collide ? (PairMask<N>)(__builtin_bitreverse32(acc) >> (32 - N)) : 0;
+  if constexpr (N == 0) cm32 &= (PairMask<N>)(~0ull >> (64 - n));  // run-time sizes: members only
   return (unsigned long long)(cm32 & ~((PairMask<N>)1 << me));  // not the quad itself
 }
 
