@@ -314,8 +314,8 @@ int qs_rollout(qs_handle* h, const float* d_actions, int32_t n_calls, int32_t n_
  * [n_calls][Q][4] and ADDS dL/d(mass, ixx, iyy, izz, thrust_to_weight,
  * motor_tau) into d_gparams [Q][6].  Each segment of ckpt_every calls is
  * recomputed from its checkpoint into a tape of ckpt_every*n_substeps
- * states and motor-noise draws (31 floats per quad and substep; device
- * scratch owned by the handle, grown on first use, at most the tape budget:
+ * states and motor-noise draws (31 floats per quad and substep, 34 with a
+ * penalty gradient; device scratch owned by the handle, grown on first use, at most the tape budget:
  * environment QS_TAPE_BYTES, default 8 GiB, and one segment).  Does not
  * change the handle's state.
  */

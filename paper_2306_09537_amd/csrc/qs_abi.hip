@@ -318,6 +318,7 @@ int qs_create(const qs_desc* desc, const qs_quad_params* h_params, const float* 
   int max_n = 1;
   for (int e = 0; e < E; ++e)
     max_n = std::max(max_n, desc->env_offsets[e + 1] - desc->env_offsets[e]);
+  h->max_n = max_n;
   h->bs = pick_block(Q, max_n);
 
   // constants (derived in double, rounded once)

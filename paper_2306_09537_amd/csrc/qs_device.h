@@ -582,13 +582,14 @@ using PairMask = typename std::conditional<(N > 0 && N <= 32), uint32_t,
 // For a compile-time swarm size the reads go out a chunk of eight partners
 // at a time, ahead of the per-pair branches, so they overlap instead of
 // waiting one by one.
-template <int BS, int N, int XR = -1, typename T, typename F>
+// FEW: chunks of four in swarms of 8 too (kernels short of registers).
+template <int BS, int N, int XR = -1, bool FEW = false, typename T, typename F>
 __device__ __forceinline__ void for_partners(T tile, int ls, int n, F&& f) {
   if constexpr (N > 0) {
     // chunks of eight partners, four in swarms of 16 and more (32-quad
     // swarms: 168 -> 120 VGPRs in the step, four wavefronts per SIMD
     // instead of three)
-    constexpr int CH = N < 8 ? N : (N >= 16 ? 4 : 8);
+    constexpr int CH = N < 8 ? N : (N >= 16 || FEW ? 4 : 8);
     auto chunk = [&](int j0) {
       float pj[CH][7];
 #pragma unroll
@@ -600,7 +601,7 @@ __device__ __forceinline__ void for_partners(T tile, int ls, int n, F&& f) {
 #pragma unroll
       for (int u = 0; u < CH; ++u) f(j0 + u, pj[u]);
     };
-    if constexpr (N >= 16) {
+    if constexpr (N >= 16 || (N == 8 && FEW)) {
       // large swarms: a run-time loop over the chunks keeps the registers
       // of an eight-partner body
 #pragma unroll 1
@@ -737,6 +738,155 @@ __device__ __forceinline__ float sq_dist(const float pj[3], const float x[3]) {
   return dx * dx + dy * dy + dz * dz;
 }
 
+// Expanded screen of swarms of 16 and 32: mask of the partners whose
+// post-motion positions lie within r of the lane's, and perhaps a few more.
+// The bit is the sign of
+//   e = |b|^2 + (|a|^2 - thr_x) - 2 a.b  (= |a - b|^2 - thr_x),
+// three FMAs and an add per partner (|b|^2 from row XSQ, the rest once per
+// lane), shifted in by one funnel shift ((acc << 1) | (e >> 31), v_alignbit):
+// partner jj's bit lands at position N - 1 - jj and the mask is bit-reversed
+// once.  Rounding: |e - (|a - b|^2 - thr_x)| <= 7 u ((|a| + |b|)^2 + thr_x),
+// u = 2^-24.  For a lane with every |a_k| <= SCREEN_BOX and a partner within r,
+// |a| + |b| <= reach = 2 sqrt(3) SCREEN_BOX + r + 1 mm, so the widening
+// thr_x - r^2 = 3 err, err = 7 u (reach^2 + r^2) (+1 %), exceeds the
+// rounding three times over and no such partner is dropped; a lane outside
+// the box takes every partner.
+template <int BS, int N>
+__device__ __forceinline__ uint32_t screen_expanded(const float (*tile)[BS], const float x[3],
+                                                    int ls, int n, float r, float r2) {
+  const float reach = 2.0f * 1.7320508f * SCREEN_BOX + r + 1e-3f;
+  const float err = 1.01f * 7.0f * 5.9604645e-8f * (reach * reach + r2);
+  const float thr_x = r2 + 3.0f * err;
+  const float na = fmaf(x[2], x[2], fmaf(x[1], x[1], fmaf(x[0], x[0], -thr_x)));
+  const float a0 = -2.0f * x[0], a1 = -2.0f * x[1], a2 = -2.0f * x[2];
+  uint32_t acc = 0u;
+  for_partner_pos<BS, N, 4>(tile, ls, n, [&](int, const float* pj) {
+    const float e = fmaf(a2, pj[2], fmaf(a1, pj[1], fmaf(a0, pj[0], pj[3] + na)));
+    acc = __builtin_amdgcn_alignbit(acc, __float_as_uint(e), 31u);
+  });
+  return __builtin_bitreverse32(acc) >> (32 - N);
+}
+__device__ __forceinline__ float max_abs(const float x[3]) {
+  return fmaxf(fabsf(x[0]), fmaxf(fabsf(x[1]), fabsf(x[2])));
+}
+
+// What a pass over the partners of a substep sums up beside the contacts:
+//  PEN_SUM: the smoothed collision penalty, softplus(beta (d_col - d)) / (2 beta)
+//           per partner (each quad of a pair carries half), into acc[0];
+//  PEN_GRAD: its adjoint w.r.t. the quad's position,
+//             d pen / d x_i = -(g_i + g_j)/2 sigmoid(beta (d_col - d)) (x_i - x_j) / d,
+//           into acc[0..2].  h_me = -g_i/2, and row PENROW of the tile holds
+//           -g_j/2 for the partners (halving is exact, so h_me + h_j rounds
+//           as -(g_i + g_j)/2).
+// Either way the sum runs in partner order.
+enum PenMode { PEN_NONE = 0, PEN_SUM = 1, PEN_GRAD = 2 };
+constexpr int PENROW = TILE_ROWS_CO;
+struct Pen {
+  float beta, hb;
+  // Beyond the contact distance + 106 / beta, softplus (2^-152 before its
+  // rounding) and sigmoid (1 / infinity) are exactly 0 in float32, so passes
+  // over the partners within r give the same sums bit for bit.
+  float r;
+  int few;      // passes over the near partners pay up to this many of them; 0: never
+  float h_me;
+  float acc[3];
+};
+
+// n_max: the wavefront's largest swarm.  Over all partners a pass costs about
+// 27 vector instructions a partner; over the near ones 10 a partner for the
+// screen and 38 a near one (their reads are gathered and their index found),
+// so it pays up to 0.45 n_max of them, and not at all in swarms of up to 8.
+// 32768 x 32, 100 substeps with beta = 100: forward 3.27 -> 2.43 ms.
+// A radius of several metres leaves nothing out; with a weight that is not
+// finite every partner counts (its product with 0 is not 0).
+__device__ __forceinline__ Pen make_pen(const Consts& c, float beta, int n_max, float h_me = 0.f) {
+  Pen p;
+  p.beta = beta;
+  p.hb = 0.5f / beta;
+  p.r = c.dcol + 106.0f / beta;
+  p.h_me = h_me;
+  p.acc[0] = p.acc[1] = p.acc[2] = 0.f;
+  const bool odd = __ballot(!(fabsf(h_me) < INFINITY)) != 0ull;
+  p.few = (n_max <= 8 || odd || !(p.r < 3.0f)) ? 0 : (n_max * 29) >> 6;
+  return p;
+}
+
+// The largest value of the wavefront.
+__device__ __forceinline__ int wave_max(int v) {
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) v = max(v, __shfl_xor(v, d, 64));
+  return v;
+}
+
+template <int P>
+__device__ __forceinline__ void pen_term(const Consts& c, Pen& p, bool other, float hj, float dx,
+                                         float dy, float dz, float d2) {
+  if constexpr (P == PEN_SUM) {
+    const float sp = p.hb * softplus_hw(p.beta * (c.dcol - __builtin_amdgcn_sqrtf(d2)));
+    p.acc[0] = other ? p.acc[0] + sp : p.acc[0];
+  } else if constexpr (P == PEN_GRAD) {
+    // the quad itself has d^2 = 0 exactly, so d^2 > 0 also leaves it out
+    const float rd = __builtin_amdgcn_rsqf(d2);
+    const float coef = d2 > 0.f && other
+                           ? (p.h_me + hj) * sigmoid_hw(p.beta * (c.dcol - d2 * rd)) * rd
+                           : 0.f;
+    p.acc[0] = fmaf(coef, dx, p.acc[0]);
+    p.acc[1] = fmaf(coef, dy, p.acc[1]);
+    p.acc[2] = fmaf(coef, dz, p.acc[2]);
+  }
+}
+
+// Contact bits (by the exact test) and penalty terms of the partners within
+// p.r of the lane, two at a time so that the second one's gathered reads run
+// under the first one's arithmetic.  Returns false, and has done nothing, where
+// the wavefront does better over all partners.  Needs rows XROW.. of the tile.
+template <int BS, int N, int P>
+__device__ __forceinline__ bool near_pass(const Consts& c, const float (*tile)[BS], const Quad& s,
+                                          int ls, int n, int me, Pen& p, PairMask<N>& cm) {
+  using M = PairMask<N>;
+  if (p.few == 0) return false;
+  const float far = max_abs(s.x);
+  const float lim = kScreenSq<N> ? SCREEN_BOX : 1000.0f;
+  // (NaN included: max_abs skips it, the sum does not)
+  if (__ballot(!(far <= lim && s.x[0] + s.x[1] + s.x[2] < INFINITY)) != 0ull) return false;
+  M near;
+  if constexpr (kScreenSq<N>) {
+    near = (M)screen_expanded<BS, N>(tile, s.x, ls, n, p.r, p.r * p.r);
+  } else {
+    const float w = p.r + 1e-3f, thr = w * w;
+    near = 0;
+    for_partner_pos<BS, N>(tile, ls, n, [&](int jj, const float* pj) {
+      near |= sq_dist(pj, s.x) < thr ? (M)1 << jj : (M)0;
+    });
+    if constexpr (N == 0) near &= (M)(~0ull >> (64 - n));
+  }
+  near &= ~((M)1 << me);
+  if (__ballot(__popcll((unsigned long long)near) > p.few) != 0ull) return false;
+  while (near != 0) {
+    int jj[2];
+    jj[0] = __builtin_ctzll((unsigned long long)near);
+    near &= near - 1;
+    const bool two = near != 0;
+    jj[1] = two ? __builtin_ctzll((unsigned long long)near) : jj[0];
+    near &= near - 1;
+    float pj[2][7];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+#pragma unroll
+      for (int r = 0; r < 6; ++r) pj[u][r] = tile[r][ls + jj[u]];
+      pj[u][6] = P == PEN_GRAD ? tile[P == PEN_GRAD ? PENROW : 0][ls + jj[u]] : 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      float dx, dy, dz, d2;
+      const bool con = pair_geom_v(c, pj[u], s, dx, dy, dz, d2);
+      cm |= con ? (M)1 << jj[u] : (M)0;
+      pen_term<P>(c, p, u == 0 || two, pj[u][6], dx, dy, dz, d2);
+    }
+  }
+  return true;
+}
+
 // In-swarm pass of one live lane after the tile (start positions,
 // displacements, velocities) is written and the workgroup synchronised:
 // §III-B.1 contact detection and Jacobi velocity exchange (every response
@@ -744,7 +894,10 @@ __device__ __forceinline__ float sq_dist(const float pj[3], const float x[3]) {
 // and §III-B.4 downwash from the swarm-mates above, applied as a velocity
 // kick after the response.  N > 0 unrolls over the swarm slot; padding
 // partners hold far-away sentinels.  Returns the contact mask.
-// CO (no penalty, tile rows XROW.. written): without downwash, partners are
+// P (PenMode): also sum the penalty or its adjoint into *pen; with CO over
+// the near partners where that pays (near_pass).  resp (optional): the
+// partners whose response the quad received.
+// CO (tile rows XROW.. written): without penalty and downwash, partners are
 // first screened on the post-motion positions with a contact distance
 // widened by 1 mm, and the exact test runs for the survivors only.  The
 // screen never drops a pair the exact test would mark: for positions within
@@ -756,21 +909,21 @@ __device__ __forceinline__ float sq_dist(const float pj[3], const float x[3]) {
 // neighbour key list key[0..L-1] (knn_insert); the pass changes only
 // velocities and body rates, so they are the distances of the post-pass
 // positions.
-template <int BS, int N, bool PEN, bool CO = false, int L = 0>
+template <int BS, int N, int P, bool CO = false, int L = 0>
 __device__ __forceinline__ unsigned long long pair_pass(const Consts& c, const float (*tile)[BS],
                                                         Quad& s, int ls, int n, int me,
                                                         uint32_t q, unsigned long long t,
-                                                        float& pacc, float beta,
-                                                        uint32_t* key = nullptr) {
-  static_assert(L == 0 || (CO && !PEN && N != 8), "keys from the plain screen only");
+                                                        Pen* pen = nullptr,
+                                                        uint32_t* key = nullptr,
+                                                        unsigned long long* resp = nullptr) {
+  static_assert(L == 0 || (CO && P == PEN_NONE && N != 8), "keys from the plain screen only");
   const bool collide = (c.flags & F_COLLIDE) != 0;
   const bool dw = (c.flags & F_DOWNWASH) != 0 && s.fl == 0.0f;
   using M = PairMask<N>;
   M cm = 0;
   float dv[3] = {0.f, 0.f, 0.f};
   float adw = 0.f;
-  bool hit = false, dwhit = false;
-  const float hb = PEN ? 0.5f / beta : 0.f;  // each quad of a pair carries half
+  bool dwhit = false;
   // Every partner's geometry, branch-free (contacts are rare; a branch per
   // partner would end the scheduling region and serialise the partners'
   // arithmetic): the contact set, the penalty and, when it is on (a uniform
@@ -785,10 +938,8 @@ __device__ __forceinline__ unsigned long long pair_pass(const Consts& c, const f
   auto pair = [&](int jj, const float* pj, auto with_dw, auto in_order) {
     float dx, dy, dz, d2;
     const bool con = pair_geom_v(c, pj, s, dx, dy, dz, d2);
-    if constexpr (PEN) {
-      const float sp = hb * softplus_hw(beta * (c.dcol - __builtin_amdgcn_sqrtf(d2)));
-      pacc = jj != me ? pacc + sp : pacc;
-    }
+    if constexpr (P != PEN_NONE)
+      pen_term<P>(c, *pen, P == PEN_GRAD || jj != me, pj[6], dx, dy, dz, d2);
     if constexpr (ACC && decltype(in_order)::value)
       acc = __builtin_amdgcn_alignbit(acc, __float_as_uint(d2 - c.dcol2), 31u);
     else
@@ -801,11 +952,12 @@ __device__ __forceinline__ unsigned long long pair_pass(const Consts& c, const f
       dwhit = dwhit | dwc;
     }
   };
+  constexpr int XR = P == PEN_GRAD ? PENROW : -1;
   if (c.flags & F_DOWNWASH) {
-    for_partners<BS, N>(tile, ls, n,
-                        [&](int jj, const float* pj) { pair(jj, pj, TrueT{}, TrueT{}); });
+    for_partners<BS, N, XR>(tile, ls, n,
+                            [&](int jj, const float* pj) { pair(jj, pj, TrueT{}, TrueT{}); });
     if constexpr (ACC) cm = (M)(__builtin_bitreverse32(acc) >> (32 - N));
-  } else if constexpr (CO && !PEN) {
+  } else if constexpr (CO && P == PEN_NONE) {
     const float dw = c.dcol + 1e-3f, thr = dw * dw;
     M cand = 0;
     bool in_box = true;  // the expanded screen's domain (swarms of 16 and 32)
@@ -853,41 +1005,20 @@ __device__ __forceinline__ unsigned long long pair_pass(const Consts& c, const f
       cand = (M)(me == 0 ? rot : ((rot << me) | (rot >> (N - me))) & full);
     } else {
       if constexpr (N >= 16 && N <= 32) {
-        // Partners arrive in index order, so the mask is accumulated as
-        // acc = 2 acc + bit and bit-reversed once: partner jj's bit lands at
-        // position N - 1 - jj, then at jj.
-        uint32_t acc = 0u;
         if constexpr (L > 0) {
+          // partners arrive in index order, so the mask is accumulated as
+          // acc = 2 acc + bit and bit-reversed once
+          uint32_t acc = 0u;
           for_partner_pos<BS, N>(tile, ls, n, [&](int jj, const float* pj) {
             const float d2 = sq_dist(pj, s.x);
             acc = acc + acc + (d2 < thr ? 1u : 0u);
             knn_insert<L>(key, jj, me, d2);
           });
+          cand = (M)(__builtin_bitreverse32(acc) >> (32 - N));
         } else {
-          // Without keys the bit is the sign of
-          //   e = |b|^2 + (|a|^2 - thr_x) - 2 a.b  (= |a - b|^2 - thr_x),
-          // three FMAs and an add per partner (|b|^2 from row XSQ, the rest
-          // once per lane), shifted in by one funnel shift
-          // ((acc << 1) | (e >> 31), v_alignbit).  Rounding: |e - (|a - b|^2
-          // - thr_x)| <= 7 u ((|a| + |b|)^2 + thr_x), u = 2^-24.  For a lane
-          // with every |a_k| <= SCREEN_BOX and a partner in contact,
-          // |a| + |b| <= reach = 2 sqrt(3) SCREEN_BOX + d_col + 1 mm, so the
-          // widening thr_x - d_col^2 = 3 err, err = 7 u (reach^2 + d_col^2)
-          // (+1 %), exceeds the rounding three times over and no contact is
-          // dropped; a lane outside the box tests every partner exactly.
-          // An extra survivor only meets the exact test.
-          const float reach = 2.0f * 1.7320508f * SCREEN_BOX + c.dcol + 1e-3f;
-          const float err = 1.01f * 7.0f * 5.9604645e-8f * (reach * reach + c.dcol2);
-          const float thr_x = c.dcol2 + 3.0f * err;
-          const float na = fmaf(s.x[2], s.x[2], fmaf(s.x[1], s.x[1], fmaf(s.x[0], s.x[0], -thr_x)));
-          const float a0 = -2.0f * s.x[0], a1 = -2.0f * s.x[1], a2 = -2.0f * s.x[2];
-          for_partner_pos<BS, N, 4>(tile, ls, n, [&](int, const float* pj) {
-            const float e = fmaf(a2, pj[2], fmaf(a1, pj[1], fmaf(a0, pj[0], pj[3] + na)));
-            acc = __builtin_amdgcn_alignbit(acc, __float_as_uint(e), 31u);
-          });
-          in_box = fmaxf(fabsf(s.x[0]), fmaxf(fabsf(s.x[1]), fabsf(s.x[2]))) <= SCREEN_BOX;
+          cand = (M)screen_expanded<BS, N>(tile, s.x, ls, n, c.dcol, c.dcol2);
+          in_box = max_abs(s.x) <= SCREEN_BOX;
         }
-        cand = (M)(__builtin_bitreverse32(acc) >> (32 - N));
       } else {
         for_partner_pos<BS, N>(tile, ls, n, [&](int jj, const float* pj) {
           const float d2 = sq_dist(pj, s.x);
@@ -896,8 +1027,7 @@ __device__ __forceinline__ unsigned long long pair_pass(const Consts& c, const f
         });
       }
     }
-    const bool near_origin =
-        fmaxf(fabsf(s.x[0]), fmaxf(fabsf(s.x[1]), fabsf(s.x[2]))) <= 1000.0f;
+    const bool near_origin = max_abs(s.x) <= 1000.0f;
     if (!(near_origin && in_box)) cand = (M)(n >= 64 ? ~0ull : (1ull << n) - 1ull);
     // the quad itself (distance 0) leaves the contact mask below anyway
     cand &= ~((M)1 << me);
@@ -908,14 +1038,20 @@ __device__ __forceinline__ unsigned long long pair_pass(const Consts& c, const f
       pair(jj, pj, FalseT{}, FalseT{});
     }
   } else {
-    for_partners<BS, N>(tile, ls, n,
-                        [&](int jj, const float* pj) { pair(jj, pj, FalseT{}, TrueT{}); });
-    if constexpr (ACC) cm = (M)(__builtin_bitreverse32(acc) >> (32 - N));
+    bool done = false;
+    if constexpr (CO && N != 8) done = near_pass<BS, N, P>(c, tile, s, ls, n, me, *pen, cm);
+    if (!done) {
+      for_partners<BS, N, XR, true>(tile, ls, n, [&](int jj, const float* pj) {
+        pair(jj, pj, FalseT{}, TrueT{});
+      });
+      if constexpr (ACC) cm = (M)(__builtin_bitreverse32(acc) >> (32 - N));
+    }
   }
   // (run-time sizes: nor the places past the swarm's end)
   if constexpr (N == 0) cm &= (M)(~0ull >> (64 - n));
   const unsigned long long cmask = collide ? (unsigned long long)(cm & ~((M)1 << me)) : 0ull;
   // The responses, for the partners in contact only, in partner order.
+  unsigned long long rm = 0ull;
   for (unsigned long long m = cmask; m != 0ull; m &= m - 1ull) {
     const int jj = __builtin_ctzll(m);
     const int j = ls + jj;
@@ -926,10 +1062,11 @@ __device__ __forceinline__ unsigned long long pair_pass(const Consts& c, const f
     if (!(c.flags & F_APPROACH) || sp > 0.f) {
 #pragma unroll
       for (int k = 0; k < 3; ++k) dv[k] = fmaf(sp, nn[k], dv[k]);
-      hit = true;
+      rm |= 1ull << jj;
     }
   }
-  if (hit) {
+  if (resp) *resp = rm;
+  if (rm != 0ull) {
     s.ev |= EVF_QUAD;
     float zv[4] = {0.f, 0.f, 0.f, 0.f}, zw[4] = {0.f, 0.f, 0.f, 0.f};
     if (c.col_nv > 0.0f || c.col_nw > 0.0f) {
@@ -958,19 +1095,21 @@ __device__ __forceinline__ unsigned long long pair_pass(const Consts& c, const f
   return cmask;
 }
 
-// The smoothed collision penalty of one live lane alone: the PEN term of
+// The penalty (or its adjoint) of one live lane alone: the P terms of
 // pair_pass (same partners, same order, same arithmetic), for a wavefront
-// that sums it apart from the motion.
-template <int BS, int N>
+// that sums them apart from the motion.  s: the quad's start position,
+// displacement and post-motion position.
+template <int BS, int N, int P>
 __device__ __forceinline__ void penalty_pass(const Consts& c, const float (*tile)[BS],
-                                             const Quad& s, int ls, int n, int me, float& pacc,
-                                             float beta) {
-  const float hb = 0.5f / beta;  // each quad of a pair carries half
-  for_partners<BS, N>(tile, ls, n, [&](int jj, const float* pj) {
+                                             const Quad& s, int ls, int n, int me, Pen& pen) {
+  if constexpr (N != 8) {
+    PairMask<N> contacts = 0;
+    if (near_pass<BS, N, P>(c, tile, s, ls, n, me, pen, contacts)) return;
+  }
+  for_partners<BS, N, P == PEN_GRAD ? PENROW : -1>(tile, ls, n, [&](int jj, const float* pj) {
     float dx, dy, dz, d2;
     pair_geom_v(c, pj, s, dx, dy, dz, d2);
-    const float sp = hb * softplus_hw(beta * (c.dcol - __builtin_amdgcn_sqrtf(d2)));
-    pacc = jj != me ? pacc + sp : pacc;
+    pen_term<P>(c, pen, P == PEN_GRAD || jj != me, pj[6], dx, dy, dz, d2);
   });
 }
 

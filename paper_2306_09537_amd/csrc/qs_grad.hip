@@ -25,7 +25,7 @@ bool use_rollout_pipe(const qs_handle* h) {
 template <int BS, int N, bool PEN>
 void go_roll(qs_handle* h, const float* act, int ncalls, int nsub, float* ckpt, int ce, float* pen,
              float beta, hipStream_t s) {
-  if constexpr (BS == 64 && (N == 1 || N == 8)) {
+  if constexpr (BS == 64 && (N == 8 || (N == 1 && !PEN))) {
     if (use_rollout_pipe(h)) {
       hipLaunchKernelGGL((qs::rollout_pipe_kernel<N, PEN>), dim3(h->nblk),
                          dim3(64 * qs::kRollWaves<N, PEN>), 0, s, h->d_c,
@@ -46,6 +46,9 @@ struct AdjScratch {
   float* gpar;
 };
 
+// Swarms above 32: the tape's word holds no contact set (tape_word).
+int is_wide(const qs_handle* h) { return h->max_n > 32 ? 1 : 0; }
+
 // The two-wavefront recompute (motor part one substep ahead) for small
 // batches, as the rollout (QS_RECOMPUTE_PIPE=0/1 forces it off/on).
 bool use_recompute_pipe(const qs_handle* h) {
@@ -55,18 +58,20 @@ bool use_recompute_pipe(const qs_handle* h) {
 
 template <int BS, int N, bool PEN>
 void go_recompute(qs_handle* h, const AdjScratch& sc, const float* ckpt, const float* act,
-                  int ncalls, int ce, int nsub, uint64_t t0, hipStream_t s) {
+                  int ncalls, int ce, int nsub, uint64_t t0, const float* gpen, float beta,
+                  hipStream_t s) {
   const int nseg = (ncalls + ce - 1) / ce;
-  if constexpr (BS == 64 && (N == 1 || N == 8)) {
+  if constexpr (BS == 64 && (N == 8 || (N == 1 && !PEN))) {
     if (use_recompute_pipe(h)) {
-      hipLaunchKernelGGL((qs::recompute_pipe_kernel<N>), dim3(h->nblk, nseg), dim3(128), 0, s,
-                         h->d_c, ptrs(h), ckpt, act, ncalls, ce, nsub, (unsigned long long)t0,
-                         sc.tape);
+      hipLaunchKernelGGL((qs::recompute_pipe_kernel<N, PEN>), dim3(h->nblk, nseg),
+                         dim3(PEN ? 192 : 128), 0, s, h->d_c, ptrs(h), ckpt, act, ncalls, ce, nsub,
+                         (unsigned long long)t0, sc.tape, is_wide(h), gpen, beta);
       return;
     }
   }
-  hipLaunchKernelGGL((qs::recompute_kernel<BS, N>), dim3(h->nblk, nseg), dim3(BS), 0, s, h->d_c,
-                     ptrs(h), ckpt, act, ncalls, ce, nsub, (unsigned long long)t0, sc.tape);
+  hipLaunchKernelGGL((qs::recompute_kernel<BS, N, PEN>), dim3(h->nblk, nseg), dim3(BS), 0, s,
+                     h->d_c, ptrs(h), ckpt, act, ncalls, ce, nsub, (unsigned long long)t0, sc.tape,
+                     is_wide(h), gpen, beta);
 }
 
 // The four-wavefront reverse sweep pays where the batch leaves SIMDs idle:
@@ -78,39 +83,40 @@ bool use_reverse_pipe(const qs_handle* h) {
 
 template <int N, bool PEN>
 void go_reverse_pipe(qs_handle* h, const AdjScratch& sc, const float* act, int ncalls, int nsub,
-                     uint64_t t0, const float* gpen, float beta, float* gact, hipStream_t s) {
+                     uint64_t t0, float* gact, hipStream_t s) {
   hipLaunchKernelGGL((qs::reverse_pipe_kernel<N, PEN>), dim3(h->nblk), dim3(256), 0, s, h->d_c,
-                     ptrs(h), act, ncalls, nsub, (unsigned long long)t0, sc.tape, sc.lam, gpen,
-                     beta, gact, sc.gpar);
+                     ptrs(h), act, ncalls, nsub, (unsigned long long)t0, sc.tape, sc.lam,
+                     is_wide(h), gact, sc.gpar);
 }
 
 template <int BS, int N, bool PEN>
 void go_reverse(qs_handle* h, const AdjScratch& sc, const float* act, int ncalls, int nsub,
-                uint64_t t0, const float* gpen, float beta, float* gact, hipStream_t s) {
-  if constexpr (BS == 64 && (N == 1 || N == 8)) {
+                uint64_t t0, float* gact, hipStream_t s) {
+  if constexpr (BS == 64 && (N == 8 || (N == 1 && !PEN))) {
     if (use_reverse_pipe(h)) {
-      go_reverse_pipe<N, PEN>(h, sc, act, ncalls, nsub, t0, gpen, beta, gact, s);
+      go_reverse_pipe<N, PEN>(h, sc, act, ncalls, nsub, t0, gact, s);
       return;
     }
   }
   hipLaunchKernelGGL((qs::reverse_kernel<BS, N, PEN>), dim3(h->nblk), dim3(BS), 0, s, h->d_c,
-                     ptrs(h), act, ncalls, nsub, (unsigned long long)t0, sc.tape, sc.lam, gpen,
-                     beta, gact, sc.gpar);
+                     ptrs(h), act, ncalls, nsub, (unsigned long long)t0, sc.tape, sc.lam,
+                     is_wide(h), gact, sc.gpar);
 }
 
 // Dispatch on (block size, uniform swarm size) for a launcher template F.
+// Callers pass no penalty for swarms of one, which have none.
 template <template <int, int, bool> class F, bool PEN, typename... A>
 void dispatch(qs_handle* h, A... a) {
   if (h->bs == 128) {
     switch (h->uniform_n) {
-      case 1: F<128, 1, PEN>::run(h, a...); break;
+      case 1: F<128, 1, false>::run(h, a...); break;
       case 8: F<128, 8, PEN>::run(h, a...); break;
       case 32: F<128, 32, PEN>::run(h, a...); break;
       default: F<128, 0, PEN>::run(h, a...); break;
     }
   } else {
     switch (h->uniform_n) {
-      case 1: F<64, 1, PEN>::run(h, a...); break;
+      case 1: F<64, 1, false>::run(h, a...); break;
       case 8: F<64, 8, PEN>::run(h, a...); break;
       case 32: F<64, 32, PEN>::run(h, a...); break;
       default: F<64, 0, PEN>::run(h, a...); break;
@@ -129,16 +135,17 @@ struct RollF {
 template <int BS, int N, bool PEN>
 struct RecF {
   static void run(qs_handle* h, const AdjScratch* sc, const float* ckpt, const float* act,
-                  int ncalls, int ce, int nsub, uint64_t t0, hipStream_t s) {
-    go_recompute<BS, N, PEN>(h, *sc, ckpt, act, ncalls, ce, nsub, t0, s);
+                  int ncalls, int ce, int nsub, uint64_t t0, const float* gpen, float beta,
+                  hipStream_t s) {
+    go_recompute<BS, N, PEN>(h, *sc, ckpt, act, ncalls, ce, nsub, t0, gpen, beta, s);
   }
 };
 
 template <int BS, int N, bool PEN>
 struct RevF {
   static void run(qs_handle* h, const AdjScratch* sc, const float* act, int ncalls, int nsub,
-                  uint64_t t0, const float* gpen, float beta, float* gact, hipStream_t s) {
-    go_reverse<BS, N, PEN>(h, *sc, act, ncalls, nsub, t0, gpen, beta, gact, s);
+                  uint64_t t0, float* gact, hipStream_t s) {
+    go_reverse<BS, N, PEN>(h, *sc, act, ncalls, nsub, t0, gact, s);
   }
 };
 
@@ -185,8 +192,9 @@ void convert(const float* src, float* dst, int Q, int rows, bool to_row_major, b
 }
 
 // Floats of tape one checkpoint segment needs.
-size_t segment_tape_floats(const qs_handle* h, int n_calls, int nsub, int ce) {
-  return (size_t)std::min(ce, n_calls) * nsub * qs::NTAPE * h->Q;
+size_t segment_tape_floats(const qs_handle* h, int n_calls, int nsub, int ce, bool pen) {
+  return (size_t)std::min(ce, n_calls) * nsub * (pen ? qs::kTapeRows<true> : qs::kTapeRows<false>) *
+         h->Q;
 }
 
 // Backward pass over n_calls calls with checkpoints every ce calls (ckpt:
@@ -205,11 +213,13 @@ int run_adjoint(qs_handle* h, const AdjScratch& sc, int G, const float* act, int
     const float* a = act + (size_t)c0 * h->Q * 4;
     float* ga = gact + (size_t)c0 * h->Q * 4;
     const uint64_t ts = t0 + (uint64_t)c0 * nsub;
-    dispatch<RecF, false>(h, &sc, ck, a, nc, ce, nsub, ts, s);
-    if (gpen)
-      dispatch<RevF, true>(h, &sc, a, nc, nsub, ts, gpen, beta, ga, s);
-    else
-      dispatch<RevF, false>(h, &sc, a, nc, nsub, ts, gpen, beta, ga, s);
+    if (gpen) {
+      dispatch<RecF, true>(h, &sc, ck, a, nc, ce, nsub, ts, gpen, beta, s);
+      dispatch<RevF, true>(h, &sc, a, nc, nsub, ts, ga, s);
+    } else {
+      dispatch<RecF, false>(h, &sc, ck, a, nc, ce, nsub, ts, gpen, beta, s);
+      dispatch<RevF, false>(h, &sc, a, nc, nsub, ts, ga, s);
+    }
     if (hipGetLastError() != hipSuccess) return QS_ERR_HIP;
   }
   return QS_OK;
@@ -321,6 +331,7 @@ int qs_rollout(qs_handle* h, const float* d_actions, int32_t n_calls, int32_t n_
   }
   if (hipSetDevice(h->dev) != hipSuccess) return QS_ERR_HIP;
   hipStream_t s = (hipStream_t)stream;
+  if (h->max_n == 1) d_penalty = nullptr;  // swarms of one have no penalty
   if (d_penalty)
     dispatch<RollF, true>(h, d_actions, (int)n_calls, (int)n_substeps, d_ckpt, (int)ckpt_every,
                           d_penalty, beta, s);
@@ -355,6 +366,7 @@ int qs_rollout_backward(qs_handle* h, const float* d_actions, int32_t n_calls,
   if (hipSetDevice(h->dev) != hipSuccess) return QS_ERR_HIP;
   int rc = ensure_adjoint_scratch(h);
   if (rc != QS_OK) return rc;
+  if (h->max_n == 1) d_gpenalty = nullptr;  // swarms of one have no penalty
   hipStream_t s = (hipStream_t)stream;
   convert(d_gstate, h->d_lam, h->Q, qs::NSTATE, false, false, s);
   hipLaunchKernelGGL(qs::fill_kernel, dim3((unsigned)((6LL * h->Q + 255) / 256)), dim3(256), 0, s,
@@ -362,7 +374,7 @@ int qs_rollout_backward(qs_handle* h, const float* d_actions, int32_t n_calls,
   // segments per chunk: as many as fit the tape budget (also the recompute
   // grid's y extent, at most 65535), at least one
   const int nseg = (n_calls + ckpt_every - 1) / ckpt_every;
-  const size_t seg = segment_tape_floats(h, n_calls, n_substeps, ckpt_every);
+  const size_t seg = segment_tape_floats(h, n_calls, n_substeps, ckpt_every, d_gpenalty != nullptr);
   const size_t fit = tape_budget() / (seg * sizeof(float));
   const int G = (int)std::max<size_t>(1, std::min<size_t>({(size_t)nseg, fit, (size_t)65535}));
   rc = grow(&h->d_tape, &h->tape_cap, (size_t)G * seg);
@@ -385,7 +397,7 @@ int qs_step_backward(qs_handle* h, const float* d_state_in, const float* d_actio
   if (hipSetDevice(h->dev) != hipSuccess) return QS_ERR_HIP;
   rc = ensure_adjoint_scratch(h);
   if (rc == QS_OK && n_substeps > 0)
-    rc = grow(&h->d_tape, &h->tape_cap, segment_tape_floats(h, 1, n_substeps, 1));
+    rc = grow(&h->d_tape, &h->tape_cap, segment_tape_floats(h, 1, n_substeps, 1, false));
   if (rc != QS_OK) return rc;
   const AdjScratch sc{h->d_tape, h->d_lam, h->d_gpar};
   return step_backward_run(h, sc, h->d_ck1, d_state_in, d_actions, n_substeps, substep_index,
@@ -403,7 +415,7 @@ int qs_step_backward_noalloc(qs_handle* h, const float* d_state_in, const float*
   auto part = [](size_t n) { return (n + 63) / 64 * 64; };
   const size_t Q = (size_t)h->Q;
   const size_t n_ck = part(qs::NSTATE * Q), n_lam = part(qs::NSTATE * Q), n_g = part(6 * Q);
-  const size_t n_tape = n_substeps > 0 ? part(segment_tape_floats(h, 1, n_substeps, 1)) : 0;
+  const size_t n_tape = n_substeps > 0 ? part(segment_tape_floats(h, 1, n_substeps, 1, false)) : 0;
   if (n_ck + n_lam + n_g + n_tape > kNoAllocScratchFloats) return QS_ERR_TOO_LARGE;
   if (hipSetDevice(h->dev) != hipSuccess) return QS_ERR_HIP;
   float* base = nullptr;

@@ -17,6 +17,7 @@ struct qs_handle {
   int dev = 0;
   int E = 0, Q = 0, Qp = 0, K = 0, OD = 0;
   int bs = 64, nblk = 0;
+  int max_n = 1;      // largest swarm
   int uniform_n = 0;  // every swarm holds this many quads (power of two), else 0
   Consts c{};
   Consts* d_c = nullptr;  // device copy of c, read by every kernel

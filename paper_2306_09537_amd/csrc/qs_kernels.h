@@ -299,17 +299,14 @@ __device__ __forceinline__ void step_body(const Consts& c, const Ptrs& p,
       quad_sync();
       cmask = 0ull;
       if (live) {
-        float unused = 0.f;
         if constexpr (SCREEN_KEYS) {
           if (sub == nsub - 1)
-            cmask = pair_pass<BS, NU, false, true, KT + 1>(c, tile, s, ls, n, me, (uint32_t)q, t,
-                                                            unused, 0.f, skey);
+            cmask = pair_pass<BS, NU, PEN_NONE, true, KT + 1>(c, tile, s, ls, n, me, (uint32_t)q,
+                                                              t, nullptr, skey);
           else
-            cmask = pair_pass<BS, NU, false, true>(c, tile, s, ls, n, me, (uint32_t)q, t, unused,
-                                                   0.f);
+            cmask = pair_pass<BS, NU, PEN_NONE, true>(c, tile, s, ls, n, me, (uint32_t)q, t);
         } else {
-          cmask = pair_pass<BS, NU, false, true>(c, tile, s, ls, n, me, (uint32_t)q, t, unused,
-                                                 0.f);
+          cmask = pair_pass<BS, NU, PEN_NONE, true>(c, tile, s, ls, n, me, (uint32_t)q, t);
         }
       }
     }

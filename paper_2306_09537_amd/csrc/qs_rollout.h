@@ -1,26 +1,16 @@
 // Differentiable rollouts: a multi-call forward kernel (a fresh action per
 // call, checkpoints of the state, the smoothed collision penalty) and the
 // backward pass: a kernel that recomputes checkpoint segments in parallel,
-// taping the per-substep states and motor-noise draws, and a kernel that
+// taping what the reverse sweep needs of each substep, and a kernel that
 // sweeps the tape in reverse.
 //
 // Layouts: checkpoints and adjoint scratch are field-major [27][Q], tape
-// rows [31][Q] (state and draws; coalesced per field); actions and their
-// gradients are [call][Q][4].
+// rows [31][Q] or, with the penalty, [34][Q] (coalesced per field); actions
+// and their gradients are [call][Q][4].
 #pragma once
 #include "qs_adjoint.h"
 
 namespace qs {
-
-// Partner count the forward rollout's in-swarm loop is specialised for.
-// With the penalty, swarms of 16 and more take their partners in chunks of
-// four in a run-time loop (for_partners; 118 VGPRs at 32768 x 32, four
-// wavefronts per SIMD), which measured faster than one partner at a time
-// (forward 3.76 -> 3.43 ms; a fully unrolled loop had taken 6.4 ms against
-// 4.2 for one at a time).  Without the penalty the chunked loop would
-// cross 128 VGPRs, so those rollouts loop one partner at a time.
-template <int N, bool PEN>
-constexpr int kUnroll = (PEN || N < 16) ? N : 0;
 
 // Workgroup -> quads mapping shared by the kernels (see step_kernel).
 template <int BS, int N>
@@ -59,6 +49,8 @@ __device__ __forceinline__ void load_state(const float* __restrict__ S, long lon
   s.ev = 0u;
 }
 
+// FLAG: the resting flag too (a tape row has a word of its own there).
+template <bool FLAG = true>
 __device__ __forceinline__ void store_state(float* __restrict__ S, long long ld, int q,
                                             const Quad& s) {
 #pragma unroll
@@ -73,12 +65,35 @@ __device__ __forceinline__ void store_state(float* __restrict__ S, long long ld,
   for (int k = 0; k < 4; ++k) S[(S_U + k) * ld + q] = s.u[k];
 #pragma unroll
   for (int k = 0; k < 4; ++k) S[(S_E + k) * ld + q] = s.e[k];
-  S[S_F * ld + q] = s.fl;
+  if constexpr (FLAG) S[S_F * ld + q] = s.fl;
 }
 
-// A tape row: the state at the start of a substep (27 fields) and the
-// motor-noise draws of that substep (4 fields), field-major over Q quads.
-constexpr int NTAPE = NSTATE + 4;
+// A tape row, field-major over Q quads: the state at the start of a substep
+// (27 fields, the resting flag as part of a word, below), the motor-noise
+// draws of that substep (4 fields) and, with the penalty, its adjoint w.r.t.
+// the position after the motion (3 fields).  The recompute passes over the
+// partners anyway, at twice the reverse sweep's occupancy and bound by the
+// tape's stores, so it is the place for what the partners add; the sweep had
+// passed over them again (32768 x 32, 100 substeps: recompute 3.44 -> 3.82,
+// sweep 5.71 -> 4.16 ms).
+template <bool PEN>
+constexpr int kTapeRows = NSTATE + 4 + (PEN ? 3 : 0);
+constexpr int T_PEN = NSTATE + 4;
+
+// The word in the resting flag's field: the partners whose collision response
+// the quad received in the substep, and, on the quad's own place, the resting
+// flag.  Handles with swarms above 32 (wide) keep the flag alone, in bit 0,
+// and the sweep finds their contacts again.
+__device__ __forceinline__ float tape_word(float fl, unsigned long long resp, int me, int wide) {
+  const uint32_t f = fl != 0.f ? 1u : 0u;
+  return __uint_as_float(wide ? f : (uint32_t)resp | f << me);
+}
+__device__ __forceinline__ float word_flag(uint32_t w, int me, int wide) {
+  return (wide ? w : w >> me) & 1u ? 1.f : 0.f;
+}
+__device__ __forceinline__ uint32_t word_resp(uint32_t w, int me, int wide) {
+  return wide ? 0u : w & ~(1u << me);
+}
 
 __device__ __forceinline__ void load_draws(const Consts& c, const float* __restrict__ row,
                                            long long ld, int q, float z[4]) {
@@ -86,6 +101,12 @@ __device__ __forceinline__ void load_draws(const Consts& c, const float* __restr
 #pragma unroll
     for (int i = 0; i < 4; ++i) z[i] = row[(NSTATE + i) * ld + q];
   }
+}
+
+__device__ __forceinline__ void load_pen(const float* __restrict__ row, long long ld, int q,
+                                         float pen3[3]) {
+#pragma unroll
+  for (int k = 0; k < 3; ++k) pen3[k] = row[(T_PEN + k) * ld + q];
 }
 
 __device__ __forceinline__ void load_params(const Ptrs& p, const Consts& c, int q, QuadPar& pp,
@@ -147,12 +168,12 @@ __device__ __forceinline__ float duhat_da(const Consts& c, float a, float uhat) 
 // sum over substeps and env-mates of softplus(beta (d_col - d))/(2 beta).
 // ---------------------------------------------------------------------------
 template <int BS, int N, bool PEN>
-__global__ __launch_bounds__(BS) void rollout_kernel(const Consts* __restrict__ cp, Ptrs p,
+__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(N == 8 && PEN ? 3 : 4))) void rollout_kernel(const Consts* __restrict__ cp, Ptrs p,
                                                      const float* __restrict__ act, int ncalls,
                                                      int nsub, unsigned long long t0,
                                                      float* __restrict__ ckpt, int ckpt_every,
                                                      float* __restrict__ pen, float beta) {
-  __shared__ float sxv[2][9][BS];
+  __shared__ float sxv[2][TILE_ROWS_CO][BS];
   const Consts& c = *cp;
   const int tid = threadIdx.x;
   int qb, cnt, ls, n;
@@ -170,7 +191,9 @@ __global__ __launch_bounds__(BS) void rollout_kernel(const Consts* __restrict__ 
     load_params(p, c, q, pp, pa);
   }
   const bool pairs = N != 1 && ((c.flags & (F_COLLIDE | F_DOWNWASH)) != 0 || PEN);
-  float pacc = 0.f;
+  constexpr int P = PEN ? PEN_SUM : PEN_NONE;
+  Pen pn;
+  if constexpr (PEN) pn = make_pen(c, beta, N > 0 ? N : wave_max(live ? n : 0));
   int sidx = 0;
   float4 a_nx = make_float4(0.f, 0.f, 0.f, 0.f);
   if (live && ncalls > 0) a_nx = load_act(act, q);
@@ -193,9 +216,10 @@ __global__ __launch_bounds__(BS) void rollout_kernel(const Consts* __restrict__ 
             tile[3 + k][tid] = s.inc[k];
             tile[6 + k][tid] = s.v[k];
           }
+          put_screen_rows<kScreenSq<N>>(tile, tid, s.x);
         }
         __syncthreads();
-        if (live) pair_pass<BS, kUnroll<N, PEN>, PEN>(c, tile, s, ls, n, me, (uint32_t)q, t, pacc, beta);
+        if (live) pair_pass<BS, N, P, true>(c, tile, s, ls, n, me, (uint32_t)q, t, &pn);
       }
     }
   }
@@ -208,7 +232,7 @@ __global__ __launch_bounds__(BS) void rollout_kernel(const Consts* __restrict__ 
     for (int k = 0; k < 9; ++k) chk += s.R[k];
     if (!isfinite(chk))
       __hip_atomic_fetch_or(p.err, ERRBIT_STATE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if constexpr (PEN) pen[q] += pacc;
+    if constexpr (PEN) pen[q] += pn.acc[0];
   }
 }
 
@@ -218,20 +242,24 @@ __global__ __launch_bounds__(BS) void rollout_kernel(const Consts* __restrict__ 
 //
 // recompute_kernel, grid (workgroups, segments of the chunk): workgroup
 // (b, g) re-runs segment g of the chunk from its checkpoint ckpt + g 27 Q
-// and tapes, for the chunk's k-th substep, the state at its start and its
-// motor-noise draws, tape[k][31][Q] (the reverse sweep then re-runs the
-// substep without regenerating the draws).  Given the checkpoints the
-// segments are independent, so a chunk is recomputed in one parallel launch.
+// and tapes the chunk's k-th substep in row k (the reverse sweep then re-runs
+// the substep without regenerating the draws and without a pass over the
+// partners).  Given the checkpoints the segments are independent, so a chunk
+// is recomputed in one parallel launch.
 //  act: the chunk's first call; ncalls: calls in the chunk; t0: substep
-//  index of the chunk's first substep.
+//  index of the chunk's first substep; wide: see tape_word; gpen: dL/d pen
+//  (PEN).
 // ---------------------------------------------------------------------------
-template <int BS, int N>
-__global__ __launch_bounds__(BS) void recompute_kernel(const Consts* __restrict__ cp, Ptrs p,
+template <int BS, int N, bool PEN>
+__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(N == 8 && PEN ? 3 : 4))) void recompute_kernel(const Consts* __restrict__ cp, Ptrs p,
                                                        const float* __restrict__ ckpt,
                                                        const float* __restrict__ act, int ncalls,
                                                        int ce, int nsub, unsigned long long t0,
-                                                       float* __restrict__ tape) {
-  __shared__ float sxv[2][TILE_ROWS_CO][BS];
+                                                       float* __restrict__ tape, int wide,
+                                                       const float* __restrict__ gpen,
+                                                       float beta) {
+  constexpr int P = PEN ? PEN_GRAD : PEN_NONE, NTAPE = kTapeRows<PEN>;
+  __shared__ float sxv[2][PEN ? PENROW + 1 : TILE_ROWS_CO][BS];
   const Consts& c = *cp;
   const int tid = threadIdx.x;
   int qb, cnt, ls, n;
@@ -242,11 +270,18 @@ __global__ __launch_bounds__(BS) void recompute_kernel(const Consts* __restrict_
   const long long Q = p.Q;
   const int c0 = blockIdx.y * ce;
   const int nc = min(ce, ncalls - c0);
-  const bool pairs = N != 1 && (c.flags & (F_COLLIDE | F_DOWNWASH)) != 0;
+  const bool pairs = N != 1 && (PEN || (c.flags & (F_COLLIDE | F_DOWNWASH)) != 0);
 
   Quad s;
   QuadPar pp;
   ParAdj pa;
+  Pen pn;
+  if constexpr (PEN) {
+    const float h_me = live ? -0.5f * gpen[q] : 0.f;
+    sxv[0][PENROW][tid] = h_me;
+    sxv[1][PENROW][tid] = h_me;
+    pn = make_pen(c, beta, N > 0 ? N : wave_max(live ? n : 0), h_me);
+  }
   if (live) {
     load_state(ckpt + (long long)blockIdx.y * NSTATE * Q, Q, q, s);
     load_params(p, c, q, pp, pa);
@@ -261,9 +296,11 @@ __global__ __launch_bounds__(BS) void recompute_kernel(const Consts* __restrict_
     if (live) act_uhat(c, p, a4, uhat);
     for (int sub = 0; sub < nsub; ++sub, ++sidx) {
       const unsigned long long t = t0 + (unsigned long long)sidx;
+      float* row = tape + (long long)sidx * NTAPE * Q;
+      const float fl0 = s.fl;
+      unsigned long long resp = 0ull;
       if (live) {
-        float* row = tape + (long long)sidx * NTAPE * Q;
-        store_state(row, Q, q, s);
+        store_state<false>(row, Q, q, s);
         float z[4];
         quad_substep<false, Z_EXPORT>(c, pp, s, uhat, (uint32_t)q, t, nullptr, z);
         if (c.flags & F_NOISE) {
@@ -283,9 +320,16 @@ __global__ __launch_bounds__(BS) void recompute_kernel(const Consts* __restrict_
           put_screen_rows<kScreenSq<N>>(tile, tid, s.x);
         }
         __syncthreads();
-        float unused = 0.f;
-        if (live) pair_pass<BS, N, false, true>(c, tile, s, ls, n, me, (uint32_t)q, t, unused, 0.f);
+        if (live) {
+          if constexpr (PEN) pn.acc[0] = pn.acc[1] = pn.acc[2] = 0.f;
+          pair_pass<BS, N, P, true>(c, tile, s, ls, n, me, (uint32_t)q, t, &pn, nullptr, &resp);
+          if constexpr (PEN) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k) row[(T_PEN + k) * Q + q] = pn.acc[k];
+          }
+        }
       }
+      if (live) row[S_F * Q + q] = tape_word(fl0, resp, me, wide);
     }
   }
 }
@@ -306,26 +350,44 @@ __device__ __forceinline__ void load_body(const float* __restrict__ row, long lo
   s.ev = 0u;
 }
 
+// A quad's start position, displacement, velocity and post-motion position
+// from its column of an exchange tile.
+template <int BS>
+__device__ __forceinline__ Quad tile_quad(const float (*tile)[BS], int tid) {
+  Quad s;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    s.xo[k] = tile[k][tid];
+    s.inc[k] = tile[3 + k][tid];
+    s.v[k] = tile[6 + k][tid];
+    s.x[k] = tile[XROW + k][tid];
+  }
+  return s;
+}
+
 // recompute_pipe_kernel: recompute_kernel for small batches (swarms of 1
-// or 8, up to 1024 workgroups of 64 quads), over two wavefronts per
+// or 8, up to 1024 workgroups of 64 quads), over two or three wavefronts per
 // workgroup as in rollout_pipe_kernel: wavefront 0 runs the motor part of
 // each substep one substep ahead (taping the rotor state and the draws) and
 // hands thrust and torques through a two-slot LDS ring; wavefront 1 tapes the
-// pose, velocity, rates and floor flag, runs the body part and the in-swarm
-// pass.  Same arithmetic in the same order as recompute_kernel, so the tape
-// is identical.
+// pose, velocity, rates and the word, runs the body part and the in-swarm
+// pass; with a penalty wavefront 2 tapes its adjoint one substep behind.
+// Same arithmetic in the same order as recompute_kernel, so the tape is
+// identical.
 // ---------------------------------------------------------------------------
-template <int N>
-__global__ __launch_bounds__(128) void recompute_pipe_kernel(const Consts* __restrict__ cp,
+template <int N, bool PEN>
+__global__ __launch_bounds__(192) void recompute_pipe_kernel(const Consts* __restrict__ cp,
                                                              Ptrs p,
                                                              const float* __restrict__ ckpt,
                                                              const float* __restrict__ act,
                                                              int ncalls, int ce, int nsub,
                                                              unsigned long long t0,
-                                                             float* __restrict__ tape) {
-  constexpr int BS = 64;
-  static_assert(N == 1 || N == 8, "pipelined recompute for swarms of 1 or 8");
-  __shared__ float sxv[2][TILE_ROWS_CO][BS];
+                                                             float* __restrict__ tape, int wide,
+                                                             const float* __restrict__ gpen,
+                                                             float beta) {
+  constexpr int BS = 64, NTAPE = kTapeRows<PEN>;
+  static_assert(N == 8 || (N == 1 && !PEN), "pipelined recompute for swarms of 1 or 8");
+  __shared__ float sxv[2][PENROW + 1][BS];
   __shared__ float ring[2][4][BS];
   const Consts& c = *cp;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -340,6 +402,7 @@ __global__ __launch_bounds__(128) void recompute_pipe_kernel(const Consts* __res
   const int nc = min(ce, ncalls - c0);
   const int n_steps = nc * nsub;  // substeps of the segment
   const int s0 = c0 * nsub;       // its first substep within the chunk
+  const int n_pipe = n_steps + (PEN ? 2 : 1);  // steps of the pipeline
   const float* ck = ckpt + (long long)blockIdx.y * NSTATE * Q;
   QuadPar pp;
   ParAdj pa;
@@ -358,7 +421,7 @@ __global__ __launch_bounds__(128) void recompute_pipe_kernel(const Consts* __res
     float uhat[4] = {0.f, 0.f, 0.f, 0.f};
     float4 a_nx = make_float4(0.f, 0.f, 0.f, 0.f);
     if (live && nc > 0) a_nx = load_act(act + (long long)c0 * Q * 4, q);
-    for (int i = 0; i <= n_steps; ++i) {
+    for (int i = 0; i < n_pipe; ++i) {
       if (i < n_steps) {
         const int cl = i / nsub, sub = i - cl * nsub;
         const int call = c0 + cl;
@@ -392,94 +455,91 @@ __global__ __launch_bounds__(128) void recompute_pipe_kernel(const Consts* __res
     }
   } else {
     // ---- body part and in-swarm pass of substep i - 1 at step i
-    Quad s;
-    if (live) load_body(ck, Q, q, s);
-    const bool pairs = N != 1 && (c.flags & (F_COLLIDE | F_DOWNWASH)) != 0;
-    wg_sync();  // step 0: no thrust yet
-    for (int i = 1; i <= n_steps; ++i) {
-      const int sidx = i - 1;
-      const unsigned long long t = t0 + (unsigned long long)(s0 + sidx);
-      if (live) {
+    if (wave == 1) {
+      Quad s;
+      if (live) load_body(ck, Q, q, s);
+      const bool pairs = N != 1 && (c.flags & (F_COLLIDE | F_DOWNWASH)) != 0;
+      wg_sync();  // step 0: no thrust yet
+      for (int i = 1; i < n_pipe; ++i) {
+        const int sidx = i - 1;
+        const unsigned long long t = t0 + (unsigned long long)(s0 + sidx);
         float* row = tape + (long long)(s0 + sidx) * NTAPE * Q;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          row[(S_X + k) * Q + q] = s.x[k];
-          row[(S_V + k) * Q + q] = s.v[k];
-          row[(S_W + k) * Q + q] = s.w[k];
-        }
-#pragma unroll
-        for (int k = 0; k < 9; ++k) row[(S_R + k) * Q + q] = s.R[k];
-        row[S_F * Q + q] = s.fl;
-        const float(*slot)[BS] = ring[sidx & 1];
-        Drive d;
-        d.T = slot[0][tid];
-        d.tx = slot[1][tid];
-        d.ty = slot[2][tid];
-        d.tz = slot[3][tid];
-        body_step(c, pp, s, d, (uint32_t)q, t);
-      }
-      if (pairs) {
-        float(*tile)[BS] = sxv[sidx & 1];
-        if (live) {
+        const float fl0 = s.fl;
+        unsigned long long resp = 0ull;
+        const bool run = i <= n_steps && live;
+        if (run) {
 #pragma unroll
           for (int k = 0; k < 3; ++k) {
-            tile[k][tid] = s.xo[k];
-            tile[3 + k][tid] = s.inc[k];
-            tile[6 + k][tid] = s.v[k];
+            row[(S_X + k) * Q + q] = s.x[k];
+            row[(S_V + k) * Q + q] = s.v[k];
+            row[(S_W + k) * Q + q] = s.w[k];
           }
-          put_screen_rows<kScreenSq<N>>(tile, tid, s.x);
+#pragma unroll
+          for (int k = 0; k < 9; ++k) row[(S_R + k) * Q + q] = s.R[k];
+          const float(*slot)[BS] = ring[sidx & 1];
+          Drive d;
+          d.T = slot[0][tid];
+          d.tx = slot[1][tid];
+          d.ty = slot[2][tid];
+          d.tz = slot[3][tid];
+          body_step(c, pp, s, d, (uint32_t)q, t);
         }
-        wave_sync();
-        float unused = 0.f;
-        if (live) pair_pass<BS, N, false, true>(c, tile, s, ls, n, me, (uint32_t)q, t, unused, 0.f);
+        if (pairs || PEN) {
+          float(*tile)[BS] = sxv[sidx & 1];
+          if (run) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+              tile[k][tid] = s.xo[k];
+              tile[3 + k][tid] = s.inc[k];
+              tile[6 + k][tid] = s.v[k];
+            }
+            put_screen_rows<kScreenSq<N>>(tile, tid, s.x);
+          }
+          wave_sync();
+          if (run && pairs)
+            pair_pass<BS, N, PEN_NONE, true>(c, tile, s, ls, n, me, (uint32_t)q, t, nullptr,
+                                             nullptr, &resp);
+        }
+        if (run) row[S_F * Q + q] = tape_word(fl0, resp, me, wide);
+        wg_sync();
       }
+    } else if constexpr (PEN) {
+      // ---- the penalty's adjoint of substep i - 2 at step i
+      const float h_me = live ? -0.5f * gpen[q] : 0.f;
+      sxv[0][PENROW][tid] = h_me;
+      sxv[1][PENROW][tid] = h_me;
+      Pen pn = make_pen(c, beta, N > 0 ? N : wave_max(live ? n : 0), h_me);
+      wg_sync();  // steps 0 and 1: no tile yet
       wg_sync();
+      for (int i = 2; i < n_pipe; ++i) {
+        if (live) {
+          const float(*tile)[BS] = sxv[(i - 2) & 1];
+          const Quad so = tile_quad(tile, tid);
+          pn.acc[0] = pn.acc[1] = pn.acc[2] = 0.f;
+          penalty_pass<BS, N, PEN_GRAD>(c, tile, so, ls, n, me, pn);
+          float* row = tape + (long long)(s0 + i - 2) * NTAPE * Q;
+#pragma unroll
+          for (int k = 0; k < 3; ++k) row[(T_PEN + k) * Q + q] = pn.acc[k];
+        }
+        wg_sync();
+      }
     }
   }
 }
 
-// One branch-free pass over the partners of a substep in the reverse sweep:
-// the contact set (the quad itself excluded) and, with the penalty, its
-// adjoint w.r.t. the quad's position,
-//   d pen / d x_i = -(g_i + g_j)/2 sigmoid(beta (d_col - d)) (x_i - x_j) / d,
-// summed over the partners in partner order into pen3 (added to lambda_x by
-// the caller).  h_me = -g_me/2, and row 12 of the tile holds -g_j/2 for the
-// partners (halving is exact, so h_me + h_j rounds as -(g_me + g_j)/2).
-template <int BS, int N, bool PEN, typename T>
-__device__ __forceinline__ unsigned long long mark_contacts(const Consts& c, T tile, const Quad& s,
-                                                            int ls, int n, int me, float beta,
-                                                            float h_me, float pen3[3]) {
-  const bool collide = (c.flags & F_COLLIDE) != 0;
-  PairMask<N> cm32 = 0;
-  // Swarms of 16 and 32: partners arrive in index order, so the contact
-  // bits are shifted in ((acc << 1) | sign bit of d^2 - d_col^2, one funnel
-  // shift; for finite d^2 the sign of the difference is exactly the outcome
-  // of the comparison)
-  // and bit-reversed once, as in the forward screen.
-  constexpr bool ACC = N >= 16 && N <= 32;
-  uint32_t acc = 0u;
-  auto mark = [&](int jj, const float* pj) {
+// The contact set of a substep in the reverse sweep of handles with swarms
+// above 32, whose tape does not hold it (the quad itself excluded).
+template <int BS>
+__device__ __forceinline__ unsigned long long mark_contacts(const Consts& c,
+                                                            const float (*tile)[BS], const Quad& s,
+                                                            int ls, int n, int me) {
+  unsigned long long cm = 0ull;
+  for_partners<BS, 0>(tile, ls, n, [&](int jj, const float* pj) {
     float dx, dy, dz, d2;
-    const bool con = pair_geom_v(c, pj, s, dx, dy, dz, d2);
-    if constexpr (ACC)
-      acc = __builtin_amdgcn_alignbit(acc, __float_as_uint(d2 - c.dcol2), 31u);
-    else
-      cm32 |= (collide & con) ? (PairMask<N>)1 << jj : (PairMask<N>)0;
-    if constexpr (PEN) {
-      // the quad itself has d^2 = 0 exactly, so d^2 > 0 also leaves it out
-      const float rd = __builtin_amdgcn_rsqf(d2);
-      const float coef = d2 > 0.f
-                             ? (h_me + pj[6]) * sigmoid_hw(beta * (c.dcol - d2 * rd)) * rd
-                             : 0.f;
-      pen3[0] = fmaf(coef, dx, pen3[0]);
-      pen3[1] = fmaf(coef, dy, pen3[1]);
-      pen3[2] = fmaf(coef, dz, pen3[2]);
-    }
-  };
-  for_partners<BS, N, PEN ? 12 : -1>(tile, ls, n, mark);
-  if constexpr (ACC) cm32 = collide ? (PairMask<N>)(__builtin_bitreverse32(acc) >> (32 - N)) : 0;
-  if constexpr (N == 0) cm32 &= (PairMask<N>)(~0ull >> (64 - n));  // run-time sizes: members only
-  return (unsigned long long)(cm32 & ~((PairMask<N>)1 << me));  // not the quad itself
+    cm |= pair_geom_v(c, pj, s, dx, dy, dz, d2) ? 1ull << jj : 0ull;
+  });
+  cm &= ~0ull >> (64 - n) & ~(1ull << me);
+  return (c.flags & F_COLLIDE) ? cm : 0ull;
 }
 
 // Approach test of the contact set: does the quad receive a response?
@@ -538,22 +598,22 @@ __device__ __forceinline__ void response_vjp(const Consts& c, const float (*tile
 // last to first, from the tape; the adjoint of the state stays in
 // registers for the whole chunk and the tape row of the next substep to
 // process is loaded while the current one is differentiated.
-//  lam: [27][Q] dL/d(chunk end) in, dL/d(chunk start) out; gpen: dL/d pen
-//  (PEN); act/gact: the chunk's first call; gpar: [6][Q]
-//  dL/d(m, ixx, iyy, izz, t2w, tau), accumulated.
+//  lam: [27][Q] dL/d(chunk end) in, dL/d(chunk start) out; act/gact: the
+//  chunk's first call; gpar: [6][Q] dL/d(m, ixx, iyy, izz, t2w, tau),
+//  accumulated.
 // ---------------------------------------------------------------------------
 template <int BS, int N, bool PEN>
 __global__ __launch_bounds__(BS) void reverse_kernel(const Consts* __restrict__ cp, Ptrs p,
                                                      const float* __restrict__ act, int ncalls,
                                                      int nsub, unsigned long long t0,
                                                      const float* __restrict__ tape,
-                                                     float* __restrict__ lam,
-                                                     const float* __restrict__ gpen, float beta,
+                                                     float* __restrict__ lam, int wide,
                                                      float* __restrict__ gact,
                                                      float* __restrict__ gpar) {
+  constexpr int NTAPE = kTapeRows<PEN>;
   // rows 0-8 as in the forward tile; 9-11: adjoint of the collision
-  // velocity change; 12: penalty weight dL/d pen
-  __shared__ float tl[13][BS];
+  // velocity change
+  __shared__ float tl[12][BS];
   const Consts& c = *cp;
   const int tid = threadIdx.x;
   int qb, cnt, ls, n;
@@ -562,12 +622,12 @@ __global__ __launch_bounds__(BS) void reverse_kernel(const Consts* __restrict__ 
   const int q = qb + (live ? tid : 0);
   const int me = tid - ls;
   const long long Q = p.Q;
-  const bool collide = (c.flags & F_COLLIDE) != 0;
-  const bool pairs = N != 1 && (collide || PEN);
+  const bool pairs = N != 1 && (c.flags & F_COLLIDE) != 0;
   float(*tile)[BS] = tl;
 
   Quad s, sn;
   float z[4], zn[4] = {0.f, 0.f, 0.f, 0.f};  // motor-noise draws of s and sn
+  float pn[3] = {0.f, 0.f, 0.f}, pen3[3];     // penalty adjoint of sn and s
   QuadPar pp;
   ParAdj pa;
   const int n_steps = ncalls * nsub;
@@ -575,9 +635,7 @@ __global__ __launch_bounds__(BS) void reverse_kernel(const Consts* __restrict__ 
     load_params(p, c, q, pp, pa);
     load_state(tape + (long long)(n_steps - 1) * NTAPE * Q, Q, q, sn);
     load_draws(c, tape + (long long)(n_steps - 1) * NTAPE * Q, Q, q, zn);
-  }
-  if constexpr (PEN) {
-    tl[12][tid] = live ? -0.5f * gpen[q] : 0.f;  // -g/2 (mark_contacts)
+    if constexpr (PEN) load_pen(tape + (long long)(n_steps - 1) * NTAPE * Q, Q, q, pn);
   }
 
   // ---- reverse sweep
@@ -609,18 +667,35 @@ __global__ __launch_bounds__(BS) void reverse_kernel(const Consts* __restrict__ 
       const int k_s = call * nsub + sub;
       const unsigned long long t = t0 + (unsigned long long)k_s;
       Rec r;
+      unsigned long long cm = 0ull;  // partners whose response the quad received
       if (live) {
         s = sn;
+        const uint32_t word = __float_as_uint(s.fl);
+        s.fl = word_flag(word, me, wide);
+        cm = word_resp(word, me, wide);
 #pragma unroll
         for (int i = 0; i < 4; ++i) z[i] = zn[i];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) pen3[k] = pn[k];
         if (k_s > 0) {
           const float* row = tape + (long long)(k_s - 1) * NTAPE * Q;
           load_state(row, Q, q, sn);
           load_draws(c, row, Q, q, zn);
+          if constexpr (PEN) load_pen(row, Q, q, pn);
         }
         quad_substep<true, Z_IMPORT>(c, pp, s, uhat, (uint32_t)q, t, &r, z);
+        if constexpr (PEN) {
+#pragma unroll
+          for (int k = 0; k < 3; ++k) l.x[k] += pen3[k];
+        }
       }
-      if (pairs) {
+      // the exchange, where a quad of the workgroup received a response (rare)
+      bool any = wide != 0;
+      if (pairs && !any) {
+        if constexpr (BS == 64) any = __ballot(cm != 0ull) != 0ull;
+        else any = __syncthreads_or(cm != 0ull) != 0;
+      }
+      if (pairs && any) {
         __syncthreads();  // previous readers of the tile are done
         if (live) {
 #pragma unroll
@@ -631,21 +706,14 @@ __global__ __launch_bounds__(BS) void reverse_kernel(const Consts* __restrict__ 
           }
         }
         __syncthreads();
-        // which quads responded, and the adjoint of their velocity change:
-        // one branch-free pass over the partners gives the contact set and
-        // the penalty's adjoint (penalty weights in row 12, written before the
-        // sweep); the approach test runs for the (rare) contacts only
-        bool hit = false;
-        unsigned long long cm = 0ull;  // contact set of this substep
-        if (live) {
-          float pen3[3] = {0.f, 0.f, 0.f};
-          cm = mark_contacts<BS, N, PEN>(c, tile, s, ls, n, me, beta, tile[12][tid], pen3);
-          if constexpr (PEN) {
-#pragma unroll
-            for (int k = 0; k < 3; ++k) l.x[k] += pen3[k];
+        bool hit = cm != 0ull;
+        if constexpr (N == 0) {
+          if (wide && live) {
+            cm = mark_contacts<BS>(c, tile, s, ls, n, me);
+            hit = any_response<BS>(c, tile, s, ls, me, cm);
           }
-          hit = any_response<BS>(c, tile, s, ls, me, cm);
         }
+        // the adjoint of the quad's velocity change
         float ldv[3] = {0.f, 0.f, 0.f};
         if (live && hit) {
 #pragma unroll
@@ -780,16 +848,15 @@ __global__ __launch_bounds__(256) void reverse_pipe_kernel(const Consts* __restr
                                                            int ncalls, int nsub,
                                                            unsigned long long t0,
                                                            const float* __restrict__ tape,
-                                                           float* __restrict__ lam,
-                                                           const float* __restrict__ gpen,
-                                                           float beta, float* __restrict__ gact,
+                                                           float* __restrict__ lam, int wide,
+                                                           float* __restrict__ gact,
                                                            float* __restrict__ gpar) {
-  constexpr int BS = 64;
+  constexpr int BS = 64, NTAPE = kTapeRows<PEN>;
   static_assert(N == 1 || N == 8, "pipelined reverse sweep for swarms of 1 or 8");
   // Slots are indexed by the substep k.  Tile rows 0-8 post-motion start
   // position, displacement, velocity (wavefront 1); 9-11 adjoint of the
-  // collision velocity change (wavefront 3); 12 penalty weights.
-  __shared__ float tl[3][13][BS];
+  // collision velocity change (wavefront 3).
+  __shared__ float tl[3][12][BS];
   __shared__ float4 ring[3][RING_VEC][BS];
   __shared__ float4 mring[4][MOTOR_VEC][BS];
   __shared__ float cring[2][CON_WORDS][BS];
@@ -810,11 +877,6 @@ __global__ __launch_bounds__(256) void reverse_pipe_kernel(const Consts* __restr
   QuadPar pp;
   ParAdj pa;
   if (live) load_params(p, c, q, pp, pa);
-  if (PEN && wave == 2) {
-    const float g = live ? -0.5f * gpen[q] : 0.f;  // -g/2 (mark_contacts)
-#pragma unroll
-    for (int m = 0; m < 3; ++m) tl[m][12][tid] = g;
-  }
 
   if (wave == 0) {
     // ---- motor part of substep k = n_steps - 1 - i at step i
@@ -871,6 +933,7 @@ __global__ __launch_bounds__(256) void reverse_pipe_kernel(const Consts* __restr
       if (i <= n_steps && live) {
         const int k = n_steps - i;
         Quad s = sn;
+        s.fl = word_flag(__float_as_uint(s.fl), me, wide);
         if (k > 0) load_body(tape + (long long)(k - 1) * NTAPE * Q, Q, q, sn);
         const float4 dv = mring[k & 3][3][tid];
         Drive d;
@@ -904,27 +967,25 @@ __global__ __launch_bounds__(256) void reverse_pipe_kernel(const Consts* __restr
   } else if (wave == 2) {
     // ---- contacts of substep k = n_steps + 1 - i at step i >= 2
     wg_sync();  // steps 0 and 1: no exchange tile yet
+    uint32_t wn = 0u;
+    float pn[3] = {0.f, 0.f, 0.f};
+    auto load = [&](int k) {
+      const float* row = tape + (long long)k * NTAPE * Q;
+      wn = __float_as_uint(row[S_F * Q + q]);
+      if constexpr (PEN) load_pen(row, Q, q, pn);
+    };
+    if (live && n_steps > 0) load(n_steps - 1);
     wg_sync();
     for (int i = 2; i < n_pipe; ++i) {
       if (pairs && i <= n_steps + 1 && live) {
         const int k = n_steps + 1 - i;
-        const float(*tile)[BS] = tl[k % 3];
-        Quad so;  // the quad's post-motion position and velocity
-#pragma unroll
-        for (int m = 0; m < 3; ++m) {
-          so.xo[m] = tile[m][tid];
-          so.inc[m] = tile[3 + m][tid];
-          so.v[m] = tile[6 + m][tid];
-        }
-        float pen3[3] = {0.f, 0.f, 0.f};
-        const unsigned long long cm =
-            mark_contacts<BS, N, PEN>(c, tile, so, ls, n, me, beta, tile[12][tid], pen3);
-        const bool hit = any_response<BS>(c, tile, so, ls, me, cm);
+        const uint32_t cm = word_resp(wn, me, wide);
         float(*cs)[BS] = cring[k & 1];
-        cs[0][tid] = hit ? 1.f : 0.f;
-        cs[1][tid] = __uint_as_float((uint32_t)cm);
+        cs[0][tid] = cm != 0u ? 1.f : 0.f;
+        cs[1][tid] = __uint_as_float(cm);
 #pragma unroll
-        for (int m = 0; m < 3; ++m) cs[2 + m][tid] = pen3[m];
+        for (int m = 0; m < 3; ++m) cs[2 + m][tid] = pn[m];
+        if (k > 0) load(k - 1);
       }
       wg_sync();
     }
@@ -1073,7 +1134,7 @@ __global__ __launch_bounds__(192) void rollout_pipe_kernel(const Consts* __restr
                                                            float* __restrict__ pen, float beta) {
   constexpr int BS = 64;
   constexpr bool PW = kRollWaves<N, PEN> == 3;  // penalty on its own wavefront
-  static_assert(N == 1 || N == 8, "pipelined rollout for swarms of 1 or 8");
+  static_assert(N == 8 || (N == 1 && !PEN), "pipelined rollout for swarms of 1 or 8");
   __shared__ float sxv[2][TILE_ROWS_CO][BS];
   __shared__ float ring[2][4][BS];
   const Consts& c = *cp;
@@ -1144,7 +1205,6 @@ __global__ __launch_bounds__(192) void rollout_pipe_kernel(const Consts* __restr
     Quad s;
     if (live) load_state(p.st, p.Qp, q, s);
     const bool pairs = N != 1 && ((c.flags & (F_COLLIDE | F_DOWNWASH)) != 0 || PEN);
-    float pacc = 0.f;
     wg_sync();  // step 0: no thrust yet
     for (int i = 1; i < n_pipe; ++i) {
       if (i <= n_steps) {
@@ -1181,12 +1241,10 @@ __global__ __launch_bounds__(192) void rollout_pipe_kernel(const Consts* __restr
               tile[3 + k][tid] = s.inc[k];
               tile[6 + k][tid] = s.v[k];
             }
-            put_screen_rows<kScreenSq<kUnroll<N, PEN>>>(tile, tid, s.x);
+            put_screen_rows<kScreenSq<N>>(tile, tid, s.x);
           }
           wave_sync();
-          if (live)
-            pair_pass<BS, kUnroll<N, PEN>, PEN && !PW, !(PEN && !PW)>(c, tile, s, ls, n, me,
-                                                                (uint32_t)q, t, pacc, beta);
+          if (live) pair_pass<BS, N, PEN_NONE, true>(c, tile, s, ls, n, me, (uint32_t)q, t);
         }
       }
       wg_sync();
@@ -1208,27 +1266,21 @@ __global__ __launch_bounds__(192) void rollout_pipe_kernel(const Consts* __restr
       for (int k = 0; k < 9; ++k) chk += s.R[k];
       if (!isfinite(chk))
         __hip_atomic_fetch_or(p.err, ERRBIT_STATE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if constexpr (PEN && !PW) pen[q] += pacc;
     }
   } else if constexpr (PW) {
     // ---- penalty of substep i - 2 at step i, from the exchange tile
-    float pacc = 0.f;
+    Pen pn = make_pen(c, beta, N > 0 ? N : wave_max(live ? n : 0));
     wg_sync();  // steps 0 and 1: no tile yet
     wg_sync();
     for (int i = 2; i < n_pipe; ++i) {
       if (live) {
         const float(*tile)[BS] = sxv[(i - 2) & 1];
-        Quad so;  // the quad's start position and displacement
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          so.xo[k] = tile[k][tid];
-          so.inc[k] = tile[3 + k][tid];
-        }
-        penalty_pass<BS, kUnroll<N, PEN>>(c, tile, so, ls, n, me, pacc, beta);
+        const Quad so = tile_quad(tile, tid);
+        penalty_pass<BS, N, PEN_SUM>(c, tile, so, ls, n, me, pn);
       }
       wg_sync();
     }
-    if (live) pen[q] += pacc;
+    if (live) pen[q] += pn.acc[0];
   }
 }
 
