@@ -39,12 +39,15 @@
  *      QS_REVERSE_PIPE = 0|1
  *                            force the multi-wavefront forms off or on:
  *                            multi-substep step calls on two wavefronts
- *                            per workgroup (uniform 8-quad swarms),
- *                            qs_rollout on two (three with the penalty in
- *                            8-quad swarms), the recompute of
- *                            qs_rollout_backward on two and its reverse
- *                            sweep on four (swarms of 1 or 8); default on
- *                            up to 1024 workgroups; read on every call;
+ *                            per workgroup (uniform 8-quad swarms; default
+ *                            up to 1024 workgroups), qs_rollout on three to
+ *                            five (default up to 1024 workgroups, 2048 of
+ *                            single quads), the recompute of
+ *                            qs_rollout_backward on three or four (default
+ *                            up to 2048 workgroups, over its segments) and
+ *                            its reverse sweep on seven (default up to 512
+ *                            workgroups); the backward forms only without
+ *                            swarms above 32; read on every call;
  *      QS_STAGE_ROWS=n       observation rows per LDS staging pass (a power
  *                            of two up to the workgroup size; 0: each lane
  *                            stores its own row), read once;
@@ -406,12 +409,12 @@ int qs_autotune(qs_handle* h, const float* d_actions, int32_t n_substeps, const 
                 float* d_obs, int32_t* choice, void* stream);
 
 /*
- * Bucketed form: the slot sizes whose work items take the in-swarm
- * partners in chunks of four (their loads in flight together) instead of
- * one at a time: bit k of slot_mask for slots of 2^k quads, k = 4 or 5
- * (slots of 16 and 32; QS_ERR_INVALID for other bits).  Results are
- * bit-identical either way.  Synchronises the device.  (qs_autotune sets it
- * from its measurements.)
+ * Bucketed form: the slot sizes whose work items pass over all the slot's
+ * places, in a loop of known length, instead of over the swarm's size: bit k
+ * of slot_mask for slots of 2^k quads, k = 4 or 5 (slots of 16 and 32, both
+ * at creation; QS_ERR_INVALID for other bits).  Results are bit-identical
+ * either way.  Synchronises the device.  (qs_autotune sets it from its
+ * measurements.)
  */
 int qs_set_partner_chunks(qs_handle* h, uint32_t slot_mask);
 

@@ -145,14 +145,24 @@ __device__ __forceinline__ float rotor_cmd(float a, bool unit) {
   return sqrtf(unit ? fu : fs);
 }
 
+// Events of one substep of one quad.
+enum : uint32_t {
+  SUB_REST = 1u,      // resting on the floor
+  SUB_GUARD = 2u,     // friction stopped it
+  SUB_BOUNCED = 4u,   // off a wall or the ceiling
+  SUB_HIT = 8u,       // hit the floor
+  SUB_CLAMP = 16u,    // << axis: position held to the room
+  SUB_FLIP = 128u,    // << axis: velocity mirrored
+  SUB_PAIR = 1024u,   // collision response received
+  SUB_DOWNWASH = 2048u,
+  SUB_TURNS = SUB_REST | SUB_BOUNCED | SUB_HIT | SUB_PAIR | SUB_DOWNWASH  // those that touch R or w
+};
+
 // Intermediates of one substep kept for the reverse sweep (adjoint).
 struct Rec {
-  float z[4], u0[4], u1[4], P[9], w0[3], v0[3], T, F[3];
+  float z[4], u0[4], u1[4], P[9], w0[3], v0[3], T;
   float wdot[3], w1[3], A1[3], i0, c0[3], dp, i1, c1[3];  // i0, i1: inverse column norms
-  float mu_n, fb[2], nv, nf, mag;
-  float hx, hy, nh, kx, ky, nk;
-  bool rest, statik, guard, bounced, hit, fallback;
-  bool clamp[3], flip[3];
+  uint32_t ev;  // SUB_*
 };
 
 // Where the motor-noise draws of a substep come from: generated (Z_DRAW),
@@ -203,172 +213,96 @@ __device__ __forceinline__ Drive motor_step(const Consts& c, const QuadPar& p, f
   return d;
 }
 
-// The rest of a substep from its thrust and torques: floor-rest or
-// free-flight dynamics with semi-implicit Euler and Gram-Schmidt, walls and
-// floor (not the rotor state).  REC: also record the intermediates the
-// adjoint needs into *r (the rotor fields are the caller's).
-template <bool REC = false>
-__device__ __forceinline__ void body_step(const Consts& c, const QuadPar& p, Quad& s,
-                                          const Drive& d, uint32_t q, uint64_t t,
-                                          Rec* r = nullptr) {
-  if constexpr (REC) {
-#pragma unroll
-    for (int k = 0; k < 9; ++k) r->P[k] = s.R[k];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      r->w0[k] = s.w[k];
-      r->v0[k] = s.v[k];
-      r->clamp[k] = false;
-      r->flip[k] = false;
-    }
-    r->statik = r->guard = r->bounced = r->hit = r->fallback = false;
+// Friction force in the plane on a quad resting on the floor under thrust F
+// (static when still, kinetic when sliding).
+struct Friction {
+  float mu_n, fb[2], nv, nf, mag;
+  bool still;
+};
+__device__ __forceinline__ Friction floor_friction(const Consts& c, const QuadPar& p,
+                                                   const float F[3], const float v[2]) {
+  Friction f;
+  f.mu_n = c.mu * (p.m * c.g - F[2]);
+  f.still = v[0] == 0.0f && v[1] == 0.0f;
+  f.nv = f.nf = f.mag = 0.0f;
+  if (f.still) {
+    f.nf = sqrtf(F[0] * F[0] + F[1] * F[1]);
+    const float mag = fmaxf(f.nf - f.mu_n, 0.0f);
+    const float sc = f.nf > 0.0f ? mag / f.nf : 0.0f;
+    f.fb[0] = sc * F[0];
+    f.fb[1] = sc * F[1];
+    f.mag = f.nf > 0.0f ? mag : 0.0f;
+  } else {
+    f.nv = sqrtf(v[0] * v[0] + v[1] * v[1]);
+    const float iv = f.mu_n / f.nv;
+    f.fb[0] = F[0] - iv * v[0];
+    f.fb[1] = F[1] - iv * v[1];
   }
+  return f;
+}
+
+// The translation of a substep in free flight from its world-frame thrust F,
+// by semi-implicit Euler.  Updates x, v, xo, inc and fl of s; returns whether
+// the quad rests on the floor instead: free flight is computed for every lane
+// (one scheduling region) and the rare resting lane then redoes the substep
+// (trans_rest) from the start values v0, fl0.
+__device__ __forceinline__ bool trans_free(const Consts& c, const QuadPar& p, Quad& s,
+                                           const float F[3], float v0[2], float& fl0) {
 #pragma unroll
   for (int k = 0; k < 3; ++k) s.xo[k] = s.x[k];
-  const float T = d.T, tx = d.tx, ty = d.ty, tz = d.tz;
-  // world-frame thrust = T * third column of R
-  const float Fx = T * s.R[2], Fy = T * s.R[5], Fz = T * s.R[8];
+  const bool rest = (c.flags & F_FLOOR) && s.fl != 0.0f && F[2] <= p.m * c.g;
+  v0[0] = s.v[0];
+  v0[1] = s.v[1];
+  fl0 = s.fl;
+  s.fl = 0.0f;
+  const float dm = c.drag * p.inv_m;
+  const float ax = fmaf(F[0], p.inv_m, -dm * s.v[0]);
+  const float ay = fmaf(F[1], p.inv_m, -dm * s.v[1]);
+  const float az = fmaf(F[2], p.inv_m, -dm * s.v[2]) - c.g;
+  // semi-implicit Euler
+  s.v[0] = fmaf(c.dt, ax, s.v[0]);
+  s.v[1] = fmaf(c.dt, ay, s.v[1]);
+  s.v[2] = fmaf(c.dt, az, s.v[2]);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    s.inc[k] = c.dt * s.v[k];
+    s.x[k] = fmaf(c.dt, s.v[k], s.x[k]);
+  }
+  return rest;
+}
 
-  const bool rest = (c.flags & F_FLOOR) && s.fl != 0.0f && Fz <= p.m * c.g;
-  if constexpr (REC) {
-    r->T = T;
-    r->F[0] = Fx;
-    r->F[1] = Fy;
-    r->F[2] = Fz;
-    r->rest = rest;
+// §III-B.3 resting on the floor: friction in xy, no vertical motion, no
+// rotation.
+__device__ __forceinline__ uint32_t trans_rest(const Consts& c, const QuadPar& p, Quad& s,
+                                               const float F[3], const float v0[2], float fl0) {
+  uint32_t ev = SUB_REST;
+  s.fl = fl0;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) s.x[k] = s.xo[k];  // the substep's start position
+  const Friction f = floor_friction(c, p, F, v0);
+  s.v[0] = fmaf(c.dt, (f.fb[0] - c.drag * v0[0]) * p.inv_m, v0[0]);
+  s.v[1] = fmaf(c.dt, (f.fb[1] - c.drag * v0[1]) * p.inv_m, v0[1]);
+  s.v[2] = 0.0f;
+  if (s.v[0] * v0[0] + s.v[1] * v0[1] < 0.0f) {
+    s.v[0] = 0.0f;
+    s.v[1] = 0.0f;
+    ev |= SUB_GUARD;
   }
-  // Free flight is computed for every lane (one scheduling region); the
-  // rare resting lane then redoes the substep from the saved start values.
-  const float v0r[2] = {s.v[0], s.v[1]};
-  float R0r[9];
-#pragma unroll
-  for (int k = 0; k < 9; ++k) R0r[k] = s.R[k];
-  const float fl0 = s.fl;
-  {
-    s.fl = 0.0f;
-    const float dm = c.drag * p.inv_m;
-    const float ax = fmaf(Fx, p.inv_m, -dm * s.v[0]);
-    const float ay = fmaf(Fy, p.inv_m, -dm * s.v[1]);
-    const float az = fmaf(Fz, p.inv_m, -dm * s.v[2]) - c.g;
-    // Euler's equation with the start-of-substep body rate
-    const float Lx = p.jx * s.w[0], Ly = p.jy * s.w[1], Lz = p.jz * s.w[2];
-    const float cx = s.w[1] * Lz - s.w[2] * Ly;
-    const float cy = s.w[2] * Lx - s.w[0] * Lz;
-    const float cz = s.w[0] * Ly - s.w[1] * Lx;
-    const float wdx = (tx - cx) * p.ijx, wdy = (ty - cy) * p.ijy, wdz = (tz - cz) * p.ijz;
-    // semi-implicit Euler
-    s.v[0] = fmaf(c.dt, ax, s.v[0]);
-    s.v[1] = fmaf(c.dt, ay, s.v[1]);
-    s.v[2] = fmaf(c.dt, az, s.v[2]);
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      s.inc[k] = c.dt * s.v[k];
-      s.x[k] = fmaf(c.dt, s.v[k], s.x[k]);
-    }
-    s.w[0] = fmaf(c.dt, wdx, s.w[0]);
-    s.w[1] = fmaf(c.dt, wdy, s.w[1]);
-    s.w[2] = fmaf(c.dt, wdz, s.w[2]);
-    if constexpr (REC) {
-      r->wdot[0] = wdx;
-      r->wdot[1] = wdy;
-      r->wdot[2] = wdz;
-#pragma unroll
-      for (int k = 0; k < 3; ++k) r->w1[k] = s.w[k];
-    }
-    // R <- R + dt R [w]x (body rate), then Gram-Schmidt on the columns
-    const float hx = c.dt * s.w[0], hy = c.dt * s.w[1], hz = c.dt * s.w[2];
-    float c0[3], c1[3];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      const float r0 = s.R[3 * k], r1 = s.R[3 * k + 1], r2 = s.R[3 * k + 2];
-      c0[k] = r0 + (r1 * hz - r2 * hy);
-      c1[k] = r1 + (r2 * hx - r0 * hz);
-    }
-    if constexpr (REC) {
-#pragma unroll
-      for (int k = 0; k < 3; ++k) r->A1[k] = c1[k];
-    }
-    const float i0 = rsqrtf(c0[0] * c0[0] + c0[1] * c0[1] + c0[2] * c0[2]);
-#pragma unroll
-    for (int k = 0; k < 3; ++k) c0[k] *= i0;
-    const float dp = c0[0] * c1[0] + c0[1] * c1[1] + c0[2] * c1[2];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) c1[k] = fmaf(-dp, c0[k], c1[k]);
-    const float i1 = rsqrtf(c1[0] * c1[0] + c1[1] * c1[1] + c1[2] * c1[2]);
-#pragma unroll
-    for (int k = 0; k < 3; ++k) c1[k] *= i1;
-    if constexpr (REC) {
-      r->i0 = i0;
-      r->i1 = i1;
-      r->dp = dp;
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        r->c0[k] = c0[k];
-        r->c1[k] = c1[k];
-      }
-    }
-    s.R[0] = c0[0]; s.R[3] = c0[1]; s.R[6] = c0[2];
-    s.R[1] = c1[0]; s.R[4] = c1[1]; s.R[7] = c1[2];
-    s.R[2] = c0[1] * c1[2] - c0[2] * c1[1];
-    s.R[5] = c0[2] * c1[0] - c0[0] * c1[2];
-    s.R[8] = c0[0] * c1[1] - c0[1] * c1[0];
-  }
-  if (rest) {
-    // §III-B.3 resting on the floor: friction in xy, no vertical motion,
-    // no rotation; static friction when still, kinetic when sliding.
-    s.fl = fl0;
-#pragma unroll
-    for (int k = 0; k < 9; ++k) s.R[k] = R0r[k];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) s.x[k] = s.xo[k];  // the substep's start position
-    const float mu_n = c.mu * (p.m * c.g - Fz);
-    float fbx, fby;
-    // the record's fields are written once after the branch: stores to
-    // different fields on the two sides get merged into one store through a
-    // selected address, which keeps the record out of registers
-    float rnf = 0.0f, rmag = 0.0f, rnv = 0.0f;
-    const float vx0 = v0r[0], vy0 = v0r[1];
-    const bool still = vx0 == 0.0f && vy0 == 0.0f;
-    if (still) {
-      const float nf = sqrtf(Fx * Fx + Fy * Fy);
-      const float mag = fmaxf(nf - mu_n, 0.0f);
-      const float sc = nf > 0.0f ? mag / nf : 0.0f;
-      fbx = sc * Fx;
-      fby = sc * Fy;
-      rnf = nf;
-      rmag = nf > 0.0f ? mag : 0.0f;
-    } else {
-      const float nv = sqrtf(vx0 * vx0 + vy0 * vy0);
-      const float iv = mu_n / nv;
-      fbx = Fx - iv * vx0;
-      fby = Fy - iv * vy0;
-      rnv = nv;
-    }
-    if constexpr (REC) {
-      r->statik = still;
-      r->nf = rnf;
-      r->mag = rmag;
-      r->nv = rnv;
-      r->mu_n = mu_n;
-      r->fb[0] = fbx;
-      r->fb[1] = fby;
-    }
-    s.v[0] = fmaf(c.dt, (fbx - c.drag * vx0) * p.inv_m, vx0);
-    s.v[1] = fmaf(c.dt, (fby - c.drag * vy0) * p.inv_m, vy0);
-    s.v[2] = 0.0f;
-    if (s.v[0] * vx0 + s.v[1] * vy0 < 0.0f) {
-      s.v[0] = 0.0f;
-      s.v[1] = 0.0f;
-      if constexpr (REC) r->guard = true;
-    }
-    s.inc[0] = c.dt * s.v[0];
-    s.inc[1] = c.dt * s.v[1];
-    s.inc[2] = 0.0f;
-    s.x[0] = fmaf(c.dt, s.v[0], s.x[0]);
-    s.x[1] = fmaf(c.dt, s.v[1], s.x[1]);
-    s.w[0] = s.w[1] = s.w[2] = 0.0f;
-  }
+  s.inc[0] = c.dt * s.v[0];
+  s.inc[1] = c.dt * s.v[1];
+  s.inc[2] = 0.0f;
+  s.x[0] = fmaf(c.dt, s.v[0], s.x[0]);
+  s.x[1] = fmaf(c.dt, s.v[1], s.x[1]);
+  return ev;
+}
 
+// Walls, ceiling and floor, after the motion.  bounced() and hit() are called
+// in their rare branches, for a rotation at hand.  REC: the events the adjoint
+// needs too, beside those that the rotation answers to.
+template <bool REC, typename B, typename H>
+__device__ __forceinline__ uint32_t trans_room(const Consts& c, Quad& s, uint32_t q, uint64_t t,
+                                               B&& bounced, H&& hit) {
+  uint32_t ev = 0u;
   // §III-B.2 walls and ceiling: the quad meets its mirror image
   if (c.flags & F_ROOM) {
     bool b = false;
@@ -386,10 +320,7 @@ __device__ __forceinline__ void body_step(const Consts& c, const QuadPar& p, Qua
         s.v[k] = flip ? -c.e_wall * s.v[k] : s.v[k];
         b = b | flip;
         s.ev |= flip ? (uint32_t)EVF_WALL : 0u;
-        if constexpr (REC) {
-          r->clamp[k] = r->clamp[k] | out;
-          r->flip[k] = r->flip[k] | flip;
-        }
+        if constexpr (REC) ev |= (out ? SUB_CLAMP << k : 0u) | (flip ? SUB_FLIP << k : 0u);
       }
       const bool out = s.x[k] > hi[k];
       const bool flip = out && s.v[k] > 0.0f;
@@ -398,61 +329,210 @@ __device__ __forceinline__ void body_step(const Consts& c, const QuadPar& p, Qua
       s.v[k] = flip ? -c.e_wall * s.v[k] : s.v[k];
       b = b | flip;
       s.ev |= flip ? (uint32_t)(k == 2 ? EVF_CEILING : EVF_WALL) : 0u;
-      if constexpr (REC) {
-        r->clamp[k] = r->clamp[k] | out;
-        r->flip[k] = r->flip[k] | flip;
-      }
+      if constexpr (REC) ev |= (out ? SUB_CLAMP << k : 0u) | (flip ? SUB_FLIP << k : 0u);
     }
-    if constexpr (REC) r->bounced = b;
     if (b) {
-      float zv[4] = {0.f, 0.f, 0.f, 0.f}, zw[4] = {0.f, 0.f, 0.f, 0.f};
-      if (c.col_nv > 0.0f || c.col_nw > 0.0f) {
-        normal4(c, q, t, STREAM_WALL, 0, zv);
-        normal4(c, q, t, STREAM_WALL, 1, zw);
-      }
+      ev |= SUB_BOUNCED;
+      float zv[4] = {0.f, 0.f, 0.f, 0.f};
+      if (c.col_nv > 0.0f || c.col_nw > 0.0f) normal4(c, q, t, STREAM_WALL, 0, zv);
 #pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        s.v[k] = c.col_decay * fmaf(c.col_nv, zv[k], s.v[k]);
-        s.w[k] = fmaf(c.col_nw, zw[k], s.w[k]);
-      }
+      for (int k = 0; k < 3; ++k) s.v[k] = c.col_decay * fmaf(c.col_nv, zv[k], s.v[k]);
+      bounced();
     }
   }
 
-  // §III-B.3 floor hit: stop, level the body keeping its heading, rest
+  // §III-B.3 floor hit: stop and rest (the rotation levels the body)
   if ((c.flags & F_FLOOR) && s.x[2] < c.rmin2) {
     s.ev |= EVF_FLOOR_HIT;
+    ev |= SUB_HIT;
     s.x[2] = c.rmin2;
     s.inc[2] = s.x[2] - s.xo[2];
     s.v[0] = s.v[1] = s.v[2] = 0.0f;
-    s.w[0] = s.w[1] = s.w[2] = 0.0f;
     s.fl = 1.0f;
-    const float hx = s.R[0], hy = s.R[3];
-    const float nh = sqrtf(hx * hx + hy * hy);
-    if constexpr (REC) {
-      r->hit = true;
-      r->hx = hx;
-      r->hy = hy;
-      r->nh = nh;
-      r->fallback = !(nh >= 1e-6f);
-      r->kx = s.R[1];
-      r->ky = s.R[4];
-      r->nk = sqrtf(s.R[1] * s.R[1] + s.R[4] * s.R[4]);
-    }
-    float ax, ay;  // unit heading of body x in the floor plane
-    if (nh >= 1e-6f) {
-      ax = hx / nh;
-      ay = hy / nh;
-    } else {
-      const float kx = s.R[1], ky = s.R[4];
-      const float nk = sqrtf(kx * kx + ky * ky);
-      const float bx = nk > 0.0f ? kx / nk : 0.0f, by = nk > 0.0f ? ky / nk : 1.0f;
-      ax = by;   // body x = body y x e_z
-      ay = -bx;
-    }
-    s.R[0] = ax;  s.R[1] = -ay; s.R[2] = 0.0f;
-    s.R[3] = ay;  s.R[4] = ax;  s.R[5] = 0.0f;
-    s.R[6] = 0.0f; s.R[7] = 0.0f; s.R[8] = 1.0f;
+    hit();
   }
+  return ev;
+}
+
+// The whole translation, for a rotation kept elsewhere: from the thrust T along
+// body z, the column (r2, r5, r8) of R.  Returns the substep's events.
+template <bool REC = false>
+__device__ __forceinline__ uint32_t trans_step(const Consts& c, const QuadPar& p, Quad& s, float T,
+                                               float r2, float r5, float r8, uint32_t q,
+                                               uint64_t t) {
+  const float F[3] = {T * r2, T * r5, T * r8};
+  float v0[2], fl0;
+  uint32_t ev = 0u;
+  if (trans_free(c, p, s, F, v0, fl0)) ev = trans_rest(c, p, s, F, v0, fl0);
+  return ev | trans_room<REC>(c, s, q, t, [] {}, [] {});
+}
+
+// The rotation of a substep in free flight from its torques: Euler's
+// equation, then R <- R + dt R [w]x with Gram-Schmidt.  REC: also record the
+// intermediates the adjoint needs into *r.
+template <bool REC = false>
+__device__ __forceinline__ void rot_step(const Consts& c, const QuadPar& p, float R[9], float w[3],
+                                         float tx, float ty, float tz, Rec* r = nullptr) {
+  if constexpr (REC) {
+#pragma unroll
+    for (int k = 0; k < 9; ++k) r->P[k] = R[k];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) r->w0[k] = w[k];
+  }
+  // Euler's equation with the start-of-substep body rate
+  const float Lx = p.jx * w[0], Ly = p.jy * w[1], Lz = p.jz * w[2];
+  const float cx = w[1] * Lz - w[2] * Ly;
+  const float cy = w[2] * Lx - w[0] * Lz;
+  const float cz = w[0] * Ly - w[1] * Lx;
+  const float wdx = (tx - cx) * p.ijx, wdy = (ty - cy) * p.ijy, wdz = (tz - cz) * p.ijz;
+  w[0] = fmaf(c.dt, wdx, w[0]);
+  w[1] = fmaf(c.dt, wdy, w[1]);
+  w[2] = fmaf(c.dt, wdz, w[2]);
+  if constexpr (REC) {
+    r->wdot[0] = wdx;
+    r->wdot[1] = wdy;
+    r->wdot[2] = wdz;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) r->w1[k] = w[k];
+  }
+  // R <- R + dt R [w]x (body rate), then Gram-Schmidt on the columns
+  const float hx = c.dt * w[0], hy = c.dt * w[1], hz = c.dt * w[2];
+  float c0[3], c1[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const float r0 = R[3 * k], r1 = R[3 * k + 1], r2 = R[3 * k + 2];
+    c0[k] = r0 + (r1 * hz - r2 * hy);
+    c1[k] = r1 + (r2 * hx - r0 * hz);
+  }
+  if constexpr (REC) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) r->A1[k] = c1[k];
+  }
+  const float i0 = rsqrtf(c0[0] * c0[0] + c0[1] * c0[1] + c0[2] * c0[2]);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) c0[k] *= i0;
+  const float dp = c0[0] * c1[0] + c0[1] * c1[1] + c0[2] * c1[2];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) c1[k] = fmaf(-dp, c0[k], c1[k]);
+  const float i1 = rsqrtf(c1[0] * c1[0] + c1[1] * c1[1] + c1[2] * c1[2]);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) c1[k] *= i1;
+  if constexpr (REC) {
+    r->i0 = i0;
+    r->i1 = i1;
+    r->dp = dp;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      r->c0[k] = c0[k];
+      r->c1[k] = c1[k];
+    }
+  }
+  R[0] = c0[0]; R[3] = c0[1]; R[6] = c0[2];
+  R[1] = c1[0]; R[4] = c1[1]; R[7] = c1[2];
+  R[2] = c0[1] * c1[2] - c0[2] * c1[1];
+  R[5] = c0[2] * c1[0] - c0[0] * c1[2];
+  R[8] = c0[0] * c1[1] - c0[1] * c1[0];
+}
+
+// Heading of body x in the floor plane, its length, and what takes its place
+// where the body stands on its nose.
+struct Heading {
+  float hx, hy, nh, kx, ky, nk;
+  bool fallback;
+};
+__device__ __forceinline__ Heading floor_heading(float R0, float R1, float R3, float R4) {
+  Heading h;
+  h.hx = R0;
+  h.hy = R3;
+  h.nh = sqrtf(h.hx * h.hx + h.hy * h.hy);
+  h.kx = R1;
+  h.ky = R4;
+  h.nk = sqrtf(R1 * R1 + R4 * R4);
+  h.fallback = !(h.nh >= 1e-6f);
+  return h;
+}
+
+// What a substep's events do to the rotation, after rot_step: rest holds the
+// start attitude R0 without rotation; then a wall's kick turns the body, and a
+// floor hit levels it keeping its heading.
+__device__ __forceinline__ void rot_rest(float R[9], float w[3], const float R0[9]) {
+#pragma unroll
+  for (int k = 0; k < 9; ++k) R[k] = R0[k];
+  w[0] = w[1] = w[2] = 0.0f;
+}
+__device__ __forceinline__ void rot_bounced(const Consts& c, float w[3], uint32_t q, uint64_t t) {
+  float zw[4] = {0.f, 0.f, 0.f, 0.f};
+  if (c.col_nv > 0.0f || c.col_nw > 0.0f) normal4(c, q, t, STREAM_WALL, 1, zw);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) w[k] = fmaf(c.col_nw, zw[k], w[k]);
+}
+__device__ __forceinline__ void rot_hit(float R[9], float w[3]) {
+  w[0] = w[1] = w[2] = 0.0f;
+  const Heading h = floor_heading(R[0], R[1], R[3], R[4]);
+  float ax, ay;  // unit heading of body x in the floor plane
+  if (!h.fallback) {
+    ax = h.hx / h.nh;
+    ay = h.hy / h.nh;
+  } else {
+    const float bx = h.nk > 0.0f ? h.kx / h.nk : 0.0f, by = h.nk > 0.0f ? h.ky / h.nk : 1.0f;
+    ax = by;   // body x = body y x e_z
+    ay = -bx;
+  }
+  R[0] = ax;  R[1] = -ay; R[2] = 0.0f;
+  R[3] = ay;  R[4] = ax;  R[5] = 0.0f;
+  R[6] = 0.0f; R[7] = 0.0f; R[8] = 1.0f;
+}
+__device__ __forceinline__ void rot_events(const Consts& c, uint32_t ev, float R[9], float w[3],
+                                           const float R0[9], uint32_t q, uint64_t t) {
+  if (ev & SUB_REST) rot_rest(R, w, R0);
+  if (ev & SUB_BOUNCED) rot_bounced(c, w, q, t);
+  if (ev & SUB_HIT) rot_hit(R, w);
+}
+
+// What the in-swarm pass's events do to the body rates, after rot_events: the
+// noise of a collision response and of downwash.
+__device__ __forceinline__ void rot_pair_events(const Consts& c, uint32_t ev, float w[3],
+                                                uint32_t q, uint64_t t) {
+  if ((ev & SUB_PAIR) && (c.col_nv > 0.0f || c.col_nw > 0.0f)) {
+    float zw[4];
+    normal4(c, q, t, STREAM_PAIR, 1, zw);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) w[k] = fmaf(c.col_nw, zw[k], w[k]);
+  }
+  if ((ev & SUB_DOWNWASH) && (c.dw_na > 0.0f || c.dw_nw > 0.0f)) {
+    float zw[4];
+    normal4(c, q, t, STREAM_DOWNWASH, 1, zw);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) w[k] = fmaf(c.dt, c.dw_nw * zw[k], w[k]);
+  }
+}
+
+// The rest of a substep from its thrust and torques (not the rotor state):
+// translation and rotation.  REC: also record the intermediates the adjoint
+// needs into *r (the rotor fields are the caller's).
+template <bool REC = false>
+__device__ __forceinline__ void body_step(const Consts& c, const QuadPar& p, Quad& s,
+                                          const Drive& d, uint32_t q, uint64_t t,
+                                          Rec* r = nullptr) {
+  if constexpr (REC) {
+    r->T = d.T;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) r->v0[k] = s.v[k];
+  }
+  const float F[3] = {d.T * s.R[2], d.T * s.R[5], d.T * s.R[8]};
+  float v0[2], fl0, R0[9];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) R0[k] = s.R[k];
+  uint32_t ev = 0u;
+  const bool rest = trans_free(c, p, s, F, v0, fl0);
+  rot_step<REC>(c, p, s.R, s.w, d.tx, d.ty, d.tz, r);
+  if (rest) {
+    ev = trans_rest(c, p, s, F, v0, fl0);
+    rot_rest(s.R, s.w, R0);
+  }
+  ev |= trans_room<REC>(
+      c, s, q, t, [&] { rot_bounced(c, s.w, q, t); }, [&] { rot_hit(s.R, s.w); });
+  if constexpr (REC) r->ev = ev;
 }
 
 // One substep of one quad up to (not including) the in-env pair pass: the
@@ -544,26 +624,39 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// The value of lane (lane xor D) for 1 <= D <= 7: a swarm of at most 8
-// quads in an aligned group of 8 lanes takes a swarm-mate's register by a
-// data-parallel-primitive move, with no LDS.  quad_perm covers D = 1, 2, 3
-// within groups of 4 lanes; row_half_mirror (lane i of each group of 8 from
-// lane 7 - i, i.e. xor 7) composed with one of them covers D = 4 .. 7.
-// Every source lane lies inside the destination's own group of 8.  Callers
-// run it with every lane of the wavefront active (uniform control flow);
-// `none` is only the value a move would leave where no source lane were
-// available.
+// A lane's values and their half-mirrored copies, from which the values of lane
+// (lane xor D), 1 <= D <= 7, come by one data-parallel-primitive move each,
+// with no LDS: quad_perm covers D = 1, 2, 3 within groups of 4 lanes;
+// row_half_mirror (lane i of each group of 8 from lane 7 - i, i.e. xor 7)
+// composed with one of them covers D = 4 .. 7.  Every source lane lies inside
+// the destination's own group of 8, so the moves leave their unmasked form and
+// fold into the subtraction that takes them.  Callers run them with every lane
+// of the wavefront active (uniform control flow).
+struct LaneXyz {
+  float v[3], h[3];
+};
+template <int CTRL>
+__device__ __forceinline__ float lane_move(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+template <int N>
+__device__ __forceinline__ LaneXyz lane_xyz(float x, float y, float z) {
+  constexpr int HALF_MIRROR = 0x141;
+  LaneXyz p{{x, y, z}, {0.f, 0.f, 0.f}};
+  if constexpr (N > 4) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) p.h[k] = lane_move<HALF_MIRROR>(p.v[k]);
+  }
+  return p;
+}
 template <int D>
-__device__ __forceinline__ float lane_xor8(float v, float none) {
+__device__ __forceinline__ float lane_xor8(const LaneXyz& p, int k) {
   static_assert(D >= 1 && D <= 7, "partners within a group of 8 lanes");
   constexpr int QP[4] = {0xE4, 0xB1, 0x4E, 0x1B};  // quad_perm: identity, xor 1, xor 2, xor 3
-  constexpr int HALF_MIRROR = 0x141;
-  const int o = __float_as_int(none);
-  int x = __float_as_int(v);
-  if constexpr (D >= 4) x = __builtin_amdgcn_update_dpp(o, x, HALF_MIRROR, 0xF, 0xF, false);
   constexpr int r = D >= 4 ? (D ^ 7) : D;
-  if constexpr (r != 0) x = __builtin_amdgcn_update_dpp(o, x, QP[r], 0xF, 0xF, false);
-  return __int_as_float(x);
+  const float v = D >= 4 ? p.h[k] : p.v[k];
+  if constexpr (r == 0) return v;
+  else return lane_move<QP[r]>(v);
 }
 
 // compile-time booleans for generic lambdas
@@ -887,6 +980,52 @@ __device__ __forceinline__ bool near_pass(const Consts& c, const float (*tile)[B
   return true;
 }
 
+// Adds partner jj's collision response to the velocity change dv and its bit
+// to rm, where the pair in contact responds (see pair_geom_v).
+template <int BS>
+__device__ __forceinline__ void pair_response(const Consts& c, const float (*tile)[BS],
+                                              const Quad& s, int j, int jj, int me, float dx,
+                                              float dy, float dz, float d2, float dv[3],
+                                              unsigned long long& rm) {
+  float nn[3], sp;
+  pair_normal<BS>(tile, s, j, jj, me, dx, dy, dz, d2, nn, sp);
+  if (!(c.flags & F_APPROACH) || sp > 0.f) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) dv[k] = fmaf(sp, nn[k], dv[k]);
+    rm |= 1ull << jj;
+  }
+}
+
+// The end of the in-swarm pass: the velocity change dv of the partners rm and
+// the downwash kick; resp and events as in pair_pass.
+__device__ __forceinline__ void pair_apply(const Consts& c, Quad& s, uint32_t q,
+                                           unsigned long long t, unsigned long long rm,
+                                           const float dv[3], float adw, bool dwhit,
+                                           unsigned long long* resp, uint32_t* events) {
+  if (resp) *resp = rm;
+  uint32_t ev = 0u;
+  if (rm != 0ull) {
+    s.ev |= EVF_QUAD;
+    ev |= SUB_PAIR;
+    float zv[4] = {0.f, 0.f, 0.f, 0.f};
+    if (c.col_nv > 0.0f || c.col_nw > 0.0f) normal4(c, q, t, STREAM_PAIR, 0, zv);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) s.v[k] = c.col_decay * (s.v[k] + dv[k] + c.col_nv * zv[k]);
+  }
+  if (dwhit) {
+    ev |= SUB_DOWNWASH;
+    float za[4] = {0.f, 0.f, 0.f, 0.f};
+    if (c.dw_na > 0.0f || c.dw_nw > 0.0f) normal4(c, q, t, STREAM_DOWNWASH, 0, za);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const float a = (k == 2 ? adw : 0.f) + c.dw_na * za[k];
+      s.v[k] = fmaf(c.dt, a, s.v[k]);
+    }
+  }
+  if (events) *events = ev;
+  else if (ev != 0u) rot_pair_events(c, ev, s.w, q, t);
+}
+
 // In-swarm pass of one live lane after the tile (start positions,
 // displacements, velocities) is written and the workgroup synchronised:
 // §III-B.1 contact detection and Jacobi velocity exchange (every response
@@ -896,7 +1035,8 @@ __device__ __forceinline__ bool near_pass(const Consts& c, const float (*tile)[B
 // partners hold far-away sentinels.  Returns the contact mask.
 // P (PenMode): also sum the penalty or its adjoint into *pen; with CO over
 // the near partners where that pays (near_pass).  resp (optional): the
-// partners whose response the quad received.
+// partners whose response the quad received.  events (optional): receives the
+// pass's events, and the body rates are the caller's (rot_pair_events).
 // CO (tile rows XROW.. written): without penalty and downwash, partners are
 // first screened on the post-motion positions with a contact distance
 // widened by 1 mm, and the exact test runs for the survivors only.  The
@@ -915,13 +1055,14 @@ __device__ __forceinline__ unsigned long long pair_pass(const Consts& c, const f
                                                         uint32_t q, unsigned long long t,
                                                         Pen* pen = nullptr,
                                                         uint32_t* key = nullptr,
-                                                        unsigned long long* resp = nullptr) {
-  static_assert(L == 0 || (CO && P == PEN_NONE && N != 8), "keys from the plain screen only");
+                                                        unsigned long long* resp = nullptr,
+                                                        uint32_t* events = nullptr) {
+  static_assert(L == 0 || (CO && P == PEN_NONE), "keys from the plain screen only");
+  static_assert(!CO || P != PEN_NONE || N <= 1 || N > 8, "lane_pair_pass for swarms of up to 8");
   const bool collide = (c.flags & F_COLLIDE) != 0;
   const bool dw = (c.flags & F_DOWNWASH) != 0 && s.fl == 0.0f;
   using M = PairMask<N>;
   M cm = 0;
-  float dv[3] = {0.f, 0.f, 0.f};
   float adw = 0.f;
   bool dwhit = false;
   // Every partner's geometry, branch-free (contacts are rare; a branch per
@@ -961,71 +1102,27 @@ __device__ __forceinline__ unsigned long long pair_pass(const Consts& c, const f
     const float dw = c.dcol + 1e-3f, thr = dw * dw;
     M cand = 0;
     bool in_box = true;  // the expanded screen's domain (swarms of 16 and 32)
-    if constexpr (N == 8) {
-      // Each unordered pair screened once: the lane screens partner
-      // me + o (mod N) for o = 1 .. N/2 and takes from lane me - o its
-      // screen of the same pair (the squared distance is symmetric bit for
-      // bit); for o = N/2 both lanes of the pair screen it.  Bit b of rot
-      // stands for partner me + b (mod N).  A swarm never straddles a
-      // wavefront.  Half the screens for a lane permute per pair: in swarms
-      // of 8 the forward rollout at 1024 x 8 went from 0.242 to 0.225 ms;
-      // in swarms of 32 the per-lane tile reads and permutes cost more than
-      // the broadcast reads of the plain screen (ten substeps at
-      // 32768 x 32: 49.1 -> 47.4 G quad-steps/s), so larger swarms keep it.
-      const int base = ((ls + me) & 63) - me;  // the swarm's first lane
-      uint32_t rot = 0u;
-      // offsets four at a time (their reads ahead of their arithmetic); a
-      // run-time loop over the groups keeps the registers of one group
-#pragma unroll 1
-      for (int o0 = 1; o0 <= N / 2; o0 += 4) {
-        float pj[4][3];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int j = ls + ((me + o0 + u) & (N - 1));
-#pragma unroll
-          for (int r = 0; r < 3; ++r) pj[u][r] = tile[XROW + r][j];
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int o = o0 + u;
-          const float dx = pj[u][0] - s.x[0], dy = pj[u][1] - s.x[1], dz = pj[u][2] - s.x[2];
-          // the sign of d^2 - thr as one FMA chain (as in larger swarms);
-          // dx -> -dx leaves it unchanged, so both lanes of a pair agree
-          const uint32_t h = __float_as_uint(fmaf(dz, dz, fmaf(dy, dy, fmaf(dx, dx, -thr)))) >> 31;
-          rot |= h << o;
-          if (o < N / 2) {
-            const int src = base + ((me - o) & (N - 1));
-            const uint32_t g = (uint32_t)__builtin_amdgcn_ds_bpermute(src << 2, (int)h) & 1u;
-            rot |= g << (N - o);
-          }
-        }
-      }
-      constexpr uint32_t full = (1u << N) - 1u;
-      rot &= full;
-      cand = (M)(me == 0 ? rot : ((rot << me) | (rot >> (N - me))) & full);
-    } else {
-      if constexpr (N >= 16 && N <= 32) {
-        if constexpr (L > 0) {
-          // partners arrive in index order, so the mask is accumulated as
-          // acc = 2 acc + bit and bit-reversed once
-          uint32_t acc = 0u;
-          for_partner_pos<BS, N>(tile, ls, n, [&](int jj, const float* pj) {
-            const float d2 = sq_dist(pj, s.x);
-            acc = acc + acc + (d2 < thr ? 1u : 0u);
-            knn_insert<L>(key, jj, me, d2);
-          });
-          cand = (M)(__builtin_bitreverse32(acc) >> (32 - N));
-        } else {
-          cand = (M)screen_expanded<BS, N>(tile, s.x, ls, n, c.dcol, c.dcol2);
-          in_box = max_abs(s.x) <= SCREEN_BOX;
-        }
-      } else {
+    if constexpr (N >= 16 && N <= 32) {
+      if constexpr (L > 0) {
+        // partners arrive in index order, so the mask is accumulated as
+        // acc = 2 acc + bit and bit-reversed once
+        uint32_t acc = 0u;
         for_partner_pos<BS, N>(tile, ls, n, [&](int jj, const float* pj) {
           const float d2 = sq_dist(pj, s.x);
-          cand |= d2 < thr ? (M)1 << jj : (M)0;
-          if constexpr (L > 0) knn_insert<L>(key, jj, me, d2);
+          acc = acc + acc + (d2 < thr ? 1u : 0u);
+          knn_insert<L>(key, jj, me, d2);
         });
+        cand = (M)(__builtin_bitreverse32(acc) >> (32 - N));
+      } else {
+        cand = (M)screen_expanded<BS, N>(tile, s.x, ls, n, c.dcol, c.dcol2);
+        in_box = max_abs(s.x) <= SCREEN_BOX;
       }
+    } else {
+      for_partner_pos<BS, N>(tile, ls, n, [&](int jj, const float* pj) {
+        const float d2 = sq_dist(pj, s.x);
+        cand |= d2 < thr ? (M)1 << jj : (M)0;
+        if constexpr (L > 0) knn_insert<L>(key, jj, me, d2);
+      });
     }
     const bool near_origin = max_abs(s.x) <= 1000.0f;
     if (!(near_origin && in_box)) cand = (M)(n >= 64 ? ~0ull : (1ull << n) - 1ull);
@@ -1051,47 +1148,121 @@ __device__ __forceinline__ unsigned long long pair_pass(const Consts& c, const f
   if constexpr (N == 0) cm &= (M)(~0ull >> (64 - n));
   const unsigned long long cmask = collide ? (unsigned long long)(cm & ~((M)1 << me)) : 0ull;
   // The responses, for the partners in contact only, in partner order.
+  float dv[3] = {0.f, 0.f, 0.f};
   unsigned long long rm = 0ull;
   for (unsigned long long m = cmask; m != 0ull; m &= m - 1ull) {
     const int jj = __builtin_ctzll(m);
     const int j = ls + jj;
     const float pj[6] = {tile[0][j], tile[1][j], tile[2][j], tile[3][j], tile[4][j], tile[5][j]};
-    float dx, dy, dz, d2, nn[3], sp;
+    float dx, dy, dz, d2;
     pair_geom_v(c, pj, s, dx, dy, dz, d2);
-    pair_normal<BS>(tile, s, j, jj, me, dx, dy, dz, d2, nn, sp);
-    if (!(c.flags & F_APPROACH) || sp > 0.f) {
+    pair_response<BS>(c, tile, s, j, jj, me, dx, dy, dz, d2, dv, rm);
+  }
+  pair_apply(c, s, q, t, rm, dv, adw, dwhit, resp, events);
+  return cmask;
+}
+
+// The exchange tile's rows of one lane (padding lanes: far away).
+template <bool SQ, bool SCREEN, typename T>
+__device__ __forceinline__ void put_tile(T tile, int tid, const Quad& s) {
 #pragma unroll
-      for (int k = 0; k < 3; ++k) dv[k] = fmaf(sp, nn[k], dv[k]);
-      rm |= 1ull << jj;
+  for (int k = 0; k < 3; ++k) {
+    tile[k][tid] = s.xo[k];
+    tile[3 + k][tid] = s.inc[k];
+    tile[6 + k][tid] = s.v[k];
+  }
+  if constexpr (SCREEN) put_screen_rows<SQ>(tile, tid, s.x);
+}
+template <typename T>
+__device__ __forceinline__ void put_tile_pad(T tile, int tid) {
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    tile[k][tid] = 1e30f;
+    tile[3 + k][tid] = 0.f;
+    tile[6 + k][tid] = 0.f;
+  }
+}
+
+// The in-swarm pass in slots of 2, 4 and 8 quads (aligned groups of a
+// wavefront's lanes), by every lane of the wavefront: partners are screened on
+// their post-motion positions (with the contact distance widened by 1 mm,
+// as in pair_pass) by cross-lane moves, with no LDS, and most substeps end
+// there.  Only where a lane of the wavefront finds a partner do the lanes write
+// the exchange tile (PUT; otherwise the caller has) for the exact test and the
+// responses, as in pair_pass, whose results these are.  Downwash passes over
+// every partner.  (Screened through the tile, and tested and answered in two
+// passes: forward of 1024 x 8, 200 substeps, 206 -> 183 us.)
+template <int BS, int N, bool PUT>
+__device__ __forceinline__ unsigned long long lane_pair_pass(
+    const Consts& c, float (*tile)[BS], Quad& s, bool live, int ls, int n, int me, int tid,
+    uint32_t q, unsigned long long t, unsigned long long* resp = nullptr,
+    uint32_t* events = nullptr) {
+  static_assert(N == 2 || N == 4 || N == 8, "aligned groups of up to 8 lanes");
+  auto put = [&] {
+    if constexpr (PUT) {
+      if (live) put_tile<false, false>(tile, tid, s);
+      else put_tile_pad(tile, tid);
+    }
+    wave_sync();
+  };
+  if (c.flags & F_DOWNWASH) {
+    put();
+    return live ? pair_pass<BS, N, PEN_NONE>(c, tile, s, ls, n, me, q, t, nullptr, nullptr, resp,
+                                             events)
+                : 0ull;
+  }
+  const float dw = c.dcol + 1e-3f, thr = dw * dw;
+  const float x = live ? s.x[0] : 1e30f, y = live ? s.x[1] : 1e30f, z = live ? s.x[2] : 1e30f;
+  // the sign of d^2 - thr as one FMA chain, shifted in: bit N - 1 - d for the
+  // partner me ^ d
+  const LaneXyz xyz = lane_xyz<N>(x, y, z);
+  uint32_t bits = 0u;
+  auto screen = [&](auto dc) {
+    constexpr int D = decltype(dc)::value;
+    if constexpr (D < N) {
+      const float dx = lane_xor8<D>(xyz, 0) - x, dy = lane_xor8<D>(xyz, 1) - y,
+                  dz = lane_xor8<D>(xyz, 2) - z;
+      const float e = fmaf(dz, dz, fmaf(dy, dy, fmaf(dx, dx, -thr)));
+      bits = __builtin_amdgcn_alignbit(bits, __float_as_uint(e), 31u);
+    }
+  };
+  screen(std::integral_constant<int, 1>{});
+  screen(std::integral_constant<int, 2>{});
+  screen(std::integral_constant<int, 3>{});
+  screen(std::integral_constant<int, 4>{});
+  screen(std::integral_constant<int, 5>{});
+  screen(std::integral_constant<int, 6>{});
+  screen(std::integral_constant<int, 7>{});
+  const float far = fmaxf(fabsf(x), fmaxf(fabsf(y), fabsf(z)));
+  if (!(far <= 1000.0f)) bits = (1u << (N - 1)) - 1u;  // every partner
+  if (!live || !(c.flags & F_COLLIDE)) bits = 0u;
+  if (__ballot(bits != 0u) == 0ull) {
+    if (resp) *resp = 0ull;
+    if (events) *events = 0u;
+    return 0ull;
+  }
+  put();
+  if (!live) return 0ull;
+  // bits by d -> bits by partner, me ^ d: each bit of me swaps places
+  uint32_t m = __builtin_bitreverse32(bits) >> (32 - N);
+  if (me & 1) m = ((m & 0x55u) << 1) | ((m >> 1) & 0x55u);
+  if (N > 2 && (me & 2)) m = ((m & 0x33u) << 2) | ((m >> 2) & 0x33u);
+  if (N > 4 && (me & 4)) m = ((m & 0x0fu) << 4) | (m >> 4);
+  m &= (1u << n) - 1u;
+  // exact test and response in one pass: a contact lasts some tens of
+  // substeps, and the workgroup that holds one sets the launch's time
+  unsigned long long cmask = 0ull, rm = 0ull;
+  float dv[3] = {0.f, 0.f, 0.f};
+  for (; m != 0u; m &= m - 1u) {
+    const int jj = __builtin_ctz(m), j = ls + jj;
+    const float pj[6] = {tile[0][j], tile[1][j], tile[2][j], tile[3][j], tile[4][j], tile[5][j]};
+    float dx, dy, dz, d2;
+    if (pair_geom_v(c, pj, s, dx, dy, dz, d2)) {
+      cmask |= 1ull << jj;
+      pair_response<BS>(c, tile, s, j, jj, me, dx, dy, dz, d2, dv, rm);
     }
   }
-  if (resp) *resp = rm;
-  if (rm != 0ull) {
-    s.ev |= EVF_QUAD;
-    float zv[4] = {0.f, 0.f, 0.f, 0.f}, zw[4] = {0.f, 0.f, 0.f, 0.f};
-    if (c.col_nv > 0.0f || c.col_nw > 0.0f) {
-      normal4(c, q, t, STREAM_PAIR, 0, zv);
-      normal4(c, q, t, STREAM_PAIR, 1, zw);
-    }
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      s.v[k] = c.col_decay * (s.v[k] + dv[k] + c.col_nv * zv[k]);
-      s.w[k] = fmaf(c.col_nw, zw[k], s.w[k]);
-    }
-  }
-  if (dwhit) {
-    float za[4] = {0.f, 0.f, 0.f, 0.f}, zw[4] = {0.f, 0.f, 0.f, 0.f};
-    if (c.dw_na > 0.0f || c.dw_nw > 0.0f) {
-      normal4(c, q, t, STREAM_DOWNWASH, 0, za);
-      normal4(c, q, t, STREAM_DOWNWASH, 1, zw);
-    }
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      const float a = (k == 2 ? adw : 0.f) + c.dw_na * za[k];
-      s.v[k] = fmaf(c.dt, a, s.v[k]);
-      s.w[k] = fmaf(c.dt, c.dw_nw * zw[k], s.w[k]);
-    }
-  }
+  pair_apply(c, s, q, t, rm, dv, 0.f, false, resp, events);
   return cmask;
 }
 

@@ -15,21 +15,50 @@ using qs_host::outputs_overlap;
 using qs_host::ptrs;
 
 // ---- differentiable rollouts ------------------------------------------------
-// The two-wavefront rollout (motor part one substep ahead) for small
-// batches, as the reverse sweep (QS_ROLLOUT_PIPE=0/1 forces it off/on).
+// Small batches run the parts of a substep on wavefronts of their own
+// (forward_pipe, reverse_pipe_kernel) for as long as their workgroups are
+// resident together; QS_ROLLOUT_PIPE, QS_RECOMPUTE_PIPE and QS_REVERSE_PIPE =
+// 0/1 force it off/on.  The tape of handles with swarms above 32 holds no
+// contact set (tape_word): their backward pass keeps one wavefront.  Measured
+// over 40 substeps, us with one wavefront -> with the pipeline:
+//  - forward, five wavefronts: 512 workgroups of 8: 122 -> 61, of 32:
+//    216 -> 162; 1024: 126 -> 140, 214 -> 326 (a CU holds three);
+//    four wavefronts at 1024: 126 -> 85, 214 -> 172; 4096 of 8: equal.  Swarms
+//    of one: 2048: 91 -> 88;
+//  - recompute (workgroups times segments): 2048: equal, 4096: 466 -> 496 with
+//    the sweep behind it;
+//  - reverse, two resident on a CU: 512 of 8: 210 -> 127; 1024: 275 -> 300.
+int is_wide(const qs_handle* h) { return h->max_n > 32 ? 1 : 0; }
+bool pipe(const qs_handle* h, const char* env, bool pays) {
+  if (h->Q > 1 << 24) return false;  // a row's byte offsets are 32-bit
+  if (const char* e = std::getenv(env)) return e[0] == '1';
+  return pays;
+}
 bool use_rollout_pipe(const qs_handle* h) {
-  if (const char* e = std::getenv("QS_ROLLOUT_PIPE")) return e[0] == '1';
-  return h->nblk <= 1024;
+  return pipe(h, "QS_ROLLOUT_PIPE", h->nblk <= (h->max_n == 1 ? 2048 : 1024));
+}
+bool use_noise_wave(const qs_handle* h) { return h->max_n == 1 || h->nblk <= 512; }
+bool use_recompute_pipe(const qs_handle* h, int nseg) {
+  return !is_wide(h) && pipe(h, "QS_RECOMPUTE_PIPE", (long long)h->nblk * nseg <= 2048);
+}
+bool use_reverse_pipe(const qs_handle* h) {
+  return !is_wide(h) && pipe(h, "QS_REVERSE_PIPE", h->nblk <= 512);
 }
 
 template <int BS, int N, bool PEN>
 void go_roll(qs_handle* h, const float* act, int ncalls, int nsub, float* ckpt, int ce, float* pen,
              float beta, hipStream_t s) {
-  if constexpr (BS == 64 && (N == 8 || (N == 1 && !PEN))) {
+  if constexpr (BS == 64) {
     if (use_rollout_pipe(h)) {
-      hipLaunchKernelGGL((qs::rollout_pipe_kernel<N, PEN>), dim3(h->nblk),
-                         dim3(64 * qs::kRollWaves<N, PEN>), 0, s, h->d_c,
-                         ptrs(h), act, ncalls, nsub, (unsigned long long)h->t, ckpt, ce, pen, beta);
+      constexpr int P = PEN ? qs::PEN_SUM : qs::PEN_NONE;
+      if (use_noise_wave(h))
+        hipLaunchKernelGGL((qs::rollout_pipe_kernel<N, PEN, true>), dim3(h->nblk),
+                           dim3(64 * qs::kPipeWaves<P, true>), 0, s, h->d_c, ptrs(h), act, ncalls,
+                           nsub, (unsigned long long)h->t, ckpt, ce, pen, beta);
+      else
+        hipLaunchKernelGGL((qs::rollout_pipe_kernel<N, PEN, false>), dim3(h->nblk),
+                           dim3(64 * qs::kPipeWaves<P, false>), 0, s, h->d_c, ptrs(h), act, ncalls,
+                           nsub, (unsigned long long)h->t, ckpt, ce, pen, beta);
       return;
     }
   }
@@ -46,26 +75,17 @@ struct AdjScratch {
   float* gpar;
 };
 
-// Swarms above 32: the tape's word holds no contact set (tape_word).
-int is_wide(const qs_handle* h) { return h->max_n > 32 ? 1 : 0; }
-
-// The two-wavefront recompute (motor part one substep ahead) for small
-// batches, as the rollout (QS_RECOMPUTE_PIPE=0/1 forces it off/on).
-bool use_recompute_pipe(const qs_handle* h) {
-  if (const char* e = std::getenv("QS_RECOMPUTE_PIPE")) return e[0] == '1';
-  return h->nblk <= 1024;
-}
-
 template <int BS, int N, bool PEN>
 void go_recompute(qs_handle* h, const AdjScratch& sc, const float* ckpt, const float* act,
                   int ncalls, int ce, int nsub, uint64_t t0, const float* gpen, float beta,
                   hipStream_t s) {
   const int nseg = (ncalls + ce - 1) / ce;
-  if constexpr (BS == 64 && (N == 8 || (N == 1 && !PEN))) {
-    if (use_recompute_pipe(h)) {
+  if constexpr (BS == 64) {
+    if (use_recompute_pipe(h, nseg)) {
+      constexpr int P = PEN ? qs::PEN_GRAD : qs::PEN_NONE;
       hipLaunchKernelGGL((qs::recompute_pipe_kernel<N, PEN>), dim3(h->nblk, nseg),
-                         dim3(PEN ? 192 : 128), 0, s, h->d_c, ptrs(h), ckpt, act, ncalls, ce, nsub,
-                         (unsigned long long)t0, sc.tape, is_wide(h), gpen, beta);
+                         dim3(64 * qs::kPipeWaves<P, false>), 0, s, h->d_c, ptrs(h), ckpt, act, ncalls, ce,
+                         nsub, (unsigned long long)t0, sc.tape, gpen, beta);
       return;
     }
   }
@@ -74,27 +94,14 @@ void go_recompute(qs_handle* h, const AdjScratch& sc, const float* ckpt, const f
                      is_wide(h), gpen, beta);
 }
 
-// The four-wavefront reverse sweep pays where the batch leaves SIMDs idle:
-// up to 1024 workgroups of 64 quads (QS_REVERSE_PIPE=0/1 forces it off/on).
-bool use_reverse_pipe(const qs_handle* h) {
-  if (const char* e = std::getenv("QS_REVERSE_PIPE")) return e[0] == '1';
-  return h->nblk <= 1024;
-}
-
-template <int N, bool PEN>
-void go_reverse_pipe(qs_handle* h, const AdjScratch& sc, const float* act, int ncalls, int nsub,
-                     uint64_t t0, float* gact, hipStream_t s) {
-  hipLaunchKernelGGL((qs::reverse_pipe_kernel<N, PEN>), dim3(h->nblk), dim3(256), 0, s, h->d_c,
-                     ptrs(h), act, ncalls, nsub, (unsigned long long)t0, sc.tape, sc.lam,
-                     is_wide(h), gact, sc.gpar);
-}
-
 template <int BS, int N, bool PEN>
 void go_reverse(qs_handle* h, const AdjScratch& sc, const float* act, int ncalls, int nsub,
                 uint64_t t0, float* gact, hipStream_t s) {
-  if constexpr (BS == 64 && (N == 8 || (N == 1 && !PEN))) {
+  if constexpr (BS == 64) {
     if (use_reverse_pipe(h)) {
-      go_reverse_pipe<N, PEN>(h, sc, act, ncalls, nsub, t0, gact, s);
+      hipLaunchKernelGGL((qs::reverse_pipe_kernel<PEN>), dim3(h->nblk), dim3(448), 0, s, h->d_c,
+                         ptrs(h), act, ncalls, nsub, sc.tape, sc.lam, h->uniform_n, gact, sc.gpar,
+                         (unsigned long long)t0);
       return;
     }
   }

@@ -274,26 +274,19 @@ __device__ __forceinline__ void step_body(const Consts& c, const Ptrs& p,
     } else {
       if (live) quad_substep<false, Z_IMPORT>(c, pp, s, uhat, (uint32_t)q, t, nullptr, zs);
     }
-    if (collide) {
-      // §III-B.1 in-env pair pass (Jacobi: every response from the
-      // pre-response velocities of this substep)
+    // §III-B.1 in-env pair pass (Jacobi: every response from the
+    // pre-response velocities of this substep)
+    if constexpr (N > 1 && N <= 8) {
+      if (collide)
+        cmask = lane_pair_pass<BS, N, true>(c, sxv[sub & 1], s, live, ls, n, me, tid, (uint32_t)q,
+                                            t);
+    } else if (collide) {
       float(*tile)[BS] = sxv[sub & 1];
       if (live) {
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          tile[k][tid] = s.xo[k];
-          tile[3 + k][tid] = s.inc[k];
-          tile[6 + k][tid] = s.v[k];
-        }
-        put_screen_rows<kScreenSq<NU>>(tile, tid, s.x);
+        put_tile<kScreenSq<NU>, true>(tile, tid, s);
       } else if constexpr (MAP == MAP_ITEM) {
         // padding lane: far away, so it is never in contact
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          tile[k][tid] = 1e30f;
-          tile[3 + k][tid] = 0.f;
-          tile[6 + k][tid] = 0.f;
-        }
+        put_tile_pad(tile, tid);
         put_screen_pad<kScreenSq<NU>>(tile, tid);
       }
       quad_sync();
@@ -430,11 +423,11 @@ __device__ __forceinline__ void step_body(const Consts& c, const Ptrs& p,
           if constexpr (LANE_KNN) {
             const float mx = live ? s.x[0] : 1e30f, my = live ? s.x[1] : 1e30f,
                         mz = live ? s.x[2] : 1e30f;
+            const LaneXyz xyz = lane_xyz<N>(mx, my, mz);
             auto mate = [&](auto dc) {
               constexpr int D = decltype(dc)::value;
               if constexpr (D < N)
-                cand(me ^ D, lane_xor8<D>(mx, 1e30f), lane_xor8<D>(my, 1e30f),
-                     lane_xor8<D>(mz, 1e30f));
+                cand(me ^ D, lane_xor8<D>(xyz, 0), lane_xor8<D>(xyz, 1), lane_xor8<D>(xyz, 2));
             };
             mate(std::integral_constant<int, 1>{});
             mate(std::integral_constant<int, 2>{});
@@ -734,14 +727,11 @@ constexpr int BUCKET_STAGE_ROWS = 32;
 
 // Persistent launch over the work items [item0, item0 + n_items) of uneven
 // swarm sizes; workgroups stride over them and run the body specialised for
-// each item's slot size N.  Slots of 4 and more loop over the swarm at run
-// time, one partner at a time, in the pair pass (and slots of 16 and 32 in
-// the neighbour search as well): unrolled, their bodies would set the whole
-// kernel's register count, and with it the occupancy (135 VGPRs instead of
-// 381: 3 wavefronts per SIMD instead of 1).  Slots of 16 and 32 also have a
-// body that takes the partners in chunks of four (their loads in flight
-// together), chosen per item (items[it].w, set per slot size by the
-// autotuner); with both bodies the kernel stays at 3 wavefronts per SIMD.
+// each item's slot size N.  Slots of 64 loop over the swarm at run time: with
+// all of them unrolled, their bodies would set the whole kernel's register
+// count, and with it the occupancy (381 VGPRs: 1 wavefront per SIMD; held to
+// 168, 3).  Slots of 16 and 32 have a body of either kind, chosen per item
+// (items[it].w, set per slot size by default and by the autotuner).
 template <int BS, int KT>
 __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(3))) void bucket_kernel(
                                                     float* __restrict__ st,

@@ -124,9 +124,6 @@ __device__ __forceinline__ void load_params(const Ptrs& p, const Consts& c, int 
   pp.ijz = 1.0f / pp.jz;
   pp.a_ns = c.ns_scale * pp.f_max;
   pa.m = pp.m;
-  pa.jx = pp.jx;
-  pa.jy = pp.jy;
-  pa.jz = pp.jz;
   pa.t2w = p.par[P_T2W * Qp + q];
   const float tau = p.par[P_TAU * Qp + q];
   pa.dlag_dtau = -(1.0f - pp.a_lag) * c.dt / (tau * tau);
@@ -209,17 +206,13 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(N == 8 && PE
       if (live) quad_substep(c, pp, s, uhat, (uint32_t)q, t);
       if (pairs) {
         float(*tile)[BS] = sxv[sidx & 1];
-        if (live) {
-#pragma unroll
-          for (int k = 0; k < 3; ++k) {
-            tile[k][tid] = s.xo[k];
-            tile[3 + k][tid] = s.inc[k];
-            tile[6 + k][tid] = s.v[k];
-          }
-          put_screen_rows<kScreenSq<N>>(tile, tid, s.x);
+        if constexpr (N == 8 && P == PEN_NONE) {
+          lane_pair_pass<BS, N, true>(c, tile, s, live, ls, n, me, tid, (uint32_t)q, t);
+        } else {
+          if (live) put_tile<kScreenSq<N>, true>(tile, tid, s);
+          __syncthreads();
+          if (live) pair_pass<BS, N, P, true>(c, tile, s, ls, n, me, (uint32_t)q, t, &pn);
         }
-        __syncthreads();
-        if (live) pair_pass<BS, N, P, true>(c, tile, s, ls, n, me, (uint32_t)q, t, &pn);
       }
     }
   }
@@ -310,44 +303,24 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(N == 8 && PE
       }
       if (pairs) {
         float(*tile)[BS] = sxv[sidx & 1];
-        if (live) {
+        if constexpr (N == 8 && !PEN) {
+          lane_pair_pass<BS, N, true>(c, tile, s, live, ls, n, me, tid, (uint32_t)q, t, &resp);
+        } else {
+          if (live) put_tile<kScreenSq<N>, true>(tile, tid, s);
+          __syncthreads();
+          if (live) {
+            if constexpr (PEN) pn.acc[0] = pn.acc[1] = pn.acc[2] = 0.f;
+            pair_pass<BS, N, P, true>(c, tile, s, ls, n, me, (uint32_t)q, t, &pn, nullptr, &resp);
+            if constexpr (PEN) {
 #pragma unroll
-          for (int k = 0; k < 3; ++k) {
-            tile[k][tid] = s.xo[k];
-            tile[3 + k][tid] = s.inc[k];
-            tile[6 + k][tid] = s.v[k];
-          }
-          put_screen_rows<kScreenSq<N>>(tile, tid, s.x);
-        }
-        __syncthreads();
-        if (live) {
-          if constexpr (PEN) pn.acc[0] = pn.acc[1] = pn.acc[2] = 0.f;
-          pair_pass<BS, N, P, true>(c, tile, s, ls, n, me, (uint32_t)q, t, &pn, nullptr, &resp);
-          if constexpr (PEN) {
-#pragma unroll
-            for (int k = 0; k < 3; ++k) row[(T_PEN + k) * Q + q] = pn.acc[k];
+              for (int k = 0; k < 3; ++k) row[(T_PEN + k) * Q + q] = pn.acc[k];
+            }
           }
         }
       }
       if (live) row[S_F * Q + q] = tape_word(fl0, resp, me, wide);
     }
   }
-}
-
-// Position, velocity, attitude, body rates and the floor flag of one tape
-// or checkpoint row (field-major, leading dimension ld).
-__device__ __forceinline__ void load_body(const float* __restrict__ row, long long ld, int q,
-                                          Quad& s) {
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    s.x[k] = row[(S_X + k) * ld + q];
-    s.v[k] = row[(S_V + k) * ld + q];
-    s.w[k] = row[(S_W + k) * ld + q];
-  }
-#pragma unroll
-  for (int k = 0; k < 9; ++k) s.R[k] = row[(S_R + k) * ld + q];
-  s.fl = row[S_F * ld + q];
-  s.ev = 0u;
 }
 
 // A quad's start position, displacement, velocity and post-motion position
@@ -363,168 +336,6 @@ __device__ __forceinline__ Quad tile_quad(const float (*tile)[BS], int tid) {
     s.x[k] = tile[XROW + k][tid];
   }
   return s;
-}
-
-// recompute_pipe_kernel: recompute_kernel for small batches (swarms of 1
-// or 8, up to 1024 workgroups of 64 quads), over two or three wavefronts per
-// workgroup as in rollout_pipe_kernel: wavefront 0 runs the motor part of
-// each substep one substep ahead (taping the rotor state and the draws) and
-// hands thrust and torques through a two-slot LDS ring; wavefront 1 tapes the
-// pose, velocity, rates and the word, runs the body part and the in-swarm
-// pass; with a penalty wavefront 2 tapes its adjoint one substep behind.
-// Same arithmetic in the same order as recompute_kernel, so the tape is
-// identical.
-// ---------------------------------------------------------------------------
-template <int N, bool PEN>
-__global__ __launch_bounds__(192) void recompute_pipe_kernel(const Consts* __restrict__ cp,
-                                                             Ptrs p,
-                                                             const float* __restrict__ ckpt,
-                                                             const float* __restrict__ act,
-                                                             int ncalls, int ce, int nsub,
-                                                             unsigned long long t0,
-                                                             float* __restrict__ tape, int wide,
-                                                             const float* __restrict__ gpen,
-                                                             float beta) {
-  constexpr int BS = 64, NTAPE = kTapeRows<PEN>;
-  static_assert(N == 8 || (N == 1 && !PEN), "pipelined recompute for swarms of 1 or 8");
-  __shared__ float sxv[2][PENROW + 1][BS];
-  __shared__ float ring[2][4][BS];
-  const Consts& c = *cp;
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int tid = threadIdx.x & 63;
-  int qb, cnt, ls, n;
-  block_map<BS, N>(p, tid, qb, cnt, ls, n);
-  const bool live = tid < cnt;
-  const int q = qb + (live ? tid : 0);
-  const int me = tid - ls;
-  const long long Q = p.Q;
-  const int c0 = blockIdx.y * ce;
-  const int nc = min(ce, ncalls - c0);
-  const int n_steps = nc * nsub;  // substeps of the segment
-  const int s0 = c0 * nsub;       // its first substep within the chunk
-  const int n_pipe = n_steps + (PEN ? 2 : 1);  // steps of the pipeline
-  const float* ck = ckpt + (long long)blockIdx.y * NSTATE * Q;
-  QuadPar pp;
-  ParAdj pa;
-  if (live) load_params(p, c, q, pp, pa);
-
-  if (wave == 0) {
-    // ---- motor part of substep i at step i
-    float u[4], e[4];
-    if (live) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        u[k] = ck[(S_U + k) * Q + q];
-        e[k] = ck[(S_E + k) * Q + q];
-      }
-    }
-    float uhat[4] = {0.f, 0.f, 0.f, 0.f};
-    float4 a_nx = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (live && nc > 0) a_nx = load_act(act + (long long)c0 * Q * 4, q);
-    for (int i = 0; i < n_pipe; ++i) {
-      if (i < n_steps) {
-        const int cl = i / nsub, sub = i - cl * nsub;
-        const int call = c0 + cl;
-        if (sub == 0) {
-          const float4 a4 = a_nx;
-          if (live && call + 1 < c0 + nc) a_nx = load_act(act + (long long)(call + 1) * Q * 4, q);
-          if (live) act_uhat(c, p, a4, uhat);
-        }
-        if (live) {
-          float* row = tape + (long long)(s0 + i) * NTAPE * Q;
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            row[(S_U + k) * Q + q] = u[k];
-            row[(S_E + k) * Q + q] = e[k];
-          }
-          float z[4] = {0.f, 0.f, 0.f, 0.f}, zio[4];
-          const Drive d = motor_step<Z_EXPORT>(c, pp, u, e, uhat, (uint32_t)q,
-                                               t0 + (unsigned long long)(s0 + i), z, zio);
-          if (c.flags & F_NOISE) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) row[(NSTATE + k) * Q + q] = zio[k];
-          }
-          float(*slot)[BS] = ring[i & 1];
-          slot[0][tid] = d.T;
-          slot[1][tid] = d.tx;
-          slot[2][tid] = d.ty;
-          slot[3][tid] = d.tz;
-        }
-      }
-      wg_sync();
-    }
-  } else {
-    // ---- body part and in-swarm pass of substep i - 1 at step i
-    if (wave == 1) {
-      Quad s;
-      if (live) load_body(ck, Q, q, s);
-      const bool pairs = N != 1 && (c.flags & (F_COLLIDE | F_DOWNWASH)) != 0;
-      wg_sync();  // step 0: no thrust yet
-      for (int i = 1; i < n_pipe; ++i) {
-        const int sidx = i - 1;
-        const unsigned long long t = t0 + (unsigned long long)(s0 + sidx);
-        float* row = tape + (long long)(s0 + sidx) * NTAPE * Q;
-        const float fl0 = s.fl;
-        unsigned long long resp = 0ull;
-        const bool run = i <= n_steps && live;
-        if (run) {
-#pragma unroll
-          for (int k = 0; k < 3; ++k) {
-            row[(S_X + k) * Q + q] = s.x[k];
-            row[(S_V + k) * Q + q] = s.v[k];
-            row[(S_W + k) * Q + q] = s.w[k];
-          }
-#pragma unroll
-          for (int k = 0; k < 9; ++k) row[(S_R + k) * Q + q] = s.R[k];
-          const float(*slot)[BS] = ring[sidx & 1];
-          Drive d;
-          d.T = slot[0][tid];
-          d.tx = slot[1][tid];
-          d.ty = slot[2][tid];
-          d.tz = slot[3][tid];
-          body_step(c, pp, s, d, (uint32_t)q, t);
-        }
-        if (pairs || PEN) {
-          float(*tile)[BS] = sxv[sidx & 1];
-          if (run) {
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-              tile[k][tid] = s.xo[k];
-              tile[3 + k][tid] = s.inc[k];
-              tile[6 + k][tid] = s.v[k];
-            }
-            put_screen_rows<kScreenSq<N>>(tile, tid, s.x);
-          }
-          wave_sync();
-          if (run && pairs)
-            pair_pass<BS, N, PEN_NONE, true>(c, tile, s, ls, n, me, (uint32_t)q, t, nullptr,
-                                             nullptr, &resp);
-        }
-        if (run) row[S_F * Q + q] = tape_word(fl0, resp, me, wide);
-        wg_sync();
-      }
-    } else if constexpr (PEN) {
-      // ---- the penalty's adjoint of substep i - 2 at step i
-      const float h_me = live ? -0.5f * gpen[q] : 0.f;
-      sxv[0][PENROW][tid] = h_me;
-      sxv[1][PENROW][tid] = h_me;
-      Pen pn = make_pen(c, beta, N > 0 ? N : wave_max(live ? n : 0), h_me);
-      wg_sync();  // steps 0 and 1: no tile yet
-      wg_sync();
-      for (int i = 2; i < n_pipe; ++i) {
-        if (live) {
-          const float(*tile)[BS] = sxv[(i - 2) & 1];
-          const Quad so = tile_quad(tile, tid);
-          pn.acc[0] = pn.acc[1] = pn.acc[2] = 0.f;
-          penalty_pass<BS, N, PEN_GRAD>(c, tile, so, ls, n, me, pn);
-          float* row = tape + (long long)(s0 + i - 2) * NTAPE * Q;
-#pragma unroll
-          for (int k = 0; k < 3; ++k) row[(T_PEN + k) * Q + q] = pn.acc[k];
-        }
-        wg_sync();
-      }
-    }
-  }
 }
 
 // The contact set of a substep in the reverse sweep of handles with swarms
@@ -566,7 +377,7 @@ template <int BS>
 __device__ __forceinline__ void response_vjp(const Consts& c, const float (*tile)[BS],
                                              const float (*ldvt)[BS], const Quad& s, int ls,
                                              int me, unsigned long long cm, const float ldv[3],
-                                             Adj& l) {
+                                             float lx[3], float lv[3]) {
   for (unsigned long long m = cm; m != 0ull; m &= m - 1ull) {
     const int jj = __builtin_ctzll(m);
     const int j = ls + jj;
@@ -578,7 +389,7 @@ __device__ __forceinline__ void response_vjp(const Consts& c, const float (*tile
       const float mu[3] = {ldv[0] - ldvt[0][j], ldv[1] - ldvt[1][j], ldv[2] - ldvt[2][j]};
       const float mn = dot3f(mu, nn);
 #pragma unroll
-      for (int k = 0; k < 3; ++k) l.v[k] = fmaf(-mn, nn[k], l.v[k]);
+      for (int k = 0; k < 3; ++k) lv[k] = fmaf(-mn, nn[k], lv[k]);
       if (!(d2 < 1e-12f)) {
         const float wv[3] = {tile[6][j] - s.v[0], tile[7][j] - s.v[1], tile[8][j] - s.v[2]};
         float gn[3];
@@ -587,7 +398,7 @@ __device__ __forceinline__ void response_vjp(const Consts& c, const float (*tile
         const float gnn = dot3f(gn, nn);
         const float id = rsqrtf(d2);
 #pragma unroll
-        for (int k = 0; k < 3; ++k) l.x[k] = fmaf(gn[k] - gnn * nn[k], id, l.x[k]);
+        for (int k = 0; k < 3; ++k) lx[k] = fmaf(gn[k] - gnn * nn[k], id, lx[k]);
       }
     }
   }
@@ -727,7 +538,7 @@ __global__ __launch_bounds__(BS) void reverse_kernel(const Consts* __restrict__ 
           for (int k = 0; k < 3; ++k) tile[9 + k][tid] = ldv[k];
         }
         __syncthreads();
-        if (live) response_vjp<BS>(c, tile, tile + 9, s, ls, me, cm, ldv, l);
+        if (live) response_vjp<BS>(c, tile, tile + 9, s, ls, me, cm, ldv, l.x, l.v);
       }
       if (live) quad_vjp(c, pp, pa, r, uhat, l, gu, gp);
     }
@@ -761,106 +572,77 @@ __global__ __launch_bounds__(BS) void reverse_kernel(const Consts* __restrict__ 
 }
 
 // ---------------------------------------------------------------------------
-// reverse_pipe_kernel: the reverse sweep of reverse_kernel for small batches
-// (one wavefront per SIMD or fewer), as a four-stage pipeline over the
-// substeps (last to first) on four wavefronts per workgroup of 64 quads, one
-// per SIMD of the compute unit.  Substep k passes through
-//  - wavefront 0 at step i: the motor part re-run (lag, noise, thrust, mix)
-//    from the taped rotor state and draws; the thrust, the torques, the
-//    rotor fields of the record and the call's rotor commands with their
-//    derivatives w.r.t. the action go on through a four-slot LDS ring;
-//  - wavefront 1 at step i + 1: the body part re-run (body_step with its
-//    record) from the taped pose and rates; the post-motion exchange tile and
-//    the body fields of the record (in 16-byte groups) go on through
-//    three-slot rings;
-//  - wavefront 2 at step i + 2: the contact set, the approach test and the
-//    penalty's adjoint from the exchange tile, through a two-slot ring;
-//  - wavefront 3 at step i + 3: the derivative (response adjoint, quad_vjp);
-//    it holds the adjoint state.
-// A substep's re-run starts from its taped state, so no stage waits for the
-// substep after it; one workgroup barrier per step hands the slots over.
-// Same arithmetic in the same order as reverse_kernel, so the results are
-// identical.
+// Small batches (up to 1024 workgroups of 64 quads) leave most SIMDs without a
+// wavefront, and the time of a substep is the time of its dependent
+// instructions.  The forward pass, the recompute and the reverse sweep then run
+// the parts of a substep on wavefronts of their own, over the same 64 quads,
+// with one workgroup barrier per substep; results pass through LDS rings.
+//
+// forward_pipe: the forward pass (TAPE false: checkpoints into out, the penalty
+// summed into pen) or the recompute of a segment (TAPE: a tape row per substep
+// into out, with the penalty's adjoint).
+//  - the last wavefront draws the motor noise of substep i at step i (NW; where
+//    the workgroups fill the chip it is left to wavefront 0, which starts);
+//  - wavefront 0, at step i + 1, runs the motor part (it depends on the rotor
+//    state, the action and the draws only) and hands on T and torques;
+//  - wavefront 1, at step i + 2, the translation and the in-swarm pass;
+//  - wavefront 2, at step i + 2, the rotation: the two need of each other only
+//    what the substep before left, R's third column one way and the events
+//    the other, so both answer to the events of substep i - 1 at the start of
+//    substep i;
+//  - with a penalty (P) wavefront 3 sums it at step i + 3 from the exchange
+//    tile (it never feeds back into the motion).
+// Each wavefront stores its own fields.  Same arithmetic in the same order as
+// the one-wavefront kernels, so identical results.  With noise and motor, and
+// translation and rotation, on one wavefront each and loads one substep ahead:
+// 1024 x 8, 200 substeps, forward 222 us, now 185.
+//  S, ld: the start state; act: its first call; t0: its first substep.
 // ---------------------------------------------------------------------------
-constexpr int REC_BODY = 49;  // the float fields of Rec that body_step sets
-// ring of the body stage: the body fields and Rec's flags, in 16-byte
-// groups (one LDS vector access per group)
-constexpr int RING_WORDS = REC_BODY + 1;
-constexpr int RING_VEC = (RING_WORDS + 3) / 4;
-// motor ring, 16-byte groups: draws, rotor speeds before and after, thrust
-// and torques, the rotor commands and their derivatives w.r.t. the action
-constexpr int MOTOR_VEC = 6;
-// contact ring words: response flag, contact set, penalty adjoint
-constexpr int CON_WORDS = 5;
+// Loads whose address is known go out AHEAD substeps before their use: a
+// substep of these pipelines is shorter than a read from HBM, which had set
+// their pace at one substep ahead (1.1-1.3 us a substep whatever the stages
+// did).  A value in flight cannot move between registers, so the steps are
+// unrolled and each has a register set of its own.
+constexpr int AHEAD = 4;
 
-template <typename R, typename F>
-__device__ __forceinline__ void rec_body_floats(R& r, F&& f) {
-  int w = 0;
-  auto g = [&](auto& v) { f(w++, v); };
-#pragma unroll
-  for (int k = 0; k < 9; ++k) g(r.P[k]);
-#pragma unroll
-  for (int k = 0; k < 3; ++k) { g(r.w0[k]); g(r.v0[k]); g(r.F[k]); g(r.wdot[k]); g(r.w1[k]); }
-#pragma unroll
-  for (int k = 0; k < 3; ++k) { g(r.A1[k]); g(r.c0[k]); g(r.c1[k]); }
-  g(r.T); g(r.i0); g(r.dp); g(r.i1);
-  g(r.mu_n); g(r.fb[0]); g(r.fb[1]); g(r.nv); g(r.nf); g(r.mag);
-  g(r.hx); g(r.hy); g(r.nh); g(r.kx); g(r.ky); g(r.nk);
-}
-
-__device__ __forceinline__ uint32_t rec_flags(const Rec& r) {
-  uint32_t b = (uint32_t)r.rest | (uint32_t)r.statik << 1 | (uint32_t)r.guard << 2 |
-               (uint32_t)r.bounced << 3 | (uint32_t)r.hit << 4 | (uint32_t)r.fallback << 5;
-#pragma unroll
-  for (int k = 0; k < 3; ++k) b |= (uint32_t)r.clamp[k] << (6 + k) | (uint32_t)r.flip[k] << (9 + k);
-  return b;
-}
-
-__device__ __forceinline__ void rec_unflag(Rec& r, uint32_t b) {
-  r.rest = b & 1u;
-  r.statik = (b >> 1) & 1u;
-  r.guard = (b >> 2) & 1u;
-  r.bounced = (b >> 3) & 1u;
-  r.hit = (b >> 4) & 1u;
-  r.fallback = (b >> 5) & 1u;
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    r.clamp[k] = (b >> (6 + k)) & 1u;
-    r.flip[k] = (b >> (9 + k)) & 1u;
+// f(i, slot) for the steps i of a wavefront's pipeline, slot = i mod A at
+// compile time, and the workgroup's barrier after each.
+template <int A, typename F>
+__device__ __forceinline__ void pipe_steps(int n_pipe, F&& f) {
+  static_assert(A == 1 || A == 4, "unrolled by one or four");
+  auto step = [&](int i, auto slot) {
+    if (i < n_pipe) {
+      f(i, slot);
+      wg_sync();
+    }
+  };
+  for (int i = 0; i < n_pipe; i += A) {
+    step(i, std::integral_constant<int, 0>{});
+    if constexpr (A == 4) {
+      step(i + 1, std::integral_constant<int, 1>{});
+      step(i + 2, std::integral_constant<int, 2>{});
+      step(i + 3, std::integral_constant<int, 3>{});
+    }
   }
 }
 
-// The rotor state and the draws of one tape row.
-__device__ __forceinline__ void load_rotor(const Consts& c, const float* __restrict__ row,
-                                           long long ld, int q, float u[4], float e[4],
-                                           float z[4]) {
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    u[k] = row[(S_U + k) * ld + q];
-    e[k] = row[(S_E + k) * ld + q];
-  }
-  load_draws(c, row, ld, q, z);
-}
+template <int P, bool NW>
+constexpr int kPipeWaves = 3 + (P != PEN_NONE ? 1 : 0) + (NW ? 1 : 0);
 
-template <int N, bool PEN>
-__global__ __launch_bounds__(256) void reverse_pipe_kernel(const Consts* __restrict__ cp, Ptrs p,
-                                                           const float* __restrict__ act,
-                                                           int ncalls, int nsub,
-                                                           unsigned long long t0,
-                                                           const float* __restrict__ tape,
-                                                           float* __restrict__ lam, int wide,
-                                                           float* __restrict__ gact,
-                                                           float* __restrict__ gpar) {
-  constexpr int BS = 64, NTAPE = kTapeRows<PEN>;
-  static_assert(N == 1 || N == 8, "pipelined reverse sweep for swarms of 1 or 8");
-  // Slots are indexed by the substep k.  Tile rows 0-8 post-motion start
-  // position, displacement, velocity (wavefront 1); 9-11 adjoint of the
-  // collision velocity change (wavefront 3).
-  __shared__ float tl[3][12][BS];
-  __shared__ float4 ring[3][RING_VEC][BS];
-  __shared__ float4 mring[4][MOTOR_VEC][BS];
-  __shared__ float cring[2][CON_WORDS][BS];
-  const Consts& c = *cp;
+template <int N, int P, bool TAPE, bool NW>
+__device__ __forceinline__ void forward_pipe(const Consts& c, const Ptrs& p,
+                                             const float* __restrict__ S, long long ld,
+                                             const float* __restrict__ act, int nc, int nsub,
+                                             unsigned long long t0, float* __restrict__ out,
+                                             int every, const float* __restrict__ gpen,
+                                             float* __restrict__ pen, float beta) {
+  constexpr int BS = 64, NTAPE = kTapeRows<P == PEN_GRAD>;
+  constexpr int M = NW ? 1 : 0;     // step of the first substep's motor part
+  __shared__ float sxv[2][PENROW + 1][BS];
+  __shared__ float4 zring[2][BS];   // motor noise
+  __shared__ float ring[2][4][BS];  // T, torques
+  __shared__ float r3[2][3][BS];    // third column of R after free flight
+  __shared__ uint32_t evr[2][BS];   // the substep's events
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int tid = threadIdx.x & 63;
   int qb, cnt, ls, n;
@@ -869,331 +651,85 @@ __global__ __launch_bounds__(256) void reverse_pipe_kernel(const Consts* __restr
   const int q = qb + (live ? tid : 0);
   const int me = tid - ls;
   const long long Q = p.Q;
-  const bool collide = (c.flags & F_COLLIDE) != 0;
-  const bool pairs = N != 1 && (collide || PEN);
-  const int n_steps = ncalls * nsub;
-  const int n_pipe = n_steps + 3;  // steps of the pipeline
-
+  const int n_steps = nc * nsub;
+  const int n_pipe = n_steps + M + (P != PEN_NONE ? 2 : 1);  // steps of the pipeline
   QuadPar pp;
   ParAdj pa;
   if (live) load_params(p, c, q, pp, pa);
+  // field f of the quad in a row of Q (a 32-bit byte offset from the row:
+  // these batches stay far below 2^32 bytes a row)
+  const uint32_t qo = 4u * (uint32_t)q, fo = 4u * (uint32_t)p.Q;
+  auto at = [&](float* row, int f) -> float& {
+    return *reinterpret_cast<float*>(reinterpret_cast<char*>(row) + (qo + (uint32_t)f * fo));
+  };
+  // where the state before substep k goes (uniform), or null
+  auto row_of = [&](int k) -> float* {
+    if constexpr (TAPE) return out + (long long)k * NTAPE * Q;
+    const int call = k / nsub;
+    if (!out || k != call * nsub || call % every != 0) return nullptr;
+    return out + (long long)(call / every) * NSTATE * Q;
+  };
 
   if (wave == 0) {
-    // ---- motor part of substep k = n_steps - 1 - i at step i
-    float un[4], en[4], zn[4] = {0.f, 0.f, 0.f, 0.f};
-    float uhat[4] = {0.f, 0.f, 0.f, 0.f}, dua[4] = {0.f, 0.f, 0.f, 0.f};
-    float4 a_nx = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (live && n_steps > 0) {
-      load_rotor(c, tape + (long long)(n_steps - 1) * NTAPE * Q, Q, q, un, en, zn);
-      a_nx = load_act(act + (long long)(ncalls - 1) * Q * 4, q);
-    }
-    for (int i = 0; i < n_pipe; ++i) {
-      if (i < n_steps) {
-        const int k = n_steps - 1 - i;
-        const int call = k / nsub, sub = k - call * nsub;
-        if (sub == nsub - 1) {  // the call's last substep comes first
-          const float4 a4 = a_nx;
-          if (live && call > 0) a_nx = load_act(act + (long long)(call - 1) * Q * 4, q);
-          if (live) {
-            act_uhat(c, p, a4, uhat);
-            dua[0] = duhat_da(c, a4.x, uhat[0]);
-            dua[1] = duhat_da(c, a4.y, uhat[1]);
-            dua[2] = duhat_da(c, a4.z, uhat[2]);
-            dua[3] = duhat_da(c, a4.w, uhat[3]);
-          }
-        }
-        if (live) {
-          float u[4], e[4], zi[4], z[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int m = 0; m < 4; ++m) {
-            u[m] = un[m];
-            e[m] = en[m];
-            zi[m] = zn[m];
-          }
-          if (k > 0) load_rotor(c, tape + (long long)(k - 1) * NTAPE * Q, Q, q, un, en, zn);
-          float4(*ms)[BS] = mring[k & 3];
-          ms[1][tid] = make_float4(u[0], u[1], u[2], u[3]);
-          const Drive d = motor_step<Z_IMPORT>(c, pp, u, e, uhat, (uint32_t)q,
-                                               t0 + (unsigned long long)k, z, zi);
-          ms[0][tid] = make_float4(z[0], z[1], z[2], z[3]);
-          ms[2][tid] = make_float4(u[0], u[1], u[2], u[3]);
-          ms[3][tid] = make_float4(d.T, d.tx, d.ty, d.tz);
-          ms[4][tid] = make_float4(uhat[0], uhat[1], uhat[2], uhat[3]);
-          ms[5][tid] = make_float4(dua[0], dua[1], dua[2], dua[3]);
-        }
-      }
-      wg_sync();
-    }
-  } else if (wave == 1) {
-    // ---- body part of substep k = n_steps - i at step i >= 1
-    Quad sn;
-    if (live && n_steps > 0) load_body(tape + (long long)(n_steps - 1) * NTAPE * Q, Q, q, sn);
-    wg_sync();  // step 0: no thrust yet
-    for (int i = 1; i < n_pipe; ++i) {
-      if (i <= n_steps && live) {
-        const int k = n_steps - i;
-        Quad s = sn;
-        s.fl = word_flag(__float_as_uint(s.fl), me, wide);
-        if (k > 0) load_body(tape + (long long)(k - 1) * NTAPE * Q, Q, q, sn);
-        const float4 dv = mring[k & 3][3][tid];
-        Drive d;
-        d.T = dv.x;
-        d.tx = dv.y;
-        d.ty = dv.z;
-        d.tz = dv.w;
-        Rec r;
-        body_step<true>(c, pp, s, d, (uint32_t)q, t0 + (unsigned long long)k, &r);
-        if (pairs) {
-          float(*tile)[BS] = tl[k % 3];
-#pragma unroll
-          for (int m = 0; m < 3; ++m) {
-            tile[m][tid] = s.xo[m];
-            tile[3 + m][tid] = s.inc[m];
-            tile[6 + m][tid] = s.v[m];
-          }
-        }
-        float w4[4 * RING_VEC];
-        rec_body_floats(r, [&](int w, const float& v) { w4[w] = v; });
-        w4[REC_BODY] = __uint_as_float(rec_flags(r));
-#pragma unroll
-        for (int w = RING_WORDS; w < 4 * RING_VEC; ++w) w4[w] = 0.f;
-        float4(*slot)[BS] = ring[k % 3];
-#pragma unroll
-        for (int g = 0; g < RING_VEC; ++g)
-          slot[g][tid] = make_float4(w4[4 * g], w4[4 * g + 1], w4[4 * g + 2], w4[4 * g + 3]);
-      }
-      wg_sync();
-    }
-  } else if (wave == 2) {
-    // ---- contacts of substep k = n_steps + 1 - i at step i >= 2
-    wg_sync();  // steps 0 and 1: no exchange tile yet
-    uint32_t wn = 0u;
-    float pn[3] = {0.f, 0.f, 0.f};
-    auto load = [&](int k) {
-      const float* row = tape + (long long)k * NTAPE * Q;
-      wn = __float_as_uint(row[S_F * Q + q]);
-      if constexpr (PEN) load_pen(row, Q, q, pn);
-    };
-    if (live && n_steps > 0) load(n_steps - 1);
-    wg_sync();
-    for (int i = 2; i < n_pipe; ++i) {
-      if (pairs && i <= n_steps + 1 && live) {
-        const int k = n_steps + 1 - i;
-        const uint32_t cm = word_resp(wn, me, wide);
-        float(*cs)[BS] = cring[k & 1];
-        cs[0][tid] = cm != 0u ? 1.f : 0.f;
-        cs[1][tid] = __uint_as_float(cm);
-#pragma unroll
-        for (int m = 0; m < 3; ++m) cs[2 + m][tid] = pn[m];
-        if (k > 0) load(k - 1);
-      }
-      wg_sync();
-    }
-  } else {
-    // ---- differentiate substep k = n_steps + 2 - i at step i >= 3
-    Adj l;
-    float gp[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    if (live) {
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        l.x[k] = lam[(S_X + k) * Q + q];
-        l.v[k] = lam[(S_V + k) * Q + q];
-        l.w[k] = lam[(S_W + k) * Q + q];
-      }
-#pragma unroll
-      for (int k = 0; k < 9; ++k) l.R[k] = lam[(S_R + k) * Q + q];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        l.u[k] = lam[(S_U + k) * Q + q];
-        l.e[k] = lam[(S_E + k) * Q + q];
-      }
-    }
-    // the rotor commands and their derivatives come from the motor stage
-    float gu[4] = {0.f, 0.f, 0.f, 0.f};
-    wg_sync();  // steps 0 to 2: no record complete yet
-    wg_sync();
-    wg_sync();
-    for (int i = 3; i < n_pipe; ++i) {
-      const int k = n_steps + 2 - i;
-      const int call = k / nsub, sub = k - call * nsub;
-      if (sub == nsub - 1) {
-#pragma unroll
-        for (int m = 0; m < 4; ++m) gu[m] = 0.f;
-      }
-      if (live) {
-        const float4(*slot)[BS] = ring[k % 3];
-        const float4(*ms)[BS] = mring[k & 3];
-        Rec r;
-        const float4 z4 = ms[0][tid], u04 = ms[1][tid], u14 = ms[2][tid], uh4 = ms[4][tid];
-        r.z[0] = z4.x; r.z[1] = z4.y; r.z[2] = z4.z; r.z[3] = z4.w;
-        r.u0[0] = u04.x; r.u0[1] = u04.y; r.u0[2] = u04.z; r.u0[3] = u04.w;
-        r.u1[0] = u14.x; r.u1[1] = u14.y; r.u1[2] = u14.z; r.u1[3] = u14.w;
-        const float uhat[4] = {uh4.x, uh4.y, uh4.z, uh4.w};
-        float w4[4 * RING_VEC];
-#pragma unroll
-        for (int g = 0; g < RING_VEC; ++g) {
-          const float4 v4 = slot[g][tid];
-          w4[4 * g] = v4.x;
-          w4[4 * g + 1] = v4.y;
-          w4[4 * g + 2] = v4.z;
-          w4[4 * g + 3] = v4.w;
-        }
-        rec_body_floats(r, [&](int w, float& v) { v = w4[w]; });
-        rec_unflag(r, __float_as_uint(w4[REC_BODY]));
-        if (pairs) {
-          const float(*cs)[BS] = cring[k & 1];
-          const bool hit = cs[0][tid] != 0.f;
-          const unsigned long long cm = __float_as_uint(cs[1][tid]);
-          if constexpr (PEN) {
-#pragma unroll
-            for (int m = 0; m < 3; ++m) l.x[m] += cs[2 + m][tid];
-          }
-          float(*tile)[BS] = tl[k % 3];
-          float ldv[3] = {0.f, 0.f, 0.f};
-          if (hit) {
-#pragma unroll
-            for (int m = 0; m < 3; ++m) {
-              ldv[m] = c.col_decay * l.v[m];
-              l.v[m] = ldv[m];
-            }
-          }
-#pragma unroll
-          for (int m = 0; m < 3; ++m) tile[9 + m][tid] = ldv[m];
-          wave_sync();
-          if (cm != 0ull) {
-            Quad so;  // the quad's post-motion position and velocity
-#pragma unroll
-            for (int m = 0; m < 3; ++m) {
-              so.xo[m] = tile[m][tid];
-              so.inc[m] = tile[3 + m][tid];
-              so.v[m] = tile[6 + m][tid];
-            }
-            response_vjp<BS>(c, tile, tile + 9, so, ls, me, cm, ldv, l);
-          }
-        }
-        quad_vjp(c, pp, pa, r, uhat, l, gu, gp);
-        if (sub == 0) {
-          const float4 da = ms[5][tid];
-          float4 g;
-          g.x = gu[0] * da.x;
-          g.y = gu[1] * da.y;
-          g.z = gu[2] * da.z;
-          g.w = gu[3] * da.w;
-          reinterpret_cast<float4*>(gact + (long long)call * Q * 4)[q] = g;
-        }
-      } else if (pairs) {
-        wave_sync();
-      }
-      wg_sync();
-    }
-    if (live) {
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        lam[(S_X + k) * Q + q] = l.x[k];
-        lam[(S_V + k) * Q + q] = l.v[k];
-        lam[(S_W + k) * Q + q] = l.w[k];
-      }
-#pragma unroll
-      for (int k = 0; k < 9; ++k) lam[(S_R + k) * Q + q] = l.R[k];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        lam[(S_U + k) * Q + q] = l.u[k];
-        lam[(S_E + k) * Q + q] = l.e[k];
-      }
-      lam[S_F * Q + q] = 0.f;
-#pragma unroll
-      for (int k = 0; k < 6; ++k) gpar[k * Q + q] += gp[k];
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// rollout_pipe_kernel: rollout_kernel for small batches, over two or three
-// wavefronts per workgroup of 64 quads.  The motor part of a substep (lag,
-// noise, thrust, mix) depends on the rotor state, the action and the
-// substep's draws only, so wavefront 0 runs it one substep ahead and hands
-// the thrust and torques (4 words per quad) to wavefront 1 through a
-// two-slot LDS ring; wavefront 1 runs the body part and the in-swarm pass.
-// The smoothed collision penalty never feeds back into the motion, so in
-// swarms with a penalty wavefront 2 sums it one substep behind, from the
-// post-motion exchange tile.  One workgroup barrier per substep; each
-// wavefront stores its own fields of the checkpoints and of the final state.
-// Same arithmetic in the same order as rollout_kernel, so the results are
-// identical.
-// ---------------------------------------------------------------------------
-template <int N, bool PEN>
-constexpr int kRollWaves = (PEN && N != 1) ? 3 : 2;
-
-template <int N, bool PEN>
-__global__ __launch_bounds__(192) void rollout_pipe_kernel(const Consts* __restrict__ cp, Ptrs p,
-                                                           const float* __restrict__ act,
-                                                           int ncalls, int nsub,
-                                                           unsigned long long t0,
-                                                           float* __restrict__ ckpt,
-                                                           int ckpt_every,
-                                                           float* __restrict__ pen, float beta) {
-  constexpr int BS = 64;
-  constexpr bool PW = kRollWaves<N, PEN> == 3;  // penalty on its own wavefront
-  static_assert(N == 8 || (N == 1 && !PEN), "pipelined rollout for swarms of 1 or 8");
-  __shared__ float sxv[2][TILE_ROWS_CO][BS];
-  __shared__ float ring[2][4][BS];
-  const Consts& c = *cp;
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int tid = threadIdx.x & 63;
-  int qb, cnt, ls, n;
-  block_map<BS, N>(p, tid, qb, cnt, ls, n);
-  const bool live = tid < cnt;
-  const int q = qb + (live ? tid : 0);
-  const int me = tid - ls;
-  const long long Q = p.Q;
-  const int n_steps = ncalls * nsub;
-  const int n_pipe = n_steps + (PW ? 2 : 1);  // steps of the pipeline
-  QuadPar pp;
-  ParAdj pa;
-  if (live) load_params(p, c, q, pp, pa);
-
-  if (wave == 0) {
-    // ---- motor part of substep i at step i
+    // ---- motor part of substep i - M at step i
     float u[4], e[4];
     if (live) {
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        u[k] = p.st[(S_U + k) * p.Qp + q];
-        e[k] = p.st[(S_E + k) * p.Qp + q];
+        u[k] = S[(S_U + k) * ld + q];
+        e[k] = S[(S_E + k) * ld + q];
       }
     }
     float uhat[4] = {0.f, 0.f, 0.f, 0.f};
-    float4 a_nx = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (live && ncalls > 0) a_nx = load_act(act, q);
-    for (int i = 0; i < n_pipe; ++i) {
+    // each substep's action row, A substeps before its use (the recompute's
+    // many workgroups hide the read, and its stores want the registers)
+    constexpr int A = TAPE ? 1 : AHEAD;
+    float4 aq[A];
+#pragma unroll
+    for (int d = 0; d < A; ++d) aq[d] = load_act(act + (long long)min(d / nsub, nc - 1) * Q * 4, q);
+    int sub = 0, call_a = A / nsub, sub_a = A % nsub;  // of substeps i and i + A
+    if constexpr (M > 0) wg_sync();  // step 0: no draws yet
+    pipe_steps<A>(n_pipe - M, [&](int i, auto slot_c) {
+      constexpr int D = decltype(slot_c)::value;
       if (i < n_steps) {
-        const int call = i / nsub, sub = i - call * nsub;
-        if (sub == 0) {
-          const float4 a4 = a_nx;
-          if (live && call + 1 < ncalls) a_nx = load_act(act + (long long)(call + 1) * Q * 4, q);
-          if (ckpt && call % ckpt_every == 0 && live) {
-            float* ck = ckpt + (long long)(call / ckpt_every) * NSTATE * Q;
+        const float4 a4 = aq[D];
+        aq[D] = load_act(act + (long long)min(call_a, nc - 1) * Q * 4, q);
+        if (sub == 0 && live) act_uhat(c, p, a4, uhat);
+        if (live) {
+          float* row = row_of(i);
+          if (row) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-              ck[(S_U + k) * Q + q] = u[k];
-              ck[(S_E + k) * Q + q] = e[k];
+              at(row, S_U + k) = u[k];
+              at(row, S_E + k) = e[k];
             }
           }
-          if (live) act_uhat(c, p, a4, uhat);
-        }
-        if (live) {
-          float z[4] = {0.f, 0.f, 0.f, 0.f};
-          const Drive d = motor_step(c, pp, u, e, uhat, (uint32_t)q, t0 + (unsigned long long)i, z);
+          float z[4] = {0.f, 0.f, 0.f, 0.f}, zi[4] = {0.f, 0.f, 0.f, 0.f};
+          if constexpr (M > 0) {
+            const float4 z4 = zring[i & 1][tid];
+            zi[0] = z4.x;
+            zi[1] = z4.y;
+            zi[2] = z4.z;
+            zi[3] = z4.w;
+          }
+          const Drive d = motor_step<M == 0 ? Z_DRAW : Z_IMPORT>(
+              c, pp, u, e, uhat, (uint32_t)q, t0 + (unsigned long long)i, z, zi);
+          if (TAPE && (c.flags & F_NOISE)) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) at(row, NSTATE + k) = z[k];
+          }
           float(*slot)[BS] = ring[i & 1];
           slot[0][tid] = d.T;
           slot[1][tid] = d.tx;
           slot[2][tid] = d.ty;
           slot[3][tid] = d.tz;
         }
+        sub = sub + 1 == nsub ? 0 : sub + 1;
+        sub_a = sub_a + 1 == nsub ? 0 : sub_a + 1;
+        call_a += sub_a == 0 ? 1 : 0;
       }
-      wg_sync();
-    }
-    if (live) {
+    });
+    if (!TAPE && live) {
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         p.st[(S_U + k) * p.Qp + q] = u[k];
@@ -1201,86 +737,599 @@ __global__ __launch_bounds__(192) void rollout_pipe_kernel(const Consts* __restr
       }
     }
   } else if (wave == 1) {
-    // ---- body part and in-swarm pass of substep i - 1 at step i
+    // ---- translation and in-swarm pass of substep i - M - 1 at step i
     Quad s;
-    if (live) load_state(p.st, p.Qp, q, s);
-    const bool pairs = N != 1 && ((c.flags & (F_COLLIDE | F_DOWNWASH)) != 0 || PEN);
-    wg_sync();  // step 0: no thrust yet
-    for (int i = 1; i < n_pipe; ++i) {
-      if (i <= n_steps) {
-        const int sidx = i - 1;
-        const int call = sidx / nsub, sub = sidx - call * nsub;
-        if (sub == 0 && ckpt && call % ckpt_every == 0 && live) {
-          float* ck = ckpt + (long long)(call / ckpt_every) * NSTATE * Q;
+    float c2[3] = {0.f, 0.f, 0.f};  // third column of R at the substep's start
+    uint32_t ev = 0u;
+    s.ev = 0u;
+    if (live) {
 #pragma unroll
-          for (int k = 0; k < 3; ++k) {
-            ck[(S_X + k) * Q + q] = s.x[k];
-            ck[(S_V + k) * Q + q] = s.v[k];
-            ck[(S_W + k) * Q + q] = s.w[k];
-          }
-#pragma unroll
-          for (int k = 0; k < 9; ++k) ck[(S_R + k) * Q + q] = s.R[k];
-          ck[S_F * Q + q] = s.fl;
-        }
-        const unsigned long long t = t0 + (unsigned long long)sidx;
+      for (int k = 0; k < 3; ++k) {
+        s.x[k] = S[(S_X + k) * ld + q];
+        s.v[k] = S[(S_V + k) * ld + q];
+        c2[k] = S[(S_R + 3 * k + 2) * ld + q];
+      }
+      s.fl = S[S_F * ld + q];
+    }
+    const bool pairs = N != 1 && (c.flags & (F_COLLIDE | F_DOWNWASH)) != 0;
+    for (int i = 0; i < M + 1; ++i) wg_sync();  // no thrust yet
+    for (int k_s = 0; k_s < n_pipe - M - 1; ++k_s) {
+      if (k_s < n_steps) {
+        const unsigned long long t = t0 + (unsigned long long)k_s;
+        float* row = row_of(k_s);
+        const float fl0 = s.fl;
+        unsigned long long resp = 0ull;
+        float(*tile)[BS] = sxv[k_s & 1];
         if (live) {
-          const float(*slot)[BS] = ring[sidx & 1];
-          Drive d;
-          d.T = slot[0][tid];
-          d.tx = slot[1][tid];
-          d.ty = slot[2][tid];
-          d.tz = slot[3][tid];
-          body_step(c, pp, s, d, (uint32_t)q, t);
-        }
-        if (pairs) {
-          float(*tile)[BS] = sxv[sidx & 1];
-          if (live) {
+          if (row) {
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
-              tile[k][tid] = s.xo[k];
-              tile[3 + k][tid] = s.inc[k];
-              tile[6 + k][tid] = s.v[k];
+              at(row, S_X + k) = s.x[k];
+              at(row, S_V + k) = s.v[k];
             }
-            put_screen_rows<kScreenSq<N>>(tile, tid, s.x);
+            if constexpr (!TAPE) at(row, S_F) = s.fl;
           }
-          wave_sync();
-          if (live) pair_pass<BS, N, PEN_NONE, true>(c, tile, s, ls, n, me, (uint32_t)q, t);
+          if (k_s > 0) {
+            // the events of the substep before decide what became of R
+            const float(*col)[BS] = r3[(k_s - 1) & 1];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+              c2[k] = (ev & SUB_REST) ? c2[k] : col[k][tid];
+              c2[k] = (ev & SUB_HIT) ? (k == 2 ? 1.0f : 0.0f) : c2[k];
+            }
+          }
+          ev = trans_step(c, pp, s, ring[k_s & 1][0][tid], c2[0], c2[1], c2[2], (uint32_t)q, t);
+          if ((pairs && N != 8) || P != PEN_NONE) put_tile<kScreenSq<N>, true>(tile, tid, s);
         }
+        if constexpr (N == 8) {
+          if (pairs) {
+            uint32_t pev = 0u;
+            lane_pair_pass<BS, N, P == PEN_NONE>(c, tile, s, live, ls, n, me, tid, (uint32_t)q, t,
+                                                 &resp, &pev);
+            ev |= live ? pev : 0u;
+          }
+        } else if (pairs) {
+          wave_sync();
+          uint32_t pev = 0u;
+          if (live)
+            pair_pass<BS, N, PEN_NONE, true>(c, tile, s, ls, n, me, (uint32_t)q, t, nullptr,
+                                             nullptr, &resp, &pev);
+          ev |= pev;
+        }
+        evr[k_s & 1][tid] = ev;
+        if (TAPE && live) at(row, S_F) = tape_word(fl0, resp, me, 0);
       }
       wg_sync();
     }
-    if (live) {
+    if (!TAPE && live) {
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
         p.st[(S_X + k) * p.Qp + q] = s.x[k];
         p.st[(S_V + k) * p.Qp + q] = s.v[k];
-        p.st[(S_W + k) * p.Qp + q] = s.w[k];
       }
-#pragma unroll
-      for (int k = 0; k < 9; ++k) p.st[(S_R + k) * p.Qp + q] = s.R[k];
       p.st[S_F * p.Qp + q] = s.fl;
       float chk = 0.f;
 #pragma unroll
-      for (int k = 0; k < 3; ++k) chk += s.x[k] + s.v[k] + s.w[k];
-#pragma unroll
-      for (int k = 0; k < 9; ++k) chk += s.R[k];
+      for (int k = 0; k < 3; ++k) chk += s.x[k] + s.v[k];
       if (!isfinite(chk))
         __hip_atomic_fetch_or(p.err, ERRBIT_STATE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-  } else if constexpr (PW) {
-    // ---- penalty of substep i - 2 at step i, from the exchange tile
-    Pen pn = make_pen(c, beta, N > 0 ? N : wave_max(live ? n : 0));
-    wg_sync();  // steps 0 and 1: no tile yet
-    wg_sync();
-    for (int i = 2; i < n_pipe; ++i) {
-      if (live) {
-        const float(*tile)[BS] = sxv[(i - 2) & 1];
-        const Quad so = tile_quad(tile, tid);
-        penalty_pass<BS, N, PEN_SUM>(c, tile, so, ls, n, me, pn);
+  } else if (wave == 2) {
+    // ---- rotation of substep i - M - 1 at step i
+    float R[9], w[3], R0[9];
+    if (live) {
+#pragma unroll
+      for (int k = 0; k < 9; ++k) R[k] = R0[k] = S[(S_R + k) * ld + q];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) w[k] = S[(S_W + k) * ld + q];
+    }
+    // the events of substep k, which started from R0
+    auto answer = [&](int k) {
+      const uint32_t ev = evr[k & 1][tid];
+      if (ev & SUB_TURNS) {
+        const unsigned long long t = t0 + (unsigned long long)k;
+        rot_events(c, ev, R, w, R0, (uint32_t)q, t);
+        rot_pair_events(c, ev, w, (uint32_t)q, t);
+      }
+    };
+    for (int i = 0; i < M + 1; ++i) wg_sync();  // no torques yet
+    for (int k_s = 0; k_s < n_pipe - M - 1; ++k_s) {
+      if (k_s < n_steps && live) {
+        if (k_s > 0) answer(k_s - 1);
+        float* row = row_of(k_s);
+        if (row) {
+#pragma unroll
+          for (int k = 0; k < 9; ++k) at(row, S_R + k) = R[k];
+#pragma unroll
+          for (int k = 0; k < 3; ++k) at(row, S_W + k) = w[k];
+        }
+        const float(*slot)[BS] = ring[k_s & 1];
+#pragma unroll
+        for (int k = 0; k < 9; ++k) R0[k] = R[k];
+        rot_step(c, pp, R, w, slot[1][tid], slot[2][tid], slot[3][tid]);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) r3[k_s & 1][k][tid] = R[3 * k + 2];
       }
       wg_sync();
     }
-    if (live) pen[q] += pn.acc[0];
+    if (!TAPE && live) {
+      if (n_steps > 0) answer(n_steps - 1);
+#pragma unroll
+      for (int k = 0; k < 9; ++k) p.st[(S_R + k) * p.Qp + q] = R[k];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) p.st[(S_W + k) * p.Qp + q] = w[k];
+      float chk = 0.f;
+#pragma unroll
+      for (int k = 0; k < 9; ++k) chk += R[k];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) chk += w[k];
+      if (!isfinite(chk))
+        __hip_atomic_fetch_or(p.err, ERRBIT_STATE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  } else if (NW && (P == PEN_NONE || wave == 4)) {
+    // ---- motor noise of substep i at step i
+    for (int i = 0; i < n_pipe; ++i) {
+      if (i < n_steps && live && (c.flags & F_NOISE)) {
+        float z[4];
+        normal4(c, (uint32_t)q, t0 + (unsigned long long)i, STREAM_MOTOR, 0, z);
+        zring[i & 1][tid] = make_float4(z[0], z[1], z[2], z[3]);
+      }
+      wg_sync();
+    }
+  } else if constexpr (P != PEN_NONE) {
+    // ---- the penalty, or its adjoint, of substep i - M - 2 at step i
+    float h_me = 0.f;
+    if constexpr (P == PEN_GRAD) {
+      h_me = live ? -0.5f * gpen[q] : 0.f;
+      sxv[0][PENROW][tid] = h_me;
+      sxv[1][PENROW][tid] = h_me;
+    }
+    Pen pn = make_pen(c, beta, N > 0 ? N : wave_max(live ? n : 0), h_me);
+    for (int i = 0; i < M + 2; ++i) wg_sync();  // no tile yet
+    for (int k_s = 0; k_s < n_steps; ++k_s) {
+      if (live) {
+        const float(*tile)[BS] = sxv[k_s & 1];
+        const Quad so = tile_quad(tile, tid);
+        if constexpr (P == PEN_GRAD) pn.acc[0] = pn.acc[1] = pn.acc[2] = 0.f;
+        penalty_pass<BS, N, P>(c, tile, so, ls, n, me, pn);
+        if constexpr (P == PEN_GRAD) {
+          float* row = row_of(k_s);
+#pragma unroll
+          for (int k = 0; k < 3; ++k) at(row, T_PEN + k) = pn.acc[k];
+        }
+      }
+      wg_sync();
+    }
+    if (P == PEN_SUM && live) pen[q] += pn.acc[0];
+  }
+}
+
+template <int N, bool PEN, bool NW>
+__global__ __launch_bounds__(NW ? 320 : 256) void rollout_pipe_kernel(const Consts* __restrict__ cp, Ptrs p,
+                                                           const float* __restrict__ act,
+                                                           int ncalls, int nsub,
+                                                           unsigned long long t0,
+                                                           float* __restrict__ ckpt,
+                                                           int ckpt_every,
+                                                           float* __restrict__ pen, float beta) {
+  const Consts c = *cp;  // (a copy: kept in registers across the barriers)
+  forward_pipe<N, PEN ? PEN_SUM : PEN_NONE, false, NW>(c, p, p.st, p.Qp, act, ncalls, nsub, t0, ckpt,
+                                                   ckpt_every, nullptr, pen, beta);
+}
+
+// grid (workgroups, segments of the chunk); arguments as recompute_kernel
+template <int N, bool PEN>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void recompute_pipe_kernel(const Consts* __restrict__ cp, Ptrs p,
+                                                             const float* __restrict__ ckpt,
+                                                             const float* __restrict__ act,
+                                                             int ncalls, int ce, int nsub,
+                                                             unsigned long long t0,
+                                                             float* __restrict__ tape,
+                                                             const float* __restrict__ gpen,
+                                                             float beta) {
+  const long long Q = p.Q;
+  const int c0 = blockIdx.y * ce;
+  const Consts c = *cp;
+  forward_pipe<N, PEN ? PEN_GRAD : PEN_NONE, true, false>(
+      c, p, ckpt + (long long)blockIdx.y * NSTATE * Q, Q, act + (long long)c0 * Q * 4,
+      min(ce, ncalls - c0), nsub, t0 + (unsigned long long)c0 * nsub,
+      tape + (long long)c0 * nsub * kTapeRows<PEN> * Q, 1, gpen, nullptr, beta);
+}
+
+// ---------------------------------------------------------------------------
+// reverse_pipe_kernel: the reverse sweep of reverse_kernel for small batches
+// without swarms above 32 (see forward_pipe), on seven wavefronts.  A substep's
+// re-run starts from its taped state, so no stage waits for the substep after
+// it, and of the derivative only the parts that feed themselves are serial.
+// Substep k passes through:
+//  step i      wavefront 6: the rotor commands and their derivatives;
+//  step i + 1  wavefront 0: the motor part re-run from the taped rotor state
+//              and draws;
+//  step i + 2  wavefront 1: the translation re-run (dL's factors and the
+//              exchange tile), wavefront 2: the rotation re-run;
+//  step i + 3  wavefront 5: the responses' and the translation's derivative;
+//  step i + 4  wavefront 3: the rotation's;
+//  step i + 5  wavefront 4: the motor's, and the action gradients.
+// Wavefronts 4 to 6 share the SIMDs of the lighter ones of the first four.
+// Same arithmetic in the same order as reverse_kernel, so identical results.
+// The derivative, the body's re-run and the commands with the motor's on one
+// wavefront each, and loads one substep ahead: 1024 x 8, 200 substeps, 241 us,
+// now 185.
+//  un: the uniform swarm size (a power of two) or 0 (table of sizes)
+// ---------------------------------------------------------------------------
+template <bool PEN>
+__global__ __launch_bounds__(448) void reverse_pipe_kernel(const Consts* __restrict__ cp, Ptrs p,
+                                                           const float* __restrict__ act,
+                                                           int ncalls, int nsub,
+                                                           const float* __restrict__ tape,
+                                                           float* __restrict__ lam, int un,
+                                                           float* __restrict__ gact,
+                                                           float* __restrict__ gpar,
+                                                           unsigned long long t0) {
+  constexpr int BS = 64, NTAPE = kTapeRows<PEN>;
+  // rings, indexed by the substep; as many slots as steps pass from the first
+  // write of one to its last read
+  __shared__ float4 uring[6][2][BS];  // rotor command; its derivative w.r.t. the action
+  __shared__ float4 mring[5][4][BS];  // T and torques; draws; u before, after
+  __shared__ float4 tring[2][2][BS];  // F, start velocity, events
+  __shared__ float4 rring[3][8][BS];  // the rotation's record
+  __shared__ float tile[2][9][BS];    // start position, displacement, velocity
+  __shared__ float ldvt[3][BS];       // adjoint of the collision velocity change
+  __shared__ float4 aring[2][BS];     // lF, events
+  __shared__ float lring[3][BS];      // lm
+  __shared__ float4 bring[2][BS];     // lT, lt
+  const Consts c = *cp;  // (a copy: kept in registers across the barriers)
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int tid = threadIdx.x & 63;
+  int qb, cnt, ls, n;
+  if (un > 0) {
+    qb = blockIdx.x * BS;
+    cnt = min(BS, p.Q - qb);
+    ls = tid & ~(un - 1);
+  } else {
+    block_map<BS, 0>(p, tid, qb, cnt, ls, n);
+  }
+  const bool live = tid < cnt;
+  const int q = qb + (live ? tid : 0);
+  const int me = tid - ls;
+  const long long Q = p.Q;
+  const int n_steps = ncalls * nsub;
+  const int n_pipe = n_steps + 5;  // steps of the pipeline
+  QuadPar pp;
+  ParAdj pa;
+  if (live) load_params(p, c, q, pp, pa);
+  const uint32_t qo = 4u * (uint32_t)q, fo = 4u * (uint32_t)p.Q;
+  auto at = [&](const float* row, int f) -> float {  // (see forward_pipe)
+    return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(row) +
+                                           (qo + (uint32_t)f * fo));
+  };
+  auto row_of = [&](int k) { return tape + (long long)k * NTAPE * Q; };
+  // the stage's substeps, last to first, each f(k); every wavefront passes
+  // the same barriers
+  // (with a load of substep k's row AHEAD steps before its f)
+  auto loading_stages = [&](int stage, auto&& load, auto&& f) {
+    if (live) {
+      auto first = [&](auto slot) { load(max(n_steps - 1 - decltype(slot)::value, 0), slot); };
+      first(std::integral_constant<int, 0>{});
+      first(std::integral_constant<int, 1>{});
+      first(std::integral_constant<int, 2>{});
+      first(std::integral_constant<int, 3>{});
+    }
+    for (int i = 0; i < stage; ++i) wg_sync();
+    pipe_steps<AHEAD>(n_pipe - stage, [&](int i, auto slot) {
+      const int k = n_steps - 1 - i;
+      if (k >= 0) f(k, slot, [&] { load(max(k - AHEAD, 0), slot); });
+    });
+  };
+  auto stages = [&](int stage, auto&& f) {
+    for (int i = 0; i < stage; ++i) wg_sync();
+    for (int i = stage; i < n_pipe; ++i) {
+      const int k = n_steps - 1 - (i - stage);
+      if (k >= 0) f(k);
+      wg_sync();
+    }
+  };
+
+  if (wave == 0) {
+    float un4[AHEAD][4], en[AHEAD][4], zn[AHEAD][4];
+    loading_stages(
+        1,
+        [&](int k, auto slot) {
+          constexpr int D = decltype(slot)::value;
+          const float* row = row_of(k);
+#pragma unroll
+          for (int m = 0; m < 4; ++m) {
+            un4[D][m] = at(row, S_U + m);
+            en[D][m] = at(row, S_E + m);
+            zn[D][m] = (c.flags & F_NOISE) ? at(row, NSTATE + m) : 0.f;
+          }
+        },
+        [&](int k, auto slot, auto&& next) {
+          constexpr int D = decltype(slot)::value;
+          if (!live) return;
+          float u[4], e[4], zi[4], z[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int m = 0; m < 4; ++m) {
+            u[m] = un4[D][m];
+            e[m] = en[D][m];
+            zi[m] = zn[D][m];
+          }
+          next();
+          const float4 uh = uring[k % 6][0][tid];
+          const float uhat[4] = {uh.x, uh.y, uh.z, uh.w};
+          float4(*ms)[BS] = mring[k % 5];
+          ms[2][tid] = make_float4(u[0], u[1], u[2], u[3]);
+          const Drive d = motor_step<Z_IMPORT>(c, pp, u, e, uhat, (uint32_t)q,
+                                               t0 + (unsigned long long)k, z, zi);
+          ms[0][tid] = make_float4(d.T, d.tx, d.ty, d.tz);
+          ms[1][tid] = make_float4(z[0], z[1], z[2], z[3]);
+          ms[3][tid] = make_float4(u[0], u[1], u[2], u[3]);
+        });
+  } else if (wave == 6) {
+    float4 aq[AHEAD];
+    float4 uh = make_float4(0.f, 0.f, 0.f, 0.f), du = uh;
+    int sub = nsub - 1, call_a = (n_steps - 1) / nsub, sub_a = nsub - 1;  // of the row to load
+    loading_stages(
+        0,
+        [&](int, auto slot) {
+          aq[decltype(slot)::value] = load_act(act + (long long)max(call_a, 0) * Q * 4, q);
+          call_a -= sub_a == 0 ? 1 : 0;
+          sub_a = sub_a == 0 ? nsub - 1 : sub_a - 1;
+        },
+        [&](int k, auto slot, auto&& next) {
+          const float4 a4 = aq[decltype(slot)::value];
+          if (live) {
+            if (sub == nsub - 1) {  // the call's last substep comes first
+              float uhat[4];
+              act_uhat(c, p, a4, uhat);
+              uh = make_float4(uhat[0], uhat[1], uhat[2], uhat[3]);
+              du = make_float4(duhat_da(c, a4.x, uhat[0]), duhat_da(c, a4.y, uhat[1]),
+                               duhat_da(c, a4.z, uhat[2]), duhat_da(c, a4.w, uhat[3]));
+            }
+            uring[k % 6][0][tid] = uh;
+            uring[k % 6][1][tid] = du;
+            next();
+          }
+          sub = sub == 0 ? nsub - 1 : sub - 1;
+        });
+  } else if (wave == 1) {
+    float xn[AHEAD][3], vn[AHEAD][3], cn[AHEAD][3], fn[AHEAD];
+    loading_stages(
+        2,
+        [&](int k, auto slot) {
+          constexpr int D = decltype(slot)::value;
+          const float* row = row_of(k);
+#pragma unroll
+          for (int m = 0; m < 3; ++m) {
+            xn[D][m] = at(row, S_X + m);
+            vn[D][m] = at(row, S_V + m);
+            cn[D][m] = at(row, S_R + 3 * m + 2);
+          }
+          fn[D] = at(row, S_F);
+        },
+        [&](int k, auto slot, auto&& next) {
+          constexpr int D = decltype(slot)::value;
+          if (!live) return;
+          Quad s;
+          s.ev = 0u;
+          float c2[3], v0[3];
+#pragma unroll
+          for (int m = 0; m < 3; ++m) {
+            s.x[m] = xn[D][m];
+            s.v[m] = v0[m] = vn[D][m];
+            c2[m] = cn[D][m];
+          }
+          s.fl = word_flag(__float_as_uint(fn[D]), me, 0);
+          next();
+          const float T = mring[k % 5][0][tid].x;
+          const uint32_t ev = trans_step<true>(c, pp, s, T, c2[0], c2[1], c2[2], (uint32_t)q,
+                                         t0 + (unsigned long long)k);
+          float(*tl)[BS] = tile[k & 1];
+#pragma unroll
+          for (int m = 0; m < 3; ++m) {
+            tl[m][tid] = s.xo[m];
+            tl[3 + m][tid] = s.inc[m];
+            tl[6 + m][tid] = s.v[m];
+          }
+          tring[k & 1][0][tid] = make_float4(T * c2[0], T * c2[1], T * c2[2], v0[0]);
+          tring[k & 1][1][tid] = make_float4(v0[1], v0[2], __uint_as_float(ev), 0.f);
+        });
+  } else if (wave == 2) {
+    float Rn[AHEAD][9], wn[AHEAD][3];
+    auto load = [&](int k, auto slot) {
+      constexpr int D = decltype(slot)::value;
+      const float* row = row_of(k);
+#pragma unroll
+      for (int m = 0; m < 9; ++m) Rn[D][m] = at(row, S_R + m);
+#pragma unroll
+      for (int m = 0; m < 3; ++m) wn[D][m] = at(row, S_W + m);
+    };
+    loading_stages(2, load, [&](int k, auto slot, auto&& next) {
+      constexpr int D = decltype(slot)::value;
+      if (!live) return;
+      float R[9], w[3];
+#pragma unroll
+      for (int m = 0; m < 9; ++m) R[m] = Rn[D][m];
+#pragma unroll
+      for (int m = 0; m < 3; ++m) w[m] = wn[D][m];
+      next();
+      const float4 d = mring[k % 5][0][tid];
+      Rec r;
+      rot_step<true>(c, pp, R, w, d.y, d.z, d.w, &r);
+      float4(*rs)[BS] = rring[k % 3];
+      rs[0][tid] = make_float4(r.P[0], r.P[1], r.P[2], r.P[3]);
+      rs[1][tid] = make_float4(r.P[4], r.P[5], r.P[6], r.P[7]);
+      rs[2][tid] = make_float4(r.P[8], r.w0[0], r.w0[1], r.w0[2]);
+      rs[3][tid] = make_float4(r.wdot[0], r.wdot[1], r.wdot[2], r.i0);
+      rs[4][tid] = make_float4(r.w1[0], r.w1[1], r.w1[2], r.i1);
+      rs[5][tid] = make_float4(r.A1[0], r.A1[1], r.A1[2], r.dp);
+      rs[6][tid] = make_float4(r.c0[0], r.c0[1], r.c0[2], 0.f);
+      rs[7][tid] = make_float4(r.c1[0], r.c1[1], r.c1[2], 0.f);
+    });
+  } else if (wave == 5) {
+    // the translation's derivative
+    float lx[3], lv[3], pn[AHEAD][3];
+    float wn[AHEAD];
+    if (live) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        lx[k] = lam[(S_X + k) * Q + q];
+        lv[k] = lam[(S_V + k) * Q + q];
+      }
+    }
+    auto load = [&](int k, auto slot) {
+      constexpr int D = decltype(slot)::value;
+      wn[D] = at(row_of(k), S_F);
+      if constexpr (PEN) {
+#pragma unroll
+        for (int m = 0; m < 3; ++m) pn[D][m] = at(row_of(k), T_PEN + m);
+      }
+    };
+    loading_stages(3, load, [&](int k, auto slot, auto&& next) {
+      constexpr int D = decltype(slot)::value;
+      uint32_t cm = 0u;  // partners whose response the quad received
+      if (live) {
+        cm = word_resp(__float_as_uint(wn[D]), me, 0);
+        if constexpr (PEN) {
+#pragma unroll
+          for (int m = 0; m < 3; ++m) lx[m] += pn[D][m];
+        }
+        next();
+      }
+      if (__ballot(cm != 0u) != 0ull) {  // rare
+        const float(*tl)[BS] = tile[k & 1];
+        float ldv[3] = {0.f, 0.f, 0.f};
+        if (cm != 0u) {
+#pragma unroll
+          for (int m = 0; m < 3; ++m) {
+            ldv[m] = c.col_decay * lv[m];
+            lv[m] = ldv[m];
+          }
+        }
+#pragma unroll
+        for (int m = 0; m < 3; ++m) ldvt[m][tid] = ldv[m];
+        wave_sync();
+        if (cm != 0u) {
+          Quad so;
+#pragma unroll
+          for (int m = 0; m < 3; ++m) {
+            so.xo[m] = tl[m][tid];
+            so.inc[m] = tl[3 + m][tid];
+            so.v[m] = tl[6 + m][tid];
+          }
+          response_vjp<BS>(c, tl, ldvt, so, ls, me, cm, ldv, lx, lv);
+        }
+        wave_sync();
+      }
+      if (live) {
+        const float4 a = tring[k & 1][0][tid], b = tring[k & 1][1][tid];
+        const float F[3] = {a.x, a.y, a.z}, v0[3] = {a.w, b.x, b.y};
+        float lF[3];
+        lring[k % 3][tid] = vjp_trans(c, pp, __float_as_uint(b.z), F, v0, lx, lv, lF);
+        aring[k & 1][tid] = make_float4(lF[0], lF[1], lF[2], b.z);
+      }
+    });
+    if (live) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        lam[(S_X + k) * Q + q] = lx[k];
+        lam[(S_V + k) * Q + q] = lv[k];
+      }
+      lam[S_F * Q + q] = 0.f;
+    }
+  } else if (wave == 3) {
+    // the rotation's derivative
+    float lR[9], lw[3], gJ[3] = {0.f, 0.f, 0.f};
+    if (live) {
+#pragma unroll
+      for (int k = 0; k < 9; ++k) lR[k] = lam[(S_R + k) * Q + q];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) lw[k] = lam[(S_W + k) * Q + q];
+    }
+    stages(4, [&](int k) {
+      if (!live) return;
+      const float4(*rs)[BS] = rring[k % 3];
+      float4 v[8];
+#pragma unroll
+      for (int m = 0; m < 8; ++m) v[m] = rs[m][tid];
+      const float4 a = aring[k & 1][tid];
+      Rec r;
+      r.T = mring[k % 5][0][tid].x;
+      r.P[0] = v[0].x; r.P[1] = v[0].y; r.P[2] = v[0].z; r.P[3] = v[0].w;
+      r.P[4] = v[1].x; r.P[5] = v[1].y; r.P[6] = v[1].z; r.P[7] = v[1].w;
+      r.P[8] = v[2].x; r.w0[0] = v[2].y; r.w0[1] = v[2].z; r.w0[2] = v[2].w;
+      r.wdot[0] = v[3].x; r.wdot[1] = v[3].y; r.wdot[2] = v[3].z; r.i0 = v[3].w;
+      r.w1[0] = v[4].x; r.w1[1] = v[4].y; r.w1[2] = v[4].z; r.i1 = v[4].w;
+      r.A1[0] = v[5].x; r.A1[1] = v[5].y; r.A1[2] = v[5].z; r.dp = v[5].w;
+      r.c0[0] = v[6].x; r.c0[1] = v[6].y; r.c0[2] = v[6].z;
+      r.c1[0] = v[7].x; r.c1[1] = v[7].y; r.c1[2] = v[7].z;
+      const float lF[3] = {a.x, a.y, a.z};
+      float lt[3], lJ[3];
+      const float lT = vjp_rot(c, pp, r, __float_as_uint(a.w), lF, lR, lw, lt, lJ);
+      bring[k & 1][tid] = make_float4(lT, lt[0], lt[1], lt[2]);
+#pragma unroll
+      for (int m = 0; m < 3; ++m) gJ[m] += lJ[m];
+    });
+    if (live) {
+#pragma unroll
+      for (int k = 0; k < 9; ++k) lam[(S_R + k) * Q + q] = lR[k];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        lam[(S_W + k) * Q + q] = lw[k];
+        gpar[(1 + k) * Q + q] += gJ[k];
+      }
+    }
+  } else {
+    // the motor's derivative
+    float lu[4], le[4], gu[4] = {0.f, 0.f, 0.f, 0.f}, gm = 0.f, gt2w = 0.f, gtau = 0.f;
+    if (live) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        lu[k] = lam[(S_U + k) * Q + q];
+        le[k] = lam[(S_E + k) * Q + q];
+      }
+    }
+    int call = ncalls - 1, sub = nsub - 1;
+    stages(5, [&](int k) {
+      if (sub == nsub - 1) {
+#pragma unroll
+        for (int m = 0; m < 4; ++m) gu[m] = 0.f;
+      }
+      if (live) {
+        const float4(*ms)[BS] = mring[k % 5];
+        const float4 z4 = ms[1][tid], u04 = ms[2][tid], u14 = ms[3][tid],
+                     uh4 = uring[k % 6][0][tid];
+        const float4 b = bring[k & 1][tid];
+        const float z[4] = {z4.x, z4.y, z4.z, z4.w}, u0[4] = {u04.x, u04.y, u04.z, u04.w};
+        const float u1[4] = {u14.x, u14.y, u14.z, u14.w}, uhat[4] = {uh4.x, uh4.y, uh4.z, uh4.w};
+        const float lt[3] = {b.y, b.z, b.w};
+        vjp_motor(c, pp, pa, u0, u1, z, uhat, b.x, lt, lring[k % 3][tid], lu, le, gu, gm, gt2w,
+                  gtau);
+        if (sub == 0) {
+          const float4 da = uring[k % 6][1][tid];
+          float4 g;
+          g.x = gu[0] * da.x;
+          g.y = gu[1] * da.y;
+          g.z = gu[2] * da.z;
+          g.w = gu[3] * da.w;
+          reinterpret_cast<float4*>(gact + (long long)call * Q * 4)[q] = g;
+        }
+      }
+      if (--sub < 0) {
+        sub = nsub - 1;
+        --call;
+      }
+    });
+    if (live) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        lam[(S_U + k) * Q + q] = lu[k];
+        lam[(S_E + k) * Q + q] = le[k];
+      }
+      gpar[0 * Q + q] += gm;
+      gpar[4 * Q + q] += gt2w;
+      gpar[5 * Q + q] += gtau;
+    }
   }
 }
 
