@@ -59,8 +59,6 @@ void free_all(qs_handle* h) {
   (void)hipFree(h->d_contacts);
   (void)hipFree(h->d_err);
   (void)hipFree(h->d_tape);
-  (void)hipFree(h->d_lam);
-  (void)hipFree(h->d_gpar);
   (void)hipFree(h->d_ck1);
   (void)hipFree(h->d_items);
   (void)hipFree(h->d_item_envs);

@@ -66,17 +66,18 @@ void go_roll(qs_handle* h, const float* act, int ncalls, int nsub, float* ckpt, 
                      act, ncalls, nsub, (unsigned long long)h->t, ckpt, ce, pen, beta);
 }
 
-// Device scratch of one backward pass: the tape of the chunk of segments in
-// flight ([S][31][Q]), the state adjoint ([27][Q]) and the parameter
-// gradient ([6][Q]).
-struct AdjScratch {
+// The arrays of one backward pass: the tape of the chunk of segments in flight
+// ([S][31 or 34][Q]) and the caller's state adjoint in, out ([Q][27], may be
+// one array) and parameter gradient ([Q][6], accumulated).
+struct AdjBuffers {
   float* tape;
-  float* lam;
+  const float* gin;
+  float* gout;
   float* gpar;
 };
 
 template <int BS, int N, bool PEN>
-void go_recompute(qs_handle* h, const AdjScratch& sc, const float* ckpt, const float* act,
+void go_recompute(qs_handle* h, const AdjBuffers& sc, const float* ckpt, const float* act,
                   int ncalls, int ce, int nsub, uint64_t t0, const float* gpen, float beta,
                   hipStream_t s) {
   const int nseg = (ncalls + ce - 1) / ce;
@@ -95,19 +96,19 @@ void go_recompute(qs_handle* h, const AdjScratch& sc, const float* ckpt, const f
 }
 
 template <int BS, int N, bool PEN>
-void go_reverse(qs_handle* h, const AdjScratch& sc, const float* act, int ncalls, int nsub,
+void go_reverse(qs_handle* h, const AdjBuffers& sc, const float* act, int ncalls, int nsub,
                 uint64_t t0, float* gact, hipStream_t s) {
   if constexpr (BS == 64) {
     if (use_reverse_pipe(h)) {
       hipLaunchKernelGGL((qs::reverse_pipe_kernel<PEN>), dim3(h->nblk), dim3(448), 0, s, h->d_c,
-                         ptrs(h), act, ncalls, nsub, sc.tape, sc.lam, h->uniform_n, gact, sc.gpar,
+                         ptrs(h), act, ncalls, nsub, sc.tape, sc.gin, sc.gout, h->uniform_n, gact, sc.gpar,
                          (unsigned long long)t0);
       return;
     }
   }
   hipLaunchKernelGGL((qs::reverse_kernel<BS, N, PEN>), dim3(h->nblk), dim3(BS), 0, s, h->d_c,
-                     ptrs(h), act, ncalls, nsub, (unsigned long long)t0, sc.tape, sc.lam,
-                     is_wide(h), gact, sc.gpar);
+                     ptrs(h), act, ncalls, nsub, (unsigned long long)t0, sc.tape, sc.gin,
+                     sc.gout, is_wide(h), gact, sc.gpar);
 }
 
 // Dispatch on (block size, uniform swarm size) for a launcher template F.
@@ -141,7 +142,7 @@ struct RollF {
 
 template <int BS, int N, bool PEN>
 struct RecF {
-  static void run(qs_handle* h, const AdjScratch* sc, const float* ckpt, const float* act,
+  static void run(qs_handle* h, const AdjBuffers* sc, const float* ckpt, const float* act,
                   int ncalls, int ce, int nsub, uint64_t t0, const float* gpen, float beta,
                   hipStream_t s) {
     go_recompute<BS, N, PEN>(h, *sc, ckpt, act, ncalls, ce, nsub, t0, gpen, beta, s);
@@ -150,7 +151,7 @@ struct RecF {
 
 template <int BS, int N, bool PEN>
 struct RevF {
-  static void run(qs_handle* h, const AdjScratch* sc, const float* act, int ncalls, int nsub,
+  static void run(qs_handle* h, const AdjBuffers* sc, const float* act, int ncalls, int nsub,
                   uint64_t t0, float* gact, hipStream_t s) {
     go_reverse<BS, N, PEN>(h, *sc, act, ncalls, nsub, t0, gact, s);
   }
@@ -169,15 +170,6 @@ int grow(float** p, size_t* cap, size_t need) {
   return QS_OK;
 }
 
-int ensure_adjoint_scratch(qs_handle* h) {
-  size_t cap_lam = h->d_lam ? 1 : 0, cap_g = h->d_gpar ? 1 : 0, cap_c = h->d_ck1 ? 1 : 0;
-  int rc = QS_OK;
-  if (!h->d_lam) rc = grow(&h->d_lam, &cap_lam, (size_t)qs::NSTATE * h->Q);
-  if (rc == QS_OK && !h->d_gpar) rc = grow(&h->d_gpar, &cap_g, (size_t)6 * h->Q);
-  if (rc == QS_OK && !h->d_ck1) rc = grow(&h->d_ck1, &cap_c, (size_t)qs::NSTATE * h->Q);
-  return rc;
-}
-
 // Bytes of tape the backward pass may hold at once (QS_TAPE_BYTES overrides);
 // at least one segment is always taped.
 size_t tape_budget() {
@@ -188,16 +180,6 @@ size_t tape_budget() {
   return (size_t)8 << 30;
 }
 
-void convert(const float* src, float* dst, int Q, int rows, bool to_row_major, bool acc,
-             hipStream_t s) {
-  const long long n = (long long)Q * rows;
-  const dim3 grid((unsigned)((n + 255) / 256)), block(256);
-  if (to_row_major)
-    hipLaunchKernelGGL(qs::fm_to_rm_kernel, grid, block, 0, s, src, dst, Q, rows, acc ? 1 : 0);
-  else
-    hipLaunchKernelGGL(qs::rm_to_fm_kernel, grid, block, 0, s, src, dst, Q, rows);
-}
-
 // Floats of tape one checkpoint segment needs.
 size_t segment_tape_floats(const qs_handle* h, int n_calls, int nsub, int ce, bool pen) {
   return (size_t)std::min(ce, n_calls) * nsub * (pen ? qs::kTapeRows<true> : qs::kTapeRows<false>) *
@@ -205,11 +187,10 @@ size_t segment_tape_floats(const qs_handle* h, int n_calls, int nsub, int ce, bo
 }
 
 // Backward pass over n_calls calls with checkpoints every ce calls (ckpt:
-// [27][Q] each); sc.lam and sc.gpar already hold the incoming adjoint and
-// zeros, and sc.tape holds G segments.  Segments are taken in chunks of G,
+// [27][Q] each); sc.tape holds G segments.  Segments are taken in chunks of G,
 // last chunk first: one launch recomputes every segment of the chunk in
 // parallel, one launch sweeps the chunk in reverse.
-int run_adjoint(qs_handle* h, const AdjScratch& sc, int G, const float* act, int n_calls,
+int run_adjoint(qs_handle* h, AdjBuffers sc, int G, const float* act, int n_calls,
                 int nsub, int ce, const float* ckpt, uint64_t t0, const float* gpen, float beta,
                 float* gact, hipStream_t s) {
   const int nseg = (n_calls + ce - 1) / ce;
@@ -228,6 +209,7 @@ int run_adjoint(qs_handle* h, const AdjScratch& sc, int G, const float* act, int
       dispatch<RevF, false>(h, &sc, a, nc, nsub, ts, ga, s);
     }
     if (hipGetLastError() != hipSuccess) return QS_ERR_HIP;
+    sc.gin = sc.gout;  // the next chunk goes on from here
   }
   return QS_OK;
 }
@@ -254,29 +236,50 @@ int check_step_backward(const qs_handle* h, const float* d_state_in, const float
   return QS_OK;
 }
 
-// The launches of one qs_step_backward call on the given scratch: ck1 [27][Q]
-// receives the state before the call, sc.lam the incoming adjoint, sc.gpar
-// zeros (a fill kernel, not a memset, so the sequence can be captured), then
-// the recompute and reverse sweeps of one segment, and the results are
-// converted back to the caller's row-major layouts.
-int step_backward_run(qs_handle* h, const AdjScratch& sc, float* ck1, const float* d_state_in,
+// One qs_step_backward call: up to VJP_MAX_SUBSTEPS substeps in one launch; more
+// through the recompute and reverse sweeps of one segment, with ck1 [27][Q]
+// for the state before the call.  (us a call with eight launches -> one, for 1,
+// 2 and 4 substeps: 512 x 8: 23 -> 8.4, 25 -> 11, 30 -> 17; 4096 x 8: 36 -> 9.4,
+// 40 -> 13, 46 -> 19; 32768 x 8: 113 -> 25, 127 -> 34, 190 -> 75.  Five, by the
+// sweeps, take 19, 26 and 93: more substeps in one launch lose to the pipelines
+// in the smallest batches and to their own LDS in the largest.)
+bool one_launch(const qs_handle* h, int nsub) {
+  return h->bs == 64 && nsub >= 1 && nsub <= qs::VJP_MAX_SUBSTEPS;
+}
+
+template <int N>
+void go_step_vjp(qs_handle* h, const AdjBuffers& b, const float* state_in, const float* act,
+                 int nsub, uint64_t t0, float* gact, hipStream_t s) {
+  const size_t dyn = (size_t)(nsub - 1) * qs::VJP_ROW * 64 * sizeof(float);
+  hipLaunchKernelGGL((qs::step_vjp_kernel<N>), dim3(h->nblk), dim3(64), dyn, s, h->d_c, ptrs(h),
+                     state_in, act, nsub, (unsigned long long)t0, b.gin, b.gout, gact, b.gpar);
+}
+
+int step_backward_run(qs_handle* h, float* tape, float* ck1, const float* d_state_in,
                       const float* d_actions, int32_t n_substeps, uint64_t substep_index,
                       const float* d_gstate_out, float* d_gstate_in, float* d_gactions,
                       float* d_gparams, hipStream_t s) {
-  convert(d_state_in, ck1, h->Q, qs::NSTATE, false, false, s);
-  convert(d_gstate_out, sc.lam, h->Q, qs::NSTATE, false, false, s);
-  hipLaunchKernelGGL(qs::fill_kernel, dim3((unsigned)((6LL * h->Q + 255) / 256)), dim3(256), 0, s,
-                     sc.gpar, 6LL * h->Q, 0.0f);
-  if (n_substeps > 0) {
-    const int rc = run_adjoint(h, sc, 1, d_actions, 1, n_substeps, 1, ck1, substep_index, nullptr,
-                               0.f, d_gactions, s);
-    if (rc != QS_OK) return rc;
-  } else {
+  const AdjBuffers b{tape, d_gstate_out, d_gstate_in, d_gparams};
+  if (one_launch(h, n_substeps)) {
+    switch (h->uniform_n) {
+      case 1: go_step_vjp<1>(h, b, d_state_in, d_actions, n_substeps, substep_index, d_gactions, s); break;
+      case 8: go_step_vjp<8>(h, b, d_state_in, d_actions, n_substeps, substep_index, d_gactions, s); break;
+      case 32: go_step_vjp<32>(h, b, d_state_in, d_actions, n_substeps, substep_index, d_gactions, s); break;
+      default: go_step_vjp<0>(h, b, d_state_in, d_actions, n_substeps, substep_index, d_gactions, s); break;
+    }
+  } else if (n_substeps > 0) {
+    hipLaunchKernelGGL(qs::rows_to_fields_kernel, dim3((h->Q + 63) / 64), dim3(64), 0, s,
+                       d_state_in, ck1, h->Q);
+    return run_adjoint(h, b, 1, d_actions, 1, n_substeps, 1, ck1, substep_index, nullptr, 0.f,
+                       d_gactions, s);
+  } else {  // kernels, not memory operations, so the sequence can be captured
     hipLaunchKernelGGL(qs::fill_kernel, dim3((unsigned)((4LL * h->Q + 255) / 256)), dim3(256), 0,
                        s, d_gactions, 4LL * h->Q, 0.0f);
+    const long long n = (long long)qs::NSTATE * h->Q;
+    if (d_gstate_in != d_gstate_out)
+      hipLaunchKernelGGL(qs::copy_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
+                         d_gstate_out, d_gstate_in, n);
   }
-  convert(sc.lam, d_gstate_in, h->Q, qs::NSTATE, true, false, s);
-  convert(sc.gpar, d_gparams, h->Q, 6, true, true, s);
   return hipGetLastError() == hipSuccess ? QS_OK : QS_ERR_HIP;
 }
 
@@ -371,28 +374,19 @@ int qs_rollout_backward(qs_handle* h, const float* d_actions, int32_t n_calls,
   }
   if (n_calls == 0 || n_substeps == 0) return QS_OK;
   if (hipSetDevice(h->dev) != hipSuccess) return QS_ERR_HIP;
-  int rc = ensure_adjoint_scratch(h);
-  if (rc != QS_OK) return rc;
   if (h->max_n == 1) d_gpenalty = nullptr;  // swarms of one have no penalty
   hipStream_t s = (hipStream_t)stream;
-  convert(d_gstate, h->d_lam, h->Q, qs::NSTATE, false, false, s);
-  hipLaunchKernelGGL(qs::fill_kernel, dim3((unsigned)((6LL * h->Q + 255) / 256)), dim3(256), 0, s,
-                     h->d_gpar, 6LL * h->Q, 0.0f);
   // segments per chunk: as many as fit the tape budget (also the recompute
   // grid's y extent, at most 65535), at least one
   const int nseg = (n_calls + ckpt_every - 1) / ckpt_every;
   const size_t seg = segment_tape_floats(h, n_calls, n_substeps, ckpt_every, d_gpenalty != nullptr);
   const size_t fit = tape_budget() / (seg * sizeof(float));
   const int G = (int)std::max<size_t>(1, std::min<size_t>({(size_t)nseg, fit, (size_t)65535}));
-  rc = grow(&h->d_tape, &h->tape_cap, (size_t)G * seg);
+  int rc = grow(&h->d_tape, &h->tape_cap, (size_t)G * seg);
   if (rc != QS_OK) return rc;
-  const AdjScratch sc{h->d_tape, h->d_lam, h->d_gpar};
-  rc = run_adjoint(h, sc, G, d_actions, n_calls, n_substeps, ckpt_every, d_ckpt, substep_index0,
+  const AdjBuffers b{h->d_tape, d_gstate, d_gstate, d_gparams};
+  return run_adjoint(h, b, G, d_actions, n_calls, n_substeps, ckpt_every, d_ckpt, substep_index0,
                    d_gpenalty, beta, d_gactions, s);
-  if (rc != QS_OK) return rc;
-  convert(h->d_lam, d_gstate, h->Q, qs::NSTATE, true, false, s);
-  convert(h->d_gpar, d_gparams, h->Q, 6, true, true, s);
-  return hipGetLastError() == hipSuccess ? QS_OK : QS_ERR_HIP;
 }
 
 int qs_step_backward(qs_handle* h, const float* d_state_in, const float* d_actions,
@@ -402,12 +396,12 @@ int qs_step_backward(qs_handle* h, const float* d_state_in, const float* d_actio
                                d_gactions, d_gparams);
   if (rc != QS_OK) return rc;
   if (hipSetDevice(h->dev) != hipSuccess) return QS_ERR_HIP;
-  rc = ensure_adjoint_scratch(h);
-  if (rc == QS_OK && n_substeps > 0)
+  if (n_substeps > 0 && !one_launch(h, n_substeps)) {
     rc = grow(&h->d_tape, &h->tape_cap, segment_tape_floats(h, 1, n_substeps, 1, false));
-  if (rc != QS_OK) return rc;
-  const AdjScratch sc{h->d_tape, h->d_lam, h->d_gpar};
-  return step_backward_run(h, sc, h->d_ck1, d_state_in, d_actions, n_substeps, substep_index,
+    if (rc == QS_OK) rc = grow(&h->d_ck1, &h->ck1_cap, (size_t)qs::NSTATE * h->Q);
+    if (rc != QS_OK) return rc;
+  }
+  return step_backward_run(h, h->d_tape, h->d_ck1, d_state_in, d_actions, n_substeps, substep_index,
                            d_gstate_out, d_gstate_in, d_gactions, d_gparams, (hipStream_t)stream);
 }
 
@@ -428,8 +422,7 @@ int qs_step_backward_noalloc(qs_handle* h, const float* d_state_in, const float*
   float* base = nullptr;
   rc = noalloc_scratch(h->dev, &base);
   if (rc != QS_OK) return rc;
-  const AdjScratch sc{base + n_ck + n_lam + n_g, base + n_ck, base + n_ck + n_lam};
-  return step_backward_run(h, sc, base, d_state_in, d_actions, n_substeps, substep_index,
+  return step_backward_run(h, base + n_ck + n_lam + n_g, base, d_state_in, d_actions, n_substeps, substep_index,
                            d_gstate_out, d_gstate_in, d_gactions, d_gparams, (hipStream_t)stream);
 }
 

@@ -31,10 +31,6 @@ struct qs_handle {
   int* h_err = nullptr;  // pinned
   uint64_t t = 0;
   bool record = false;
-  // adjoint scratch, grown on demand: tape [S][31][Q] (state and motor-noise
-  // draws of the S substeps of the chunk of segments in flight), adjoint
-  // [27][Q], parameter gradient [6][Q],
-  // one checkpoint [27][Q]
   // uneven swarm sizes: work items of the persistent bucketed launch
   std::vector<int> env_start, env_n;  // host copy of the environments
   int4* d_items = nullptr;
@@ -57,11 +53,12 @@ struct qs_handle {
   bool graph_mode = false;
   unsigned long long* d_t = nullptr;
   unsigned int* d_done = nullptr;
+  // backward passes' scratch, grown on demand: the tape of the chunk of
+  // segments in flight, and one checkpoint [27][Q]
   float* d_tape = nullptr;
   size_t tape_cap = 0;
-  float* d_lam = nullptr;
-  float* d_gpar = nullptr;
   float* d_ck1 = nullptr;
+  size_t ck1_cap = 0;
 };
 
 namespace qs_host {

@@ -4,9 +4,10 @@
 // taping what the reverse sweep needs of each substep, and a kernel that
 // sweeps the tape in reverse.
 //
-// Layouts: checkpoints and adjoint scratch are field-major [27][Q], tape
-// rows [31][Q] or, with the penalty, [34][Q] (coalesced per field); actions
-// and their gradients are [call][Q][4].
+// Layouts: checkpoints are field-major [27][Q], tape rows [31][Q] or, with the
+// penalty, [34][Q] (coalesced per field); the state's adjoint is the caller's
+// row-major [Q][27], the parameters' [Q][6]; actions and their gradients are
+// [call][Q][4].
 #pragma once
 #include "qs_adjoint.h"
 
@@ -404,27 +405,130 @@ __device__ __forceinline__ void response_vjp(const Consts& c, const float (*tile
   }
 }
 
+// A workgroup's rows of a row-major [Q][27] array (quads [qb, qb + cnt)) to or
+// from LDS, words in order (one run of memory), by T threads; callers
+// synchronise.  The sweeps take the adjoint from the caller's rows and put it
+// back this way: converting it to fields and back, the parameters' with it,
+// were four launches more (32768 x 32: 0.26 of 10.7 ms).
+template <int BS, int T, bool IN, typename G>
+__device__ __forceinline__ void move_rows(G* g, int qb, int cnt, float* sh, int tid) {
+  G* run = g + (size_t)qb * NSTATE;
+  constexpr int PER = (BS * NSTATE + T - 1) / T;
+  const int total = cnt * NSTATE;
+  // (the indexes of a kernel's last move are not to be shared with those of
+  // its first and kept in registers between)
+  asm volatile("" : "+v"(tid));
+  float v[PER];  // (all reads go out before the first write)
+#pragma unroll
+  for (int m = 0; m < PER; ++m) {
+    const int i = min(tid + m * T, total - 1);
+    v[m] = IN ? run[i] : sh[i];
+  }
+#pragma unroll
+  for (int m = 0; m < PER; ++m) {
+    const int i = tid + m * T;
+    if (i < total) {
+      if constexpr (IN) sh[i] = v[m];
+      else run[i] = v[m];
+    }
+  }
+}
+__device__ __forceinline__ void get_adj(const float* row, Adj& l) {
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    l.x[k] = row[S_X + k];
+    l.v[k] = row[S_V + k];
+    l.w[k] = row[S_W + k];
+  }
+#pragma unroll
+  for (int k = 0; k < 9; ++k) l.R[k] = row[S_R + k];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    l.u[k] = row[S_U + k];
+    l.e[k] = row[S_E + k];
+  }
+}
+__device__ __forceinline__ void put_adj(float* row, const Adj& l) {
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    row[S_X + k] = l.x[k];
+    row[S_V + k] = l.v[k];
+    row[S_W + k] = l.w[k];
+  }
+#pragma unroll
+  for (int k = 0; k < 9; ++k) row[S_R + k] = l.R[k];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    row[S_U + k] = l.u[k];
+    row[S_E + k] = l.e[k];
+  }
+  row[S_F] = 0.f;
+}
+
+// The reverse of a substep's collision responses, by every lane of the
+// workgroup: s the quads after the motion, cm the partners whose response the
+// quad received (wide: found here).  tile: rows 0-8 as in the forward pass,
+// 9-11 the adjoint of the collision velocity change.
+template <int BS, int N>
+__device__ __forceinline__ void reverse_responses(const Consts& c, float (*tile)[BS],
+                                                  const Quad& s, bool live, int ls, int n, int me,
+                                                  int tid, unsigned long long cm, int wide,
+                                                  Adj& l) {
+  // the exchange, where a quad of the workgroup received a response (rare)
+  bool any = wide != 0;
+  if (!any) {
+    if constexpr (BS == 64) any = __ballot(cm != 0ull) != 0ull;
+    else any = __syncthreads_or(cm != 0ull) != 0;
+  }
+  if (!any) return;
+  __syncthreads();  // previous readers of the tile are done
+  if (live) put_tile<false, false>(tile, tid, s);
+  __syncthreads();
+  bool hit = cm != 0ull;
+  if constexpr (N == 0) {
+    if (wide && live) {
+      cm = mark_contacts<BS>(c, tile, s, ls, n, me);
+      hit = any_response<BS>(c, tile, s, ls, me, cm);
+    }
+  }
+  // the adjoint of the quad's velocity change
+  float ldv[3] = {0.f, 0.f, 0.f};
+  if (live && hit) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      ldv[k] = c.col_decay * l.v[k];
+      l.v[k] = ldv[k];
+    }
+  }
+  if (live) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) tile[9 + k][tid] = ldv[k];
+  }
+  __syncthreads();
+  if (live) response_vjp<BS>(c, tile, tile + 9, s, ls, me, cm, ldv, l.x, l.v);
+}
+
 // ---------------------------------------------------------------------------
 // reverse_kernel: the reverse sweep over the chunk's ncalls nsub substeps,
 // last to first, from the tape; the adjoint of the state stays in
 // registers for the whole chunk and the tape row of the next substep to
 // process is loaded while the current one is differentiated.
-//  lam: [27][Q] dL/d(chunk end) in, dL/d(chunk start) out; act/gact: the
-//  chunk's first call; gpar: [6][Q] dL/d(m, ixx, iyy, izz, t2w, tau),
-//  accumulated.
+//  gin, gout: [Q][27] dL/d(chunk end), dL/d(chunk start) (may be one array);
+//  act/gact: the chunk's first call; gpar: [Q][6]
+//  dL/d(m, ixx, iyy, izz, t2w, tau), accumulated.
 // ---------------------------------------------------------------------------
 template <int BS, int N, bool PEN>
 __global__ __launch_bounds__(BS) void reverse_kernel(const Consts* __restrict__ cp, Ptrs p,
                                                      const float* __restrict__ act, int ncalls,
                                                      int nsub, unsigned long long t0,
                                                      const float* __restrict__ tape,
-                                                     float* __restrict__ lam, int wide,
+                                                     const float* gin, float* gout, int wide,
                                                      float* __restrict__ gact,
                                                      float* __restrict__ gpar) {
   constexpr int NTAPE = kTapeRows<PEN>;
-  // rows 0-8 as in the forward tile; 9-11: adjoint of the collision
-  // velocity change
-  __shared__ float tl[12][BS];
+  // the rows on their way in and out; the exchange tile between
+  __shared__ float sh[NSTATE * BS];
+  float(*tile)[BS] = reinterpret_cast<float(*)[BS]>(sh);
   const Consts& c = *cp;
   const int tid = threadIdx.x;
   int qb, cnt, ls, n;
@@ -434,8 +538,12 @@ __global__ __launch_bounds__(BS) void reverse_kernel(const Consts* __restrict__ 
   const int me = tid - ls;
   const long long Q = p.Q;
   const bool pairs = N != 1 && (c.flags & F_COLLIDE) != 0;
-  float(*tile)[BS] = tl;
 
+  Adj l;
+  move_rows<BS, BS, true>(gin, qb, cnt, sh, tid);
+  __syncthreads();
+  if (live) get_adj(sh + tid * NSTATE, l);
+  __syncthreads();
   Quad s, sn;
   float z[4], zn[4] = {0.f, 0.f, 0.f, 0.f};  // motor-noise draws of s and sn
   float pn[3] = {0.f, 0.f, 0.f}, pen3[3];     // penalty adjoint of sn and s
@@ -450,23 +558,7 @@ __global__ __launch_bounds__(BS) void reverse_kernel(const Consts* __restrict__ 
   }
 
   // ---- reverse sweep
-  Adj l;
   float gp[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  if (live) {
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      l.x[k] = lam[(S_X + k) * Q + q];
-      l.v[k] = lam[(S_V + k) * Q + q];
-      l.w[k] = lam[(S_W + k) * Q + q];
-    }
-#pragma unroll
-    for (int k = 0; k < 9; ++k) l.R[k] = lam[(S_R + k) * Q + q];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      l.u[k] = lam[(S_U + k) * Q + q];
-      l.e[k] = lam[(S_E + k) * Q + q];
-    }
-  }
   float4 a_nx = make_float4(0.f, 0.f, 0.f, 0.f);
   if (live && ncalls > 0) a_nx = load_act(act + (long long)(ncalls - 1) * Q * 4, q);
   for (int call = ncalls - 1; call >= 0; --call) {
@@ -500,46 +592,7 @@ __global__ __launch_bounds__(BS) void reverse_kernel(const Consts* __restrict__ 
           for (int k = 0; k < 3; ++k) l.x[k] += pen3[k];
         }
       }
-      // the exchange, where a quad of the workgroup received a response (rare)
-      bool any = wide != 0;
-      if (pairs && !any) {
-        if constexpr (BS == 64) any = __ballot(cm != 0ull) != 0ull;
-        else any = __syncthreads_or(cm != 0ull) != 0;
-      }
-      if (pairs && any) {
-        __syncthreads();  // previous readers of the tile are done
-        if (live) {
-#pragma unroll
-          for (int k = 0; k < 3; ++k) {
-            tile[k][tid] = s.xo[k];
-            tile[3 + k][tid] = s.inc[k];
-            tile[6 + k][tid] = s.v[k];
-          }
-        }
-        __syncthreads();
-        bool hit = cm != 0ull;
-        if constexpr (N == 0) {
-          if (wide && live) {
-            cm = mark_contacts<BS>(c, tile, s, ls, n, me);
-            hit = any_response<BS>(c, tile, s, ls, me, cm);
-          }
-        }
-        // the adjoint of the quad's velocity change
-        float ldv[3] = {0.f, 0.f, 0.f};
-        if (live && hit) {
-#pragma unroll
-          for (int k = 0; k < 3; ++k) {
-            ldv[k] = c.col_decay * l.v[k];
-            l.v[k] = ldv[k];
-          }
-        }
-        if (live) {
-#pragma unroll
-          for (int k = 0; k < 3; ++k) tile[9 + k][tid] = ldv[k];
-        }
-        __syncthreads();
-        if (live) response_vjp<BS>(c, tile, tile + 9, s, ls, me, cm, ldv, l.x, l.v);
-      }
+      if (pairs) reverse_responses<BS, N>(c, tile, s, live, ls, n, me, tid, cm, wide, l);
       if (live) quad_vjp(c, pp, pa, r, uhat, l, gu, gp);
     }
     if (live) {
@@ -551,24 +604,139 @@ __global__ __launch_bounds__(BS) void reverse_kernel(const Consts* __restrict__ 
       reinterpret_cast<float4*>(gact + (long long)call * Q * 4)[q] = g;
     }
   }
+  __syncthreads();
   if (live) {
+    put_adj(sh + tid * NSTATE, l);
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      lam[(S_X + k) * Q + q] = l.x[k];
-      lam[(S_V + k) * Q + q] = l.v[k];
-      lam[(S_W + k) * Q + q] = l.w[k];
-    }
-#pragma unroll
-    for (int k = 0; k < 9; ++k) lam[(S_R + k) * Q + q] = l.R[k];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      lam[(S_U + k) * Q + q] = l.u[k];
-      lam[(S_E + k) * Q + q] = l.e[k];
-    }
-    lam[S_F * Q + q] = 0.f;
-#pragma unroll
-    for (int k = 0; k < 6; ++k) gpar[k * Q + q] += gp[k];
+    for (int k = 0; k < 6; ++k) gpar[(size_t)q * 6 + k] += gp[k];
   }
+  __syncthreads();
+  move_rows<BS, BS, false>(gout, qb, cnt, sh, tid);
+}
+
+// ---------------------------------------------------------------------------
+// step_vjp_kernel: the derivative of one call of a few substeps in one launch
+// and without a tape in memory: the substeps before the last leave their start
+// state, draws and responding partners in LDS, the last one's record is still at hand when
+// the sweep starts.  Same arithmetic in the same order as recompute_kernel and
+// reverse_kernel, so identical results.  The conversions, fills, recompute and
+// sweep were eight launches (4096 x 8, two substeps: 34.3 -> 12.8 us a call).
+//  state_in, gin, gout: [Q][27]; act, gact: [Q][4]; gpar: [Q][6] accumulated;
+//  dynamic LDS: VJP_ROW floats per quad and substep before the last.
+// ---------------------------------------------------------------------------
+constexpr int VJP_ROW = NSTATE + 4 + 2;  // state, draws, responding partners
+constexpr int VJP_MAX_SUBSTEPS = 4;
+
+template <int N>
+__global__ __launch_bounds__(64) void step_vjp_kernel(const Consts* __restrict__ cp, Ptrs p,
+                                                      const float* __restrict__ state_in,
+                                                      const float* __restrict__ act, int nsub,
+                                                      unsigned long long t0, const float* gin,
+                                                      float* gout, float* __restrict__ gact,
+                                                      float* __restrict__ gpar) {
+  constexpr int BS = 64;
+  // the rows on their way in and out; the exchange tiles between (forward rows
+  // with the screen's, then the reverse's twelve)
+  __shared__ float sh[NSTATE * BS];
+  extern __shared__ float rows[];
+  const Consts& c = *cp;
+  const int tid = threadIdx.x;
+  int qb, cnt, ls, n;
+  block_map<BS, N>(p, tid, qb, cnt, ls, n);
+  const bool live = tid < cnt;
+  const int q = qb + (live ? tid : 0);
+  const int me = tid - ls;
+  const bool pairs = N != 1 && (c.flags & F_COLLIDE) != 0;
+  float(*tile)[BS] = reinterpret_cast<float(*)[BS]>(sh);
+  QuadPar pp;
+  ParAdj pa;
+  Quad s;
+  Adj l;
+  float4 a4 = load_act(act, q);
+  move_rows<BS, BS, true>(state_in, qb, cnt, sh, tid);
+  if (live) load_params(p, c, q, pp, pa);
+  __syncthreads();
+  if (live) load_state(sh, 1, tid * NSTATE, s);
+  __syncthreads();
+  move_rows<BS, BS, true>(gin, qb, cnt, sh, tid);
+  __syncthreads();
+  if (live) get_adj(sh + tid * NSTATE, l);
+  __syncthreads();
+  float uhat[4] = {0.f, 0.f, 0.f, 0.f}, gu[4] = {0.f, 0.f, 0.f, 0.f};
+  float gp[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  if (live) act_uhat(c, p, a4, uhat);
+  // the substep's in-swarm pass on sp: its responding partners
+  auto responding = [&](Quad& sp, unsigned long long t) {
+    unsigned long long resp = 0ull;
+    if constexpr (N == 8) {
+      lane_pair_pass<BS, N, true>(c, tile, sp, live, ls, n, me, tid, (uint32_t)q, t, &resp);
+    } else {
+      if (live) put_tile<kScreenSq<N>, true>(tile, tid, sp);
+      __syncthreads();
+      if (live)
+        pair_pass<BS, N, PEN_NONE, true>(c, tile, sp, ls, n, me, (uint32_t)q, t, nullptr, nullptr,
+                                         &resp);
+      __syncthreads();
+    }
+    return resp;
+  };
+  for (int k = 0; k < nsub - 1; ++k) {
+    const unsigned long long t = t0 + (unsigned long long)k;
+    float* row = rows + k * VJP_ROW * BS;
+    if (live) {
+      store_state(row, BS, tid, s);
+      float z[4] = {0.f, 0.f, 0.f, 0.f};
+      quad_substep<false, Z_EXPORT>(c, pp, s, uhat, (uint32_t)q, t, nullptr, z);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) row[(NSTATE + i) * BS + tid] = z[i];
+    }
+    const unsigned long long cm = pairs ? responding(s, t) : 0ull;
+    row[(NSTATE + 4) * BS + tid] = __uint_as_float((uint32_t)cm);
+    row[(NSTATE + 5) * BS + tid] = __uint_as_float((uint32_t)(cm >> 32));
+  }
+  {
+    const unsigned long long t = t0 + (unsigned long long)(nsub - 1);
+    Rec r;
+    if (live) quad_substep<true>(c, pp, s, uhat, (uint32_t)q, t, &r);
+    if (pairs) {
+      Quad sp = s;
+      const unsigned long long cm = responding(sp, t);
+      reverse_responses<BS, N == 0 ? -1 : N>(c, tile, s, live, ls, n, me, tid, cm, 0, l);
+    }
+    if (live) quad_vjp(c, pp, pa, r, uhat, l, gu, gp);
+  }
+  for (int k = nsub - 2; k >= 0; --k) {
+    const float* row = rows + k * VJP_ROW * BS;
+    Rec r;
+    if (live) {
+      load_state(row, BS, tid, s);
+      float z[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) z[i] = row[(NSTATE + i) * BS + tid];
+      quad_substep<true, Z_IMPORT>(c, pp, s, uhat, (uint32_t)q, t0 + (unsigned long long)k, &r, z);
+    }
+    if (pairs) {
+      const unsigned long long cm =
+          __float_as_uint(row[(NSTATE + 4) * BS + tid]) |
+          (unsigned long long)__float_as_uint(row[(NSTATE + 5) * BS + tid]) << 32;
+      reverse_responses<BS, N == 0 ? -1 : N>(c, tile, s, live, ls, n, me, tid, cm, 0, l);
+    }
+    if (live) quad_vjp(c, pp, pa, r, uhat, l, gu, gp);
+  }
+  __syncthreads();
+  if (live) {
+    float4 g;
+    g.x = gu[0] * duhat_da(c, a4.x, uhat[0]);
+    g.y = gu[1] * duhat_da(c, a4.y, uhat[1]);
+    g.z = gu[2] * duhat_da(c, a4.z, uhat[2]);
+    g.w = gu[3] * duhat_da(c, a4.w, uhat[3]);
+    reinterpret_cast<float4*>(gact)[q] = g;
+    put_adj(sh + tid * NSTATE, l);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) gpar[(size_t)q * 6 + k] += gp[k];
+  }
+  __syncthreads();
+  move_rows<BS, BS, false>(gout, qb, cnt, sh, tid);
 }
 
 // ---------------------------------------------------------------------------
@@ -962,7 +1130,7 @@ __global__ __launch_bounds__(448) void reverse_pipe_kernel(const Consts* __restr
                                                            const float* __restrict__ act,
                                                            int ncalls, int nsub,
                                                            const float* __restrict__ tape,
-                                                           float* __restrict__ lam, int un,
+                                                           const float* gin, float* gout, int un,
                                                            float* __restrict__ gact,
                                                            float* __restrict__ gpar,
                                                            unsigned long long t0) {
@@ -998,6 +1166,14 @@ __global__ __launch_bounds__(448) void reverse_pipe_kernel(const Consts* __restr
   QuadPar pp;
   ParAdj pa;
   if (live) load_params(p, c, q, pp, pa);
+  // the adjoint's rows on their way in and out, where the record's ring is in
+  // between
+  float* sh = reinterpret_cast<float*>(&rring[0][0][0]);
+  static_assert(sizeof(rring) >= NSTATE * BS * sizeof(float), "room for the rows");
+  const float* my = sh + tid * NSTATE;
+  float* out = sh + tid * NSTATE;
+  move_rows<BS, 448, true>(gin, qb, cnt, sh, threadIdx.x);
+  wg_sync();
   const uint32_t qo = 4u * (uint32_t)q, fo = 4u * (uint32_t)p.Q;
   auto at = [&](const float* row, int f) -> float {  // (see forward_pipe)
     return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(row) +
@@ -1173,8 +1349,8 @@ __global__ __launch_bounds__(448) void reverse_pipe_kernel(const Consts* __restr
     if (live) {
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
-        lx[k] = lam[(S_X + k) * Q + q];
-        lv[k] = lam[(S_V + k) * Q + q];
+        lx[k] = my[S_X + k];
+        lv[k] = my[S_V + k];
       }
     }
     auto load = [&](int k, auto slot) {
@@ -1232,19 +1408,19 @@ __global__ __launch_bounds__(448) void reverse_pipe_kernel(const Consts* __restr
     if (live) {
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
-        lam[(S_X + k) * Q + q] = lx[k];
-        lam[(S_V + k) * Q + q] = lv[k];
+        out[S_X + k] = lx[k];
+        out[S_V + k] = lv[k];
       }
-      lam[S_F * Q + q] = 0.f;
+      out[S_F] = 0.f;
     }
   } else if (wave == 3) {
     // the rotation's derivative
     float lR[9], lw[3], gJ[3] = {0.f, 0.f, 0.f};
     if (live) {
 #pragma unroll
-      for (int k = 0; k < 9; ++k) lR[k] = lam[(S_R + k) * Q + q];
+      for (int k = 0; k < 9; ++k) lR[k] = my[S_R + k];
 #pragma unroll
-      for (int k = 0; k < 3; ++k) lw[k] = lam[(S_W + k) * Q + q];
+      for (int k = 0; k < 3; ++k) lw[k] = my[S_W + k];
     }
     stages(4, [&](int k) {
       if (!live) return;
@@ -1272,11 +1448,11 @@ __global__ __launch_bounds__(448) void reverse_pipe_kernel(const Consts* __restr
     });
     if (live) {
 #pragma unroll
-      for (int k = 0; k < 9; ++k) lam[(S_R + k) * Q + q] = lR[k];
+      for (int k = 0; k < 9; ++k) out[S_R + k] = lR[k];
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
-        lam[(S_W + k) * Q + q] = lw[k];
-        gpar[(1 + k) * Q + q] += gJ[k];
+        out[S_W + k] = lw[k];
+        gpar[(size_t)q * 6 + 1 + k] += gJ[k];
       }
     }
   } else {
@@ -1285,8 +1461,8 @@ __global__ __launch_bounds__(448) void reverse_pipe_kernel(const Consts* __restr
     if (live) {
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        lu[k] = lam[(S_U + k) * Q + q];
-        le[k] = lam[(S_E + k) * Q + q];
+        lu[k] = my[S_U + k];
+        le[k] = my[S_E + k];
       }
     }
     int call = ncalls - 1, sub = nsub - 1;
@@ -1323,34 +1499,35 @@ __global__ __launch_bounds__(448) void reverse_pipe_kernel(const Consts* __restr
     if (live) {
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        lam[(S_U + k) * Q + q] = lu[k];
-        lam[(S_E + k) * Q + q] = le[k];
+        out[S_U + k] = lu[k];
+        out[S_E + k] = le[k];
       }
-      gpar[0 * Q + q] += gm;
-      gpar[4 * Q + q] += gt2w;
-      gpar[5 * Q + q] += gtau;
+      gpar[(size_t)q * 6] += gm;
+      gpar[(size_t)q * 6 + 4] += gt2w;
+      gpar[(size_t)q * 6 + 5] += gtau;
     }
   }
+  wg_sync();
+  move_rows<BS, 448, false>(gout, qb, cnt, sh, threadIdx.x);
 }
 
 // ---------------------------------------------------------------------------
-// [rows][Q] field-major <-> [Q][rows] row-major conversions (optionally
-// adding into the destination).
-__global__ void fm_to_rm_kernel(const float* __restrict__ src, float* __restrict__ dst, int Q,
-                                int rows, int accumulate) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (long long)Q * rows) return;
-  const int q = (int)(i / rows), f = (int)(i - (long long)q * rows);
-  const float v = src[(long long)f * Q + q];
-  dst[i] = accumulate ? dst[i] + v : v;
+// Row-major [Q][27] to field-major [27][Q], 64 quads a workgroup.
+__global__ __launch_bounds__(64) void rows_to_fields_kernel(const float* __restrict__ src,
+                                                            float* __restrict__ dst, int Q) {
+  __shared__ float sh[64 * NSTATE];
+  const int tid = threadIdx.x, qb = blockIdx.x * 64, cnt = min(64, Q - qb);
+  move_rows<64, 64, true>(src, qb, cnt, sh, tid);
+  __syncthreads();
+  if (tid < cnt) {
+#pragma unroll
+    for (int f = 0; f < NSTATE; ++f) dst[(size_t)f * Q + qb + tid] = sh[tid * NSTATE + f];
+  }
 }
 
-__global__ void rm_to_fm_kernel(const float* __restrict__ src, float* __restrict__ dst, int Q,
-                                int rows) {
+__global__ void copy_kernel(const float* __restrict__ src, float* __restrict__ dst, long long n) {
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (long long)Q * rows) return;
-  const int q = (int)(i / rows), f = (int)(i - (long long)q * rows);
-  dst[(long long)f * Q + q] = src[i];
+  if (i < n) dst[i] = src[i];
 }
 
 __global__ void fill_kernel(float* __restrict__ dst, long long n, float v) {
