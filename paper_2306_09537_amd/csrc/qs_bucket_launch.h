@@ -13,7 +13,7 @@ using qs_host::ptrs;
 template <int BS, int KT>
 void go_range(qs_handle* h, int item0, int count, int grid, const float* act, int nsub,
               const float* goals, float* obs, hipStream_t s, float* rw) {
-  const size_t dyn = KT >= 0 ? (size_t)qs::BUCKET_STAGE_ROWS * (18 + 6 * KT) * sizeof(float) : 0;
+  const size_t dyn = KT >= 0 ? (size_t)qs::BUCKET_STAGE_ROWS * h->OD * sizeof(float) : 0;
   hipLaunchKernelGGL((qs::bucket_kernel<BS, KT>), dim3(std::max(grid, 1)), dim3(BS), dyn, s,
                      h->d_st, h->d_par, act, goals, h->d_c, h->Qp, h->Q, nsub,
                      (unsigned long long)h->t, ptrs(h), obs, item0, count,
@@ -36,6 +36,8 @@ void items_bs(qs_handle* h, const float* act, int nsub, const float* goals, floa
     go_items<BS, 6>(h, act, nsub, goals, obs, s, rw);
   else if (h->K == 0)
     go_items<BS, 0>(h, act, nsub, goals, obs, s, rw);
+  else if (h->K <= qs::kSlots<qs::K_UPTO8>)
+    go_items<BS, qs::K_UPTO8>(h, act, nsub, goals, obs, s, rw);
   else
     go_items<BS, -1>(h, act, nsub, goals, obs, s, rw);
 }
@@ -51,6 +53,8 @@ void range_bs(qs_handle* h, int item0, int count, const float* act, int nsub,
     go_range<BS, 6>(h, item0, count, count, act, nsub, goals, obs, s, nullptr);
   else if (h->K == 0)
     go_range<BS, 0>(h, item0, count, count, act, nsub, goals, obs, s, nullptr);
+  else if (h->K <= qs::kSlots<qs::K_UPTO8>)
+    go_range<BS, qs::K_UPTO8>(h, item0, count, count, act, nsub, goals, obs, s, nullptr);
   else
     go_range<BS, -1>(h, item0, count, count, act, nsub, goals, obs, s, nullptr);
 }

@@ -72,9 +72,19 @@ __device__ __forceinline__ void advance_counter(unsigned long long* tdev, unsign
   }
 }
 
+// Observation forms of the step kernels, their KT:
+//  -2    none;
+//  -1    any K (K passes of selection, each lane its own row);
+//  0, 6  that K, known at compile time (register insertion network);
+//  K_UPTO8  any K from 1 to 8: the network of 8, of which the first K are taken.
+//  K passes over the swarm and 18 + 6 K scattered stores a lane had cost
+//  1024 x 8 with K = 3, two substeps and a reward 13 us, now KU1.
+constexpr int K_UPTO8 = 24;
+template <int KT>
+constexpr int kSlots = KT == K_UPTO8 ? 8 : KT;
+
 // Body of one step (+ observation) over one workgroup's quads.
-// KT: -2 step only; -1 observation with runtime K (selection); >= 0 observation
-// with compile-time K (register insertion network).
+// KT: the observation's form (above).
 // N: swarm (slot) size known at compile time (MAP_DENSE, MAP_ITEM), or 0.
 // NU: partner count the in-swarm loops are unrolled for (N, or 0 for loops
 // over the swarm's runtime size: fewer registers for large slots).
@@ -238,7 +248,8 @@ __device__ __forceinline__ void step_body(const Consts& c, const Ptrs& p,
   // observation builds the list itself.
   constexpr bool SCREEN_KEYS = OBS && KT > 0 && MAP == MAP_DENSE && NU >= 16 && ROLE < 0;
   static_assert(!SCREEN_KEYS || N > 8, "swarms of up to 8 use cross-lane candidates");
-  constexpr int NKEY = KT > 0 ? KT + 1 : 1;
+  constexpr int KC = kSlots<KT>;
+  constexpr int NKEY = KC > 0 ? KC + 1 : 1;
   uint32_t skey[NKEY];
 #pragma unroll
   for (int k = 0; k < NKEY; ++k) skey[k] = KEY_EMPTY;
@@ -294,8 +305,8 @@ __device__ __forceinline__ void step_body(const Consts& c, const Ptrs& p,
       if (live) {
         if constexpr (SCREEN_KEYS) {
           if (sub == nsub - 1)
-            cmask = pair_pass<BS, NU, PEN_NONE, true, KT + 1>(c, tile, s, ls, n, me, (uint32_t)q,
-                                                              t, nullptr, skey);
+            cmask = pair_pass<BS, NU, PEN_NONE, true, NKEY>(c, tile, s, ls, n, me, (uint32_t)q, t,
+                                                            nullptr, skey);
           else
             cmask = pair_pass<BS, NU, PEN_NONE, true>(c, tile, s, ls, n, me, (uint32_t)q, t);
         } else {
@@ -392,8 +403,10 @@ __device__ __forceinline__ void step_body(const Consts& c, const Ptrs& p,
       if constexpr (!LANE_KNN) quad_sync();
     }
     if constexpr (KT >= 0) {
-      constexpr int OD = 18 + 6 * KT;
-      float ov[OD];
+      constexpr bool ANY_K = KT == K_UPTO8;
+      const int K = ANY_K ? c.K : KT;  // (uniform)
+      const int OD = 18 + 6 * K;
+      float ov[18 + 6 * KC];
       ov[0] = s.x[0] - g0;
       ov[1] = s.x[1] - g1;
       ov[2] = s.x[2] - g2;
@@ -404,20 +417,20 @@ __device__ __forceinline__ void step_body(const Consts& c, const Ptrs& p,
 #pragma unroll
       for (int k = 0; k < 3; ++k) ov[15 + k] = s.w[k];
       if constexpr (KT > 0) {
-        // The KT nearest by (d^2, index): a sorted list of KT + 1 keys
+        // The K nearest by (d^2, index): a sorted list of KC + 1 keys
         // (knn_insert).  Keys order as (d^2 truncated to 2^-17 relative,
         // index): the list is the exact (d^2, index) order unless two
         // neighbouring entries share a truncated distance (an exact or near
         // tie); such a lane selects again with exact comparisons below.
         constexpr uint32_t EMPTY = KEY_EMPTY;
-        uint32_t key[KT + 1];
+        uint32_t key[NKEY];
         bool screened = false;  // the list came with the last pair pass
         if constexpr (SCREEN_KEYS) screened = collide && nsub > 0 && !(c.flags & F_DOWNWASH);
 #pragma unroll
-        for (int k = 0; k <= KT; ++k) key[k] = SCREEN_KEYS ? skey[k] : EMPTY;
+        for (int k = 0; k < NKEY; ++k) key[k] = SCREEN_KEYS ? skey[k] : EMPTY;
         auto cand = [&](int jj, float xj, float yj, float zj) {
           const float pj[3] = {xj, yj, zj};
-          knn_insert<KT + 1>(key, jj, me, sq_dist(pj, s.x));
+          knn_insert<NKEY>(key, jj, me, sq_dist(pj, s.x));
         };
         if (!screened) {
           if constexpr (LANE_KNN) {
@@ -471,19 +484,20 @@ __device__ __forceinline__ void step_body(const Consts& c, const Ptrs& p,
         }
         bool tie = false;
 #pragma unroll
-        for (int k = 0; k < KT; ++k) tie |= key[k + 1] != EMPTY && (key[k] >> 6) == (key[k + 1] >> 6);
+        for (int k = 0; k < KC; ++k)
+          tie |= k < K && key[k + 1] != EMPTY && (key[k] >> 6) == (key[k + 1] >> 6);
         if (tie && live) {
           // exact (d^2, index) insertion over the swarm (rare)
-          float bd[KT];
-          int bj[KT];
+          float bd[KC];
+          int bj[KC];
 #pragma unroll
-          for (int k = 0; k < KT; ++k) { bd[k] = INFINITY; bj[k] = -1; }
+          for (int k = 0; k < KC; ++k) { bd[k] = INFINITY; bj[k] = -1; }
           for (int jj = 0; jj < n; ++jj) {
             const float rx = tile[0][ls + jj] - s.x[0], ry = tile[1][ls + jj] - s.x[1],
                         rz = tile[2][ls + jj] - s.x[2];
             const float d2 = jj == me ? INFINITY : rx * rx + ry * ry + rz * rz;
 #pragma unroll
-            for (int k = KT - 1; k > 0; --k) {
+            for (int k = KC - 1; k > 0; --k) {
               const bool shift = bd[k - 1] > d2;
               const bool here = bd[k] > d2;
               bd[k] = shift ? bd[k - 1] : (here ? d2 : bd[k]);
@@ -492,17 +506,18 @@ __device__ __forceinline__ void step_body(const Consts& c, const Ptrs& p,
             if (bd[0] > d2) { bd[0] = d2; bj[0] = jj; }
           }
 #pragma unroll
-          for (int k = 0; k < KT; ++k) key[k] = bj[k] >= 0 ? (uint32_t)bj[k] : EMPTY;
+          for (int k = 0; k < KC; ++k) key[k] = bj[k] >= 0 ? (uint32_t)bj[k] : EMPTY;
         }
-        int bj[KT];
+        int bj[KC];
 #pragma unroll
-        for (int k = 0; k < KT; ++k) bj[k] = key[k] != EMPTY ? (int)(key[k] & 63u) : -1;
+        for (int k = 0; k < KC; ++k) bj[k] = key[k] != EMPTY ? (int)(key[k] & 63u) : -1;
         // the slots' rows are read unconditionally (j is always a valid
         // column) and selected afterwards, so all reads are in flight at
         // once instead of one guarded read and wait per value
-        float nb[KT][6];
+        float nb[KC][6];
 #pragma unroll
-        for (int k = 0; k < KT; ++k) {
+        for (int k = 0; k < KC; ++k) {
+          if (k >= K) break;
           const int j = ls + (bj[k] >= 0 ? bj[k] : 0);
           nb[k][0] = tile[0][j];
           nb[k][1] = tile[1][j];
@@ -512,7 +527,7 @@ __device__ __forceinline__ void step_body(const Consts& c, const Ptrs& p,
           nb[k][5] = tile[8][j];
         }
 #pragma unroll
-        for (int k = 0; k < KT; ++k) {
+        for (int k = 0; k < KC; ++k) {
           const bool have = bj[k] >= 0;
           ov[18 + 6 * k + 0] = have ? nb[k][0] - s.x[0] : 0.f;
           ov[18 + 6 * k + 1] = have ? nb[k][1] - s.x[1] : 0.f;
@@ -524,14 +539,24 @@ __device__ __forceinline__ void step_body(const Consts& c, const Ptrs& p,
         if (reward && live) {
           float rp = 0.f;
 #pragma unroll
-          for (int k = 0; k < KT; ++k)
-            if (bj[k] >= 0) rp += reward_prox(c, ov[18 + 6 * k], ov[19 + 6 * k], ov[20 + 6 * k]);
+          for (int k = 0; k < KC; ++k)
+            if (k < K && bj[k] >= 0) rp += reward_prox(c, ov[18 + 6 * k], ov[19 + 6 * k], ov[20 + 6 * k]);
           reward[q] = reward_state(c, s, pp.f_max, ov, f0) + rp;
         }
       } else {
         if (reward && live) reward[q] = reward_state(c, s, pp.f_max, ov, f0);
       }
       if (c.flags & F_SENSOR) sensor_noise(c, (uint32_t)q, t0 + nsub, &ov[0], &ov[3], &ov[15]);
+      auto put_row = [&](float2* r2) {
+#pragma unroll
+        for (int k = 0; k < 9; ++k) r2[k] = make_float2(ov[2 * k], ov[2 * k + 1]);
+#pragma unroll
+        for (int k = 0; k < KC; ++k) {
+          if (k >= K) break;
+#pragma unroll
+          for (int m = 9 + 3 * k; m < 12 + 3 * k; ++m) r2[m] = make_float2(ov[2 * m], ov[2 * m + 1]);
+        }
+      };
       if (stage_obs) {
         // the workgroup's rows leave through LDS in passes of stage_obs
         // rows, each copied out with contiguous stores: 16-byte stores when
@@ -548,9 +573,7 @@ __device__ __forceinline__ void step_body(const Consts& c, const Ptrs& p,
           const int4 itm = p.items[item];
           for (int p0 = 0; p0 < itm.z * N; p0 += R) {
             if (live && tid >= p0 && tid < p0 + R) {
-              float2* r2 = reinterpret_cast<float2*>(st_obs + (tid - p0) * OD);
-#pragma unroll
-              for (int k = 0; k < OD / 2; ++k) r2[k] = make_float2(ov[2 * k], ov[2 * k + 1]);
+              put_row(reinterpret_cast<float2*>(st_obs + (tid - p0) * OD));
             }
             quad_sync();
             const int k1 = min((p0 + R) / N, itm.z);
@@ -566,9 +589,7 @@ __device__ __forceinline__ void step_body(const Consts& c, const Ptrs& p,
         } else
         for (int p0 = 0; p0 < cnt; p0 += R) {
           if (live && tid >= p0 && tid < p0 + R) {
-            float2* r2 = reinterpret_cast<float2*>(st_obs + (tid - p0) * OD);
-#pragma unroll
-            for (int k = 0; k < OD / 2; ++k) r2[k] = make_float2(ov[2 * k], ov[2 * k + 1]);
+            put_row(reinterpret_cast<float2*>(st_obs + (tid - p0) * OD));
           }
           quad_sync();
           const int total = min(R, cnt - p0) * OD;
@@ -593,9 +614,7 @@ __device__ __forceinline__ void step_body(const Consts& c, const Ptrs& p,
           if (p0 + R < cnt) quad_sync();
         }
       } else if (live) {
-        float2* r2 = reinterpret_cast<float2*>(obs + (size_t)q * OD);
-#pragma unroll
-        for (int k = 0; k < OD / 2; ++k) r2[k] = make_float2(ov[2 * k], ov[2 * k + 1]);
+        put_row(reinterpret_cast<float2*>(obs + (size_t)q * OD));
       }
     } else {
       // runtime K (rare sizes): K passes of selection of the next

@@ -50,10 +50,10 @@ void go(qs_handle* h, const float* act, int nsub, const float* goals, float* obs
   size_t dyn = 0;
   int stage = 0;
   if constexpr (KT >= 0) {
-    stage = stage_rows(BS, 18 + 6 * KT, h->nblk);
-    dyn = (size_t)stage * (18 + 6 * KT) * sizeof(float);
+    stage = stage_rows(BS, h->OD, h->nblk);
+    dyn = (size_t)stage * h->OD * sizeof(float);
   }
-  if constexpr (BS == 64 && N == 8 && (KT == 6 || KT == -2)) {
+  if constexpr (BS == 64 && N == 8) {
     if (nsub >= 2 && use_step_pipe(h)) {
       hipLaunchKernelGGL((qs::step_pipe_kernel<KT, N>), dim3(h->nblk), dim3(128), dyn, s,
                          h->d_st, h->d_par, act, goals, h->d_c, h->Qp, h->Q, nsub,
@@ -89,10 +89,10 @@ int launch_bs(qs_handle* h, const float* act, int nsub, const float* goals, floa
     go_n<BS, -2>(h, act, nsub, goals, obs, s, rw);
   else if (h->K == 6)
     go_n<BS, 6>(h, act, nsub, goals, obs, s, rw);
-  else if (h->K == 0 && h->uniform_n == 1)
-    go<BS, 0, 1>(h, act, nsub, goals, obs, s, rw);
   else if (h->K == 0)
-    go<BS, 0, 0>(h, act, nsub, goals, obs, s, rw);
+    go_n<BS, 0>(h, act, nsub, goals, obs, s, rw);
+  else if (h->K <= qs::kSlots<qs::K_UPTO8>)
+    go_n<BS, qs::K_UPTO8>(h, act, nsub, goals, obs, s, rw);
   else
     go<BS, -1, 0>(h, act, nsub, goals, obs, s, rw);
   return hipGetLastError() == hipSuccess ? QS_OK : QS_ERR_HIP;
