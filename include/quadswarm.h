@@ -32,9 +32,10 @@
  *    itself; results are bit-identical whichever form runs):
  *      QS_BLOCK_SIZE=64|128  workgroup size, read by qs_create (default 64;
  *                            128 for >= 262,144 single-quad swarms);
- *      QS_BUCKETED=0         uneven swarm sizes run one workgroup per packed
- *                            block instead of the persistent bucketed
- *                            launch, read by qs_create;
+ *      QS_BUCKETED=0|1       uneven swarm sizes run one workgroup per packed
+ *                            block, or the persistent bucketed launch, in
+ *                            every call (default: by the substeps of the
+ *                            call), read by qs_create;
  *      QS_STEP_PIPE, QS_ROLLOUT_PIPE, QS_RECOMPUTE_PIPE,
  *      QS_REVERSE_PIPE = 0|1
  *                            force the multi-wavefront forms off or on:
@@ -364,11 +365,13 @@ int qs_step_backward_noalloc(qs_handle* h, const float* d_state_in, const float*
                              float* d_gparams, void* stream);
 
 /* ---- batching and scheduling ------------------------------------------------
- * Swarms of uneven sizes run in one persistent launch: every swarm gets a
- * slot of the next power of two >= its size, slots of one size are grouped
- * into work items, and each workgroup strides over the items running code
- * specialised for the item's slot size (environment QS_BUCKETED=0 at
- * qs_create falls back to one workgroup per greedy block of swarms).
+ * Calls of many substeps on swarms of uneven sizes run in one persistent
+ * launch: every swarm gets a slot of the next power of two >= its size, slots
+ * of one size are grouped into work items, and each workgroup strides over the
+ * items running code specialised for the item's slot size.  Calls of few
+ * substeps, and swarms that would leave many places of their slots empty, run
+ * one workgroup per greedy block of swarms (QS_BUCKETED=0 at qs_create: every
+ * call; QS_BUCKETED=1, or an explicit qs_set_launch: none).
  */
 
 /*
@@ -395,13 +398,14 @@ int qs_set_launch(qs_handle* h, int32_t block, int32_t grid);
  * same saved state), keep the fastest, and restore the state, the substep
  * counter and the sticky error word.  Uniform swarm sizes: workgroup size
  * 64 or 128.  Uneven sizes (the bucketed form): (1) workgroup sizes 64 and
- * 128 and persistent grids, every slot size with the in-swarm loops taking
- * one partner at a time; (2) per slot size of 16 and 32, its work items
- * alone with that body and with the body that takes the partners in chunks
- * of four; (3) the call with each slot size on its faster body, over the
- * grids; the faster of (1) and (3) is kept.  choice (optional, int32[3])
- * receives (workgroup size, grid size or 0 for one workgroup per item,
- * bucketed ? 1 : 0); qs_launch_plan gives the per-slot table.  Not
+ * 128 and persistent grids, every slot size with the in-swarm loops over the
+ * swarm's own size; (2) per slot size of 16 and 32, its work items
+ * alone with that body and with the body that passes over all the slot's
+ * places; (3) the call with each slot size on its faster body, over the
+ * grids; the faster of (1) and (3) is kept; (4) the call by packed blocks,
+ * which calls of n_substeps take from then on if it is faster still.
+ * choice (optional, int32[3]) receives (workgroup size, grid size or 0 for one
+ * workgroup per item, bucketed form available ? 1 : 0); qs_launch_plan gives the per-slot table.  Not
  * available in graph mode.  Synchronous.  This is the batching workload's
  * schedule search; the paper has no counterpart.
  */

@@ -3,6 +3,7 @@
 #include <initializer_list>
 #include <hip/hip_runtime.h>
 
+#include <climits>
 #include <cmath>
 #include <cstdint>
 #include <cstdlib>
@@ -102,10 +103,18 @@ int build_table(qs_handle* h, int bs) {
 }
 
 // Work items of the bucketed launch: every swarm gets a slot of the next
-// power of two >= its size; slots of one size are grouped bs/slot per item;
-// items are ordered by slot size, largest first (heaviest work first).  An
+// power of two >= its size; slots of one size are grouped bs/slot per item.  An
 // item's w field selects the chunked partner body (slot sizes in
 // h->chunked).
+//
+// Items are ordered by the quads they serve, in runs of RUN per XCD (workgroups
+// go to the eight XCDs in turn): a field's cache line holds 32 quads of several
+// swarms, whose items then share an L2 and run at about the same time.  Ordered
+// by slot size (by_size: the autotuner's trials of one slot's items), every XCD
+// fetches and writes back its own part of every line: 172,943 quads of 1 to 32,
+// ten calls of ten substeps, 472 us; by quads in runs of 32, 128 and 512: 444, 435
+// and 431; 524,289 quads of 1 to 8, one substep: 99 -> 57.  Shorter runs
+// keep swarms sorted by size from giving one XCD all the heavy items.
 int log2i(int n) {
   int k = 0;
   while ((1 << k) < n) ++k;
@@ -115,7 +124,7 @@ int log2i(int n) {
 // Slot sizes with a second, chunked body in the bucketed kernel.
 constexpr uint32_t kChunkable = (1u << 4) | (1u << 5);
 
-int build_items(qs_handle* h, int bs) {
+int build_items(qs_handle* h, int bs, bool by_size = false) {
   std::vector<int4> items;
   std::vector<int2> envs;
   for (int k = 0; k < 7; ++k) h->slot_swarms[k] = 0;
@@ -132,6 +141,20 @@ int build_items(qs_handle* h, int bs) {
       items.back().z += 1;
       if (++in_item == per) in_item = 0;
     }
+  }
+  if (!by_size) {
+    constexpr size_t RUN = 128, XCDS = 8;
+    std::stable_sort(items.begin(), items.end(), [&](const int4& a, const int4& b) {
+      return envs[(size_t)a.y].x < envs[(size_t)b.y].x;
+    });
+    std::vector<int4> order;
+    order.reserve(items.size());
+    for (size_t g = 0; g < items.size(); g += XCDS * RUN) {
+      const size_t m = std::min(XCDS * RUN, items.size() - g), run = (m + XCDS - 1) / XCDS;
+      for (size_t i = 0; i < run; ++i)
+        for (size_t j = i; j < m; j += run) order.push_back(items[g + j]);
+    }
+    items.swap(order);
   }
   (void)hipFree(h->d_items);
   (void)hipFree(h->d_item_envs);
@@ -150,11 +173,30 @@ int build_items(qs_handle* h, int bs) {
   return QS_OK;
 }
 
+// Substeps a call from which a bucketed handle takes the bucketed launch.  Fewer
+// go by the table of packed workgroups: all its lanes are in use and its reads
+// and writes are contiguous, but every wavefront passes over as many partners as
+// its largest swarm has, each substep.  (us a call with K = 6, table against
+// items.  Two substeps: 49152 quads in twelves 10.5 / 13.9, 524k of 1 to 32
+// 63 / 83.  Eight and more, slots nearly full: 131k of 1, 2, 4 .. 32: eight 41.7 /
+// 35.1, sixteen 91 / 74; 524k: 113 / 109, 202 / 180; 16k in thirties: 27.5 / 26.4,
+// 69 / 59.)  Padded slots cost lanes: with a quarter of them empty the items
+// lose once they need more wavefronts than the three a SIMD holds (524k of 1 to 32,
+// ten substeps: 130 / 143; 131k: 53 / 48), and always where the swarms are
+// small (sixteen at most: 131k in twelves 38.9 / 40.0, 524k 103 / 127).
+int default_items_from(const qs_handle* h) {
+  constexpr long long resident = 3LL * 4 * 256 * 64;  // places of 3 wavefronts on every SIMD
+  long long places = 0;
+  for (int k = 0; k < 7; ++k) places += (long long)h->slot_swarms[k] << k;
+  const bool full = 10LL * h->Q >= 9 * places;
+  return full || (h->max_n > 16 && places <= resident) ? 8 : INT_MAX;
+}
+
 int launch(qs_handle* h, const float* act, int nsub, const float* goals, float* obs,
            bool with_obs, hipStream_t s, float* rw = nullptr) {
   if (hipSetDevice(h->dev) != hipSuccess) return QS_ERR_HIP;
   int rc;
-  if (h->bucketed) {
+  if (h->bucketed && nsub >= h->items_from) {
     (h->item_bs == 128 ? qs_host::launch_items128 : qs_host::launch_items64)(
         h, act, nsub, goals, obs, with_obs, s, rw);
     rc = hipGetLastError() == hipSuccess ? QS_OK : QS_ERR_HIP;
@@ -222,23 +264,26 @@ struct BucketConfig {
   uint32_t chunked;
 };
 
-int apply(qs_handle* h, hipStream_t s, const BucketConfig& c) {
+int apply(qs_handle* h, hipStream_t s, const BucketConfig& c, bool by_size = false) {
   // no launch may still read the tables that are about to be rebuilt
   if (hipStreamSynchronize(s) != hipSuccess) return QS_ERR_HIP;
   h->chunked = c.chunked;
   h->item_grid = c.grid;
-  return build_items(h, c.bs);
+  return build_items(h, c.bs, by_size);
 }
 
 // Bucketed handles: (1) workgroup sizes 64 and 128 and persistent grids,
 // every slot size with the one-partner body; (2) per slot size with two
 // bodies (16 and 32), its items alone with each body, at the workgroup size
 // of (1); (3) the call with each slot size on its faster body, over the
-// grids; the faster of (1) and (3) is kept.
+// grids; the faster of (1) and (3) is kept.  (4) The call by the table: whichever
+// launch is the faster one, calls of this many substeps take from now on.
 int tune_buckets(Trial& tr, BucketConfig* best) {
   qs_handle* h = tr.h;
   float best_ms = 1e30f;
   int rc = QS_OK;
+  const int from = h->items_from;
+  h->items_from = 0;
   for (int bs : {64, 128})
     for (int g : {0, 1024, 2048, 4096}) {
       const BucketConfig c{bs, g, 0u};
@@ -255,8 +300,8 @@ int tune_buckets(Trial& tr, BucketConfig* best) {
     if (!(kChunkable >> k & 1u) || h->slot_swarms[k] == 0) continue;
     float t[2] = {0.f, 0.f};
     for (int v = 0; v < 2; ++v) {
-      if ((rc = apply(h, tr.s, {best->bs, 0, v ? 1u << k : 0u})) != QS_OK) return rc;
-      // the slot's item range (items are ordered by slot size)
+      if ((rc = apply(h, tr.s, {best->bs, 0, v ? 1u << k : 0u}, true)) != QS_OK) return rc;
+      // the slot's item range
       std::vector<int4> items((size_t)h->n_items);
       if (hipMemcpy(items.data(), h->d_items, items.size() * sizeof(int4),
                     hipMemcpyDeviceToHost) != hipSuccess)
@@ -273,8 +318,8 @@ int tune_buckets(Trial& tr, BucketConfig* best) {
     h->slot_ns_chunked[k] = t[1] * 1e6f;
     if (t[1] < t[0]) mask |= 1u << k;
   }
-  if (mask == 0u) return QS_OK;
   for (int g : {0, 1024, 2048, 4096}) {
+    if (mask == 0u) break;
     const BucketConfig c{best->bs, g, mask};
     float ms = 0.f;
     if ((rc = apply(h, tr.s, c)) != QS_OK || (rc = tr.call(&ms)) != QS_OK) return rc;
@@ -283,6 +328,10 @@ int tune_buckets(Trial& tr, BucketConfig* best) {
       *best = c;
     }
   }
+  float table_ms = 0.f;
+  h->items_from = INT_MAX;
+  if ((rc = tr.call(&table_ms)) != QS_OK) return rc;
+  h->items_from = table_ms < best_ms ? std::max(from, tr.nsub + 1) : std::min(from, tr.nsub);
   return QS_OK;
 }
 
@@ -415,6 +464,7 @@ int qs_create(const qs_desc* desc, const qs_quad_params* h_params, const float* 
     const char* ev = std::getenv("QS_BUCKETED");
     h->bucketed = !(ev && ev[0] == '0');
     if (h->bucketed) rc = build_items(h, 64);
+    h->items_from = ev ? 0 : default_items_from(h);
   }
   if (rc == QS_OK && hipHostMalloc((void**)&h->h_err, sizeof(int)) != hipSuccess) {
     h->h_err = nullptr;
@@ -506,6 +556,7 @@ int qs_set_launch(qs_handle* h, int32_t block, int32_t grid) {
   if (h->bucketed) {
     if (block != h->item_bs) rc = build_items(h, block);
     h->item_grid = grid;
+    h->items_from = 0;
   } else if (block != h->bs) {
     if (h->uniform_n > 64 || block % std::max(h->uniform_n, 1) != 0) return QS_ERR_INVALID;
     rc = build_table(h, block);
@@ -563,7 +614,9 @@ int qs_autotune(qs_handle* h, const float* d_actions, int32_t n_substeps, const 
   if (rc == QS_OK) {
     if (h->bucketed) {
       BucketConfig best{h->item_bs, h->item_grid, h->chunked};
+      const int from = h->items_from;
       rc = tune_buckets(tr, &best);
+      if (rc != QS_OK) h->items_from = from;
       if (rc == QS_OK) rc = apply(h, s, best);
     } else if (h->uniform_n > 0) {
       // uniform power-of-two swarms: workgroup size 64 or 128

@@ -663,6 +663,13 @@ __device__ __forceinline__ float lane_xor8(const LaneXyz& p, int k) {
 struct TrueT { static constexpr bool value = true; };
 struct FalseT { static constexpr bool value = false; };
 
+// Swarm size template argument of the bucketed launch's loops over a slot's
+// run-time size (0: run-time sizes elsewhere).  Its body shares the kernel with
+// those of the other slots, and keeps the plain screen, which needs the fewest
+// registers: the expanded one put all of them past 168 (172,943 quads of 1 to
+// 32, ten substeps, ten calls: 476 -> 494 us).
+constexpr int SLOT_LOOP = -1;
+
 // Contact mask of a swarm slot of N quads: 32 bits suffice up to 32 (one
 // select and one OR per partner instead of two of each).
 template <int N>
@@ -738,24 +745,33 @@ constexpr int TILE_ROWS_CO = XROW + 4;
 // spans [-5, 5] x [-5, 5] x [0, 10].
 constexpr float SCREEN_BOX = 10.0f;
 
-// Swarm slots whose screen reads the squared norms (row XSQ).
+// Swarm slots whose screen reads the squared norms.
 template <int N>
-constexpr bool kScreenSq = N >= 16 && N <= 32;
+constexpr bool kScreenSq = N == 0 || (N >= 16 && N <= 32);
 
-// The screen rows of one lane: x and, SQ, |x|^2 (one expression, so every
-// kernel writes the same value), or, for a padding lane, a far-away
-// sentinel.
-template <bool SQ, typename T>
-__device__ __forceinline__ void put_screen_rows(T tile, int tid, const float x[3]) {
-#pragma unroll
-  for (int k = 0; k < 3; ++k) tile[XROW + k][tid] = x[k];
-  if constexpr (SQ) tile[XSQ][tid] = fmaf(x[2], x[2], fmaf(x[1], x[1], x[0] * x[0]));
+// The screen rows of one lane: x and, for kScreenSq, |x|^2 (one expression, so
+// every kernel writes the same value), or, for a padding lane, a far-away
+// sentinel.  Sizes known at compile time read aligned runs of partners from a
+// row (16 bytes of one coordinate of four); run-time sizes have no alignment,
+// so there the four rows hold a float4 per quad, one partner a read.
+template <int N, typename T>
+__device__ __forceinline__ void put_screen(T tile, int tid, float x, float y, float z, float sq) {
+  if constexpr (N == 0) {
+    reinterpret_cast<float4*>(&tile[XROW][0])[tid] = make_float4(x, y, z, sq);
+  } else {
+    tile[XROW][tid] = x;
+    tile[XROW + 1][tid] = y;
+    tile[XROW + 2][tid] = z;
+    if constexpr (kScreenSq<N>) tile[XSQ][tid] = sq;
+  }
 }
-template <bool SQ, typename T>
+template <int N, typename T>
+__device__ __forceinline__ void put_screen_rows(T tile, int tid, const float x[3]) {
+  put_screen<N>(tile, tid, x[0], x[1], x[2], fmaf(x[2], x[2], fmaf(x[1], x[1], x[0] * x[0])));
+}
+template <int N, typename T>
 __device__ __forceinline__ void put_screen_pad(T tile, int tid) {
-#pragma unroll
-  for (int k = 0; k < 3; ++k) tile[XROW + k][tid] = 1e30f;
-  if constexpr (SQ) tile[XSQ][tid] = INFINITY;
+  put_screen<N>(tile, tid, 1e30f, 1e30f, 1e30f, INFINITY);
 }
 
 // Calls f(jj, pj) for every swarm-mate jj (itself included), in increasing
@@ -784,6 +800,7 @@ __device__ __forceinline__ void for_partner_pos(T tile, int ls, int n, F&& f) {
       for (int j0 = 0; j0 < N; j0 += CH) chunk(j0);
     }
   } else {
+    static_assert(N == SLOT_LOOP, "run-time sizes (N = 0): screen_expanded");
     for (int j0 = 0; j0 < n; j0 += 4) {
       float pj[4][NR];
 #pragma unroll
@@ -831,7 +848,9 @@ __device__ __forceinline__ float sq_dist(const float pj[3], const float x[3]) {
   return dx * dx + dy * dy + dz * dz;
 }
 
-// Expanded screen of swarms of 16 and 32: mask of the partners whose
+// Expanded screen of swarms of 16 and 32 and of run-time sizes (there 49152 quads
+// in swarms of 12, two substeps: 12.9 -> 12.1 us; the rollout of 2048 swarms of 1
+// to 16, forward and backward over 100 substeps: 485 -> 442): mask of the partners whose
 // post-motion positions lie within r of the lane's, and perhaps a few more.
 // The bit is the sign of
 //   e = |b|^2 + (|a|^2 - thr_x) - 2 a.b  (= |a - b|^2 - thr_x),
@@ -845,19 +864,43 @@ __device__ __forceinline__ float sq_dist(const float pj[3], const float x[3]) {
 // rounding three times over and no such partner is dropped; a lane outside
 // the box takes every partner.
 template <int BS, int N>
-__device__ __forceinline__ uint32_t screen_expanded(const float (*tile)[BS], const float x[3],
-                                                    int ls, int n, float r, float r2) {
+__device__ __forceinline__ PairMask<N> screen_expanded(const float (*tile)[BS], const float x[3],
+                                                       int ls, int n, float r, float r2) {
   const float reach = 2.0f * 1.7320508f * SCREEN_BOX + r + 1e-3f;
   const float err = 1.01f * 7.0f * 5.9604645e-8f * (reach * reach + r2);
   const float thr_x = r2 + 3.0f * err;
   const float na = fmaf(x[2], x[2], fmaf(x[1], x[1], fmaf(x[0], x[0], -thr_x)));
   const float a0 = -2.0f * x[0], a1 = -2.0f * x[1], a2 = -2.0f * x[2];
-  uint32_t acc = 0u;
-  for_partner_pos<BS, N, 4>(tile, ls, n, [&](int, const float* pj) {
-    const float e = fmaf(a2, pj[2], fmaf(a1, pj[1], fmaf(a0, pj[0], pj[3] + na)));
-    acc = __builtin_amdgcn_alignbit(acc, __float_as_uint(e), 31u);
-  });
-  return __builtin_bitreverse32(acc) >> (32 - N);
+  auto sign_in = [&](uint32_t acc, float px, float py, float pz, float psq) {
+    const float e = fmaf(a2, pz, fmaf(a1, py, fmaf(a0, px, psq + na)));
+    return (uint32_t)__builtin_amdgcn_alignbit(acc, __float_as_uint(e), 31u);
+  };
+  if constexpr (N > 0) {
+    uint32_t acc = 0u;
+    for_partner_pos<BS, N, 4>(tile, ls, n, [&](int, const float* pj) {
+      acc = sign_in(acc, pj[0], pj[1], pj[2], pj[3]);
+    });
+    return (PairMask<N>)(__builtin_bitreverse32(acc) >> (32 - N));
+  } else {
+    // run-time sizes: whole chunks of four (a place past the end repeats the
+    // last member and is masked off), at most 32 places to a word
+    const float4* at = reinterpret_cast<const float4*>(&tile[XROW][0]) + ls;
+    auto word = [&](int j0, int j1) {
+      uint32_t acc = 0u;
+      for (int j = j0; j < j1; j += 4) {
+        float4 p[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) p[u] = at[min(j + u, n - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) acc = sign_in(acc, p[u].x, p[u].y, p[u].z, p[u].w);
+      }
+      const int places = (j1 - j0 + 3) & ~3;
+      return __builtin_bitreverse32(acc) >> (32 - places);
+    };
+    unsigned long long m = word(0, min(n, 32));
+    if (n > 32) m |= (unsigned long long)word(32, n) << 32;
+    return m & (~0ull >> (64 - n));
+  }
 }
 __device__ __forceinline__ float max_abs(const float x[3]) {
   return fmaxf(fabsf(x[0]), fmaxf(fabsf(x[1]), fabsf(x[2])));
@@ -944,14 +987,13 @@ __device__ __forceinline__ bool near_pass(const Consts& c, const float (*tile)[B
   if (__ballot(!(far <= lim && s.x[0] + s.x[1] + s.x[2] < INFINITY)) != 0ull) return false;
   M near;
   if constexpr (kScreenSq<N>) {
-    near = (M)screen_expanded<BS, N>(tile, s.x, ls, n, p.r, p.r * p.r);
+    near = screen_expanded<BS, N>(tile, s.x, ls, n, p.r, p.r * p.r);
   } else {
     const float w = p.r + 1e-3f, thr = w * w;
     near = 0;
     for_partner_pos<BS, N>(tile, ls, n, [&](int jj, const float* pj) {
       near |= sq_dist(pj, s.x) < thr ? (M)1 << jj : (M)0;
     });
-    if constexpr (N == 0) near &= (M)(~0ull >> (64 - n));
   }
   near &= ~((M)1 << me);
   if (__ballot(__popcll((unsigned long long)near) > p.few) != 0ull) return false;
@@ -1101,22 +1143,20 @@ __device__ __forceinline__ unsigned long long pair_pass(const Consts& c, const f
   } else if constexpr (CO && P == PEN_NONE) {
     const float dw = c.dcol + 1e-3f, thr = dw * dw;
     M cand = 0;
-    bool in_box = true;  // the expanded screen's domain (swarms of 16 and 32)
-    if constexpr (N >= 16 && N <= 32) {
-      if constexpr (L > 0) {
-        // partners arrive in index order, so the mask is accumulated as
-        // acc = 2 acc + bit and bit-reversed once
-        uint32_t acc = 0u;
-        for_partner_pos<BS, N>(tile, ls, n, [&](int jj, const float* pj) {
-          const float d2 = sq_dist(pj, s.x);
-          acc = acc + acc + (d2 < thr ? 1u : 0u);
-          knn_insert<L>(key, jj, me, d2);
-        });
-        cand = (M)(__builtin_bitreverse32(acc) >> (32 - N));
-      } else {
-        cand = (M)screen_expanded<BS, N>(tile, s.x, ls, n, c.dcol, c.dcol2);
-        in_box = max_abs(s.x) <= SCREEN_BOX;
-      }
+    bool in_box = true;  // the expanded screen's domain
+    if constexpr (L == 0 && kScreenSq<N>) {
+      cand = screen_expanded<BS, N>(tile, s.x, ls, n, c.dcol, c.dcol2);
+      in_box = max_abs(s.x) <= SCREEN_BOX;
+    } else if constexpr (N >= 16 && N <= 32) {
+      // partners arrive in index order, so the mask is accumulated as
+      // acc = 2 acc + bit and bit-reversed once
+      uint32_t acc = 0u;
+      for_partner_pos<BS, N>(tile, ls, n, [&](int jj, const float* pj) {
+        const float d2 = sq_dist(pj, s.x);
+        acc = acc + acc + (d2 < thr ? 1u : 0u);
+        knn_insert<L>(key, jj, me, d2);
+      });
+      cand = (M)(__builtin_bitreverse32(acc) >> (32 - N));
     } else {
       for_partner_pos<BS, N>(tile, ls, n, [&](int jj, const float* pj) {
         const float d2 = sq_dist(pj, s.x);
@@ -1145,7 +1185,7 @@ __device__ __forceinline__ unsigned long long pair_pass(const Consts& c, const f
     }
   }
   // (run-time sizes: nor the places past the swarm's end)
-  if constexpr (N == 0) cm &= (M)(~0ull >> (64 - n));
+  if constexpr (N <= 0) cm &= (M)(~0ull >> (64 - n));
   const unsigned long long cmask = collide ? (unsigned long long)(cm & ~((M)1 << me)) : 0ull;
   // The responses, for the partners in contact only, in partner order.
   float dv[3] = {0.f, 0.f, 0.f};
@@ -1163,7 +1203,7 @@ __device__ __forceinline__ unsigned long long pair_pass(const Consts& c, const f
 }
 
 // The exchange tile's rows of one lane (padding lanes: far away).
-template <bool SQ, bool SCREEN, typename T>
+template <int N, bool SCREEN, typename T>
 __device__ __forceinline__ void put_tile(T tile, int tid, const Quad& s) {
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
@@ -1171,7 +1211,7 @@ __device__ __forceinline__ void put_tile(T tile, int tid, const Quad& s) {
     tile[3 + k][tid] = s.inc[k];
     tile[6 + k][tid] = s.v[k];
   }
-  if constexpr (SCREEN) put_screen_rows<SQ>(tile, tid, s.x);
+  if constexpr (SCREEN) put_screen_rows<N>(tile, tid, s.x);
 }
 template <typename T>
 __device__ __forceinline__ void put_tile_pad(T tile, int tid) {
@@ -1200,7 +1240,7 @@ __device__ __forceinline__ unsigned long long lane_pair_pass(
   static_assert(N == 2 || N == 4 || N == 8, "aligned groups of up to 8 lanes");
   auto put = [&] {
     if constexpr (PUT) {
-      if (live) put_tile<false, false>(tile, tid, s);
+      if (live) put_tile<N, false>(tile, tid, s);
       else put_tile_pad(tile, tid);
     }
     wave_sync();

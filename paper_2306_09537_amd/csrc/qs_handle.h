@@ -49,6 +49,7 @@ struct qs_handle {
   float slot_ns_one[7] = {0, 0, 0, 0, 0, 0, 0};
   float slot_ns_chunked[7] = {0, 0, 0, 0, 0, 0, 0};
   bool bucketed = false;
+  int items_from = 0;    // substeps a call from which it is used (fewer: the table)
   // graph-safe substep counter
   bool graph_mode = false;
   unsigned long long* d_t = nullptr;

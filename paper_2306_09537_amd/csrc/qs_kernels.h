@@ -78,7 +78,8 @@ __device__ __forceinline__ void advance_counter(unsigned long long* tdev, unsign
 //  0, 6  that K, known at compile time (register insertion network);
 //  K_UPTO8  any K from 1 to 8: the network of 8, of which the first K are taken.
 //  K passes over the swarm and 18 + 6 K scattered stores a lane had cost
-//  1024 x 8 with K = 3, two substeps and a reward 13 us, now KU1.
+//  1024 x 8 with K = 3, two substeps and a reward 12 us, now 8.2; 16384 x 32 with
+//  K = 8 140, now 61.
 constexpr int K_UPTO8 = 24;
 template <int KT>
 constexpr int kSlots = KT == K_UPTO8 ? 8 : KT;
@@ -86,8 +87,8 @@ constexpr int kSlots = KT == K_UPTO8 ? 8 : KT;
 // Body of one step (+ observation) over one workgroup's quads.
 // KT: the observation's form (above).
 // N: swarm (slot) size known at compile time (MAP_DENSE, MAP_ITEM), or 0.
-// NU: partner count the in-swarm loops are unrolled for (N, or 0 for loops
-// over the swarm's runtime size: fewer registers for large slots).
+// NU: partner count the in-swarm loops are unrolled for (N, or SLOT_LOOP for
+// loops over the swarm's runtime size: fewer registers for large slots).
 // sxv: LDS tile [2][TILE_ROWS_CO][BS]; st_obs: LDS staging of observation rows.
 // ROLE: -1 one wavefront does everything; in a workgroup of two wavefronts
 // over the same 64 quads (step_pipe_kernel), 0 runs the motor part of every
@@ -294,11 +295,11 @@ __device__ __forceinline__ void step_body(const Consts& c, const Ptrs& p,
     } else if (collide) {
       float(*tile)[BS] = sxv[sub & 1];
       if (live) {
-        put_tile<kScreenSq<NU>, true>(tile, tid, s);
+        put_tile<NU, true>(tile, tid, s);
       } else if constexpr (MAP == MAP_ITEM) {
         // padding lane: far away, so it is never in contact
         put_tile_pad(tile, tid);
-        put_screen_pad<kScreenSq<NU>>(tile, tid);
+        put_screen_pad<NU>(tile, tid);
       }
       quad_sync();
       cmask = 0ull;
@@ -468,7 +469,7 @@ __device__ __forceinline__ void step_body(const Consts& c, const Ptrs& p,
 #pragma unroll
               for (int j0 = 0; j0 < NU; j0 += CH) chunk(j0);
             }
-          } else if constexpr (NU == 0) {
+          } else if constexpr (NU <= 0) {
             if (live)
               for (int j0 = 0; j0 < n; j0 += 4) {
                 float px[4][3];
@@ -687,7 +688,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) void st
     const float* __restrict__ goals, const Consts* __restrict__ cp, int Qp, int Q, int nsub,
     unsigned long long t0, Ptrs p, float* __restrict__ obs, int stage_obs,
     unsigned long long* tdev, unsigned int* done, float* __restrict__ reward) {
-  __shared__ float sxv[2][TILE_ROWS_CO][BS];
+  __shared__ __align__(16) float sxv[2][TILE_ROWS_CO][BS];
   extern __shared__ float4 st_obs4[];
   p.st = st;
   p.par = par;
@@ -716,7 +717,7 @@ __global__ __launch_bounds__(128) void step_pipe_kernel(float* __restrict__ st,
                                                         unsigned int* done,
                                                         float* __restrict__ reward) {
   constexpr int BS = 64;
-  __shared__ float sxv[2][TILE_ROWS_CO][BS];
+  __shared__ __align__(16) float sxv[2][TILE_ROWS_CO][BS];
   __shared__ float ring[2][4][BS];
   __shared__ float rx[12][BS];
   extern __shared__ float4 st_obs4[];
@@ -763,7 +764,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(3))) void bu
                                                     int n_items, unsigned long long* tdev,
                                                     unsigned int* done,
                                                     float* __restrict__ reward) {
-  __shared__ float sxv[2][TILE_ROWS_CO][BS];
+  __shared__ __align__(16) float sxv[2][TILE_ROWS_CO][BS];
   extern __shared__ float4 st_obs4[];
   float* so = reinterpret_cast<float*>(st_obs4);
   // slots of 4 to 32 stage their observation rows, 32 rows a pass
@@ -780,17 +781,17 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(3))) void bu
     switch (item.x) {
       case 1: step_body<BS, KT, 1, MAP_ITEM>(c, p, act, nsub, t0, goals, obs, 0, sxv, nullptr, it, reward, tdev); break;
       case 2: step_body<BS, KT, 2, MAP_ITEM>(c, p, act, nsub, t0, goals, obs, 0, sxv, nullptr, it, reward, tdev); break;
-      case 4: step_body<BS, KT, 4, MAP_ITEM, 0>(c, p, act, nsub, t0, goals, obs, SR, sxv, so, it, reward, tdev); break;
-      case 8: step_body<BS, KT, 8, MAP_ITEM, 0>(c, p, act, nsub, t0, goals, obs, SR, sxv, so, it, reward, tdev); break;
+      case 4: step_body<BS, KT, 4, MAP_ITEM, SLOT_LOOP>(c, p, act, nsub, t0, goals, obs, SR, sxv, so, it, reward, tdev); break;
+      case 8: step_body<BS, KT, 8, MAP_ITEM, SLOT_LOOP>(c, p, act, nsub, t0, goals, obs, SR, sxv, so, it, reward, tdev); break;
       case 16:
         if (chunked) step_body<BS, KT, 16, MAP_ITEM>(c, p, act, nsub, t0, goals, obs, SR, sxv, so, it, reward, tdev);
-        else step_body<BS, KT, 16, MAP_ITEM, 0>(c, p, act, nsub, t0, goals, obs, SR, sxv, so, it, reward, tdev);
+        else step_body<BS, KT, 16, MAP_ITEM, SLOT_LOOP>(c, p, act, nsub, t0, goals, obs, SR, sxv, so, it, reward, tdev);
         break;
       case 32:
         if (chunked) step_body<BS, KT, 32, MAP_ITEM>(c, p, act, nsub, t0, goals, obs, SR, sxv, so, it, reward, tdev);
-        else step_body<BS, KT, 32, MAP_ITEM, 0>(c, p, act, nsub, t0, goals, obs, SR, sxv, so, it, reward, tdev);
+        else step_body<BS, KT, 32, MAP_ITEM, SLOT_LOOP>(c, p, act, nsub, t0, goals, obs, SR, sxv, so, it, reward, tdev);
         break;
-      default: step_body<BS, KT, 64, MAP_ITEM, 0>(c, p, act, nsub, t0, goals, obs, 0, sxv, nullptr, it, reward, tdev); break;
+      default: step_body<BS, KT, 64, MAP_ITEM, SLOT_LOOP>(c, p, act, nsub, t0, goals, obs, 0, sxv, nullptr, it, reward, tdev); break;
     }
   }
   if (tdev) advance_counter(tdev, done, nsub, gridDim.x);

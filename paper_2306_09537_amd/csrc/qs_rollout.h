@@ -171,7 +171,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(N == 8 && PE
                                                      int nsub, unsigned long long t0,
                                                      float* __restrict__ ckpt, int ckpt_every,
                                                      float* __restrict__ pen, float beta) {
-  __shared__ float sxv[2][TILE_ROWS_CO][BS];
+  __shared__ __align__(16) float sxv[2][TILE_ROWS_CO][BS];
   const Consts& c = *cp;
   const int tid = threadIdx.x;
   int qb, cnt, ls, n;
@@ -210,7 +210,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(N == 8 && PE
         if constexpr (N == 8 && P == PEN_NONE) {
           lane_pair_pass<BS, N, true>(c, tile, s, live, ls, n, me, tid, (uint32_t)q, t);
         } else {
-          if (live) put_tile<kScreenSq<N>, true>(tile, tid, s);
+          if (live) put_tile<N, true>(tile, tid, s);
           __syncthreads();
           if (live) pair_pass<BS, N, P, true>(c, tile, s, ls, n, me, (uint32_t)q, t, &pn);
         }
@@ -253,7 +253,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(N == 8 && PE
                                                        const float* __restrict__ gpen,
                                                        float beta) {
   constexpr int P = PEN ? PEN_GRAD : PEN_NONE, NTAPE = kTapeRows<PEN>;
-  __shared__ float sxv[2][PEN ? PENROW + 1 : TILE_ROWS_CO][BS];
+  __shared__ __align__(16) float sxv[2][PEN ? PENROW + 1 : TILE_ROWS_CO][BS];
   const Consts& c = *cp;
   const int tid = threadIdx.x;
   int qb, cnt, ls, n;
@@ -307,7 +307,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(N == 8 && PE
         if constexpr (N == 8 && !PEN) {
           lane_pair_pass<BS, N, true>(c, tile, s, live, ls, n, me, tid, (uint32_t)q, t, &resp);
         } else {
-          if (live) put_tile<kScreenSq<N>, true>(tile, tid, s);
+          if (live) put_tile<N, true>(tile, tid, s);
           __syncthreads();
           if (live) {
             if constexpr (PEN) pn.acc[0] = pn.acc[1] = pn.acc[2] = 0.f;
@@ -326,15 +326,21 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(N == 8 && PE
 
 // A quad's start position, displacement, velocity and post-motion position
 // from its column of an exchange tile.
-template <int BS>
+template <int N, int BS>
 __device__ __forceinline__ Quad tile_quad(const float (*tile)[BS], int tid) {
   Quad s;
+  const float4* at = reinterpret_cast<const float4*>(&tile[XROW][0]);
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     s.xo[k] = tile[k][tid];
     s.inc[k] = tile[3 + k][tid];
     s.v[k] = tile[6 + k][tid];
-    s.x[k] = tile[XROW + k][tid];
+    if constexpr (N > 0) s.x[k] = tile[XROW + k][tid];
+  }
+  if constexpr (N == 0) {
+    s.x[0] = at[tid].x;
+    s.x[1] = at[tid].y;
+    s.x[2] = at[tid].z;
   }
   return s;
 }
@@ -482,7 +488,7 @@ __device__ __forceinline__ void reverse_responses(const Consts& c, float (*tile)
   }
   if (!any) return;
   __syncthreads();  // previous readers of the tile are done
-  if (live) put_tile<false, false>(tile, tid, s);
+  if (live) put_tile<N, false>(tile, tid, s);
   __syncthreads();
   bool hit = cm != 0ull;
   if constexpr (N == 0) {
@@ -527,7 +533,7 @@ __global__ __launch_bounds__(BS) void reverse_kernel(const Consts* __restrict__ 
                                                      float* __restrict__ gpar) {
   constexpr int NTAPE = kTapeRows<PEN>;
   // the rows on their way in and out; the exchange tile between
-  __shared__ float sh[NSTATE * BS];
+  __shared__ __align__(16) float sh[NSTATE * BS];
   float(*tile)[BS] = reinterpret_cast<float(*)[BS]>(sh);
   const Consts& c = *cp;
   const int tid = threadIdx.x;
@@ -637,7 +643,7 @@ __global__ __launch_bounds__(64) void step_vjp_kernel(const Consts* __restrict__
   constexpr int BS = 64;
   // the rows on their way in and out; the exchange tiles between (forward rows
   // with the screen's, then the reverse's twelve)
-  __shared__ float sh[NSTATE * BS];
+  __shared__ __align__(16) float sh[NSTATE * BS];
   extern __shared__ float rows[];
   const Consts& c = *cp;
   const int tid = threadIdx.x;
@@ -671,7 +677,7 @@ __global__ __launch_bounds__(64) void step_vjp_kernel(const Consts* __restrict__
     if constexpr (N == 8) {
       lane_pair_pass<BS, N, true>(c, tile, sp, live, ls, n, me, tid, (uint32_t)q, t, &resp);
     } else {
-      if (live) put_tile<kScreenSq<N>, true>(tile, tid, sp);
+      if (live) put_tile<N, true>(tile, tid, sp);
       __syncthreads();
       if (live)
         pair_pass<BS, N, PEN_NONE, true>(c, tile, sp, ls, n, me, (uint32_t)q, t, nullptr, nullptr,
@@ -806,7 +812,7 @@ __device__ __forceinline__ void forward_pipe(const Consts& c, const Ptrs& p,
                                              float* __restrict__ pen, float beta) {
   constexpr int BS = 64, NTAPE = kTapeRows<P == PEN_GRAD>;
   constexpr int M = NW ? 1 : 0;     // step of the first substep's motor part
-  __shared__ float sxv[2][PENROW + 1][BS];
+  __shared__ __align__(16) float sxv[2][PENROW + 1][BS];
   __shared__ float4 zring[2][BS];   // motor noise
   __shared__ float ring[2][4][BS];  // T, torques
   __shared__ float r3[2][3][BS];    // third column of R after free flight
@@ -947,7 +953,7 @@ __device__ __forceinline__ void forward_pipe(const Consts& c, const Ptrs& p,
             }
           }
           ev = trans_step(c, pp, s, ring[k_s & 1][0][tid], c2[0], c2[1], c2[2], (uint32_t)q, t);
-          if ((pairs && N != 8) || P != PEN_NONE) put_tile<kScreenSq<N>, true>(tile, tid, s);
+          if ((pairs && N != 8) || P != PEN_NONE) put_tile<N, true>(tile, tid, s);
         }
         if constexpr (N == 8) {
           if (pairs) {
@@ -1057,7 +1063,7 @@ __device__ __forceinline__ void forward_pipe(const Consts& c, const Ptrs& p,
     for (int k_s = 0; k_s < n_steps; ++k_s) {
       if (live) {
         const float(*tile)[BS] = sxv[k_s & 1];
-        const Quad so = tile_quad(tile, tid);
+        const Quad so = tile_quad<N>(tile, tid);
         if constexpr (P == PEN_GRAD) pn.acc[0] = pn.acc[1] = pn.acc[2] = 0.f;
         penalty_pass<BS, N, P>(c, tile, so, ls, n, me, pn);
         if constexpr (P == PEN_GRAD) {
