@@ -92,7 +92,7 @@ void go_recompute(qs_handle* h, const AdjBuffers& sc, const float* ckpt, const f
   }
   hipLaunchKernelGGL((qs::recompute_kernel<BS, N, PEN>), dim3(h->nblk, nseg), dim3(BS), 0, s,
                      h->d_c, ptrs(h), ckpt, act, ncalls, ce, nsub, (unsigned long long)t0, sc.tape,
-                     is_wide(h), gpen, beta);
+                     is_wide(h), use_reverse_pipe(h) && BS == 64, gpen, beta);
 }
 
 template <int BS, int N, bool PEN>

@@ -71,7 +71,8 @@ __device__ __forceinline__ void store_state(float* __restrict__ S, long long ld,
 
 // A tape row, field-major over Q quads: the state at the start of a substep
 // (27 fields, the resting flag as part of a word, below), the motor-noise
-// draws of that substep (4 fields) and, with the penalty, its adjoint w.r.t.
+// draws of that substep (4 fields, for the reverse pipeline only: reverse_kernel
+// draws again) and, with the penalty, its adjoint w.r.t.
 // the position after the motion (3 fields).  The recompute passes over the
 // partners anyway, at twice the reverse sweep's occupancy and bound by the
 // tape's stores, so it is the place for what the partners add; the sweep had
@@ -94,14 +95,6 @@ __device__ __forceinline__ float word_flag(uint32_t w, int me, int wide) {
 }
 __device__ __forceinline__ uint32_t word_resp(uint32_t w, int me, int wide) {
   return wide ? 0u : w & ~(1u << me);
-}
-
-__device__ __forceinline__ void load_draws(const Consts& c, const float* __restrict__ row,
-                                           long long ld, int q, float z[4]) {
-  if (c.flags & F_NOISE) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) z[i] = row[(NSTATE + i) * ld + q];
-  }
 }
 
 __device__ __forceinline__ void load_pen(const float* __restrict__ row, long long ld, int q,
@@ -241,8 +234,8 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(N == 8 && PE
 // partners).  Given the checkpoints the segments are independent, so a chunk
 // is recomputed in one parallel launch.
 //  act: the chunk's first call; ncalls: calls in the chunk; t0: substep
-//  index of the chunk's first substep; wide: see tape_word; gpen: dL/d pen
-//  (PEN).
+//  index of the chunk's first substep; wide: see tape_word; draws: the sweep
+//  reads them from the tape; gpen: dL/d pen (PEN).
 // ---------------------------------------------------------------------------
 template <int BS, int N, bool PEN>
 __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(N == 8 && PEN ? 3 : 4))) void recompute_kernel(const Consts* __restrict__ cp, Ptrs p,
@@ -250,6 +243,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(N == 8 && PE
                                                        const float* __restrict__ act, int ncalls,
                                                        int ce, int nsub, unsigned long long t0,
                                                        float* __restrict__ tape, int wide,
+                                                       int draws,
                                                        const float* __restrict__ gpen,
                                                        float beta) {
   constexpr int P = PEN ? PEN_GRAD : PEN_NONE, NTAPE = kTapeRows<PEN>;
@@ -297,7 +291,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(N == 8 && PE
         store_state<false>(row, Q, q, s);
         float z[4];
         quad_substep<false, Z_EXPORT>(c, pp, s, uhat, (uint32_t)q, t, nullptr, z);
-        if (c.flags & F_NOISE) {
+        if (draws && (c.flags & F_NOISE)) {
 #pragma unroll
           for (int i = 0; i < 4; ++i) row[(NSTATE + i) * Q + q] = z[i];
         }
@@ -518,7 +512,10 @@ __device__ __forceinline__ void reverse_responses(const Consts& c, float (*tile)
 // reverse_kernel: the reverse sweep over the chunk's ncalls nsub substeps,
 // last to first, from the tape; the adjoint of the state stays in
 // registers for the whole chunk and the tape row of the next substep to
-// process is loaded while the current one is differentiated.
+// process is loaded while the current one is differentiated.  It and the
+// recompute wait for the tape's memory more than for their arithmetic, so the
+// motor noise is drawn again instead of being stored and read: 32768 x 32, 100
+// substeps with their derivative, 10.43 -> 9.77 ms.
 //  gin, gout: [Q][27] dL/d(chunk end), dL/d(chunk start) (may be one array);
 //  act/gact: the chunk's first call; gpar: [Q][6]
 //  dL/d(m, ixx, iyy, izz, t2w, tau), accumulated.
@@ -551,7 +548,6 @@ __global__ __launch_bounds__(BS) void reverse_kernel(const Consts* __restrict__ 
   if (live) get_adj(sh + tid * NSTATE, l);
   __syncthreads();
   Quad s, sn;
-  float z[4], zn[4] = {0.f, 0.f, 0.f, 0.f};  // motor-noise draws of s and sn
   float pn[3] = {0.f, 0.f, 0.f}, pen3[3];     // penalty adjoint of sn and s
   QuadPar pp;
   ParAdj pa;
@@ -559,7 +555,6 @@ __global__ __launch_bounds__(BS) void reverse_kernel(const Consts* __restrict__ 
   if (live) {
     load_params(p, c, q, pp, pa);
     load_state(tape + (long long)(n_steps - 1) * NTAPE * Q, Q, q, sn);
-    load_draws(c, tape + (long long)(n_steps - 1) * NTAPE * Q, Q, q, zn);
     if constexpr (PEN) load_pen(tape + (long long)(n_steps - 1) * NTAPE * Q, Q, q, pn);
   }
 
@@ -583,15 +578,14 @@ __global__ __launch_bounds__(BS) void reverse_kernel(const Consts* __restrict__ 
         s.fl = word_flag(word, me, wide);
         cm = word_resp(word, me, wide);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) z[i] = zn[i];
-#pragma unroll
         for (int k = 0; k < 3; ++k) pen3[k] = pn[k];
         if (k_s > 0) {
           const float* row = tape + (long long)(k_s - 1) * NTAPE * Q;
           load_state(row, Q, q, sn);
-          load_draws(c, row, Q, q, zn);
           if constexpr (PEN) load_pen(row, Q, q, pn);
         }
+        float z[4] = {0.f, 0.f, 0.f, 0.f};
+        if (c.flags & F_NOISE) normal4(c, (uint32_t)q, t, STREAM_MOTOR, 0, z);
         quad_substep<true, Z_IMPORT>(c, pp, s, uhat, (uint32_t)q, t, &r, z);
         if constexpr (PEN) {
 #pragma unroll
