@@ -50,8 +50,6 @@ __device__ __forceinline__ void load_state(const float* __restrict__ S, long lon
   s.ev = 0u;
 }
 
-// FLAG: the resting flag too (a tape row has a word of its own there).
-template <bool FLAG = true>
 __device__ __forceinline__ void store_state(float* __restrict__ S, long long ld, int q,
                                             const Quad& s) {
 #pragma unroll
@@ -66,21 +64,108 @@ __device__ __forceinline__ void store_state(float* __restrict__ S, long long ld,
   for (int k = 0; k < 4; ++k) S[(S_U + k) * ld + q] = s.u[k];
 #pragma unroll
   for (int k = 0; k < 4; ++k) S[(S_E + k) * ld + q] = s.e[k];
-  if constexpr (FLAG) S[S_F * ld + q] = s.fl;
+  S[S_F * ld + q] = s.fl;
 }
 
-// A tape row, field-major over Q quads: the state at the start of a substep
-// (27 fields, the resting flag as part of a word, below), the motor-noise
-// draws of that substep (4 fields, for the reverse pipeline only: reverse_kernel
-// draws again) and, with the penalty, its adjoint w.r.t.
-// the position after the motion (3 fields).  The recompute passes over the
-// partners anyway, at twice the reverse sweep's occupancy and bound by the
-// tape's stores, so it is the place for what the partners add; the sweep had
-// passed over them again (32768 x 32, 100 substeps: recompute 3.44 -> 3.82,
+// A tape row: the state at the start of a substep (27 fields, the resting flag
+// as part of a word, below), with the penalty its adjoint w.r.t. the position after
+// the motion (3 fields), and the motor-noise draws of that substep (4 fields, for
+// the reverse pipeline only: reverse_kernel draws again).  The
+// recompute passes over the partners anyway, at twice the reverse sweep's occupancy
+// and bound by the tape's stores, so it is the place for what the partners add; the
+// sweep had passed over them again (32768 x 32, 100 substeps: recompute 3.44 -> 3.82,
 // sweep 5.71 -> 4.16 ms).
+//
+// The quads of a workgroup lie together (kTapeRows words each), in groups of
+// four fields of one quad, so that a substep writes and reads eight kilobytes in a
+// row, 16 bytes a lane.  (Field by field over all quads, every wavefront went
+// to thirty places megabytes apart: the same case 9.77 ms, by workgroup 9.43; the
+// groups of four are equal there, and 2048 swarms of 1 to 16 go from 436 to 432 us.)
 template <bool PEN>
 constexpr int kTapeRows = NSTATE + 4 + (PEN ? 3 : 0);
-constexpr int T_PEN = NSTATE + 4;
+// Fields in groups of four: u, e, R[0..3], R[4..7], R[8] and w, x and v[0]; then
+// the word and the penalty's (PEN), the draws, the pair v[1..2], the word (no PEN).
+template <bool PEN>
+constexpr int T_DRAW = PEN ? 28 : 24;
+template <bool PEN>
+constexpr int T_V12 = T_DRAW<PEN> + 4;
+template <bool PEN>
+constexpr int T_WORD = PEN ? 24 : 30;
+typedef float tape4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef float tape2 __attribute__((ext_vector_type(2), aligned(4)));
+// The quad's group of four, pair or word of the part of a row that holds the
+// workgroup's cnt quads; group: the words of a quad before it.
+template <typename T, typename F>
+__device__ __forceinline__ auto& tape_at(F* part, int group, int cnt, int tid) {
+  using C = typename std::conditional<std::is_const<F>::value, const T, T>::type;
+  return reinterpret_cast<C*>(part + (unsigned)(group * cnt))[(unsigned)tid];
+}
+template <typename F>
+__device__ __forceinline__ auto& tape_four(F* part, int group, int cnt, int tid) {
+  return tape_at<tape4>(part, group, cnt, tid);
+}
+// The word: with the penalty's, the first of its group.
+template <bool PEN, typename F>
+__device__ __forceinline__ auto& tape_word_at(F* part, int cnt, int tid) {
+  return tape_at<float>(part, T_WORD<PEN>, cnt, PEN ? 4 * tid : tid);
+}
+
+// A large batch's tape is past the caches before it is read, and then read once:
+// non-temporal (32768 x 32, 100 substeps: 9.30 -> 9.10 ms; 8192 x 8, 40: 348 -> 341
+// us; 32768 x 8: 982 -> 941; 131072 single quads: 425 -> 408).
+template <typename T>
+__device__ __forceinline__ void tape_put(T& at, T v) {
+  __builtin_nontemporal_store(v, &at);
+}
+template <typename T>
+__device__ __forceinline__ T tape_get(const T& at) {
+  return __builtin_nontemporal_load(&at);
+}
+
+template <bool PEN>
+__device__ __forceinline__ void tape_store_state(float* part, int cnt, int tid, const Quad& s) {
+  tape_put(tape_four(part, 0, cnt, tid), tape4{s.u[0], s.u[1], s.u[2], s.u[3]});
+  tape_put(tape_four(part, 4, cnt, tid), tape4{s.e[0], s.e[1], s.e[2], s.e[3]});
+  tape_put(tape_four(part, 8, cnt, tid), tape4{s.R[0], s.R[1], s.R[2], s.R[3]});
+  tape_put(tape_four(part, 12, cnt, tid), tape4{s.R[4], s.R[5], s.R[6], s.R[7]});
+  tape_put(tape_four(part, 16, cnt, tid), tape4{s.R[8], s.w[0], s.w[1], s.w[2]});
+  tape_put(tape_four(part, 20, cnt, tid), tape4{s.x[0], s.x[1], s.x[2], s.v[0]});
+  tape_put(tape_at<tape2>(part, T_V12<PEN>, cnt, tid), tape2{s.v[1], s.v[2]});
+}
+
+// The state (s.fl: the word) and the penalty's adjoint (PEN).
+template <bool PEN>
+__device__ __forceinline__ void tape_load(const float* part, int cnt, int tid, Quad& s,
+                                          float pen3[3]) {
+  auto four = [&](int group) { return tape_get(tape_four(part, group, cnt, tid)); };
+  const tape4 u = four(0), e = four(4), a = four(8), b = four(12), d = four(16), x = four(20);
+  const tape2 v = tape_get(tape_at<tape2>(part, T_V12<PEN>, cnt, tid));
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    s.u[k] = u[k];
+    s.e[k] = e[k];
+    s.R[k] = a[k];
+    s.R[4 + k] = b[k];
+  }
+  s.R[8] = d[0];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    s.w[k] = d[1 + k];
+    s.x[k] = x[k];
+  }
+  s.v[0] = x[3];
+  s.v[1] = v[0];
+  s.v[2] = v[1];
+  s.ev = 0u;
+  if constexpr (PEN) {
+    const tape4 w = four(T_WORD<PEN>);
+    s.fl = w[0];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) pen3[k] = w[1 + k];
+  } else {
+    s.fl = tape_get(tape_word_at<PEN>(part, cnt, tid));
+  }
+}
 
 // The word in the resting flag's field: the partners whose collision response
 // the quad received in the substep, and, on the quad's own place, the resting
@@ -95,12 +180,6 @@ __device__ __forceinline__ float word_flag(uint32_t w, int me, int wide) {
 }
 __device__ __forceinline__ uint32_t word_resp(uint32_t w, int me, int wide) {
   return wide ? 0u : w & ~(1u << me);
-}
-
-__device__ __forceinline__ void load_pen(const float* __restrict__ row, long long ld, int q,
-                                         float pen3[3]) {
-#pragma unroll
-  for (int k = 0; k < 3; ++k) pen3[k] = row[(T_PEN + k) * ld + q];
 }
 
 __device__ __forceinline__ void load_params(const Ptrs& p, const Consts& c, int q, QuadPar& pp,
@@ -284,17 +363,15 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(N == 8 && PE
     if (live) act_uhat(c, p, a4, uhat);
     for (int sub = 0; sub < nsub; ++sub, ++sidx) {
       const unsigned long long t = t0 + (unsigned long long)sidx;
-      float* row = tape + (long long)sidx * NTAPE * Q;
+      float* row = tape + ((long long)sidx * Q + qb) * NTAPE;
       const float fl0 = s.fl;
       unsigned long long resp = 0ull;
       if (live) {
-        store_state<false>(row, Q, q, s);
+        tape_store_state<PEN>(row, cnt, tid, s);
         float z[4];
         quad_substep<false, Z_EXPORT>(c, pp, s, uhat, (uint32_t)q, t, nullptr, z);
-        if (draws && (c.flags & F_NOISE)) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) row[(NSTATE + i) * Q + q] = z[i];
-        }
+        if (draws && (c.flags & F_NOISE))
+          tape_four(row, T_DRAW<PEN>, cnt, tid) = tape4{z[0], z[1], z[2], z[3]};
       }
       if (pairs) {
         float(*tile)[BS] = sxv[sidx & 1];
@@ -306,14 +383,17 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(N == 8 && PE
           if (live) {
             if constexpr (PEN) pn.acc[0] = pn.acc[1] = pn.acc[2] = 0.f;
             pair_pass<BS, N, P, true>(c, tile, s, ls, n, me, (uint32_t)q, t, &pn, nullptr, &resp);
-            if constexpr (PEN) {
-#pragma unroll
-              for (int k = 0; k < 3; ++k) row[(T_PEN + k) * Q + q] = pn.acc[k];
-            }
           }
         }
       }
-      if (live) row[S_F * Q + q] = tape_word(fl0, resp, me, wide);
+      if (live) {
+        const float word = tape_word(fl0, resp, me, wide);
+        if constexpr (PEN)
+          tape_put(tape_four(row, T_WORD<PEN>, cnt, tid),
+                   tape4{word, pn.acc[0], pn.acc[1], pn.acc[2]});
+        else
+          tape_put(tape_word_at<PEN>(row, cnt, tid), word);
+      }
     }
   }
 }
@@ -554,8 +634,8 @@ __global__ __launch_bounds__(BS) void reverse_kernel(const Consts* __restrict__ 
   const int n_steps = ncalls * nsub;
   if (live) {
     load_params(p, c, q, pp, pa);
-    load_state(tape + (long long)(n_steps - 1) * NTAPE * Q, Q, q, sn);
-    if constexpr (PEN) load_pen(tape + (long long)(n_steps - 1) * NTAPE * Q, Q, q, pn);
+    const float* row = tape + ((long long)(n_steps - 1) * Q + qb) * NTAPE;
+    tape_load<PEN>(row, cnt, tid, sn, pn);
   }
 
   // ---- reverse sweep
@@ -580,9 +660,8 @@ __global__ __launch_bounds__(BS) void reverse_kernel(const Consts* __restrict__ 
 #pragma unroll
         for (int k = 0; k < 3; ++k) pen3[k] = pn[k];
         if (k_s > 0) {
-          const float* row = tape + (long long)(k_s - 1) * NTAPE * Q;
-          load_state(row, Q, q, sn);
-          if constexpr (PEN) load_pen(row, Q, q, pn);
+          const float* row = tape + ((long long)(k_s - 1) * Q + qb) * NTAPE;
+          tape_load<PEN>(row, cnt, tid, sn, pn);
         }
         float z[4] = {0.f, 0.f, 0.f, 0.f};
         if (c.flags & F_NOISE) normal4(c, (uint32_t)q, t, STREAM_MOTOR, 0, z);
@@ -824,15 +903,17 @@ __device__ __forceinline__ void forward_pipe(const Consts& c, const Ptrs& p,
   QuadPar pp;
   ParAdj pa;
   if (live) load_params(p, c, q, pp, pa);
-  // field f of the quad in a row of Q (a 32-bit byte offset from the row:
+  constexpr bool PN = P == PEN_GRAD;
+  // field f of the quad in a checkpoint of rows of Q (a 32-bit byte offset:
   // these batches stay far below 2^32 bytes a row)
   const uint32_t qo = 4u * (uint32_t)q, fo = 4u * (uint32_t)p.Q;
   auto at = [&](float* row, int f) -> float& {
     return *reinterpret_cast<float*>(reinterpret_cast<char*>(row) + (qo + (uint32_t)f * fo));
   };
-  // where the state before substep k goes (uniform), or null
+  // where the state before substep k goes (uniform: the workgroup's part of a tape
+  // row, or a checkpoint), or null
   auto row_of = [&](int k) -> float* {
-    if constexpr (TAPE) return out + (long long)k * NTAPE * Q;
+    if constexpr (TAPE) return out + ((long long)k * Q + qb) * NTAPE;
     const int call = k / nsub;
     if (!out || k != call * nsub || call % every != 0) return nullptr;
     return out + (long long)(call / every) * NSTATE * Q;
@@ -865,7 +946,10 @@ __device__ __forceinline__ void forward_pipe(const Consts& c, const Ptrs& p,
         if (sub == 0 && live) act_uhat(c, p, a4, uhat);
         if (live) {
           float* row = row_of(i);
-          if (row) {
+          if constexpr (TAPE) {
+            tape_four(row, 0, cnt, tid) = tape4{u[0], u[1], u[2], u[3]};
+            tape_four(row, 4, cnt, tid) = tape4{e[0], e[1], e[2], e[3]};
+          } else if (row) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
               at(row, S_U + k) = u[k];
@@ -882,10 +966,8 @@ __device__ __forceinline__ void forward_pipe(const Consts& c, const Ptrs& p,
           }
           const Drive d = motor_step<M == 0 ? Z_DRAW : Z_IMPORT>(
               c, pp, u, e, uhat, (uint32_t)q, t0 + (unsigned long long)i, z, zi);
-          if (TAPE && (c.flags & F_NOISE)) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) at(row, NSTATE + k) = z[k];
-          }
+          if (TAPE && (c.flags & F_NOISE))
+            tape_four(row, T_DRAW<PN>, cnt, tid) = tape4{z[0], z[1], z[2], z[3]};
           float(*slot)[BS] = ring[i & 1];
           slot[0][tid] = d.T;
           slot[1][tid] = d.tx;
@@ -929,13 +1011,16 @@ __device__ __forceinline__ void forward_pipe(const Consts& c, const Ptrs& p,
         unsigned long long resp = 0ull;
         float(*tile)[BS] = sxv[k_s & 1];
         if (live) {
-          if (row) {
+          if constexpr (TAPE) {
+            tape_four(row, 20, cnt, tid) = tape4{s.x[0], s.x[1], s.x[2], s.v[0]};
+            tape_at<tape2>(row, T_V12<PN>, cnt, tid) = tape2{s.v[1], s.v[2]};
+          } else if (row) {
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
               at(row, S_X + k) = s.x[k];
               at(row, S_V + k) = s.v[k];
             }
-            if constexpr (!TAPE) at(row, S_F) = s.fl;
+            at(row, S_F) = s.fl;
           }
           if (k_s > 0) {
             // the events of the substep before decide what became of R
@@ -965,7 +1050,7 @@ __device__ __forceinline__ void forward_pipe(const Consts& c, const Ptrs& p,
           ev |= pev;
         }
         evr[k_s & 1][tid] = ev;
-        if (TAPE && live) at(row, S_F) = tape_word(fl0, resp, me, 0);
+        if (TAPE && live) tape_word_at<PN>(row, cnt, tid) = tape_word(fl0, resp, me, 0);
       }
       wg_sync();
     }
@@ -1005,7 +1090,11 @@ __device__ __forceinline__ void forward_pipe(const Consts& c, const Ptrs& p,
       if (k_s < n_steps && live) {
         if (k_s > 0) answer(k_s - 1);
         float* row = row_of(k_s);
-        if (row) {
+        if constexpr (TAPE) {
+          tape_four(row, 8, cnt, tid) = tape4{R[0], R[1], R[2], R[3]};
+          tape_four(row, 12, cnt, tid) = tape4{R[4], R[5], R[6], R[7]};
+          tape_four(row, 16, cnt, tid) = tape4{R[8], w[0], w[1], w[2]};
+        } else if (row) {
 #pragma unroll
           for (int k = 0; k < 9; ++k) at(row, S_R + k) = R[k];
 #pragma unroll
@@ -1063,7 +1152,8 @@ __device__ __forceinline__ void forward_pipe(const Consts& c, const Ptrs& p,
         if constexpr (P == PEN_GRAD) {
           float* row = row_of(k_s);
 #pragma unroll
-          for (int k = 0; k < 3; ++k) at(row, T_PEN + k) = pn.acc[k];
+          for (int k = 0; k < 3; ++k)
+            tape_at<float>(row, T_WORD<PN>, cnt, 4 * tid + 1 + k) = pn.acc[k];
         }
       }
       wg_sync();
@@ -1174,12 +1264,7 @@ __global__ __launch_bounds__(448) void reverse_pipe_kernel(const Consts* __restr
   float* out = sh + tid * NSTATE;
   move_rows<BS, 448, true>(gin, qb, cnt, sh, threadIdx.x);
   wg_sync();
-  const uint32_t qo = 4u * (uint32_t)q, fo = 4u * (uint32_t)p.Q;
-  auto at = [&](const float* row, int f) -> float {  // (see forward_pipe)
-    return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(row) +
-                                           (qo + (uint32_t)f * fo));
-  };
-  auto row_of = [&](int k) { return tape + (long long)k * NTAPE * Q; };
+  auto row_of = [&](int k) { return tape + ((long long)k * Q + qb) * NTAPE; };
   // the stage's substeps, last to first, each f(k); every wavefront passes
   // the same barriers
   // (with a load of substep k's row AHEAD steps before its f)
@@ -1213,11 +1298,14 @@ __global__ __launch_bounds__(448) void reverse_pipe_kernel(const Consts* __restr
         [&](int k, auto slot) {
           constexpr int D = decltype(slot)::value;
           const float* row = row_of(k);
+          const tape4 u4 = tape_four(row, 0, cnt, tid), e4 = tape_four(row, 4, cnt, tid);
+          tape4 z4 = {0.f, 0.f, 0.f, 0.f};
+          if (c.flags & F_NOISE) z4 = tape_four(row, T_DRAW<PEN>, cnt, tid);
 #pragma unroll
           for (int m = 0; m < 4; ++m) {
-            un4[D][m] = at(row, S_U + m);
-            en[D][m] = at(row, S_E + m);
-            zn[D][m] = (c.flags & F_NOISE) ? at(row, NSTATE + m) : 0.f;
+            un4[D][m] = u4[m];
+            en[D][m] = e4[m];
+            zn[D][m] = z4[m];
           }
         },
         [&](int k, auto slot, auto&& next) {
@@ -1275,13 +1363,18 @@ __global__ __launch_bounds__(448) void reverse_pipe_kernel(const Consts* __restr
         [&](int k, auto slot) {
           constexpr int D = decltype(slot)::value;
           const float* row = row_of(k);
+          const tape4 x4 = tape_four(row, 20, cnt, tid);
+          const tape2 v2 = tape_at<tape2>(row, T_V12<PEN>, cnt, tid);
 #pragma unroll
-          for (int m = 0; m < 3; ++m) {
-            xn[D][m] = at(row, S_X + m);
-            vn[D][m] = at(row, S_V + m);
-            cn[D][m] = at(row, S_R + 3 * m + 2);
-          }
-          fn[D] = at(row, S_F);
+          for (int m = 0; m < 3; ++m) xn[D][m] = x4[m];
+          vn[D][0] = x4[3];
+          vn[D][1] = v2[0];
+          vn[D][2] = v2[1];
+          // R[2], R[5], R[8]
+          cn[D][0] = tape_at<float>(row, 8, cnt, 4 * tid + 2);
+          cn[D][1] = tape_at<float>(row, 12, cnt, 4 * tid + 1);
+          cn[D][2] = tape_at<float>(row, 16, cnt, 4 * tid);
+          fn[D] = tape_word_at<PEN>(row, cnt, tid);
         },
         [&](int k, auto slot, auto&& next) {
           constexpr int D = decltype(slot)::value;
@@ -1315,10 +1408,16 @@ __global__ __launch_bounds__(448) void reverse_pipe_kernel(const Consts* __restr
     auto load = [&](int k, auto slot) {
       constexpr int D = decltype(slot)::value;
       const float* row = row_of(k);
+      const tape4 a = tape_four(row, 8, cnt, tid), b = tape_four(row, 12, cnt, tid),
+                  d = tape_four(row, 16, cnt, tid);
 #pragma unroll
-      for (int m = 0; m < 9; ++m) Rn[D][m] = at(row, S_R + m);
+      for (int m = 0; m < 4; ++m) {
+        Rn[D][m] = a[m];
+        Rn[D][4 + m] = b[m];
+      }
+      Rn[D][8] = d[0];
 #pragma unroll
-      for (int m = 0; m < 3; ++m) wn[D][m] = at(row, S_W + m);
+      for (int m = 0; m < 3; ++m) wn[D][m] = d[1 + m];
     };
     loading_stages(2, load, [&](int k, auto slot, auto&& next) {
       constexpr int D = decltype(slot)::value;
@@ -1355,10 +1454,14 @@ __global__ __launch_bounds__(448) void reverse_pipe_kernel(const Consts* __restr
     }
     auto load = [&](int k, auto slot) {
       constexpr int D = decltype(slot)::value;
-      wn[D] = at(row_of(k), S_F);
+      const float* row = row_of(k);
       if constexpr (PEN) {
+        const tape4 w4 = tape_four(row, T_WORD<PEN>, cnt, tid);
+        wn[D] = w4[0];
 #pragma unroll
-        for (int m = 0; m < 3; ++m) pn[D][m] = at(row_of(k), T_PEN + m);
+        for (int m = 0; m < 3; ++m) pn[D][m] = w4[1 + m];
+      } else {
+        wn[D] = tape_word_at<PEN>(row, cnt, tid);
       }
     };
     loading_stages(3, load, [&](int k, auto slot, auto&& next) {
