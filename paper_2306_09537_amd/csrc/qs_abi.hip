@@ -428,23 +428,23 @@ int qs_create(const qs_desc* desc, const qs_quad_params* h_params, const float* 
     h->uniform_n = uni ? n0 : 0;
   }
 
-  // derived per-quad parameters and SoA state
+  // derived per-quad parameters and the state, in tiles
   std::vector<float> par((size_t)qs::NPARAM * h->Qp, 1.0f);
   std::vector<float> st((size_t)qs::NSTATE * h->Qp, 0.0f);
   for (int q = 0; q < Q; ++q) {
     const qs_quad_params& p = h_params[q];
-    par[(size_t)qs::P_M * h->Qp + q] = p.mass;
-    par[(size_t)qs::P_JX * h->Qp + q] = p.ixx;
-    par[(size_t)qs::P_JY * h->Qp + q] = p.iyy;
-    par[(size_t)qs::P_JZ * h->Qp + q] = p.izz;
-    par[(size_t)qs::P_FMAX * h->Qp + q] =
+    par[qs::par_index(q, qs::P_M)] = p.mass;
+    par[qs::par_index(q, qs::P_JX)] = p.ixx;
+    par[qs::par_index(q, qs::P_JY)] = p.iyy;
+    par[qs::par_index(q, qs::P_JZ)] = p.izz;
+    par[qs::par_index(q, qs::P_FMAX)] =
         (float)(0.25 * (double)p.mass * (double)desc->gravity * (double)p.thrust_to_weight);
-    par[(size_t)qs::P_ALAG * h->Qp + q] =
+    par[qs::par_index(q, qs::P_ALAG)] =
         (float)(1.0 - std::exp(-(double)desc->dt / (double)p.motor_tau));
-    par[(size_t)qs::P_T2W * h->Qp + q] = p.thrust_to_weight;
-    par[(size_t)qs::P_TAU * h->Qp + q] = p.motor_tau;
+    par[qs::par_index(q, qs::P_T2W)] = p.thrust_to_weight;
+    par[qs::par_index(q, qs::P_TAU)] = p.motor_tau;
     for (int f = 0; f < qs::NSTATE; ++f)
-      st[(size_t)f * h->Qp + q] = h_state0[(size_t)q * QS_STATE_DIM + f];
+      st[qs::st_index(q, f)] = h_state0[(size_t)q * QS_STATE_DIM + f];
   }
 
   rc = QS_OK;
@@ -713,7 +713,7 @@ int qs_get_state(qs_handle* h, float* d_state, uint64_t* substep_index, void* st
   if (!aligned(d_state, 4)) return QS_ERR_ALIGN;
   if (hipSetDevice(h->dev) != hipSuccess) return QS_ERR_HIP;
   hipLaunchKernelGGL(qs::get_state_kernel, dim3(h->Qp / qs::IO_QUADS), dim3(qs::IO_THREADS), 0,
-                     (hipStream_t)stream, h->d_st, h->Qp, h->Q, d_state);
+                     (hipStream_t)stream, h->d_st, h->Q, d_state);
   if (hipGetLastError() != hipSuccess) return QS_ERR_HIP;
   if (substep_index) *substep_index = h->t;
   return QS_OK;
@@ -725,7 +725,7 @@ int qs_set_state(qs_handle* h, const float* d_state, uint64_t substep_index,
   if (!aligned(d_state, 4)) return QS_ERR_ALIGN;
   if (hipSetDevice(h->dev) != hipSuccess) return QS_ERR_HIP;
   hipLaunchKernelGGL(qs::set_state_kernel, dim3(h->Qp / qs::IO_QUADS), dim3(qs::IO_THREADS), 0,
-                     (hipStream_t)stream, h->d_st, h->Qp, h->Q, d_state, h->d_qenv, d_env_mask);
+                     (hipStream_t)stream, h->d_st, h->Q, d_state, h->d_qenv, d_env_mask);
   if (hipGetLastError() != hipSuccess) return QS_ERR_HIP;
   h->t = substep_index;
   if (h->graph_mode)
@@ -773,7 +773,7 @@ int qs_set_params(qs_handle* h, const float* d_params, const uint8_t* d_env_mask
   if (hipSetDevice(h->dev) != hipSuccess) return QS_ERR_HIP;
   const int tb = 256;
   hipLaunchKernelGGL(qs::set_params_kernel, dim3((unsigned)((h->Q + tb - 1) / tb)), dim3(tb), 0,
-                     (hipStream_t)stream, h->d_par, h->Qp, h->Q, d_params, h->d_qenv, d_env_mask,
+                     (hipStream_t)stream, h->d_par, h->Q, d_params, h->d_qenv, d_env_mask,
                      h->c.dt, h->c.g, h->d_err);
   return hipGetLastError() == hipSuccess ? QS_OK : QS_ERR_HIP;
 }

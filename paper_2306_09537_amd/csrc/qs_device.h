@@ -22,10 +22,37 @@ enum : int { NSTATE = 27, NPARAM = 8 };
 // clang vector types, for the non-temporal store builtin
 typedef float v2f __attribute__((ext_vector_type(2)));
 typedef float v4f __attribute__((ext_vector_type(4)));
-// SoA field index of the private state: x3 v3 R9 (row-major) w3 u4 eps4 floor
+// field index of a quad's state: x3 v3 R9 (row-major) w3 u4 eps4 floor
 enum : int { S_X = 0, S_V = 3, S_R = 6, S_W = 15, S_U = 18, S_E = 22, S_F = 26 };
-// SoA field index of the per-quad parameters (the forward reads the first six)
+// index of the per-quad parameters (the forward reads the first six)
 enum : int { P_M = 0, P_JX = 1, P_JY = 2, P_JZ = 3, P_FMAX = 4, P_ALAG = 5, P_T2W = 6, P_TAU = 7 };
+// The handle's arrays hold the quads in tiles of 64, a quad's words in groups of
+// four (16 bytes a lane, a tile's state 6912 bytes in a row): u, e, R[0..3],
+// R[4..7], R[8] and w, x and v[0], then v[1], v[2] and the flag; the parameters in
+// two groups.  Field by field over all quads a wavefront went to 33 places
+// megabytes apart, and a small swarm to a part of a cache line at each.  us a call
+// of one substep: 32768 x 32 108 -> 96 and 1,048,576 single quads 71 -> 68 on two
+// handles in turn, 84 -> 84 and 53 -> 53 on one, whose arrays stay in the
+// memory-side cache; 2,097,152 quads in swarms of 1, 8, 32 and 12: 123 -> 114,
+// 195 -> 170, 202 -> 173, 272 -> 203.
+constexpr int TILE_QUADS = 64;
+constexpr int ST_U = 0, ST_E = 4 * 64, ST_R0 = 8 * 64, ST_R4 = 12 * 64, ST_R8W = 16 * 64,
+              ST_XV = 20 * 64, ST_VF = 24 * 64;  // words before a group in the tile
+__host__ __device__ constexpr int st_place(int f) {  // of field f in the order above
+  return f < S_R ? f + 20 : f < S_U ? f + 2 : f < S_F ? f - 18 : 26;
+}
+__host__ __device__ constexpr int st_field(int place) {  // its inverse
+  return place < 8 ? place + 18 : place < 20 ? place - 2 : place < 26 ? place - 20 : 26;
+}
+__host__ __device__ inline size_t st_index(int q, int f) {
+  const int place = st_place(f), lane = q & 63;
+  return (size_t)(q >> 6) * (NSTATE * TILE_QUADS) +
+         (place < 24 ? (place & ~3) * TILE_QUADS + 4 * lane + (place & 3)
+                     : ST_VF + 3 * lane + place - 24);
+}
+__host__ __device__ inline size_t par_index(int q, int k) {
+  return (size_t)(q >> 6) * (NPARAM * TILE_QUADS) + (k & ~3) * TILE_QUADS + 4 * (q & 63) + (k & 3);
+}
 // noise streams: fourth Philox counter word = stream << 8 | draw
 enum : uint32_t {
   STREAM_MOTOR = 0, STREAM_WALL = 1, STREAM_PAIR = 2, STREAM_DOWNWASH = 3, STREAM_SENSOR = 4
@@ -53,17 +80,32 @@ struct Consts {
 };
 
 struct Ptrs {
-  float* st;                    // [27][Qp] private SoA state
-  const float* par;             // [8][Qp] m, jx, jy, jz, f_max, alpha_lag, t2w, tau
+  float* st;                    // private state, tiles of 64 quads (st_index)
+  const float* par;             // the quads' parameters, the same (par_index)
   const uint32_t* sw;           // [Qp] (env start within the block << 8) | n_e
   const int2* blk;              // [nblk] (first quad, quad count)
   unsigned long long* contacts; // [Qp] or nullptr
   int* err;                     // sticky error bits
-  int Qp;                       // padded quad count (SoA field stride)
+  int Qp;                       // quad count padded to whole tiles
   int Q;                        // quad count
   const int4* items;            // uneven sizes: (slot size, first env entry, swarms, -)
   const int2* item_envs;        // uneven sizes: (first quad, size) per swarm of an item
 };
+
+// The tile words of quad q, and its group of four at word g of the tile.
+__device__ __forceinline__ const float* st_tile(const float* st, int q) {
+  return st + (size_t)(q >> 6) * (NSTATE * TILE_QUADS);
+}
+__device__ __forceinline__ float* st_tile(float* st, int q) {
+  return st + (size_t)(q >> 6) * (NSTATE * TILE_QUADS);
+}
+__device__ __forceinline__ v4f tile_four(const float* tile, int g, int q) {
+  return reinterpret_cast<const v4f*>(tile + g)[q & 63];
+}
+__device__ __forceinline__ void put_tile_four(float* tile, int g, int q, float a, float b, float c,
+                                              float d) {
+  reinterpret_cast<v4f*>(tile + g)[q & 63] = v4f{a, b, c, d};
+}
 
 // Philox4x32-10, Salmon et al. SC'11: ten rounds of two 32x32->64 products
 // with a Weyl-sequence key schedule.
@@ -126,6 +168,19 @@ struct Quad {
 struct QuadPar {
   float m, inv_m, jx, jy, jz, ijx, ijy, ijz, f_max, a_lag, a_ns;
 };
+
+// The parameters that the forward substep reads, as they are held.
+__device__ __forceinline__ void load_forward_params(const Ptrs& p, int q, QuadPar& pp) {
+  const float* t = p.par + (size_t)(q >> 6) * (NPARAM * TILE_QUADS) + 4 * (q & 63);
+  const v4f a = *reinterpret_cast<const v4f*>(t);
+  const v2f b = *reinterpret_cast<const v2f*>(t + 4 * TILE_QUADS);
+  pp.m = a[0];
+  pp.jx = a[1];
+  pp.jy = a[2];
+  pp.jz = a[3];
+  pp.f_max = b[0];
+  pp.a_lag = b[1];
+}
 
 // Median of three unsigned words (one v_med3_u32).
 __device__ __forceinline__ uint32_t umed3(uint32_t a, uint32_t b, uint32_t c) {

@@ -16,11 +16,11 @@ __global__ void set_counter_kernel(unsigned long long* tdev, unsigned int* done,
 }
 
 // Per-quad parameters [Q][6] (mass, ixx, iyy, izz, thrust-to-weight, tau_m)
-// -> private SoA, for environments selected by env_mask, with f_max and
+// -> the handle's array, for environments selected by env_mask, with f_max and
 // alpha_lag derived in double and rounded once (as at creation).  A row
 // with a non-finite or non-positive entry is left as it was and raises the
 // sticky parameter error bit.
-__global__ void set_params_kernel(float* __restrict__ par, int Qp, int Q,
+__global__ void set_params_kernel(float* __restrict__ par, int Q,
                                   const float* __restrict__ src,
                                   const int32_t* __restrict__ qenv,
                                   const uint8_t* __restrict__ env_mask, float dt, float g,
@@ -39,14 +39,11 @@ __global__ void set_params_kernel(float* __restrict__ par, int Qp, int Q,
     __hip_atomic_fetch_or(err, ERRBIT_PARAM, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return;
   }
-  par[(size_t)P_M * Qp + q] = v[0];
-  par[(size_t)P_JX * Qp + q] = v[1];
-  par[(size_t)P_JY * Qp + q] = v[2];
-  par[(size_t)P_JZ * Qp + q] = v[3];
-  par[(size_t)P_FMAX * Qp + q] = (float)(0.25 * (double)v[0] * (double)g * (double)v[4]);
-  par[(size_t)P_ALAG * Qp + q] = (float)(1.0 - exp(-(double)dt / (double)v[5]));
-  par[(size_t)P_T2W * Qp + q] = v[4];
-  par[(size_t)P_TAU * Qp + q] = v[5];
+  static_assert(P_JZ == 3 && P_FMAX == 4 && P_TAU == 7, "two groups of four");
+  *reinterpret_cast<v4f*>(par + par_index(q, P_M)) = v4f{v[0], v[1], v[2], v[3]};
+  *reinterpret_cast<v4f*>(par + par_index(q, P_FMAX)) =
+      v4f{(float)(0.25 * (double)v[0] * (double)g * (double)v[4]),
+          (float)(1.0 - exp(-(double)dt / (double)v[5])), v[4], v[5]};
 }
 
 // The library's counter-based generator, exported for tests: for quads
@@ -76,14 +73,14 @@ __global__ void philox_debug_kernel(uint32_t key0, uint32_t key1, uint32_t strea
   }
 }
 
-// Row-major [Q][27] <-> field-major [27][ld] in tiles of 64 quads: the rows of
+// Row-major [Q][27] <-> the handle's tiles of 64 quads: the rows of
 // a tile are one contiguous run, moved 16 bytes a lane where the caller's
-// buffer allows it, the fields are runs of 64 words, and the turn happens in
+// buffer allows it, as are the tile's groups, and the turn happens in
 // LDS (a row stride of 27 words is odd, so neither side meets a bank
 // conflict).  Bound by HBM; reading or writing the field-major side word by
 // word in row order touched 27 lines per wavefront access (1,048,576 quads,
 // 226 MB: state in 181 -> 36 us, state out 104 -> 45 us).
-constexpr int IO_QUADS = 64, IO_THREADS = 256;
+constexpr int IO_QUADS = TILE_QUADS, IO_THREADS = 256;
 
 // Rows [q0, q0 + cnt) of src -> t.
 __device__ __forceinline__ void load_rows(const float* __restrict__ src, int q0, int cnt,
@@ -100,9 +97,9 @@ __device__ __forceinline__ void load_rows(const float* __restrict__ src, int q0,
   for (int i = i0 + threadIdx.x; i < total; i += IO_THREADS) t[i] = run[i];
 }
 
-// Canonical [Q][27] -> private SoA, for environments selected by env_mask.
+// Canonical [Q][27] -> the handle's tiles, for environments selected by env_mask.
 __global__ __launch_bounds__(IO_THREADS) void set_state_kernel(
-    float* __restrict__ st, int Qp, int Q, const float* __restrict__ src,
+    float* __restrict__ st, int Q, const float* __restrict__ src,
     const int32_t* __restrict__ qenv, const uint8_t* __restrict__ env_mask) {
   __shared__ __align__(16) float t[IO_QUADS * NSTATE];
   const int q0 = blockIdx.x * IO_QUADS, cnt = min(IO_QUADS, Q - q0);
@@ -120,21 +117,46 @@ __global__ __launch_bounds__(IO_THREADS) void set_state_kernel(
   }
   __syncthreads();
   if (!mine) return;
-  for (int f = threadIdx.x >> 6; f < NSTATE; f += IO_THREADS / 64)
-    st[(size_t)f * Qp + q0 + lane] = t[lane * NSTATE + f];
+  float* tile = st_tile(st, q0);
+  const float* row = t + lane * NSTATE;
+  const int g = threadIdx.x >> 6;  // the wavefront's first group; its second is g + 4
+  auto put = [&](int g) {
+    put_tile_four(tile, g * 4 * TILE_QUADS, lane, row[st_field(4 * g)], row[st_field(4 * g + 1)],
+                  row[st_field(4 * g + 2)], row[st_field(4 * g + 3)]);
+  };
+  put(g);
+  if (g < 2) {
+    put(g + 4);
+  } else if (g == 2) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) tile[ST_VF + 3 * lane + k] = row[st_field(24 + k)];
+  }
 }
 
-// Private SoA -> canonical [Q][27].
+// The handle's tiles -> canonical [Q][27].
 __global__ __launch_bounds__(IO_THREADS) void get_state_kernel(const float* __restrict__ st,
-                                                               int Qp, int Q,
+                                                               int Q,
                                                                float* __restrict__ dst) {
   __shared__ __align__(16) float t[IO_QUADS * NSTATE];
   const int q0 = blockIdx.x * IO_QUADS, cnt = min(IO_QUADS, Q - q0);
   const int lane = threadIdx.x & 63;
   // (the private arrays are padded to whole tiles)
+  const float* tile = st_tile(st, q0);
+  float* row = t + lane * NSTATE;
+  const int g = threadIdx.x >> 6;  // the wavefront's first group; its second is g + 4
+  const v4f a = tile_four(tile, g * 4 * TILE_QUADS, lane);
+  if (g < 2) {
+    const v4f b = tile_four(tile, (g + 4) * 4 * TILE_QUADS, lane);
 #pragma unroll
-  for (int f = threadIdx.x >> 6; f < NSTATE; f += IO_THREADS / 64)
-    t[lane * NSTATE + f] = st[(size_t)f * Qp + q0 + lane];
+    for (int k = 0; k < 4; ++k) row[st_field(4 * g + 16 + k)] = b[k];
+  } else if (g == 2) {
+    const float* vf = tile + ST_VF + 3 * lane;
+    const float b[3] = {vf[0], vf[1], vf[2]};
+#pragma unroll
+    for (int k = 0; k < 3; ++k) row[st_field(24 + k)] = b[k];
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) row[st_field(4 * g + k)] = a[k];
   __syncthreads();
   float* run = dst + (size_t)q0 * NSTATE;
   const int total = cnt * NSTATE;

@@ -152,16 +152,6 @@ __device__ __forceinline__ void step_body(const Consts& c, const Ptrs& p,
     }
   }
   const int me = tid - ls;  // index within the swarm
-  const int Qp = p.Qp;
-  const float* __restrict__ S = p.st;
-  // field f of quad q: a uniform field base plus the quad's 32-bit byte
-  // offset (one address add per access instead of an index multiply,
-  // sign extension and shift)
-  const uint32_t qo = 4u * (uint32_t)q;
-  auto at = [&](const float* base, int f) -> const float& {
-    return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(base + (size_t)f * Qp) + qo);
-  };
-
   Quad s;
   s.ev = 0u;
   QuadPar pp;
@@ -177,30 +167,37 @@ __device__ __forceinline__ void step_body(const Consts& c, const Ptrs& p,
     g2 = goals[3 * q + 2];
   }
   if (live) {
+    const float* S = st_tile(p.st, q);
     if constexpr (ROLE != 0) {
+      const v4f a = tile_four(S, ST_R0, q), b = tile_four(S, ST_R4, q), w = tile_four(S, ST_R8W, q),
+                x = tile_four(S, ST_XV, q);
+      const float* vf = S + ST_VF + 3 * (q & 63);
 #pragma unroll
-      for (int k = 0; k < 3; ++k) s.x[k] = at(S, S_X + k);
+      for (int k = 0; k < 4; ++k) {
+        s.R[k] = a[k];
+        s.R[4 + k] = b[k];
+      }
+      s.R[8] = w[0];
 #pragma unroll
-      for (int k = 0; k < 3; ++k) s.v[k] = at(S, S_V + k);
-#pragma unroll
-      for (int k = 0; k < 9; ++k) s.R[k] = at(S, S_R + k);
-#pragma unroll
-      for (int k = 0; k < 3; ++k) s.w[k] = at(S, S_W + k);
+      for (int k = 0; k < 3; ++k) {
+        s.w[k] = w[1 + k];
+        s.x[k] = x[k];
+      }
+      s.v[0] = x[3];
+      s.v[1] = vf[0];
+      s.v[2] = vf[1];
+      s.fl = vf[2];
     }
     if (nsub > 0) {
       if constexpr (ROLE != 1) {
+        const v4f u = tile_four(S, ST_U, q), e = tile_four(S, ST_E, q);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) s.u[k] = at(S, S_U + k);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) s.e[k] = at(S, S_E + k);
+        for (int k = 0; k < 4; ++k) {
+          s.u[k] = u[k];
+          s.e[k] = e[k];
+        }
       }
-      if constexpr (ROLE != 0) s.fl = at(S, S_F);
-      pp.m = at(p.par, P_M);
-      pp.jx = at(p.par, P_JX);
-      pp.jy = at(p.par, P_JY);
-      pp.jz = at(p.par, P_JZ);
-      pp.f_max = at(p.par, P_FMAX);
-      pp.a_lag = at(p.par, P_ALAG);
+      load_forward_params(p, q, pp);
     }
   }
   // the call's action, loaded by every lane without a branch (an idle lane's
@@ -323,28 +320,34 @@ __device__ __forceinline__ void step_body(const Consts& c, const Ptrs& p,
   // stores (loads and stores share one in-order counter).
   __builtin_amdgcn_s_waitcnt(0);
   if (live && nsub > 0) {
-    float* St = p.st;
-    auto to = [&](int f) -> float& {
-      return *reinterpret_cast<float*>(reinterpret_cast<char*>(St + (size_t)f * Qp) + qo);
-    };
+    float* S = st_tile(p.st, q);
     float chk = 0.f;
     if constexpr (ROLE != 0) {
+      put_tile_four(S, ST_R0, q, s.R[0], s.R[1], s.R[2], s.R[3]);
+      put_tile_four(S, ST_R4, q, s.R[4], s.R[5], s.R[6], s.R[7]);
+      put_tile_four(S, ST_R8W, q, s.R[8], s.w[0], s.w[1], s.w[2]);
+      put_tile_four(S, ST_XV, q, s.x[0], s.x[1], s.x[2], s.v[0]);
+      float* vf = S + ST_VF + 3 * (q & 63);
+      vf[0] = s.v[1];
+      vf[1] = s.v[2];
+      vf[2] = s.fl;
 #pragma unroll
-      for (int k = 0; k < 3; ++k) { to(S_X + k) = s.x[k]; chk += s.x[k]; }
+      for (int k = 0; k < 3; ++k) chk += s.x[k];
 #pragma unroll
-      for (int k = 0; k < 3; ++k) { to(S_V + k) = s.v[k]; chk += s.v[k]; }
+      for (int k = 0; k < 3; ++k) chk += s.v[k];
 #pragma unroll
-      for (int k = 0; k < 9; ++k) { to(S_R + k) = s.R[k]; chk += s.R[k]; }
+      for (int k = 0; k < 9; ++k) chk += s.R[k];
 #pragma unroll
-      for (int k = 0; k < 3; ++k) { to(S_W + k) = s.w[k]; chk += s.w[k]; }
+      for (int k = 0; k < 3; ++k) chk += s.w[k];
     }
     if constexpr (ROLE != 1) {
+      put_tile_four(S, ST_U, q, s.u[0], s.u[1], s.u[2], s.u[3]);
+      put_tile_four(S, ST_E, q, s.e[0], s.e[1], s.e[2], s.e[3]);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) { to(S_U + k) = s.u[k]; chk += s.u[k]; }
+      for (int k = 0; k < 4; ++k) chk += s.u[k];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) { to(S_E + k) = s.e[k]; chk += s.e[k]; }
+      for (int k = 0; k < 4; ++k) chk += s.e[k];
     }
-    if constexpr (ROLE != 0) to(S_F) = s.fl;
     if (!isfinite(chk))
       __hip_atomic_fetch_or(p.err, ERRBIT_STATE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (ROLE != 0 && p.contacts) p.contacts[q] = cmask;

@@ -67,6 +67,20 @@ __device__ __forceinline__ void store_state(float* __restrict__ S, long long ld,
   S[S_F * ld + q] = s.fl;
 }
 
+// The same in the handle's tiles.
+__device__ __forceinline__ void load_handle_state(const float* __restrict__ st, int q, Quad& s) {
+  float f[NSTATE];
+#pragma unroll
+  for (int k = 0; k < NSTATE; ++k) f[k] = st[st_index(q, k)];
+  load_state(f, 1, 0, s);
+}
+__device__ __forceinline__ void store_handle_state(float* __restrict__ st, int q, const Quad& s) {
+  float f[NSTATE];
+  store_state(f, 1, 0, s);
+#pragma unroll
+  for (int k = 0; k < NSTATE; ++k) st[st_index(q, k)] = f[k];
+}
+
 // A tape row: the state at the start of a substep (27 fields, the resting flag
 // as part of a word, below), with the penalty its adjoint w.r.t. the position after
 // the motion (3 fields), and the motor-noise draws of that substep (4 fields, for
@@ -184,21 +198,15 @@ __device__ __forceinline__ uint32_t word_resp(uint32_t w, int me, int wide) {
 
 __device__ __forceinline__ void load_params(const Ptrs& p, const Consts& c, int q, QuadPar& pp,
                                             ParAdj& pa) {
-  const int Qp = p.Qp;
-  pp.m = p.par[P_M * Qp + q];
-  pp.jx = p.par[P_JX * Qp + q];
-  pp.jy = p.par[P_JY * Qp + q];
-  pp.jz = p.par[P_JZ * Qp + q];
-  pp.f_max = p.par[P_FMAX * Qp + q];
-  pp.a_lag = p.par[P_ALAG * Qp + q];
+  load_forward_params(p, q, pp);
   pp.inv_m = 1.0f / pp.m;
   pp.ijx = 1.0f / pp.jx;
   pp.ijy = 1.0f / pp.jy;
   pp.ijz = 1.0f / pp.jz;
   pp.a_ns = c.ns_scale * pp.f_max;
   pa.m = pp.m;
-  pa.t2w = p.par[P_T2W * Qp + q];
-  const float tau = p.par[P_TAU * Qp + q];
+  pa.t2w = p.par[par_index(q, P_T2W)];
+  const float tau = p.par[par_index(q, P_TAU)];
   pa.dlag_dtau = -(1.0f - pp.a_lag) * c.dt / (tau * tau);
 }
 
@@ -257,7 +265,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(N == 8 && PE
   QuadPar pp;
   ParAdj pa;
   if (live) {
-    load_state(p.st, p.Qp, q, s);
+    load_handle_state(p.st, q, s);
     load_params(p, c, q, pp, pa);
   }
   const bool pairs = N != 1 && ((c.flags & (F_COLLIDE | F_DOWNWASH)) != 0 || PEN);
@@ -290,7 +298,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(N == 8 && PE
     }
   }
   if (live) {
-    store_state(p.st, p.Qp, q, s);
+    store_handle_state(p.st, q, s);
     float chk = 0.f;
 #pragma unroll
     for (int k = 0; k < 3; ++k) chk += s.x[k] + s.v[k] + s.w[k];
@@ -843,7 +851,7 @@ __global__ __launch_bounds__(64) void step_vjp_kernel(const Consts* __restrict__
 // the one-wavefront kernels, so identical results.  With noise and motor, and
 // translation and rotation, on one wavefront each and loads one substep ahead:
 // 1024 x 8, 200 substeps, forward 222 us, now 185.
-//  S, ld: the start state; act: its first call; t0: its first substep.
+//  S: the start state (TAPE: a checkpoint; else the handle's); act: its first call; t0: its first substep.
 // ---------------------------------------------------------------------------
 // Loads whose address is known go out AHEAD substeps before their use: a
 // substep of these pipelines is shorter than a read from HBM, which had set
@@ -878,7 +886,7 @@ constexpr int kPipeWaves = 3 + (P != PEN_NONE ? 1 : 0) + (NW ? 1 : 0);
 
 template <int N, int P, bool TAPE, bool NW>
 __device__ __forceinline__ void forward_pipe(const Consts& c, const Ptrs& p,
-                                             const float* __restrict__ S, long long ld,
+                                             const float* __restrict__ S,
                                              const float* __restrict__ act, int nc, int nsub,
                                              unsigned long long t0, float* __restrict__ out,
                                              int every, const float* __restrict__ gpen,
@@ -910,6 +918,11 @@ __device__ __forceinline__ void forward_pipe(const Consts& c, const Ptrs& p,
   auto at = [&](float* row, int f) -> float& {
     return *reinterpret_cast<float*>(reinterpret_cast<char*>(row) + (qo + (uint32_t)f * fo));
   };
+  // field f of the state to start from: a checkpoint, or the handle's
+  auto start = [&](int f) -> float {
+    if constexpr (TAPE) return S[(long long)f * Q + q];
+    else return S[st_index(q, f)];
+  };
   // where the state before substep k goes (uniform: the workgroup's part of a tape
   // row, or a checkpoint), or null
   auto row_of = [&](int k) -> float* {
@@ -925,8 +938,8 @@ __device__ __forceinline__ void forward_pipe(const Consts& c, const Ptrs& p,
     if (live) {
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        u[k] = S[(S_U + k) * ld + q];
-        e[k] = S[(S_E + k) * ld + q];
+        u[k] = start(S_U + k);
+        e[k] = start(S_E + k);
       }
     }
     float uhat[4] = {0.f, 0.f, 0.f, 0.f};
@@ -982,8 +995,8 @@ __device__ __forceinline__ void forward_pipe(const Consts& c, const Ptrs& p,
     if (!TAPE && live) {
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        p.st[(S_U + k) * p.Qp + q] = u[k];
-        p.st[(S_E + k) * p.Qp + q] = e[k];
+        p.st[st_index(q, S_U + k)] = u[k];
+        p.st[st_index(q, S_E + k)] = e[k];
       }
     }
   } else if (wave == 1) {
@@ -995,11 +1008,11 @@ __device__ __forceinline__ void forward_pipe(const Consts& c, const Ptrs& p,
     if (live) {
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
-        s.x[k] = S[(S_X + k) * ld + q];
-        s.v[k] = S[(S_V + k) * ld + q];
-        c2[k] = S[(S_R + 3 * k + 2) * ld + q];
+        s.x[k] = start(S_X + k);
+        s.v[k] = start(S_V + k);
+        c2[k] = start(S_R + 3 * k + 2);
       }
-      s.fl = S[S_F * ld + q];
+      s.fl = start(S_F);
     }
     const bool pairs = N != 1 && (c.flags & (F_COLLIDE | F_DOWNWASH)) != 0;
     for (int i = 0; i < M + 1; ++i) wg_sync();  // no thrust yet
@@ -1057,10 +1070,10 @@ __device__ __forceinline__ void forward_pipe(const Consts& c, const Ptrs& p,
     if (!TAPE && live) {
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
-        p.st[(S_X + k) * p.Qp + q] = s.x[k];
-        p.st[(S_V + k) * p.Qp + q] = s.v[k];
+        p.st[st_index(q, S_X + k)] = s.x[k];
+        p.st[st_index(q, S_V + k)] = s.v[k];
       }
-      p.st[S_F * p.Qp + q] = s.fl;
+      p.st[st_index(q, S_F)] = s.fl;
       float chk = 0.f;
 #pragma unroll
       for (int k = 0; k < 3; ++k) chk += s.x[k] + s.v[k];
@@ -1072,9 +1085,9 @@ __device__ __forceinline__ void forward_pipe(const Consts& c, const Ptrs& p,
     float R[9], w[3], R0[9];
     if (live) {
 #pragma unroll
-      for (int k = 0; k < 9; ++k) R[k] = R0[k] = S[(S_R + k) * ld + q];
+      for (int k = 0; k < 9; ++k) R[k] = R0[k] = start(S_R + k);
 #pragma unroll
-      for (int k = 0; k < 3; ++k) w[k] = S[(S_W + k) * ld + q];
+      for (int k = 0; k < 3; ++k) w[k] = start(S_W + k);
     }
     // the events of substep k, which started from R0
     auto answer = [&](int k) {
@@ -1112,9 +1125,9 @@ __device__ __forceinline__ void forward_pipe(const Consts& c, const Ptrs& p,
     if (!TAPE && live) {
       if (n_steps > 0) answer(n_steps - 1);
 #pragma unroll
-      for (int k = 0; k < 9; ++k) p.st[(S_R + k) * p.Qp + q] = R[k];
+      for (int k = 0; k < 9; ++k) p.st[st_index(q, S_R + k)] = R[k];
 #pragma unroll
-      for (int k = 0; k < 3; ++k) p.st[(S_W + k) * p.Qp + q] = w[k];
+      for (int k = 0; k < 3; ++k) p.st[st_index(q, S_W + k)] = w[k];
       float chk = 0.f;
 #pragma unroll
       for (int k = 0; k < 9; ++k) chk += R[k];
@@ -1171,7 +1184,7 @@ __global__ __launch_bounds__(NW ? 320 : 256) void rollout_pipe_kernel(const Cons
                                                            int ckpt_every,
                                                            float* __restrict__ pen, float beta) {
   const Consts c = *cp;  // (a copy: kept in registers across the barriers)
-  forward_pipe<N, PEN ? PEN_SUM : PEN_NONE, false, NW>(c, p, p.st, p.Qp, act, ncalls, nsub, t0, ckpt,
+  forward_pipe<N, PEN ? PEN_SUM : PEN_NONE, false, NW>(c, p, p.st, act, ncalls, nsub, t0, ckpt,
                                                    ckpt_every, nullptr, pen, beta);
 }
 
@@ -1189,7 +1202,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
   const int c0 = blockIdx.y * ce;
   const Consts c = *cp;
   forward_pipe<N, PEN ? PEN_GRAD : PEN_NONE, true, false>(
-      c, p, ckpt + (long long)blockIdx.y * NSTATE * Q, Q, act + (long long)c0 * Q * 4,
+      c, p, ckpt + (long long)blockIdx.y * NSTATE * Q, act + (long long)c0 * Q * 4,
       min(ce, ncalls - c0), nsub, t0 + (unsigned long long)c0 * nsub,
       tape + (long long)c0 * nsub * kTapeRows<PEN> * Q, 1, gpen, nullptr, beta);
 }
