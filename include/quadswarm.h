@@ -40,8 +40,9 @@
  *      QS_REVERSE_PIPE = 0|1
  *                            force the multi-wavefront forms off or on:
  *                            multi-substep step calls on two wavefronts
- *                            per workgroup (uniform 8-quad swarms; default
- *                            up to 1024 workgroups), qs_rollout on three to
+ *                            per workgroup of 64 quads (default up to 1536
+ *                            workgroups, 2048 of single quads, 1024 of uneven
+ *                            sizes), qs_rollout on three to
  *                            five (default up to 1024 workgroups, 2048 of
  *                            single quads), the recompute of
  *                            qs_rollout_backward on three or four (default
@@ -369,7 +370,8 @@ int qs_step_backward_noalloc(qs_handle* h, const float* d_state_in, const float*
  * launch: every swarm gets a slot of the next power of two >= its size, slots
  * of one size are grouped into work items, and each workgroup strides over the
  * items running code specialised for the item's slot size.  Calls of few
- * substeps, and swarms that would leave many places of their slots empty, run
+ * substeps, small batches and swarms that would leave many places of their slots
+ * empty run
  * one workgroup per greedy block of swarms (QS_BUCKETED=0 at qs_create: every
  * call; QS_BUCKETED=1, or an explicit qs_set_launch: none).
  */

@@ -177,15 +177,18 @@ int build_items(qs_handle* h, int bs, bool by_size = false) {
 // go by the table of packed workgroups: all its lanes are in use and its reads
 // and writes are contiguous, but every wavefront passes over as many partners as
 // its largest swarm has, each substep.  (us a call with K = 6, table against
-// items.  Two substeps: 49152 quads in twelves 10.5 / 13.9, 524k of 1 to 32
-// 63 / 83.  Eight and more, slots nearly full: 131k of 1, 2, 4 .. 32: eight 41.7 /
-// 35.1, sixteen 91 / 74; 524k: 113 / 109, 202 / 180; 16k in thirties: 27.5 / 26.4,
-// 69 / 59.)  Padded slots cost lanes: with a quarter of them empty the items
-// lose once they need more wavefronts than the three a SIMD holds (524k of 1 to 32,
-// ten substeps: 130 / 143; 131k: 53 / 48), and always where the swarms are
-// small (sixteen at most: 131k in twelves 38.9 / 40.0, 524k 103 / 127).
+// items.  Two substeps: 524k of 1 to 32 63 / 83.  Eight and more, slots nearly full:
+// 131k of 1, 2, 4 .. 32: eight 41.7 / 35.1, sixteen 91 / 74; 524k: 113 / 109,
+// 202 / 180.)  Small batches keep the table, whose substeps two wavefronts
+// share (16k in thirties, eight 23.9 / 27.0; 32k of 1 to 32, ten 30.4 / 33.4;
+// 65k of 1, 2 .. 32, ten 39.7 / 39.2).  Padded slots cost lanes: with a quarter
+// of them empty the items lose once they need more wavefronts than the three a
+// SIMD holds (524k of 1 to 32, ten substeps: 130 / 143; 131k: 53 / 48), and always
+// where the swarms are small (sixteen at most: 131k in twelves 38.9 / 40.0, 524k
+// 103 / 127).
 int default_items_from(const qs_handle* h) {
   constexpr long long resident = 3LL * 4 * 256 * 64;  // places of 3 wavefronts on every SIMD
+  if (h->Q <= 65536) return INT_MAX;
   long long places = 0;
   for (int k = 0; k < 7; ++k) places += (long long)h->slot_swarms[k] << k;
   const bool full = 10LL * h->Q >= 9 * places;

@@ -106,7 +106,7 @@ __device__ __forceinline__ void step_body(const Consts& c, const Ptrs& p,
                                           const unsigned long long* tdev = nullptr,
                                           float (*ring)[4][BS] = nullptr,
                                           float (*rx)[BS] = nullptr) {
-  static_assert(ROLE < 0 || (MAP == MAP_DENSE && BS == 64), "two roles: dense 64-quad groups");
+  static_assert(ROLE < 0 || (MAP != MAP_ITEM && BS == 64), "two roles: workgroups of up to 64 quads");
   static_assert(N == 0 || BS % N == 0, "workgroups hold whole swarms");
   static_assert(MAP != MAP_TABLE || N == 0, "the table mapping has runtime sizes");
   constexpr bool OBS = KT != -2;
@@ -704,10 +704,11 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) void st
   if (tdev) advance_counter(tdev, done, nsub, gridDim.x);
 }
 
-// Several substeps per call for small batches of swarms of 8: two
-// wavefronts per workgroup of 64 quads, the motor part of each substep one
+// Several substeps per call for small batches: two
+// wavefronts per workgroup of up to 64 quads, the motor part of each substep one
 // substep ahead of the rest (step_body ROLE 0 and 1).  Same arithmetic in
-// the same order as step_kernel, so identical results.
+// the same order as step_kernel, so identical results.  Bound by the longer
+// of the two chains, the body's; figures at its rule (use_step_pipe).
 template <int KT, int N>
 __global__ __launch_bounds__(128) void step_pipe_kernel(float* __restrict__ st,
                                                         const float* __restrict__ par,
@@ -729,13 +730,14 @@ __global__ __launch_bounds__(128) void step_pipe_kernel(float* __restrict__ st,
   p.Qp = Qp;
   p.Q = Q;
   const Consts& c = *cp;
+  constexpr int MAP = (N > 0) ? MAP_DENSE : MAP_TABLE;
   const int role = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   if (role == 0)
-    step_body<BS, KT, N, MAP_DENSE, N, 0>(c, p, act, nsub, t0, goals, obs, stage_obs, sxv,
+    step_body<BS, KT, N, MAP, N, 0>(c, p, act, nsub, t0, goals, obs, stage_obs, sxv,
                                           reinterpret_cast<float*>(st_obs4), 0, reward, tdev,
                                           ring, rx);
   else
-    step_body<BS, KT, N, MAP_DENSE, N, 1>(c, p, act, nsub, t0, goals, obs, stage_obs, sxv,
+    step_body<BS, KT, N, MAP, N, 1>(c, p, act, nsub, t0, goals, obs, stage_obs, sxv,
                                           reinterpret_cast<float*>(st_obs4), 0, reward, tdev,
                                           ring, rx);
   if (tdev) advance_counter(tdev, done, nsub, gridDim.x);

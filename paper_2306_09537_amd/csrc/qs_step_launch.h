@@ -9,12 +9,23 @@ namespace {
 
 using qs_host::ptrs;
 
-// Launch one instantiation.  Calls of several substeps on small batches run
-// the motor part one substep ahead in a second wavefront (QS_STEP_PIPE=0/1
-// forces it off/on).
+// Calls of several substeps on small batches run the motor part one substep
+// ahead in a second wavefront (QS_STEP_PIPE=0/1 forces it off/on): a lone
+// wavefront waits for its own instructions, and two share a substep.  Once the
+// first wavefronts fill the SIMDs the second ones only queue behind them.  us a
+// call, one wavefront / two, of two, four and ten substeps:
+//   4096 quads in swarms of 8    6.7 / 5.7    8.9 / 7.7   17.8 / 14.1
+//   4096 in 32                   9.9 / 9.1   13.9 / 12.5  27.0 / 22.1
+//   65536 in 12 (table)         11.7 / 10.5  15.4 / 13.6  28.4 / 24.4
+//   98304 in 12                 12.9 / 15.8  16.9 / 21.0  30.8 / 37.0
+//   98304 in 8                  10.3 / 9.5   13.6 / 12.2  25.9 / 22.3
+//   98304 in 32                 15.8 / 15.4  20.1 / 18.8  36.3 / 36.5
+//   131072 in 8                 12.2 / 14.2  14.7 / 17.9  27.1 / 30.6
+//   131072 in 1                  8.1 / 7.6   10.4 / 9.7   18.0 / 16.5
+//   262144 in 1                 14.5 / 14.3  18.5 / 18.4  30.4 / 30.4
 bool use_step_pipe(const qs_handle* h) {
   if (const char* e = std::getenv("QS_STEP_PIPE")) return e[0] == '1';
-  return h->nblk <= 1024;
+  return h->nblk <= (h->uniform_n == 1 ? 2048 : h->uniform_n > 0 ? 1536 : 1024);
 }
 
 // Observation rows per staging pass.  A grid of at most 2048 workgroups
@@ -44,6 +55,7 @@ int stage_rows(int bs, int od, int nblk) {
   return r;
 }
 
+// Launch one instantiation.
 template <int BS, int KT, int N>
 void go(qs_handle* h, const float* act, int nsub, const float* goals, float* obs,
         hipStream_t s, float* rw) {
@@ -53,7 +65,7 @@ void go(qs_handle* h, const float* act, int nsub, const float* goals, float* obs
     stage = stage_rows(BS, h->OD, h->nblk);
     dyn = (size_t)stage * h->OD * sizeof(float);
   }
-  if constexpr (BS == 64 && N == 8) {
+  if constexpr (BS == 64 && KT != -1) {
     if (nsub >= 2 && use_step_pipe(h)) {
       hipLaunchKernelGGL((qs::step_pipe_kernel<KT, N>), dim3(h->nblk), dim3(128), dyn, s,
                          h->d_st, h->d_par, act, goals, h->d_c, h->Qp, h->Q, nsub,
