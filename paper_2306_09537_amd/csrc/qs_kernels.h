@@ -2,7 +2,7 @@
 //
 // Grid: one workgroup per "block" of whole environments (host-built
 // partition, at most BS quads); one lane per quad.  The state is loaded
-// from the SoA arrays once (coalesced), kept in VGPRs for all substeps of
+// from its tiles once (16 bytes a lane), kept in VGPRs for all substeps of
 // the call, and stored once.  Per substep, lanes exchange positions and
 // velocities through a double-buffered LDS tile for the in-env pair pass
 // (one barrier per substep).  The observation epilogue ranks swarm-mates
@@ -78,7 +78,7 @@ __device__ __forceinline__ void advance_counter(unsigned long long* tdev, unsign
 //  0, 6  that K, known at compile time (register insertion network);
 //  K_UPTO8  any K from 1 to 8: the network of 8, of which the first K are taken.
 //  K passes over the swarm and 18 + 6 K scattered stores a lane had cost
-//  1024 x 8 with K = 3, two substeps and a reward 12 us, now 8.2; 16384 x 32 with
+//  1024 x 8 with K = 3, two substeps and a reward 12 us, now 8.1; 16384 x 32 with
 //  K = 8 140, now 61.
 constexpr int K_UPTO8 = 24;
 template <int KT>
