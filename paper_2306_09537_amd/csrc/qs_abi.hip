@@ -446,8 +446,13 @@ int qs_create(const qs_desc* desc, const qs_quad_params* h_params, const float* 
         (float)(1.0 - std::exp(-(double)desc->dt / (double)p.motor_tau));
     par[qs::par_index(q, qs::P_T2W)] = p.thrust_to_weight;
     par[qs::par_index(q, qs::P_TAU)] = p.motor_tau;
-    for (int f = 0; f < qs::NSTATE; ++f)
-      st[qs::st_index(q, f)] = h_state0[(size_t)q * QS_STATE_DIM + f];
+    const float* row = h_state0 + (size_t)q * QS_STATE_DIM;
+    float* tile = st.data() + (size_t)(q >> 6) * (qs::NSTATE * qs::TILE_QUADS);
+    const int lane = q & 63;
+    for (int g = 0; g < 6; ++g)  // the tile's groups of four, then the last three
+      for (int k = 0; k < 4; ++k)
+        tile[(g * qs::TILE_QUADS + lane) * 4 + k] = row[qs::st_field(4 * g + k)];
+    for (int k = 0; k < 3; ++k) tile[qs::ST_VF + 3 * lane + k] = row[qs::st_field(24 + k)];
   }
 
   rc = QS_OK;
