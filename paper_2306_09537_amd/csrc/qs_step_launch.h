@@ -66,7 +66,10 @@ void go(qs_handle* h, const float* act, int nsub, const float* goals, float* obs
     dyn = (size_t)stage * h->OD * sizeof(float);
   }
   if constexpr (BS == 64 && KT != -1) {
-    if (nsub >= 2 && use_step_pipe(h)) {
+    // (swarms of 64 go over their partners once more for the observation, which
+    // their one-wavefront kernel takes from the screen: two substeps lose,
+    // 16384 quads 18.4 / 19.0 us, four gain, 26.0 / 25.3)
+    if (nsub >= (N == 64 ? 4 : 2) && use_step_pipe(h)) {
       hipLaunchKernelGGL((qs::step_pipe_kernel<KT, N>), dim3(h->nblk), dim3(128), dyn, s,
                          h->d_st, h->d_par, act, goals, h->d_c, h->Qp, h->Q, nsub,
                          (unsigned long long)h->t, ptrs(h), obs, stage,
