@@ -732,7 +732,8 @@ using PairMask = typename std::conditional<(N > 0 && N <= 32), uint32_t,
                                            unsigned long long>::type;
 
 // Calls f(jj, pj) for every swarm-mate jj of the lane's swarm (itself
-// included), in increasing jj, pj[0..5] being its start position and
+// included; N <= 0: and up to three places past its end, jj >= n), in
+// increasing jj, pj[0..5] being its start position and
 // displacement from rows 0-5 of the tile and pj[6] row XR (XR < 0: none).
 // For a compile-time swarm size the reads go out a chunk of eight partners
 // at a time, ahead of the per-pair branches, so they overlap instead of
@@ -767,8 +768,8 @@ __device__ __forceinline__ void for_partners(T tile, int ls, int n, F&& f) {
     }
   } else {
     // run-time sizes: chunks of four as well, branch-free; the places past the
-    // swarm's end hold a partner too far away to count (its squared distance
-    // is finite).  One partner at a time, every read was waited for alone:
+    // swarm's end (jj >= n) repeat its last member, and f leaves them out.
+    // One partner at a time, every read was waited for alone:
     // 2048 swarms of 1-16, differentiated over 100 substeps, 1047 -> 917 us;
     // 4096 x 12 stepped twice and observed 15.0 -> 14.5 us.
     for (int j0 = 0; j0 < n; j0 += 4) {
@@ -781,10 +782,7 @@ __device__ __forceinline__ void for_partners(T tile, int ls, int n, F&& f) {
         pj[u][6] = XR >= 0 ? tile[XR < 0 ? 0 : XR][j] : 0.f;
       }
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        pj[u][0] = j0 + u < n ? pj[u][0] : 1e18f;
-        f(j0 + u, pj[u]);
-      }
+      for (int u = 0; u < 4; ++u) f(j0 + u, pj[u]);
     }
   }
 }
@@ -1174,10 +1172,11 @@ __device__ __forceinline__ unsigned long long pair_pass(const Consts& c, const f
   constexpr bool ACC = N >= 16 && N <= 32;
   uint32_t acc = 0u;
   auto pair = [&](int jj, const float* pj, auto with_dw, auto in_order) {
+    const bool mate = N > 0 || jj < n;  // (cm drops the other places after the pass)
     float dx, dy, dz, d2;
     const bool con = pair_geom_v(c, pj, s, dx, dy, dz, d2);
     if constexpr (P != PEN_NONE)
-      pen_term<P>(c, *pen, P == PEN_GRAD || jj != me, pj[6], dx, dy, dz, d2);
+      pen_term<P>(c, *pen, mate && (P == PEN_GRAD || jj != me), pj[6], dx, dy, dz, d2);
     if constexpr (ACC && decltype(in_order)::value)
       acc = __builtin_amdgcn_alignbit(acc, __float_as_uint(d2 - c.dcol2), 31u);
     else
@@ -1185,7 +1184,7 @@ __device__ __forceinline__ unsigned long long pair_pass(const Consts& c, const f
     if constexpr (decltype(with_dw)::value) {
       // swarm-mate j above (z_j - z_i = -dz) and overlapping in xy (never
       // the quad itself: dz = 0 there)
-      const bool dwc = dw & (dx * dx + dy * dy < dw_r2) & (-dz > 0.f) & (-dz < dw_h);
+      const bool dwc = mate & dw & (dx * dx + dy * dy < dw_r2) & (-dz > 0.f) & (-dz < dw_h);
       adw = dwc ? adw - dw_k1 * (dw_k2 * -dz + dw_b1) : adw;
       dwhit = dwhit | dwc;
     }
@@ -1375,7 +1374,7 @@ __device__ __forceinline__ void penalty_pass(const Consts& c, const float (*tile
   for_partners<BS, N, P == PEN_GRAD ? PENROW : -1>(tile, ls, n, [&](int jj, const float* pj) {
     float dx, dy, dz, d2;
     pair_geom_v(c, pj, s, dx, dy, dz, d2);
-    pen_term<P>(c, pen, P == PEN_GRAD || jj != me, pj[6], dx, dy, dz, d2);
+    pen_term<P>(c, pen, (N > 0 || jj < n) && (P == PEN_GRAD || jj != me), pj[6], dx, dy, dz, d2);
   });
 }
 

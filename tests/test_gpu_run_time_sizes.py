@@ -1,0 +1,91 @@
+"""Swarms whose sizes are known at run time only, read four partners at a time:
+the places past a swarm's end are no partners of anybody, whatever the
+constants make of the values read there."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle import oracle as O  # noqa: E402
+from paper_2306_09537_amd import workloads as W  # noqa: E402
+from paper_2306_09537_amd.quadswarm import QuadSwarm  # noqa: E402
+from tests.gpu_util import TOL, fmax_of, rel_err  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).cuda()
+
+
+def spaced(sizes, flags, seed, **consts):
+    """Quads of a swarm at least half a metre apart, within four metres."""
+    w = W.custom(sizes, seed=seed, k=0, flags=flags, name="ends", **consts)
+    grid = np.stack(np.meshgrid(*[np.arange(5.0)] * 3, indexing="ij"), -1).reshape(-1, 3)
+    rng = np.random.default_rng(seed)
+    state = w.state0.copy()
+    for a, b in zip(w.env_offsets[:-1], w.env_offsets[1:]):
+        state[a:b, :3] = rng.permutation(grid)[:b - a] - 2.0
+    state[:, :3] += 0.2 * rng.uniform(-1, 1, size=(w.n_quads, 3))
+    return w.with_(state0=state.astype(np.float32))
+
+
+@pytest.mark.parametrize("pipe", ["0", "1"])
+@pytest.mark.parametrize("beta", [1e-17, 1e-18])
+@pytest.mark.parametrize("sizes", [[3] * 9, [13] * 5, [17, 6, 33], [2] * 33])
+def test_penalty_that_reaches_far(sizes, beta, pipe, monkeypatch):
+    for k in ("ROLLOUT", "RECOMPUTE", "REVERSE"):
+        monkeypatch.setenv(f"QS_{k}_PIPE", pipe)
+    w = spaced(sizes, W.QS_MOTOR_NOISE, seed=len(sizes))
+    Q, n = w.n_quads, max(sizes)
+    rng = np.random.default_rng(3)
+    acts, gpen = rng.random((2, Q, 4)).astype(np.float32), rng.random(Q).astype(np.float32)
+    sim, ora = QuadSwarm.from_workload(w), O.Oracle.from_workload(w)
+    pen, ckpt = torch.zeros(Q, device="cuda"), torch.empty((1, 27, Q), device="cuda")
+    sim.rollout(dev(acts), 1, 2, ckpt, pen, beta)
+    gs, ga = torch.zeros((Q, 27), device="cuda"), torch.empty((2, Q, 4), device="cuda")
+    sim.rollout_backward(dev(acts), 1, 2, ckpt, 0, gs, dev(gpen), beta, ga,
+                         torch.zeros((Q, 6), device="cuda"))
+    sim.sync()
+    # a term ln 2 / (2 beta): some eight roundings, and one for each term added
+    b32 = float(np.float32(beta))
+    _, want = ora.rollout(w.state0, acts, 1, 0, b32)
+    np.testing.assert_allclose(pen.cpu().numpy(), want, rtol=(8 + 2 * n) * 2.0 ** -23)
+    # a partner's direction: positions rounded at 4 m, half a metre apart; weight
+    # and sigmoid below 1; two substeps
+    want, _, _ = ora.rollout_vjp(w.state0, acts, 1, 0, np.zeros((Q, 27)), gpen, b32)
+    atol = 2 * n * (2 * 4 / 0.5) * 2.0 ** -23
+    np.testing.assert_allclose(gs.cpu().numpy()[:, :3], want[:, :3], rtol=0, atol=atol)
+
+
+def test_lone_quads_have_no_penalty():
+    w = spaced([1, 5, 1, 3], 0, seed=1)
+    lone = [0, 6]
+    state = w.state0.copy()
+    state[6, 0] = np.nan
+    sim = QuadSwarm.from_workload(w)
+    sim.set_state(dev(state), 0)
+    acts = dev(np.full((1, 10, 4), 0.5))
+    pen, ckpt = torch.zeros(10, device="cuda"), torch.empty((1, 27, 10), device="cuda")
+    sim.rollout(acts, 1, 1, ckpt, pen, 100.0)
+    assert (pen[lone] == 0).all()
+    gpen = torch.ones(10, device="cuda")
+    gpen[0] = float("inf")
+    gs, ga = torch.zeros((10, 27), device="cuda"), torch.empty((1, 10, 4), device="cuda")
+    sim.rollout_backward(acts, 1, 1, ckpt, 0, gs, gpen, 100.0, ga,
+                         torch.zeros((10, 6), device="cuda"))
+    assert (gs[0] == 0).all()
+
+
+@pytest.mark.parametrize("height", [0.5, 1e30])
+@pytest.mark.parametrize("sizes", [[3] * 9, [13] * 5, [50, 17, 6], [2, 7] * 8])
+def test_downwash_of_any_radius(sizes, height, monkeypatch):
+    w = spaced(sizes, W.QS_DOWNWASH, seed=len(sizes), dw_radius=1e30, dw_height=height)
+    want, _, _, margin = O.Oracle.from_workload(w).step(w.state0, w.actions(0), 1, 0, margins=True)
+    assert margin.min() > 1e-5
+    for routes in ("0", "1"):
+        monkeypatch.setenv("QS_BUCKETED", routes)
+        sim = QuadSwarm.from_workload(w)
+        sim.step(dev(w.actions(0)), 1)
+        got = sim.get_state()[0].cpu().numpy()
+        assert rel_err(got, want, fmax_of(w.params)).max() <= TOL
