@@ -864,7 +864,7 @@ __device__ __forceinline__ void for_partner_pos(T tile, int ls, int n, F&& f) {
       }
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        pj[u][0] = j0 + u < n ? pj[u][0] : 1e30f;  // at infinite squared distance
+        pj[u][0] = j0 + u < n ? pj[u][0] : INFINITY;  // at infinite squared distance
         f(j0 + u, pj[u]);
       }
     }
@@ -1256,7 +1256,8 @@ __device__ __forceinline__ unsigned long long pair_pass(const Consts& c, const f
   return cmask;
 }
 
-// The exchange tile's rows of one lane (padding lanes: far away).
+// The exchange tile's rows of one lane.  Padding lanes are at an infinite
+// distance of every position, the largest finite ones included.
 template <int N, bool SCREEN, typename T>
 __device__ __forceinline__ void put_tile(T tile, int tid, const Quad& s) {
 #pragma unroll
@@ -1271,7 +1272,7 @@ template <typename T>
 __device__ __forceinline__ void put_tile_pad(T tile, int tid) {
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    tile[k][tid] = 1e30f;
+    tile[k][tid] = INFINITY;
     tile[3 + k][tid] = 0.f;
     tile[6 + k][tid] = 0.f;
   }
@@ -1306,7 +1307,7 @@ __device__ __forceinline__ unsigned long long lane_pair_pass(
                 : 0ull;
   }
   const float dw = c.dcol + 1e-3f, thr = dw * dw;
-  const float x = live ? s.x[0] : 1e30f, y = live ? s.x[1] : 1e30f, z = live ? s.x[2] : 1e30f;
+  const float x = live ? s.x[0] : INFINITY, y = live ? s.x[1] : INFINITY, z = live ? s.x[2] : INFINITY;
   // the sign of d^2 - thr as one FMA chain, shifted in: bit N - 1 - d for the
   // partner me ^ d
   const LaneXyz xyz = lane_xyz<N>(x, y, z);

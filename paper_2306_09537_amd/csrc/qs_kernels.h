@@ -400,7 +400,7 @@ __device__ __forceinline__ void step_body(const Consts& c, const Ptrs& p,
         // padding lane: never among the nearest
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-          tile[k][tid] = 1e30f;
+          tile[k][tid] = INFINITY;
           tile[6 + k][tid] = 0.f;
         }
       }
@@ -438,8 +438,8 @@ __device__ __forceinline__ void step_body(const Consts& c, const Ptrs& p,
         };
         if (!screened) {
           if constexpr (LANE_KNN) {
-            const float mx = live ? s.x[0] : 1e30f, my = live ? s.x[1] : 1e30f,
-                        mz = live ? s.x[2] : 1e30f;
+            const float mx = live ? s.x[0] : INFINITY, my = live ? s.x[1] : INFINITY,
+                        mz = live ? s.x[2] : INFINITY;
             const LaneXyz xyz = lane_xyz<N>(mx, my, mz);
             auto mate = [&](auto dc) {
               constexpr int D = decltype(dc)::value;
@@ -482,7 +482,7 @@ __device__ __forceinline__ void step_body(const Consts& c, const Ptrs& p,
                   for (int r = 0; r < 3; ++r) px[u][r] = tile[r][ls + min(j0 + u, n - 1)];
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
-                  cand(j0 + u, j0 + u < n ? px[u][0] : 1e30f, px[u][1], px[u][2]);
+                  cand(j0 + u, j0 + u < n ? px[u][0] : INFINITY, px[u][1], px[u][2]);
               }
           }
         }

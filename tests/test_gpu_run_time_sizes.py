@@ -89,3 +89,25 @@ def test_downwash_of_any_radius(sizes, height, monkeypatch):
         sim.step(dev(w.actions(0)), 1)
         got = sim.get_state()[0].cpu().numpy()
         assert rel_err(got, want, fmax_of(w.params)).max() <= TOL
+
+
+@pytest.mark.parametrize("bucketed", ["0", "1"])
+@pytest.mark.parametrize("sizes", [[7] * 9, [13] * 5, [51, 19, 6, 1, 3]])
+def test_the_farthest_positions_have_no_neighbours(sizes, bucketed, monkeypatch):
+    """The squared distance from 1e30 m to anything is infinite in float32, so a
+    quad there has empty slots, in the selection network as in the K passes that
+    the largest K takes."""
+    monkeypatch.setenv("QS_BUCKETED", bucketed)
+    rows = []
+    for k in (6, 9):
+        w = W.custom(sizes, seed=5, k=k, name="ends")
+        state, far = w.state0.copy(), w.env_offsets[1:] - 2 * (w.env_sizes > 2)
+        far = np.minimum(far, w.env_offsets[1:] - 1)  # one of each swarm
+        state[far, 0] = 1e30
+        sim = QuadSwarm.from_workload(w)
+        sim.set_state(dev(state), 0)
+        o = torch.empty((w.n_quads, w.obs_dim), device="cuda")
+        sim.observe(dev(w.goals), o)
+        rows.append(o[:, :18 + 36].clone())
+    assert torch.equal(rows[0], rows[1])
+    assert (rows[0][far, 18:] == 0).all()
