@@ -1167,7 +1167,7 @@ __device__ __forceinline__ unsigned long long pair_pass(const Consts& c, const f
   const float dw_r2 = c.dw_r2, dw_h = c.dw_h, dw_k1 = c.dw_k1, dw_k2 = c.dw_k2, dw_b1 = c.dw_b1;
   // In passes over every partner in index order (in_order), swarms of 16
   // and 32 shift the contact bits in (the sign bit of d^2 - d_col^2, for
-  // finite d^2 exactly the comparison's outcome, by one funnel shift) and
+  // numbers exactly the comparison's outcome, by one funnel shift) and
   // bit-reverse them once after the pass.
   constexpr bool ACC = N >= 16 && N <= 32;
   uint32_t acc = 0u;
@@ -1240,8 +1240,10 @@ __device__ __forceinline__ unsigned long long pair_pass(const Consts& c, const f
   }
   // (run-time sizes: nor the places past the swarm's end)
   if constexpr (N <= 0) cm &= (M)(~0ull >> (64 - n));
-  const unsigned long long cmask = collide ? (unsigned long long)(cm & ~((M)1 << me)) : 0ull;
-  // The responses, for the partners in contact only, in partner order.
+  unsigned long long cmask = collide ? (unsigned long long)(cm & ~((M)1 << me)) : 0ull;
+  // The responses, for the partners in contact only, in partner order.  (The
+  // sign bits shifted in above are the comparison's outcome for numbers only: a
+  // partner at a distance that is none is not in contact.)
   float dv[3] = {0.f, 0.f, 0.f};
   unsigned long long rm = 0ull;
   for (unsigned long long m = cmask; m != 0ull; m &= m - 1ull) {
@@ -1249,8 +1251,10 @@ __device__ __forceinline__ unsigned long long pair_pass(const Consts& c, const f
     const int j = ls + jj;
     const float pj[6] = {tile[0][j], tile[1][j], tile[2][j], tile[3][j], tile[4][j], tile[5][j]};
     float dx, dy, dz, d2;
-    pair_geom_v(c, pj, s, dx, dy, dz, d2);
-    pair_response<BS>(c, tile, s, j, jj, me, dx, dy, dz, d2, dv, rm);
+    if (pair_geom_v(c, pj, s, dx, dy, dz, d2))
+      pair_response<BS>(c, tile, s, j, jj, me, dx, dy, dz, d2, dv, rm);
+    else
+      cmask &= ~(1ull << jj);
   }
   pair_apply(c, s, q, t, rm, dv, adw, dwhit, resp, events);
   return cmask;
