@@ -1033,6 +1033,10 @@ template <int BS, int N, int P>
 __device__ __forceinline__ bool near_pass(const Consts& c, const float (*tile)[BS], const Quad& s,
                                           int ls, int n, int me, Pen& p, PairMask<N>& cm) {
   using M = PairMask<N>;
+  // The votes below see one wavefront.  In a table's workgroup of two, a swarm may
+  // lie in both: a mate in the other one whose position or weight is not a
+  // number, and so counts for everybody, would be left out.
+  if constexpr (BS > 64 && N <= 0) return false;
   if (p.few == 0) return false;
   const float far = max_abs(s.x);
   const float lim = kScreenSq<N> ? SCREEN_BOX : 1000.0f;

@@ -57,3 +57,38 @@ def test_mates_of_a_lost_quad(n, value, downwash, monkeypatch):
                 assert e.code == -5
         for a, b in zip(*got):
             assert torch.isfinite(a).all() and torch.equal(a, b)
+
+
+@pytest.mark.parametrize("lost_quad,weight", [(True, 1.0), (False, np.inf), (False, np.nan)])
+@pytest.mark.parametrize("sizes", [[13] * 9, [40] * 3, [50, 50, 17, 9]])
+def test_a_lost_mate_in_the_other_wavefront(sizes, lost_quad, weight, monkeypatch):
+    """Workgroups of 128 may hold a swarm in two wavefronts: its penalty and its
+    adjoint are those of workgroups of 64, where it lies in one."""
+    w = W.custom(sizes, seed=1, k=0, name="lost", flags=W.QS_MOTOR_NOISE)
+    Q, state = w.n_quads, w.state0.copy()
+    env = int(np.searchsorted(w.env_offsets, 64, side="right")) - 1
+    first, end = w.env_offsets[env], w.env_offsets[env + 1]
+    assert first < 64 < end <= 128
+    rng = np.random.default_rng(2)
+    state[:, :3] = 6.0 * rng.uniform(-1, 1, size=(Q, 3))  # few within 1.2 m
+    if lost_quad:
+        state[first, 1] = np.nan
+    acts, g = dev(rng.random((2, Q, 4))), dev(rng.standard_normal((Q, 27)))
+    gpen = np.ones(Q)
+    gpen[first] = weight
+    outs = []
+    for block in ("64", "128"):
+        monkeypatch.setenv("QS_BLOCK_SIZE", block)
+        sim = QuadSwarm.from_workload(w)
+        sim.set_state(dev(state), 0)
+        pen, ckpt = torch.zeros(Q, device="cuda"), torch.empty((1, 27, Q), device="cuda")
+        sim.rollout(acts, 2, 2, ckpt, pen, 100.0)
+        gs, ga = g.clone(), torch.empty((2, Q, 4), device="cuda")
+        sim.rollout_backward(acts, 2, 2, ckpt, 0, gs, dev(gpen), 100.0, ga,
+                             torch.zeros((Q, 6), device="cuda"))
+        outs.append((pen, gs, ga))
+    if lost_quad:  # a swarm with a lost quad has no penalty that is a number
+        assert outs[0][0][first:end].isnan().all()
+    for a, b in zip(*outs):
+        assert torch.equal(a.isnan(), b.isnan())
+        assert torch.equal(a.nan_to_num(), b.nan_to_num())
