@@ -321,8 +321,10 @@ int qs_rollout(qs_handle* h, const float* d_actions, int32_t n_calls, int32_t n_
  * recomputed from its checkpoint into a tape of ckpt_every*n_substeps
  * states and motor-noise draws (31 floats per quad and substep, 34 with a
  * penalty gradient; device scratch owned by the handle, grown on first use, at most the tape budget:
- * environment QS_TAPE_BYTES, default 8 GiB, and one segment).  Does not
- * change the handle's state.
+ * environment QS_TAPE_BYTES, default 8 GiB, and one segment).  Segments that
+ * do not fit the tape together are taken in chunks, whose parameter gradients
+ * are summed in 24 bytes of scratch per quad and added to d_gparams once.
+ * Does not change the handle's state.
  */
 int qs_rollout_backward(qs_handle* h, const float* d_actions, int32_t n_calls,
                         int32_t n_substeps, int32_t ckpt_every, const float* d_ckpt,

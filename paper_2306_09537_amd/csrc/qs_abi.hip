@@ -61,6 +61,7 @@ void free_all(qs_handle* h) {
   (void)hipFree(h->d_err);
   (void)hipFree(h->d_tape);
   (void)hipFree(h->d_ck1);
+  (void)hipFree(h->d_gsum);
   (void)hipFree(h->d_items);
   (void)hipFree(h->d_item_envs);
   (void)hipFree(h->d_t);

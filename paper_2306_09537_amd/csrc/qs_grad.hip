@@ -73,7 +73,7 @@ struct AdjBuffers {
   float* tape;
   const float* gin;
   float* gout;
-  float* gpar;
+  qs::ParSum gpar;
 };
 
 template <int BS, int N, bool PEN>
@@ -196,6 +196,8 @@ int run_adjoint(qs_handle* h, AdjBuffers sc, int G, const float* act, int n_call
   const int nseg = (n_calls + ce - 1) / ce;
   for (int hi = nseg; hi > 0; hi -= G) {
     const int g0 = std::max(0, hi - G);
+    sc.gpar.first = hi == nseg;
+    sc.gpar.last = g0 == 0;
     const int c0 = g0 * ce, nc = std::min(n_calls, hi * ce) - c0;
     const float* ck = ckpt + (size_t)g0 * qs::NSTATE * h->Q;
     const float* a = act + (size_t)c0 * h->Q * 4;
@@ -252,14 +254,14 @@ void go_step_vjp(qs_handle* h, const AdjBuffers& b, const float* state_in, const
                  int nsub, uint64_t t0, float* gact, hipStream_t s) {
   const size_t dyn = (size_t)(nsub - 1) * qs::VJP_ROW * 64 * sizeof(float);
   hipLaunchKernelGGL((qs::step_vjp_kernel<N>), dim3(h->nblk), dim3(64), dyn, s, h->d_c, ptrs(h),
-                     state_in, act, nsub, (unsigned long long)t0, b.gin, b.gout, gact, b.gpar);
+                     state_in, act, nsub, (unsigned long long)t0, b.gin, b.gout, gact, b.gpar.out);
 }
 
 int step_backward_run(qs_handle* h, float* tape, float* ck1, const float* d_state_in,
                       const float* d_actions, int32_t n_substeps, uint64_t substep_index,
                       const float* d_gstate_out, float* d_gstate_in, float* d_gactions,
                       float* d_gparams, hipStream_t s) {
-  const AdjBuffers b{tape, d_gstate_out, d_gstate_in, d_gparams};
+  const AdjBuffers b{tape, d_gstate_out, d_gstate_in, {d_gparams, nullptr, true, true}};
   if (one_launch(h, n_substeps)) {
     switch (h->uniform_n) {
       case 1: go_step_vjp<1>(h, b, d_state_in, d_actions, n_substeps, substep_index, d_gactions, s); break;
@@ -384,7 +386,9 @@ int qs_rollout_backward(qs_handle* h, const float* d_actions, int32_t n_calls,
   const int G = (int)std::max<size_t>(1, std::min<size_t>({(size_t)nseg, fit, (size_t)65535}));
   int rc = grow(&h->d_tape, &h->tape_cap, (size_t)G * seg);
   if (rc != QS_OK) return rc;
-  const AdjBuffers b{h->d_tape, d_gstate, d_gstate, d_gparams};
+  if (G < nseg) rc = grow(&h->d_gsum, &h->gsum_cap, (size_t)6 * h->Q);
+  if (rc != QS_OK) return rc;
+  const AdjBuffers b{h->d_tape, d_gstate, d_gstate, {d_gparams, h->d_gsum, true, true}};
   return run_adjoint(h, b, G, d_actions, n_calls, n_substeps, ckpt_every, d_ckpt, substep_index0,
                    d_gpenalty, beta, d_gactions, s);
 }

@@ -55,11 +55,14 @@ struct qs_handle {
   unsigned long long* d_t = nullptr;
   unsigned int* d_done = nullptr;
   // backward passes' scratch, grown on demand: the tape of the chunk of
-  // segments in flight, and one checkpoint [27][Q]
+  // segments in flight, one checkpoint [27][Q], and the parameter gradient
+  // [Q][6] of the chunks so far where there are several
   float* d_tape = nullptr;
   size_t tape_cap = 0;
   float* d_ck1 = nullptr;
   size_t ck1_cap = 0;
+  float* d_gsum = nullptr;
+  size_t gsum_cap = 0;
 };
 
 namespace qs_host {

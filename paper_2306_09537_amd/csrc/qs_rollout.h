@@ -596,6 +596,22 @@ __device__ __forceinline__ void reverse_responses(const Consts& c, float (*tile)
   if (live) response_vjp<BS>(c, tile, tile + 9, s, ls, me, cm, ldv, l.x, l.v);
 }
 
+// Where a backward pass's parameter gradient [Q][6] goes: every chunk's share is
+// summed in sum, and the total is added to the caller's array once, by the last
+// chunk.  (Added chunk by chunk, each share would be rounded at the size of what
+// the caller's array holds already.)
+struct ParSum {
+  float* out;   // the caller's
+  float* sum;   // the handle's, where there are several chunks
+  bool first, last;
+};
+__device__ __forceinline__ void add_par(const ParSum& p, int q, int k, float g) {
+  const size_t i = (size_t)q * 6 + k;
+  if (!p.first) g = p.sum[i] + g;
+  if (p.last) p.out[i] += g;
+  else p.sum[i] = g;
+}
+
 // ---------------------------------------------------------------------------
 // reverse_kernel: the reverse sweep over the chunk's ncalls nsub substeps,
 // last to first, from the tape; the adjoint of the state stays in
@@ -605,8 +621,8 @@ __device__ __forceinline__ void reverse_responses(const Consts& c, float (*tile)
 // motor noise is drawn again instead of being stored and read: 32768 x 32, 100
 // substeps with their derivative, 10.43 -> 9.77 ms.
 //  gin, gout: [Q][27] dL/d(chunk end), dL/d(chunk start) (may be one array);
-//  act/gact: the chunk's first call; gpar: [Q][6]
-//  dL/d(m, ixx, iyy, izz, t2w, tau), accumulated.
+//  act/gact: the chunk's first call; gpar: where dL/d(m, ixx, iyy, izz, t2w,
+//  tau) goes.
 // ---------------------------------------------------------------------------
 template <int BS, int N, bool PEN>
 __global__ __launch_bounds__(BS) void reverse_kernel(const Consts* __restrict__ cp, Ptrs p,
@@ -614,8 +630,7 @@ __global__ __launch_bounds__(BS) void reverse_kernel(const Consts* __restrict__ 
                                                      int nsub, unsigned long long t0,
                                                      const float* __restrict__ tape,
                                                      const float* gin, float* gout, int wide,
-                                                     float* __restrict__ gact,
-                                                     float* __restrict__ gpar) {
+                                                     float* __restrict__ gact, ParSum gpar) {
   constexpr int NTAPE = kTapeRows<PEN>;
   // the rows on their way in and out; the exchange tile between
   __shared__ __align__(16) float sh[NSTATE * BS];
@@ -695,7 +710,7 @@ __global__ __launch_bounds__(BS) void reverse_kernel(const Consts* __restrict__ 
   if (live) {
     put_adj(sh + tid * NSTATE, l);
 #pragma unroll
-    for (int k = 0; k < 6; ++k) gpar[(size_t)q * 6 + k] += gp[k];
+    for (int k = 0; k < 6; ++k) add_par(gpar, q, k, gp[k]);
   }
   __syncthreads();
   move_rows<BS, BS, false>(gout, qb, cnt, sh, tid);
@@ -1234,8 +1249,7 @@ __global__ __launch_bounds__(448) void reverse_pipe_kernel(const Consts* __restr
                                                            int ncalls, int nsub,
                                                            const float* __restrict__ tape,
                                                            const float* gin, float* gout, int un,
-                                                           float* __restrict__ gact,
-                                                           float* __restrict__ gpar,
+                                                           float* __restrict__ gact, ParSum gpar,
                                                            unsigned long long t0) {
   constexpr int BS = 64, NTAPE = kTapeRows<PEN>;
   // rings, indexed by the substep; as many slots as steps pass from the first
@@ -1568,7 +1582,7 @@ __global__ __launch_bounds__(448) void reverse_pipe_kernel(const Consts* __restr
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
         out[S_W + k] = lw[k];
-        gpar[(size_t)q * 6 + 1 + k] += gJ[k];
+        add_par(gpar, q, 1 + k, gJ[k]);
       }
     }
   } else {
@@ -1618,9 +1632,9 @@ __global__ __launch_bounds__(448) void reverse_pipe_kernel(const Consts* __restr
         out[S_U + k] = lu[k];
         out[S_E + k] = le[k];
       }
-      gpar[(size_t)q * 6] += gm;
-      gpar[(size_t)q * 6 + 4] += gt2w;
-      gpar[(size_t)q * 6 + 5] += gtau;
+      add_par(gpar, q, 0, gm);
+      add_par(gpar, q, 4, gt2w);
+      add_par(gpar, q, 5, gtau);
     }
   }
   wg_sync();
