@@ -541,11 +541,14 @@ __device__ __forceinline__ void step_body(const Consts& c, const Ptrs& p,
           ov[18 + 6 * k + 5] = have ? nb[k][5] - s.v[2] : 0.f;
         }
         if (reward && live) {
-          float rp = 0.f;
+          // the proximity terms: summed apart for K = 6, else added one by one
+          // to the rest, as with K above 8
+          const float r = reward_state(c, s, pp.f_max, ov, f0);
+          float rp = ANY_K ? r : 0.f;
 #pragma unroll
           for (int k = 0; k < KC; ++k)
             if (k < K && bj[k] >= 0) rp += reward_prox(c, ov[18 + 6 * k], ov[19 + 6 * k], ov[20 + 6 * k]);
-          reward[q] = reward_state(c, s, pp.f_max, ov, f0) + rp;
+          reward[q] = ANY_K ? rp : r + rp;
         }
       } else {
         if (reward && live) reward[q] = reward_state(c, s, pp.f_max, ov, f0);
