@@ -406,8 +406,9 @@ int qs_set_launch(qs_handle* h, int32_t block, int32_t grid);
  * swarm's own size; (2) per slot size of 16 and 32, its work items
  * alone with that body and with the body that passes over all the slot's
  * places; (3) the call with each slot size on its faster body, over the
- * grids; the faster of (1) and (3) is kept; (4) the call by packed blocks,
- * which calls of n_substeps take from then on if it is faster still.
+ * grids; the faster of (1) and (3) is kept; (4) without QS_BUCKETED=1, the
+ * call by packed blocks, which calls of n_substeps take from then on if it is
+ * faster still.
  * choice (optional, int32[3]) receives (workgroup size, grid size or 0 for one
  * workgroup per item, bucketed form available ? 1 : 0); qs_launch_plan gives the per-slot table.  Not
  * available in graph mode.  Synchronous.  This is the batching workload's

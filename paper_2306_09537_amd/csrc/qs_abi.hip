@@ -280,8 +280,9 @@ int apply(qs_handle* h, hipStream_t s, const BucketConfig& c, bool by_size = fal
 // every slot size with the one-partner body; (2) per slot size with two
 // bodies (16 and 32), its items alone with each body, at the workgroup size
 // of (1); (3) the call with each slot size on its faster body, over the
-// grids; the faster of (1) and (3) is kept.  (4) The call by the table: whichever
-// launch is the faster one, calls of this many substeps take from now on.
+// grids; the faster of (1) and (3) is kept.  (4) Unless QS_BUCKETED asks for items
+// in every call, the call by the table: whichever launch is the faster one, calls
+// of this many substeps take from now on.
 int tune_buckets(Trial& tr, BucketConfig* best) {
   qs_handle* h = tr.h;
   float best_ms = 1e30f;
@@ -332,6 +333,7 @@ int tune_buckets(Trial& tr, BucketConfig* best) {
       *best = c;
     }
   }
+  if (h->items_always) return QS_OK;
   float table_ms = 0.f;
   h->items_from = INT_MAX;
   if ((rc = tr.call(&table_ms)) != QS_OK) return rc;
@@ -473,6 +475,7 @@ int qs_create(const qs_desc* desc, const qs_quad_params* h_params, const float* 
     const char* ev = std::getenv("QS_BUCKETED");
     h->bucketed = !(ev && ev[0] == '0');
     if (h->bucketed) rc = build_items(h, 64);
+    h->items_always = ev != nullptr;
     h->items_from = ev ? 0 : default_items_from(h);
   }
   if (rc == QS_OK && hipHostMalloc((void**)&h->h_err, sizeof(int)) != hipSuccess) {

@@ -50,6 +50,7 @@ struct qs_handle {
   float slot_ns_chunked[7] = {0, 0, 0, 0, 0, 0, 0};
   bool bucketed = false;
   int items_from = 0;    // substeps a call from which it is used (fewer: the table)
+  bool items_always = false;  // in every call, by QS_BUCKETED: the autotuner leaves it so
   // graph-safe substep counter
   bool graph_mode = false;
   unsigned long long* d_t = nullptr;

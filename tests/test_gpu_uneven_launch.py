@@ -57,3 +57,25 @@ def test_explicit_launch_after_the_tuner(monkeypatch):
         sim.set_launch(block, grid)
         a = dev(w.actions(c))
         assert torch.equal(sim.step_observe(a, 2, g), ref.step_observe(a, 2, g))
+
+
+def kernels_of(call):
+    """Names of the kernels that a call launches."""
+    from torch.profiler import ProfilerActivity, profile
+    with profile(activities=[ProfilerActivity.CUDA, ProfilerActivity.CPU]) as prof:
+        call()
+        torch.cuda.synchronize()
+    return [e.key for e in prof.key_averages() if "qs::" in e.key]
+
+
+def test_the_tuner_leaves_a_forced_launch(monkeypatch):
+    """A batch of three workgroups, which the table serves faster than any grid of
+    items does: QS_BUCKETED=1 keeps the items all the same."""
+    monkeypatch.setenv("QS_BUCKETED", "1")
+    w = W.custom([12] * 15, seed=13, k=6, name="routes")
+    sim = QuadSwarm.from_workload(w)
+    g, a = dev(w.goals), dev(w.actions(0))
+    o = torch.empty((w.n_quads, w.obs_dim), device="cuda")
+    sim.autotune(a, 4, g, o)
+    names = kernels_of(lambda: sim.step_observe(a, 4, g, o))
+    assert len(names) == 1 and "bucket_kernel" in names[0], names
