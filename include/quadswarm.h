@@ -337,8 +337,8 @@ int qs_rollout_backward(qs_handle* h, const float* d_actions, int32_t n_calls,
  * substep index, map d_gstate_out [Q][27] = dL/d(state after) to
  * d_gstate_in [Q][27] = dL/d(state before) and d_gactions [Q][4], and ADD
  * dL/d(params) into d_gparams [Q][6].  No penalty term.  d_gstate_in may
- * be the same buffer as d_gstate_out (both are staged through the handle's
- * scratch).
+ * be the same buffer as d_gstate_out (a quad's row is read before it is
+ * written).
  */
 int qs_step_backward(qs_handle* h, const float* d_state_in, const float* d_actions,
                      int32_t n_substeps, uint64_t substep_index, const float* d_gstate_out,
@@ -349,13 +349,13 @@ int qs_step_backward(qs_handle* h, const float* d_state_in, const float* d_actio
  * under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc.  Same arguments, checks and results (bit-identical) as
  * qs_step_backward, same kernels; it calls no hipMalloc, hipFree or other
- * allocating routine.  Its scratch -- the state before the call and the
- * state adjoint ([27][Q] each), the parameter gradient ([6][Q]) and the
- * tape of the call's substeps ([n_substeps][31][Q]), each part rounded up
- * to 64 floats -- lives in a fixed device array of QS_NOALLOC_SCRATCH_BYTES
- * that the library holds on every device it runs on until the process
- * ends.  A request that does not fit returns QS_ERR_TOO_LARGE before
- * anything is enqueued: (60 + 31 n_substeps) Q floats must stay within
+ * allocating routine.  Its scratch, the state before the call ([27][Q]) and the
+ * tape of the call's substeps ([n_substeps][31][Q]), lives in a fixed device
+ * array of QS_NOALLOC_SCRATCH_BYTES that the library holds on every device it
+ * runs on until the process ends (calls of up to four substeps on 64-quad
+ * workgroups need none).  A request is refused with QS_ERR_TOO_LARGE, before
+ * anything is enqueued, unless (60 + 31 n_substeps) Q floats, in parts of
+ * 27 Q, 27 Q, 6 Q and the tape each rounded up to 64, stay within
  * 16,777,216 (e.g. at most 184,000 quads for one substep, 45,000 for ten).
  * Every call on a device shares that device's array and the array keeps
  * the last call's contents (each call overwrites what it reads): calls

@@ -228,7 +228,8 @@ int check_step_backward(const qs_handle* h, const float* d_state_in, const float
   if (!aligned(d_actions, 16) || !aligned(d_gactions, 16) || !aligned(d_state_in, 4) ||
       !aligned(d_gstate_out, 4) || !aligned(d_gstate_in, 4) || !aligned(d_gparams, 4))
     return QS_ERR_ALIGN;
-  // d_gstate_in may be d_gstate_out itself (both are staged), not a part of it
+  // d_gstate_in may be d_gstate_out itself (a workgroup has read its rows before it
+  // writes them), not a part of it
   const size_t Q = (size_t)h->Q;
   const bool same = d_gstate_in == d_gstate_out;
   if (outputs_overlap({{d_gstate_in, Q * 108}, {d_gactions, Q * 16}, {d_gparams, Q * 24}},
@@ -416,17 +417,19 @@ int qs_step_backward_noalloc(qs_handle* h, const float* d_state_in, const float*
   int rc = check_step_backward(h, d_state_in, d_actions, n_substeps, d_gstate_out, d_gstate_in,
                                d_gactions, d_gparams);
   if (rc != QS_OK) return rc;
-  // parts of the fixed scratch, each rounded up to 64 floats (256 bytes)
+  // The limit is the interface's, which callers plan by: a state, an adjoint, a
+  // parameter gradient and the tape, each rounded up to 64 floats (256 bytes).
+  // In use are the state and the tape, and neither where one launch does it all.
   auto part = [](size_t n) { return (n + 63) / 64 * 64; };
   const size_t Q = (size_t)h->Q;
-  const size_t n_ck = part(qs::NSTATE * Q), n_lam = part(qs::NSTATE * Q), n_g = part(6 * Q);
+  const size_t n_ck = part(qs::NSTATE * Q);
   const size_t n_tape = n_substeps > 0 ? part(segment_tape_floats(h, 1, n_substeps, 1, false)) : 0;
-  if (n_ck + n_lam + n_g + n_tape > kNoAllocScratchFloats) return QS_ERR_TOO_LARGE;
+  if (2 * n_ck + part(6 * Q) + n_tape > kNoAllocScratchFloats) return QS_ERR_TOO_LARGE;
   if (hipSetDevice(h->dev) != hipSuccess) return QS_ERR_HIP;
   float* base = nullptr;
   rc = noalloc_scratch(h->dev, &base);
   if (rc != QS_OK) return rc;
-  return step_backward_run(h, base + n_ck + n_lam + n_g, base, d_state_in, d_actions, n_substeps, substep_index,
+  return step_backward_run(h, base + n_ck, base, d_state_in, d_actions, n_substeps, substep_index,
                            d_gstate_out, d_gstate_in, d_gactions, d_gparams, (hipStream_t)stream);
 }
 

@@ -86,3 +86,27 @@ def test_noalloc_refuses_requests_beyond_its_scratch():
     assert ei.value.code == -9
     sim.sync()
     sim.close()
+
+
+# calls whose state and tape do go through the fixed scratch: more than four
+# substeps, or workgroups of 128 quads; each with a smaller one behind it
+SWEEPS = {
+    "substeps": ("64", (([8] * 512, 6), ([8, 3, 5, 2, 7, 16, 1, 4] * 10, 5), ([1] * 70, 9))),
+    "wide": ("64", (([40, 64, 17, 1, 33] * 9, 7), ([64] * 3, 5))),
+    "blocks of 128": ("128", (([8] * 300, 3), ([13] * 31, 1), ([32] * 7, 4), ([1] * 131, 2))),
+}
+
+
+@pytest.mark.parametrize("case", sorted(SWEEPS))
+def test_noalloc_sweeps_equal_step_backward(case, monkeypatch):
+    block, calls = SWEEPS[case]
+    monkeypatch.setenv("QS_BLOCK_SIZE", block)
+    for k, (sizes, nsub) in enumerate(calls):
+        w = W.custom(sizes, seed=70 + k, k=0, name="sweeps")
+        sim = QuadSwarm.from_workload(w)
+        sim.step(dev(w.actions(100)), 2)
+        ref, got = both(sim, w, nsub, 17 + k)
+        for r, g in zip(ref, got):
+            assert torch.isfinite(r).all()
+            assert torch.equal(r, g)
+        sim.close()
