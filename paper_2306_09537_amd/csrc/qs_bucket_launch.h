@@ -15,7 +15,7 @@ void go_range(qs_handle* h, int item0, int count, int grid, const float* act, in
               const float* goals, float* obs, hipStream_t s, float* rw) {
   const size_t dyn = KT >= 0 ? (size_t)qs::BUCKET_STAGE_ROWS * h->OD * sizeof(float) : 0;
   hipLaunchKernelGGL((qs::bucket_kernel<BS, KT>), dim3(std::max(grid, 1)), dim3(BS), dyn, s,
-                     h->d_st, h->d_par, act, goals, h->d_c, h->Qp, h->Q, nsub,
+                     h->d_st, h->d_par, act, goals, h->d_c, h->Q, nsub,
                      (unsigned long long)h->t, ptrs(h), obs, item0, count,
                      h->graph_mode ? h->d_t : nullptr, h->d_done, rw);
 }

@@ -48,8 +48,7 @@ inline int check_desc(const qs_desc* d) {
     const long long n = (long long)d->env_offsets[e + 1] - d->env_offsets[e];
     if (n < 1 || n > QS_MAX_SWARM) return QS_ERR_ENV_SIZE;
   }
-  // field offsets (field * Qp + q) stay within int32 and byte offsets of a
-  // quad within a field within 32 bits
+  // a word's place in the state (27 words a quad) stays within int32
   if (d->env_offsets[d->n_envs] > QS_MAX_QUADS) return QS_ERR_INVALID;
   const float vals[] = {d->dt, d->gravity, d->arm_length, d->k_tau, d->drag_coef, d->floor_mu,
                         d->motor_noise_decay, d->motor_noise_std, d->room_min[0], d->room_min[1],

@@ -82,11 +82,10 @@ struct Consts {
 struct Ptrs {
   float* st;                    // private state, tiles of 64 quads (st_index)
   const float* par;             // the quads' parameters, the same (par_index)
-  const uint32_t* sw;           // [Qp] (env start within the block << 8) | n_e
+  const uint32_t* sw;           // (env start within the block << 8) | n_e
   const int2* blk;              // [nblk] (first quad, quad count)
-  unsigned long long* contacts; // [Qp] or nullptr
+  unsigned long long* contacts; // a word per quad, or nullptr
   int* err;                     // sticky error bits
-  int Qp;                       // quad count padded to whole tiles
   int Q;                        // quad count
   const int4* items;            // uneven sizes: (slot size, first env entry, swarms, -)
   const int2* item_envs;        // uneven sizes: (first quad, size) per swarm of an item

@@ -76,7 +76,6 @@ inline Ptrs ptrs(qs_handle* h) {
   p.blk = h->d_blk;
   p.contacts = h->record ? h->d_contacts : nullptr;
   p.err = h->d_err;
-  p.Qp = h->Qp;
   p.Q = h->Q;
   p.items = h->d_items;
   p.item_envs = h->d_item_envs;

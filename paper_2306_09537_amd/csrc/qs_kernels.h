@@ -691,14 +691,13 @@ __device__ __forceinline__ void step_body(const Consts& c, const Ptrs& p,
 template <int BS, int KT, int N>
 __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) void step_kernel(
     float* __restrict__ st, const float* __restrict__ par, const float* __restrict__ act,
-    const float* __restrict__ goals, const Consts* __restrict__ cp, int Qp, int Q, int nsub,
+    const float* __restrict__ goals, const Consts* __restrict__ cp, int Q, int nsub,
     unsigned long long t0, Ptrs p, float* __restrict__ obs, int stage_obs,
     unsigned long long* tdev, unsigned int* done, float* __restrict__ reward) {
   __shared__ __align__(16) float sxv[2][TILE_ROWS_CO][BS];
   extern __shared__ float4 st_obs4[];
   p.st = st;
   p.par = par;
-  p.Qp = Qp;
   p.Q = Q;
   const Consts& c = *cp;
   constexpr int MAP = (N > 0) ? MAP_DENSE : MAP_TABLE;
@@ -717,8 +716,8 @@ __global__ __launch_bounds__(128) void step_pipe_kernel(float* __restrict__ st,
                                                         const float* __restrict__ par,
                                                         const float* __restrict__ act,
                                                         const float* __restrict__ goals,
-                                                        const Consts* __restrict__ cp, int Qp,
-                                                        int Q, int nsub, unsigned long long t0,
+                                                        const Consts* __restrict__ cp, int Q,
+                                                        int nsub, unsigned long long t0,
                                                         Ptrs p, float* __restrict__ obs,
                                                         int stage_obs, unsigned long long* tdev,
                                                         unsigned int* done,
@@ -730,7 +729,6 @@ __global__ __launch_bounds__(128) void step_pipe_kernel(float* __restrict__ st,
   extern __shared__ float4 st_obs4[];
   p.st = st;
   p.par = par;
-  p.Qp = Qp;
   p.Q = Q;
   const Consts& c = *cp;
   constexpr int MAP = (N > 0) ? MAP_DENSE : MAP_TABLE;
@@ -766,7 +764,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(3))) void bu
                                                     const float* __restrict__ par,
                                                     const float* __restrict__ act,
                                                     const float* __restrict__ goals,
-                                                    const Consts* __restrict__ cp, int Qp, int Q,
+                                                    const Consts* __restrict__ cp, int Q,
                                                     int nsub, unsigned long long t0, Ptrs p,
                                                     float* __restrict__ obs, int item0,
                                                     int n_items, unsigned long long* tdev,
@@ -779,7 +777,6 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(3))) void bu
   constexpr int SR = KT >= 0 ? BUCKET_STAGE_ROWS : 0;
   p.st = st;
   p.par = par;
-  p.Qp = Qp;
   p.Q = Q;
   const Consts& c = *cp;
   for (int it = item0 + blockIdx.x; it < item0 + n_items; it += gridDim.x) {

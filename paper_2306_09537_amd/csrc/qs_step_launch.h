@@ -71,14 +71,14 @@ void go(qs_handle* h, const float* act, int nsub, const float* goals, float* obs
     // 16384 quads 18.4 / 19.0 us, four gain, 26.0 / 25.3)
     if (nsub >= (N == 64 ? 4 : 2) && use_step_pipe(h)) {
       hipLaunchKernelGGL((qs::step_pipe_kernel<KT, N>), dim3(h->nblk), dim3(128), dyn, s,
-                         h->d_st, h->d_par, act, goals, h->d_c, h->Qp, h->Q, nsub,
+                         h->d_st, h->d_par, act, goals, h->d_c, h->Q, nsub,
                          (unsigned long long)h->t, ptrs(h), obs, stage,
                          h->graph_mode ? h->d_t : nullptr, h->d_done, rw);
       return;
     }
   }
   hipLaunchKernelGGL((qs::step_kernel<BS, KT, N>), dim3(h->nblk), dim3(BS), dyn, s, h->d_st,
-                     h->d_par, act, goals, h->d_c, h->Qp, h->Q, nsub, (unsigned long long)h->t,
+                     h->d_par, act, goals, h->d_c, h->Q, nsub, (unsigned long long)h->t,
                      ptrs(h), obs, stage, h->graph_mode ? h->d_t : nullptr, h->d_done, rw);
 }
 
