@@ -1254,10 +1254,11 @@ __device__ __forceinline__ unsigned long long pair_pass(const Consts& c, const f
     const int j = ls + jj;
     const float pj[6] = {tile[0][j], tile[1][j], tile[2][j], tile[3][j], tile[4][j], tile[5][j]};
     float dx, dy, dz, d2;
-    if (pair_geom_v(c, pj, s, dx, dy, dz, d2))
-      pair_response<BS>(c, tile, s, j, jj, me, dx, dy, dz, d2, dv, rm);
-    else
-      cmask &= ~(1ull << jj);
+    const bool con = pair_geom_v(c, pj, s, dx, dy, dz, d2);
+    if constexpr (ACC) {
+      if (!con) cmask &= ~(1ull << jj);
+    }
+    if (!ACC || con) pair_response<BS>(c, tile, s, j, jj, me, dx, dy, dz, d2, dv, rm);
   }
   pair_apply(c, s, q, t, rm, dv, adw, dwhit, resp, events);
   return cmask;

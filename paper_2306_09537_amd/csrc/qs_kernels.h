@@ -546,8 +546,11 @@ __device__ __forceinline__ void step_body(const Consts& c, const Ptrs& p,
           const float r = reward_state(c, s, pp.f_max, ov, f0);
           float rp = ANY_K ? r : 0.f;
 #pragma unroll
-          for (int k = 0; k < KC; ++k)
-            if (k < K && bj[k] >= 0) rp += reward_prox(c, ov[18 + 6 * k], ov[19 + 6 * k], ov[20 + 6 * k]);
+          for (int k = 0; k < KC; ++k) {
+            if (k >= K) break;
+            const float px = reward_prox(c, ov[18 + 6 * k], ov[19 + 6 * k], ov[20 + 6 * k]);
+            rp += bj[k] >= 0 ? px : -0.0f;  // (leaves rp as it is)
+          }
           reward[q] = ANY_K ? rp : r + rp;
         }
       } else {
