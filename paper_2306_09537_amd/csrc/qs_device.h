@@ -29,7 +29,7 @@ enum : int { P_M = 0, P_JX = 1, P_JY = 2, P_JZ = 3, P_FMAX = 4, P_ALAG = 5, P_T2
 // The handle's arrays hold the quads in tiles of 64, a quad's words in groups of
 // four (16 bytes a lane, a tile's state 6912 bytes in a row): u, e, R[0..3],
 // R[4..7], R[8] and w, x and v[0], then v[1], v[2] and the flag; the parameters in
-// two groups.  Field by field over all quads a wavefront went to 33 places
+// a group of four and two pairs, of which the forward reads the first.  Field by field over all quads a wavefront went to 33 places
 // megabytes apart, and a small swarm to a part of a cache line at each.  us a call
 // of one substep: 32768 x 32 108 -> 96 and 1,048,576 single quads 71 -> 68 on two
 // handles in turn, 84 -> 84 and 53 -> 53 on one, whose arrays stay in the
@@ -51,7 +51,9 @@ __host__ __device__ inline size_t st_index(int q, int f) {
                      : ST_VF + 3 * lane + place - 24);
 }
 __host__ __device__ inline size_t par_index(int q, int k) {
-  return (size_t)(q >> 6) * (NPARAM * TILE_QUADS) + (k & ~3) * TILE_QUADS + 4 * (q & 63) + (k & 3);
+  const int lane = q & 63;
+  return (size_t)(q >> 6) * (NPARAM * TILE_QUADS) +
+         (k < 4 ? 4 * lane + k : (k & ~1) * TILE_QUADS + 2 * lane + (k & 1));
 }
 // noise streams: fourth Philox counter word = stream << 8 | draw
 enum : uint32_t {
@@ -170,9 +172,8 @@ struct QuadPar {
 
 // The parameters that the forward substep reads, as they are held.
 __device__ __forceinline__ void load_forward_params(const Ptrs& p, int q, QuadPar& pp) {
-  const float* t = p.par + (size_t)(q >> 6) * (NPARAM * TILE_QUADS) + 4 * (q & 63);
-  const v4f a = *reinterpret_cast<const v4f*>(t);
-  const v2f b = *reinterpret_cast<const v2f*>(t + 4 * TILE_QUADS);
+  const v4f a = *reinterpret_cast<const v4f*>(p.par + par_index(q, P_M));
+  const v2f b = *reinterpret_cast<const v2f*>(p.par + par_index(q, P_FMAX));
   pp.m = a[0];
   pp.jx = a[1];
   pp.jy = a[2];

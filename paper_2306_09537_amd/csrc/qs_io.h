@@ -39,11 +39,13 @@ __global__ void set_params_kernel(float* __restrict__ par, int Q,
     __hip_atomic_fetch_or(err, ERRBIT_PARAM, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return;
   }
-  static_assert(P_JZ == 3 && P_FMAX == 4 && P_TAU == 7, "two groups of four");
+  static_assert(P_JZ == 3 && P_FMAX == 4 && P_ALAG == 5 && P_T2W == 6 && P_TAU == 7,
+                "a group of four and two pairs");
   *reinterpret_cast<v4f*>(par + par_index(q, P_M)) = v4f{v[0], v[1], v[2], v[3]};
-  *reinterpret_cast<v4f*>(par + par_index(q, P_FMAX)) =
-      v4f{(float)(0.25 * (double)v[0] * (double)g * (double)v[4]),
-          (float)(1.0 - exp(-(double)dt / (double)v[5])), v[4], v[5]};
+  *reinterpret_cast<v2f*>(par + par_index(q, P_FMAX)) =
+      v2f{(float)(0.25 * (double)v[0] * (double)g * (double)v[4]),
+          (float)(1.0 - exp(-(double)dt / (double)v[5]))};
+  *reinterpret_cast<v2f*>(par + par_index(q, P_T2W)) = v2f{v[4], v[5]};
 }
 
 // The library's counter-based generator, exported for tests: for quads

@@ -205,8 +205,9 @@ __device__ __forceinline__ void load_params(const Ptrs& p, const Consts& c, int 
   pp.ijz = 1.0f / pp.jz;
   pp.a_ns = c.ns_scale * pp.f_max;
   pa.m = pp.m;
-  pa.t2w = p.par[par_index(q, P_T2W)];
-  const float tau = p.par[par_index(q, P_TAU)];
+  const v2f b = *reinterpret_cast<const v2f*>(p.par + par_index(q, P_T2W));
+  pa.t2w = b[0];
+  const float tau = b[1];
   pa.dlag_dtau = -(1.0f - pp.a_lag) * c.dt / (tau * tau);
 }
 
