@@ -202,10 +202,10 @@ __device__ __forceinline__ void step_body(const Consts& c, const Ptrs& p,
   }
   // the call's action, loaded by every lane without a branch (an idle lane's
   // q is still a valid quad: its workgroup's first, or quad 0 in the bucketed
-  // launch; a call without substeps reads a row of the state instead), so no
-  // merge of its value has to wait for it
+  // launch; a call without substeps reads the first words of the state instead), so
+  // no merge of its value has to wait for it
   if constexpr (ROLE != 1)
-    a4 = reinterpret_cast<const float4*>(nsub > 0 ? act : p.st)[q];
+    a4 = reinterpret_cast<const float4*>(nsub > 0 ? act : p.st)[nsub > 0 ? q : 0];
   // §III-A.2 motor noise: the draws depend on the quad, the substep index and
   // the seed only.  With the index known at launch, the first substep's are
   // drawn here, between issuing the loads above and using what they return.
