@@ -771,18 +771,30 @@ __device__ __forceinline__ void for_partners(T tile, int ls, int n, F&& f) {
     // swarm's end (jj >= n) repeat its last member, and f leaves them out.
     // One partner at a time, every read was waited for alone:
     // 2048 swarms of 1-16, differentiated over 100 substeps, 1047 -> 917 us;
-    // 4096 x 12 stepped twice and observed 15.0 -> 14.5 us.
+    // 4096 x 12 stepped twice and observed 15.0 -> 14.5 us.  Where all of the
+    // wavefront's swarms end within one, two or three more places, the last chunk
+    // holds no more than those (131072 quads, 50 substeps with the penalty: swarms
+    // of 3 162 -> 157 us, of 5 202 -> 178, of 6 202 -> 186, of 4, where the choice is
+    // all there is, 135 -> 139).
     for (int j0 = 0; j0 < n; j0 += 4) {
-      float pj[4][7];
+      auto chunk = [&](auto size) {
+        constexpr int CH = decltype(size)::value;
+        float pj[CH][7];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int j = ls + min(j0 + u, n - 1);
+        for (int u = 0; u < CH; ++u) {
+          const int j = ls + min(j0 + u, n - 1);
 #pragma unroll
-        for (int r = 0; r < 6; ++r) pj[u][r] = tile[r][j];
-        pj[u][6] = XR >= 0 ? tile[XR < 0 ? 0 : XR][j] : 0.f;
-      }
+          for (int r = 0; r < 6; ++r) pj[u][r] = tile[r][j];
+          pj[u][6] = XR >= 0 ? tile[XR < 0 ? 0 : XR][j] : 0.f;
+        }
 #pragma unroll
-      for (int u = 0; u < 4; ++u) f(j0 + u, pj[u]);
+        for (int u = 0; u < CH; ++u) f(j0 + u, pj[u]);
+      };
+      const int left = n - j0;
+      if (__ballot(left > 3) != 0ull) chunk(std::integral_constant<int, 4>{});
+      else if (__ballot(left > 2) != 0ull) chunk(std::integral_constant<int, 3>{});
+      else if (__ballot(left > 1) != 0ull) chunk(std::integral_constant<int, 2>{});
+      else chunk(std::integral_constant<int, 1>{});
     }
   }
 }
