@@ -291,9 +291,10 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(N == 8 && PE
         if constexpr (N == 8 && P == PEN_NONE) {
           lane_pair_pass<BS, N, true>(c, tile, s, live, ls, n, me, tid, (uint32_t)q, t);
         } else {
-          if (live) put_tile<N, true>(tile, tid, s);
+          constexpr bool SCREEN = N != 2;  // (one partner: no more than the exact test)
+          if (live) put_tile<N, SCREEN>(tile, tid, s);
           __syncthreads();
-          if (live) pair_pass<BS, N, P, true>(c, tile, s, ls, n, me, (uint32_t)q, t, &pn);
+          if (live) pair_pass<BS, N, P, SCREEN>(c, tile, s, ls, n, me, (uint32_t)q, t, &pn);
         }
       }
     }
