@@ -1246,9 +1246,10 @@ __device__ __forceinline__ unsigned long long pair_pass(const Consts& c, const f
     }
   } else {
     bool done = false;
-    if constexpr (CO && N != 8) done = near_pass<BS, N, P>(c, tile, s, ls, n, me, *pen, cm);
+    if constexpr (CO && (N <= 0 || N > 8))
+      done = near_pass<BS, N, P>(c, tile, s, ls, n, me, *pen, cm);
     if (!done) {
-      for_partners<BS, N, XR, true>(tile, ls, n, [&](int jj, const float* pj) {
+      for_partners<BS, N, XR, P == PEN_GRAD>(tile, ls, n, [&](int jj, const float* pj) {
         pair(jj, pj, FalseT{}, TrueT{});
       });
       if constexpr (ACC) cm = (M)(__builtin_bitreverse32(acc) >> (32 - N));
@@ -1389,7 +1390,7 @@ __device__ __forceinline__ unsigned long long lane_pair_pass(
 template <int BS, int N, int P>
 __device__ __forceinline__ void penalty_pass(const Consts& c, const float (*tile)[BS],
                                              const Quad& s, int ls, int n, int me, Pen& pen) {
-  if constexpr (N != 8) {
+  if constexpr (N <= 0 || N > 8) {
     PairMask<N> contacts = 0;
     if (near_pass<BS, N, P>(c, tile, s, ls, n, me, pen, contacts)) return;
   }

@@ -24,7 +24,9 @@ using qs_host::ptrs;
 //  - forward, five wavefronts: 512 workgroups of 8: 122 -> 61, of 32:
 //    216 -> 162; 1024: 126 -> 140, 214 -> 326 (a CU holds three);
 //    four wavefronts at 1024: 126 -> 85, 214 -> 172; 4096 of 8: equal.  Swarms
-//    of one: 2048: 91 -> 88;
+//    of one over 200 substeps: 1536: 346 -> 297, 1792: 344 -> 324, 2048: 347 ->
+//    354, over 20: 49 -> 44.  Of 8 with the penalty: 1536: 576 -> 456, 1792:
+//    576 -> 509, 2048: 580 -> 563 (without: 421 -> 363, 423 -> 408, 429 -> 470);
 //  - recompute (workgroups times segments): 2048: equal, 4096: 466 -> 496 with
 //    the sweep behind it;
 //  - reverse, two resident on a CU: 512 of 8: 210 -> 127; 1024: 275 -> 300.
@@ -34,8 +36,9 @@ bool pipe(const qs_handle* h, const char* env, bool pays) {
   if (const char* e = std::getenv(env)) return e[0] == '1';
   return pays;
 }
-bool use_rollout_pipe(const qs_handle* h) {
-  return pipe(h, "QS_ROLLOUT_PIPE", h->nblk <= (h->max_n == 1 ? 2048 : 1024));
+bool use_rollout_pipe(const qs_handle* h, bool pen) {
+  const bool to2048 = h->max_n == 1 || (h->uniform_n == 8 && pen);
+  return pipe(h, "QS_ROLLOUT_PIPE", h->nblk <= (to2048 ? 2048 : 1024));
 }
 bool use_noise_wave(const qs_handle* h) { return h->max_n == 1 || h->nblk <= 512; }
 bool use_recompute_pipe(const qs_handle* h, int nseg) {
@@ -49,7 +52,7 @@ template <int BS, int N, bool PEN>
 void go_roll(qs_handle* h, const float* act, int ncalls, int nsub, float* ckpt, int ce, float* pen,
              float beta, hipStream_t s) {
   if constexpr (BS == 64) {
-    if (use_rollout_pipe(h)) {
+    if (use_rollout_pipe(h, PEN)) {
       constexpr int P = PEN ? qs::PEN_SUM : qs::PEN_NONE;
       if (use_noise_wave(h))
         hipLaunchKernelGGL((qs::rollout_pipe_kernel<N, PEN, true>), dim3(h->nblk),

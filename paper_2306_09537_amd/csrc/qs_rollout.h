@@ -247,7 +247,7 @@ __device__ __forceinline__ float duhat_da(const Consts& c, float a, float uhat) 
 // sum over substeps and env-mates of softplus(beta (d_col - d))/(2 beta).
 // ---------------------------------------------------------------------------
 template <int BS, int N, bool PEN>
-__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(N == 8 && PEN ? 3 : 4))) void rollout_kernel(const Consts* __restrict__ cp, Ptrs p,
+__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(N == 8 ? 3 : 4))) void rollout_kernel(const Consts* __restrict__ cp, Ptrs p,
                                                      const float* __restrict__ act, int ncalls,
                                                      int nsub, unsigned long long t0,
                                                      float* __restrict__ ckpt, int ckpt_every,
