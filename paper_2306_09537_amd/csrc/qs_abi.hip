@@ -115,7 +115,12 @@ int build_table(qs_handle* h, int bs) {
 // fetches and writes back its own part of every line: 172,943 quads of 1 to 32,
 // ten calls of ten substeps, 472 us; by quads in runs of 32, 128 and 512: 444, 435
 // and 431; 524,289 quads of 1 to 8, one substep: 99 -> 57.  Shorter runs
-// keep swarms sorted by size from giving one XCD all the heavy items.
+// keep swarms sorted by size from giving one XCD all the heavy items.  Items of 64
+// places come before the others: one of them takes as long as several of the rest
+// (among them at the end, it ends the launch alone), and as a single swarm it shares
+// no more than the lines at its two ends (swarms of 1, 2, 4 .. 64, ten substeps, by
+// slot size / by quads / 64 first: 131k quads 83 / 76 / 67 us, 262k 113 / 118 / 98,
+// 524k 183 / 182 / 167 and with K = 9 334 / 363 / 336).
 int log2i(int n) {
   int k = 0;
   while ((1 << k) < n) ++k;
@@ -146,6 +151,7 @@ int build_items(qs_handle* h, int bs, bool by_size = false) {
   if (!by_size) {
     constexpr size_t RUN = 128, XCDS = 8;
     std::stable_sort(items.begin(), items.end(), [&](const int4& a, const int4& b) {
+      if ((a.x == 64) != (b.x == 64)) return a.x == 64;
       return envs[(size_t)a.y].x < envs[(size_t)b.y].x;
     });
     std::vector<int4> order;
