@@ -43,8 +43,9 @@
  *                            per workgroup of 64 quads (default up to 1536
  *                            workgroups, 2048 of single quads, 1024 of uneven
  *                            sizes), qs_rollout on three to
- *                            five (default up to 1024 workgroups, 2048 of
- *                            single quads), the recompute of
+ *                            five (default up to 1024 workgroups, 1792 of
+ *                            single quads, 2048 of swarms of 8 with a
+ *                            penalty), the recompute of
  *                            qs_rollout_backward on three or four (default
  *                            up to 2048 workgroups, over its segments) and
  *                            its reverse sweep on seven (default up to 512

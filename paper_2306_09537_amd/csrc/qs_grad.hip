@@ -25,7 +25,7 @@ using qs_host::ptrs;
 //    216 -> 162; 1024: 126 -> 140, 214 -> 326 (a CU holds three);
 //    four wavefronts at 1024: 126 -> 85, 214 -> 172; 4096 of 8: equal.  Swarms
 //    of one over 200 substeps: 1536: 346 -> 297, 1792: 344 -> 324, 2048: 347 ->
-//    354, over 20: 49 -> 44.  Of 8 with the penalty: 1536: 576 -> 456, 1792:
+//    354, over 20: 41.0 -> 42.6.  Of 8 with the penalty: 1536: 576 -> 456, 1792:
 //    576 -> 509, 2048: 580 -> 563 (without: 421 -> 363, 423 -> 408, 429 -> 470);
 //  - recompute (workgroups times segments): 2048: equal, 4096: 466 -> 496 with
 //    the sweep behind it;
@@ -37,8 +37,8 @@ bool pipe(const qs_handle* h, const char* env, bool pays) {
   return pays;
 }
 bool use_rollout_pipe(const qs_handle* h, bool pen) {
-  const bool to2048 = h->max_n == 1 || (h->uniform_n == 8 && pen);
-  return pipe(h, "QS_ROLLOUT_PIPE", h->nblk <= (to2048 ? 2048 : 1024));
+  const int limit = h->max_n == 1 ? 1792 : h->uniform_n == 8 && pen ? 2048 : 1024;
+  return pipe(h, "QS_ROLLOUT_PIPE", h->nblk <= limit);
 }
 bool use_noise_wave(const qs_handle* h) { return h->max_n == 1 || h->nblk <= 512; }
 bool use_recompute_pipe(const qs_handle* h, int nseg) {
