@@ -39,10 +39,10 @@
  *      QS_STEP_PIPE, QS_ROLLOUT_PIPE, QS_RECOMPUTE_PIPE,
  *      QS_REVERSE_PIPE = 0|1
  *                            force the multi-wavefront forms off or on:
- *                            multi-substep step calls on two wavefronts
- *                            per workgroup of 64 quads (default up to 1536
- *                            workgroups, 2048 of single quads, 1024 of uneven
- *                            sizes), qs_rollout on three to
+ *                            multi-substep step calls (of swarms of 64 from
+ *                            four substeps) on two wavefronts per workgroup
+ *                            of 64 quads (default up to 1536 workgroups,
+ *                            2048 of single quads), qs_rollout on three to
  *                            five (default up to 1024 workgroups, 1792 of
  *                            single quads, 2048 of swarms of 8 with a
  *                            penalty), the recompute of

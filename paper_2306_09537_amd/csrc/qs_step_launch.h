@@ -11,13 +11,18 @@ using qs_host::ptrs;
 
 // Calls of several substeps on small batches run the motor part one substep
 // ahead in a second wavefront (QS_STEP_PIPE=0/1 forces it off/on): a lone
-// wavefront waits for its own instructions, and two share a substep.  Once the
-// first wavefronts fill the SIMDs the second ones only queue behind them.  us a
-// call, one wavefront / two, of two, four and ten substeps:
+// wavefront waits for its own instructions, and two share a substep.  Up to 1536
+// workgroups (three wavefronts a SIMD) all of them are resident together; beyond,
+// the last ones wait for a second turn.  us a call, one wavefront / two, of two,
+// four and ten substeps:
 //   4096 quads in swarms of 8    6.7 / 5.7    8.9 / 7.7   17.8 / 14.1
 //   4096 in 32                   9.9 / 9.1   13.9 / 12.5  27.0 / 22.1
-//   65536 in 12 (table)         11.7 / 10.5  15.4 / 13.6  28.4 / 24.4
-//   98304 in 12                 12.9 / 15.8  16.9 / 21.0  30.8 / 37.0
+//   1100 workgroups of 12s      11.8 / 10.7  15.6 / 13.6  26.5 / 22.0  (table)
+//   1536                        12.6 / 11.9  16.6 / 15.0  27.6 / 24.6
+//   1700                        13.2 / 16.1  16.8 / 20.9  28.8 / 35.3
+//   1536 of 3s                  12.1 / 11.0  15.0 / 13.5  24.7 / 20.4
+//   1536 of 48s                 22.0 / 20.8  27.3 / 25.7  44.0 / 39.6
+//   1421 of 1 to 64             23.8 / 22.6  30.0 / 28.3  45.9 / 42.2
 //   98304 in 8                  10.3 / 9.5   13.6 / 12.2  25.9 / 22.3
 //   98304 in 32                 15.8 / 15.4  20.1 / 18.8  36.3 / 36.5
 //   131072 in 8                 12.2 / 14.2  14.7 / 17.9  27.1 / 30.6
@@ -25,7 +30,7 @@ using qs_host::ptrs;
 //   262144 in 1                 14.5 / 14.3  18.5 / 18.4  30.4 / 30.4
 bool use_step_pipe(const qs_handle* h) {
   if (const char* e = std::getenv("QS_STEP_PIPE")) return e[0] == '1';
-  return h->nblk <= (h->uniform_n == 1 ? 2048 : h->uniform_n > 0 ? 1536 : 1024);
+  return h->nblk <= (h->uniform_n == 1 ? 2048 : 1536);
 }
 
 // Observation rows per staging pass.  A grid of at most 2048 workgroups
