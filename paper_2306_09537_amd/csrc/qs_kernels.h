@@ -251,10 +251,11 @@ __device__ __forceinline__ void step_body(const Consts& c, const Ptrs& p,
   uint32_t skey[NKEY];
 #pragma unroll
   for (int k = 0; k < NKEY; ++k) skey[k] = KEY_EMPTY;
+  // the substep's motor-noise draws (cleared after their use, so that the first
+  // one's do not stay in registers for the whole loop)
+  float zs[4] = {z0[0], z0[1], z0[2], z0[3]};
   for (int sub = 0; sub < nsub; ++sub) {
     const unsigned long long t = t0 + (unsigned long long)sub;
-    // this substep's motor-noise draws
-    float zs[4] = {z0[0], z0[1], z0[2], z0[3]};
     if constexpr (ROLE != 1) {
       if (noise && live && !(sub == 0 && early_z)) normal4(c, (uint32_t)q, t, STREAM_MOTOR, 0, zs);
     }
@@ -283,6 +284,7 @@ __device__ __forceinline__ void step_body(const Consts& c, const Ptrs& p,
     } else {
       if (live) quad_substep<false, Z_IMPORT>(c, pp, s, uhat, (uint32_t)q, t, nullptr, zs);
     }
+    zs[0] = zs[1] = zs[2] = zs[3] = 0.f;
     // §III-B.1 in-env pair pass (Jacobi: every response from the
     // pre-response velocities of this substep)
     if constexpr (N > 1 && N <= 8) {
