@@ -431,9 +431,9 @@ int qs_set_partner_chunks(qs_handle* h, uint32_t slot_mask);
 /*
  * The per-slot-size plan of the bucketed form, into plan [7][5] (host), one
  * row per slot size present, largest first: slot size, swarms, 1 if its
- * items take the chunked body else 0, and the times (ns per launch) the
- * last qs_autotune measured for the slot's items alone with the
- * one-partner and with the chunked body (0 where not measured).  *n_rows
+ * items pass over all the slot's places else 0, and the times (ns per
+ * launch) the last qs_autotune measured for the slot's items alone over the
+ * swarms' own sizes and over all the places (0 where not measured).  *n_rows
  * receives the number of rows (0 for handles of uniform sizes).
  */
 int qs_launch_plan(const qs_handle* h, int32_t* plan, int32_t* n_rows);

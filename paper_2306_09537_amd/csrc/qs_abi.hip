@@ -109,18 +109,18 @@ int build_table(qs_handle* h, int bs) {
 // h->chunked).
 //
 // Items are ordered by the quads they serve, in runs of RUN per XCD (workgroups
-// go to the eight XCDs in turn): a field's cache line holds 32 quads of several
-// swarms, whose items then share an L2 and run at about the same time.  Ordered
-// by slot size (by_size: the autotuner's trials of one slot's items), every XCD
-// fetches and writes back its own part of every line: 172,943 quads of 1 to 32,
-// ten calls of ten substeps, 472 us; by quads in runs of 32, 128 and 512: 444, 435
-// and 431; 524,289 quads of 1 to 8, one substep: 99 -> 57.  Shorter runs
-// keep swarms sorted by size from giving one XCD all the heavy items.  Items of 64
-// places come before the others: one of them takes as long as several of the rest
-// (among them at the end, it ends the launch alone), and as a single swarm it shares
-// no more than the lines at its two ends (swarms of 1, 2, 4 .. 64, ten substeps, by
-// slot size / by quads / 64 first: 131k quads 83 / 76 / 67 us, 262k 113 / 118 / 98,
-// 524k 183 / 182 / 167 and with K = 9 334 / 363 / 336).
+// go to the eight XCDs in turn): a cache line of the state's tiles holds eight
+// quads, often of several swarms, whose items then share an L2 and run at about the
+// same time.  Ordered by slot size (by_size: the autotuner's trials of one slot's
+// items), every XCD fetches and writes back its own part of every line: 172,943
+// quads of 1 to 32, ten calls of ten substeps, 472 us; by quads in runs of 32, 128
+// and 512: 444, 435 and 431; 524,289 quads of 1 to 8, one substep: 99 -> 57.
+// Shorter runs keep swarms sorted by size from giving one XCD all the heavy items.
+// Items of 64 places come before the others: one of them takes as long as several
+// of the rest (at the end of the launch it runs alone), and as a single swarm it
+// shares no more than the lines at its two ends (swarms of 1, 2, 4 .. 64, ten
+// substeps, by slot size / by quads / 64 first: 131k quads 83 / 76 / 67 us, 262k
+// 113 / 118 / 98, 524k 183 / 182 / 167 and with K = 9 334 / 363 / 336).
 int log2i(int n) {
   int k = 0;
   while ((1 << k) < n) ++k;
@@ -283,7 +283,7 @@ int apply(qs_handle* h, hipStream_t s, const BucketConfig& c, bool by_size = fal
 }
 
 // Bucketed handles: (1) workgroup sizes 64 and 128 and persistent grids,
-// every slot size with the one-partner body; (2) per slot size with two
+// every slot size over its swarms' own sizes; (2) per slot size with two
 // bodies (16 and 32), its items alone with each body, at the workgroup size
 // of (1); (3) the call with each slot size on its faster body, over the
 // grids; the faster of (1) and (3) is kept.  (4) Unless QS_BUCKETED asks for items

@@ -32,7 +32,7 @@ enum : int { P_M = 0, P_JX = 1, P_JY = 2, P_JZ = 3, P_FMAX = 4, P_ALAG = 5, P_T2
 // a group of four and two pairs, of which the forward reads the first.  Field by field over all quads a wavefront went to 33 places
 // megabytes apart, and a small swarm to a part of a cache line at each.  us a call
 // of one substep: 32768 x 32 108 -> 96 and 1,048,576 single quads 71 -> 68 on two
-// handles in turn, 84 -> 84 and 53 -> 53 on one, whose arrays stay in the
+// handles in turn, 79.1 -> 79.9 and 52.4 -> 52.6 on one, whose arrays stay in the
 // memory-side cache; 2,097,152 quads in swarms of 1, 8, 32 and 12: 123 -> 114,
 // 195 -> 170, 202 -> 173, 272 -> 203.
 constexpr int TILE_QUADS = 64;
@@ -738,7 +738,8 @@ using PairMask = typename std::conditional<(N > 0 && N <= 32), uint32_t,
 // For a compile-time swarm size the reads go out a chunk of eight partners
 // at a time, ahead of the per-pair branches, so they overlap instead of
 // waiting one by one.
-// FEW: chunks of four in swarms of 8 too (kernels short of registers).
+// FEW: chunks of four in swarms of 8 too (the recompute with its penalty's
+// adjoint, which is short of registers).
 template <int BS, int N, int XR = -1, bool FEW = false, typename T, typename F>
 __device__ __forceinline__ void for_partners(T tile, int ls, int n, F&& f) {
   if constexpr (N > 0) {

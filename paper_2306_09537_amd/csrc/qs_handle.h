@@ -41,7 +41,8 @@ struct qs_handle {
   // slot sizes (bit log2 N; 16 and 32) whose items take the body with the size
   // known at compile time (all slot's places in chunks of four, through the
   // expanded screen) instead of the run-time size's: the faster one unless the
-  // autotuner measures otherwise (4096 x 12, two substeps: 14.5 -> 13.8 us)
+  // autotuner measures otherwise (172,943 quads of 1 to 32, ten substeps, the items
+  // of 32 alone: 49.7 -> 36.9 us)
   uint32_t chunked = (1u << 4) | (1u << 5);
   // per slot size: swarms, and the times the autotuner measured for the
   // slot's items alone with each body (ns per call)

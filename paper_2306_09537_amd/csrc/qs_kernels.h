@@ -761,7 +761,7 @@ constexpr int BUCKET_STAGE_ROWS = 32;
 // each item's slot size N.  Slots of 64 loop over the swarm at run time: with
 // all of them unrolled, their bodies would set the whole kernel's register
 // count, and with it the occupancy (381 VGPRs: 1 wavefront per SIMD; held to
-// 168, 3).  Slots of 16 and 32 have a body of either kind, chosen per item
+// 168, 3, at which of the workgroups of 64 only K_UPTO8 spills, six registers).  Slots of 16 and 32 have a body of either kind, chosen per item
 // (items[it].w, set per slot size by default and by the autotuner).
 template <int BS, int KT>
 __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(3))) void bucket_kernel(

@@ -245,6 +245,11 @@ __device__ __forceinline__ float duhat_da(const Consts& c, float a, float uhat) 
 // of every ckpt_every-th call, checkpoint k at ckpt + k 27 Q.  pen
 // (optional, PEN): each quad's share of the smoothed collision penalty,
 // sum over substeps and env-mates of softplus(beta (d_col - d))/(2 beta).
+// Bound by instruction issue, in small batches by its chain.  Four wavefronts a
+// SIMD, three for swarms of 8, which then hold eight partners a chunk (with the
+// penalty 168 registers; four a chunk, 142: 98304 / 262144 / 524288 quads, 50
+// substeps, 160 / 274 / 473 -> 152 / 261 / 456 us) and spill nothing (without, at
+// four: six registers; 118 / 196 / 340 -> 116 / 202 / 334).
 // ---------------------------------------------------------------------------
 template <int BS, int N, bool PEN>
 __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(N == 8 ? 3 : 4))) void rollout_kernel(const Consts* __restrict__ cp, Ptrs p,

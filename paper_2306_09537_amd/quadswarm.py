@@ -386,17 +386,19 @@ class QuadSwarm:
                 "slots": self.launch_plan()}
 
     def set_partner_chunks(self, slots) -> None:
-        """qs_set_partner_chunks: the slot sizes (16, 32) whose items take
-        the in-swarm partners in chunks of four in the bucketed form."""
+        """qs_set_partner_chunks: the slot sizes (16, 32; both at creation) whose
+        items pass over all the slot's places in the bucketed form, in a loop of
+        known length, instead of over the swarm's own size."""
         mask = 0
         for n in slots:
             mask |= 1 << (int(n).bit_length() - 1)
         _check(lib().qs_set_partner_chunks(self._h, mask), "qs_set_partner_chunks")
 
     def launch_plan(self) -> list:
-        """qs_launch_plan: per slot size, its swarms, whether its items take
-        the chunked body, and the autotuner's times (ns) for its items with
-        the one-partner and with the chunked body."""
+        """qs_launch_plan: per slot size, its swarms, whether its items pass over
+        all the slot's places ("chunked"), and the autotuner's times (ns) for its
+        items alone over the swarm's own size ("ns_one") and over all the places
+        ("ns_chunked")."""
         buf = (C.c_int32 * 35)()
         n = C.c_int32()
         _check(lib().qs_launch_plan(self._h, buf, C.byref(n)), "qs_launch_plan")
