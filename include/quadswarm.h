@@ -30,8 +30,7 @@
  *    allows it (qs_step_backward: d_gstate_in may be d_gstate_out).
  *  - Environment overrides of launch choices (the library picks each by
  *    itself; results are bit-identical whichever form runs):
- *      QS_BLOCK_SIZE=64|128  workgroup size, read by qs_create (default 64;
- *                            128 for >= 262,144 single-quad swarms);
+ *      QS_BLOCK_SIZE=64|128  workgroup size, read by qs_create (default 64);
  *      QS_BUCKETED=0|1       uneven swarm sizes run one workgroup per packed
  *                            block, or the persistent bucketed launch, in
  *                            every call (default: by the substeps of the

@@ -27,17 +27,18 @@ using qs_host::overlap;
 using qs_host::Span;
 using qs_host::noalloc_scratch;
 
-// Workgroup size: one wavefront (64) unless every swarm is a single quad and
-// the batch is large.  A one-wavefront workgroup needs no barrier for the
-// in-swarm exchanges (32768 x 32: 128 -> 64 made the ten-substep step 4 %,
-// the rollout 6 % and the backward 3 % faster); without exchanges, fewer
-// and larger workgroups dispatch faster (1,048,576 x 1: 2 %).
-int pick_block(int Q, int max_n) {
+// Workgroup size: one wavefront (64).  It needs no barrier for the in-swarm
+// exchanges (32768 x 32: 128 -> 64 made the ten-substep step 4 %, the rollout
+// 6 % and the backward 3 % faster), and a workgroup's quads are one tile of the
+// state.  Single quads, 128 / 64, us a call of one, four and ten substeps: 262,144
+// 12.7 / 12.3, 16.9 / 17.1, 26.7 / 27.0; 524,288 26.8 / 26.7, 30.8 / 29.6, 45.2 /
+// 43.3; 1,048,576 51.8 / 52.0, 56.8 / 56.1, 74.2 / 72.4; the derivative of one
+// substep 50.8 / 20.7, 92 / 38, 192 / 83.
+int pick_block() {
   if (const char* e = std::getenv("QS_BLOCK_SIZE")) {
     const int b = std::atoi(e);
     if (b == 64 || b == 128) return b;
   }
-  if (max_n == 1 && Q >= 128 * 2048) return 128;
   return 64;
 }
 
@@ -378,7 +379,7 @@ int qs_create(const qs_desc* desc, const qs_quad_params* h_params, const float* 
   for (int e = 0; e < E; ++e)
     max_n = std::max(max_n, desc->env_offsets[e + 1] - desc->env_offsets[e]);
   h->max_n = max_n;
-  h->bs = pick_block(Q, max_n);
+  h->bs = pick_block();
 
   // constants (derived in double, rounded once)
   Consts& c = h->c;
