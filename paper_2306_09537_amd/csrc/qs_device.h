@@ -732,16 +732,18 @@ using PairMask = typename std::conditional<(N > 0 && N <= 32), uint32_t,
                                            unsigned long long>::type;
 
 // Calls f(jj, pj) for every swarm-mate jj of the lane's swarm (itself
-// included; N <= 0: and up to three places past its end, jj >= n), in
-// increasing jj, pj[0..5] being its start position and
+// included), in increasing jj, pj[0..5] being its start position and
 // displacement from rows 0-5 of the tile and pj[6] row XR (XR < 0: none).
+// N <= 0: up to three calls for the quad itself (jj == me) follow, so a pass
+// must leave the quad itself out, or take nothing from it, however often it comes.
 // For a compile-time swarm size the reads go out a chunk of eight partners
 // at a time, ahead of the per-pair branches, so they overlap instead of
 // waiting one by one.
 // FEW: chunks of four in swarms of 8 too (the recompute with its penalty's
-// adjoint, which is short of registers).
-template <int BS, int N, int XR = -1, bool FEW = false, typename T, typename F>
-__device__ __forceinline__ void for_partners(T tile, int ls, int n, F&& f) {
+// adjoint, which is short of registers).  TAIL (N <= 0): a last chunk of less
+// than four places where the wavefront's swarms all end there.
+template <int BS, int N, int XR = -1, bool FEW = false, bool TAIL = false, typename T, typename F>
+__device__ __forceinline__ void for_partners(T tile, int ls, int n, int me, F&& f) {
   if constexpr (N > 0) {
     // chunks of eight partners, four in swarms of 16 and more (32-quad
     // swarms: 168 -> 120 VGPRs in the step, four wavefronts per SIMD
@@ -769,30 +771,35 @@ __device__ __forceinline__ void for_partners(T tile, int ls, int n, F&& f) {
     }
   } else {
     // run-time sizes: chunks of four as well, branch-free; the places past the
-    // swarm's end (jj >= n) repeat its last member, and f leaves them out.
+    // swarm's end hold the quad itself, which no pass counts.
     // One partner at a time, every read was waited for alone:
     // 2048 swarms of 1-16, differentiated over 100 substeps, 1047 -> 917 us;
-    // 4096 x 12 stepped twice and observed 15.0 -> 14.5 us.  Where all of the
-    // wavefront's swarms end within one, two or three more places, the last chunk
-    // holds no more than those (131072 quads, 50 substeps with the penalty: swarms
-    // of 3 162 -> 157 us, of 5 202 -> 178, of 6 202 -> 186, of 4, where the choice is
-    // all there is, 135 -> 139).
+    // 4096 x 12 stepped twice and observed 15.0 -> 14.5 us.
+    // TAIL, a vote for each chunk: where all of the wavefront's swarms end within
+    // one, two or three more places, the last chunk holds no more than those
+    // (131072 quads, 50 substeps with the penalty: swarms of 3 162 -> 157 us, of 5
+    // 202 -> 178, of 6 202 -> 186, of 4, where the choice is all there is,
+    // 135 -> 139).  Passes without the penalty do with less between the chunks, and
+    // longer swarms lose more by the vote than short ones gain (24576 quads, 40
+    // substeps with downwash: swarms of 1-64 262 us, with the vote 302, of 5 72 and 66).
     for (int j0 = 0; j0 < n; j0 += 4) {
       auto chunk = [&](auto size) {
         constexpr int CH = decltype(size)::value;
+        int jj[CH];
         float pj[CH][7];
 #pragma unroll
         for (int u = 0; u < CH; ++u) {
-          const int j = ls + min(j0 + u, n - 1);
+          jj[u] = j0 + u < n ? j0 + u : me;
+          const int j = ls + jj[u];
 #pragma unroll
           for (int r = 0; r < 6; ++r) pj[u][r] = tile[r][j];
           pj[u][6] = XR >= 0 ? tile[XR < 0 ? 0 : XR][j] : 0.f;
         }
 #pragma unroll
-        for (int u = 0; u < CH; ++u) f(j0 + u, pj[u]);
+        for (int u = 0; u < CH; ++u) f(jj[u], pj[u]);
       };
       const int left = n - j0;
-      if (__ballot(left > 3) != 0ull) chunk(std::integral_constant<int, 4>{});
+      if (!TAIL || __ballot(left > 3) != 0ull) chunk(std::integral_constant<int, 4>{});
       else if (__ballot(left > 2) != 0ull) chunk(std::integral_constant<int, 3>{});
       else if (__ballot(left > 1) != 0ull) chunk(std::integral_constant<int, 2>{});
       else chunk(std::integral_constant<int, 1>{});
@@ -1189,11 +1196,10 @@ __device__ __forceinline__ unsigned long long pair_pass(const Consts& c, const f
   constexpr bool ACC = N >= 16 && N <= 32;
   uint32_t acc = 0u;
   auto pair = [&](int jj, const float* pj, auto with_dw, auto in_order) {
-    const bool mate = N > 0 || jj < n;  // (cm drops the other places after the pass)
     float dx, dy, dz, d2;
     const bool con = pair_geom_v(c, pj, s, dx, dy, dz, d2);
     if constexpr (P != PEN_NONE)
-      pen_term<P>(c, *pen, mate && (P == PEN_GRAD || jj != me), pj[6], dx, dy, dz, d2);
+      pen_term<P>(c, *pen, P == PEN_GRAD || jj != me, pj[6], dx, dy, dz, d2);
     if constexpr (ACC && decltype(in_order)::value)
       acc = __builtin_amdgcn_alignbit(acc, __float_as_uint(d2 - c.dcol2), 31u);
     else
@@ -1201,15 +1207,15 @@ __device__ __forceinline__ unsigned long long pair_pass(const Consts& c, const f
     if constexpr (decltype(with_dw)::value) {
       // swarm-mate j above (z_j - z_i = -dz) and overlapping in xy (never
       // the quad itself: dz = 0 there)
-      const bool dwc = mate & dw & (dx * dx + dy * dy < dw_r2) & (-dz > 0.f) & (-dz < dw_h);
+      const bool dwc = dw & (dx * dx + dy * dy < dw_r2) & (-dz > 0.f) & (-dz < dw_h);
       adw = dwc ? adw - dw_k1 * (dw_k2 * -dz + dw_b1) : adw;
       dwhit = dwhit | dwc;
     }
   };
   constexpr int XR = P == PEN_GRAD ? PENROW : -1;
   if (c.flags & F_DOWNWASH) {
-    for_partners<BS, N, XR>(tile, ls, n,
-                            [&](int jj, const float* pj) { pair(jj, pj, TrueT{}, TrueT{}); });
+    for_partners<BS, N, XR, false, P != PEN_NONE>(
+        tile, ls, n, me, [&](int jj, const float* pj) { pair(jj, pj, TrueT{}, TrueT{}); });
     if constexpr (ACC) cm = (M)(__builtin_bitreverse32(acc) >> (32 - N));
   } else if constexpr (CO && P == PEN_NONE) {
     const float dw = c.dcol + 1e-3f, thr = dw * dw;
@@ -1250,14 +1256,11 @@ __device__ __forceinline__ unsigned long long pair_pass(const Consts& c, const f
     if constexpr (CO && (N <= 0 || N > 8))
       done = near_pass<BS, N, P>(c, tile, s, ls, n, me, *pen, cm);
     if (!done) {
-      for_partners<BS, N, XR, P == PEN_GRAD>(tile, ls, n, [&](int jj, const float* pj) {
-        pair(jj, pj, FalseT{}, TrueT{});
-      });
+      for_partners<BS, N, XR, P == PEN_GRAD, P != PEN_NONE>(
+          tile, ls, n, me, [&](int jj, const float* pj) { pair(jj, pj, FalseT{}, TrueT{}); });
       if constexpr (ACC) cm = (M)(__builtin_bitreverse32(acc) >> (32 - N));
     }
   }
-  // (run-time sizes: nor the places past the swarm's end)
-  if constexpr (N <= 0) cm &= (M)(~0ull >> (64 - n));
   unsigned long long cmask = collide ? (unsigned long long)(cm & ~((M)1 << me)) : 0ull;
   // The responses, for the partners in contact only, in partner order.  (The
   // sign bits shifted in above are the comparison's outcome for numbers only: a
@@ -1395,11 +1398,12 @@ __device__ __forceinline__ void penalty_pass(const Consts& c, const float (*tile
     PairMask<N> contacts = 0;
     if (near_pass<BS, N, P>(c, tile, s, ls, n, me, pen, contacts)) return;
   }
-  for_partners<BS, N, P == PEN_GRAD ? PENROW : -1>(tile, ls, n, [&](int jj, const float* pj) {
-    float dx, dy, dz, d2;
-    pair_geom_v(c, pj, s, dx, dy, dz, d2);
-    pen_term<P>(c, pen, (N > 0 || jj < n) && (P == PEN_GRAD || jj != me), pj[6], dx, dy, dz, d2);
-  });
+  for_partners<BS, N, P == PEN_GRAD ? PENROW : -1, false, true>(
+      tile, ls, n, me, [&](int jj, const float* pj) {
+        float dx, dy, dz, d2;
+        pair_geom_v(c, pj, s, dx, dy, dz, d2);
+        pen_term<P>(c, pen, P == PEN_GRAD || jj != me, pj[6], dx, dy, dz, d2);
+      });
 }
 
 // §III-C sensor noise on the own-state part of an observation row:

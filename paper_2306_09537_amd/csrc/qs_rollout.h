@@ -441,11 +441,11 @@ __device__ __forceinline__ unsigned long long mark_contacts(const Consts& c,
                                                             const float (*tile)[BS], const Quad& s,
                                                             int ls, int n, int me) {
   unsigned long long cm = 0ull;
-  for_partners<BS, 0>(tile, ls, n, [&](int jj, const float* pj) {
+  for_partners<BS, 0>(tile, ls, n, me, [&](int jj, const float* pj) {
     float dx, dy, dz, d2;
     cm |= pair_geom_v(c, pj, s, dx, dy, dz, d2) ? 1ull << jj : 0ull;
   });
-  cm &= ~0ull >> (64 - n) & ~(1ull << me);
+  cm &= ~(1ull << me);
   return (c.flags & F_COLLIDE) ? cm : 0ull;
 }
 
